@@ -1,6 +1,5 @@
 // pasur_cfr.hip -- full-width DCFR on one round's unfolded tree, leaf
-// utilities, average strategy, round values and exact tree values (best
-// response / minimax) as level-synchronous HIP kernels.
+// utilities, average strategy and round values.
 //
 // State is stored as T (float or double); every arithmetic step runs in
 // double registers, with the operations of each parent's update done in the
@@ -733,31 +732,6 @@ __global__ void k_leaf_util(int64_t n, const int16_t *__restrict__ base,
   out[i] = (T)(V ? V[link[i]] + pts : pts);
 }
 
-// Exact values of one level from the level below: expectation under sigma,
-// or max/min at the best-responding player's nodes.
-template <class T, class L>
-__global__ void k_values_up(int64_t np, int mover, int mode, const int32_t *__restrict__ cb,
-                            const T *__restrict__ sigma, const L *__restrict__ child,
-                            double *__restrict__ out) {
-  int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= np) return;
-  const int32_t b = cb[h], e = cb[h + 1];
-  const bool use_max = (mode == PASUR_TV_MINIMAX || mode == PASUR_TV_BR_A) && mover == 0;
-  const bool use_min = (mode == PASUR_TV_MINIMAX || mode == PASUR_TV_BR_B) && mover == 1;
-  double v;
-  if (use_max) {
-    v = -INFINITY;
-    for (int32_t q = b; q < e; ++q) v = fmax(v, (double)child[q]);
-  } else if (use_min) {
-    v = INFINITY;
-    for (int32_t q = b; q < e; ++q) v = fmin(v, (double)child[q]);
-  } else {
-    v = 0.0;
-    for (int32_t q = b; q < e; ++q) v += (double)sigma[q] * (double)child[q];
-  }
-  out[h] = v;
-}
-
 __global__ void k_div(int64_t n, const double *__restrict__ a, double T, double *__restrict__ out) {
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j < n) out[j] = a[j] / T;
@@ -1122,50 +1096,6 @@ int64_t widest_level(const pasur_fgt *f) {
   return mx;
 }
 
-// The up-sweep of tree values through two level buffers of at least
-// widest_level(f) doubles each (every level is written in full before it
-// is read, so the buffers need no clearing).
-template <class T, class L>
-void values_run(const pasur_fgt *f, const L *leaf, void *const sigma[9], int mode, double *out,
-                double *buf0, double *buf1, hipStream_t s) {
-  double *buf[2] = {buf0, buf1};
-  int cur = 0;
-  for (int l = 8; l >= 1; --l) {
-    double *dst = l == 1 ? out : buf[cur];
-    const T *sg = sigma ? (const T *)sigma[l] : nullptr;
-    if (l == 8)
-      k_values_up<T, L><<<grid_for(f->n[7]), kThreads, 0, s>>>(f->n[7], 1, mode,
-                                                               f->child_begin[7], sg, leaf, dst);
-    else
-      k_values_up<T, double><<<grid_for(f->n[l - 1]), kThreads, 0, s>>>(
-          f->n[l - 1], (l - 1) & 1, mode, f->child_begin[l - 1], sg, buf[cur ^ 1], dst);
-    cur ^= 1;
-  }
-}
-
-template <class T, class L>
-int values_t(const pasur_fgt *f, const L *leaf, void *const sigma[9], int mode, double *out,
-             hipStream_t s) {
-  const int64_t mx = widest_level(f);
-  double *buf[2] = {nullptr, nullptr};
-  PASUR_TRY_HIP(hipMallocAsync((void **)&buf[0], mx * sizeof(double), s));
-  hipError_t e = hipMallocAsync((void **)&buf[1], mx * sizeof(double), s);
-  if (e != hipSuccess) {
-    (void)hipFreeAsync(buf[0], s);
-    set_error("hipMallocAsync: %s", hipGetErrorString(e));
-    return PASUR_E_NOMEM;
-  }
-  values_run<T, L>(f, leaf, sigma, mode, out, buf[0], buf[1], s);
-  e = hipGetLastError();
-  (void)hipFreeAsync(buf[0], s);
-  (void)hipFreeAsync(buf[1], s);
-  if (e != hipSuccess) {
-    set_error("tree values: %s", hipGetErrorString(e));
-    return PASUR_E_HIP;
-  }
-  return PASUR_OK;
-}
-
 int check_tree_values(const pasur_fgt *f, const double *d_leaf, int dtype, void *const sigma[9],
                       int mode, double *d_out) {
   if (!f || !d_leaf || !d_out) {
@@ -1190,39 +1120,8 @@ int check_tree_values(const pasur_fgt *f, const double *d_leaf, int dtype, void 
   return PASUR_OK;
 }
 
-// ---- pasur_tree_values_noalloc: the level buffers in a fixed device array.
-// Each GPU the library runs on holds its own copy of `scratch` (two level
-// buffers of kNoAllocLevel doubles, 32 MiB) until the process ends.  Host
-// code never uses the array's name as an address: its per-device address
-// comes from hipGetSymbolAddress, taken once per device with that device
-// current, on the entry point's first call there.
+// Widest level pasur_tree_values_noalloc takes.
 constexpr int64_t kNoAllocLevel = (int64_t)1 << 21;
-static __device__ __align__(256) double scratch[2 * kNoAllocLevel];
-
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-double *g_scratch_ptr[kMaxDevices] = {nullptr};
-
-int scratch_for_current_device(double **out) {
-  int dev = 0;
-  PASUR_TRY_HIP(hipGetDevice(&dev));
-  if (dev < 0 || dev >= kMaxDevices) {
-    set_error("device %d beyond the %d devices the scratch table covers", dev, kMaxDevices);
-    return PASUR_E_RANGE;
-  }
-  std::lock_guard<std::mutex> g(g_scratch_mu);
-  if (!g_scratch_ptr[dev]) {
-    void *p = nullptr;
-    hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess || !p) {
-      set_error("hipGetSymbolAddress(scratch) on device %d: %s", dev, hipGetErrorString(e));
-      return PASUR_E_HIP;
-    }
-    g_scratch_ptr[dev] = (double *)p;
-  }
-  *out = g_scratch_ptr[dev];
-  return PASUR_OK;
-}
 
 }  // namespace
 
@@ -1371,18 +1270,13 @@ extern "C" int pasur_round_values(const pasur_fgt *f, const pasur_cfr_state *st,
     set_error("sigma_bar is NULL");
     return PASUR_E_INVAL;
   }
-  return st->dtype == PASUR_F32
-             ? values_t<float, float>(f, (const float *)st->u[8], sigma_bar, PASUR_TV_EXPECT, d_V, s)
-             : values_t<double, double>(f, (const double *)st->u[8], sigma_bar, PASUR_TV_EXPECT,
-                                        d_V, s);
+  return tree_values(f, st->u[8], st->dtype, st->dtype, sigma_bar, PASUR_TV_EXPECT, d_V, s);
 }
 
 extern "C" int pasur_tree_values(const pasur_fgt *f, const double *d_leaf, int dtype,
                                  void *const sigma[9], int mode, double *d_out, void *stream) {
   PASUR_TRY(check_tree_values(f, d_leaf, dtype, sigma, mode, d_out));
-  hipStream_t s = (hipStream_t)stream;
-  return dtype == PASUR_F32 ? values_t<float, double>(f, d_leaf, sigma, mode, d_out, s)
-                            : values_t<double, double>(f, d_leaf, sigma, mode, d_out, s);
+  return tree_values(f, d_leaf, PASUR_F64, dtype, sigma, mode, d_out, (hipStream_t)stream);
 }
 
 namespace {
@@ -1437,40 +1331,6 @@ int check_exploitability(const pasur_fgt *const *fgts, int n_rounds, void *const
   return PASUR_OK;
 }
 
-// One mode over all rounds, last first: each round's leaves are its round
-// points plus the next round's value of the same mode at the linked root.
-int composed_values(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar,
-                    int dtype, int leaf_flags, int mode, double *out, hipStream_t s) {
-  double *V = nullptr;  // the later round's root values
-  for (int r = n_rounds - 1; r >= 0; --r) {
-    const pasur_fgt *f = fgts[r];
-    double *leaf = nullptr, *res = out;
-    hipError_t e = hipMallocAsync((void **)&leaf, f->n[8] * sizeof(double), s);
-    if (e == hipSuccess && r > 0) e = hipMallocAsync((void **)&res, f->n[0] * sizeof(double), s);
-    int st = PASUR_OK;
-    if (e != hipSuccess) {
-      set_error("hipMallocAsync: %s", hipGetErrorString(e));
-      st = PASUR_E_NOMEM;
-    } else {
-      const int8_t *b0 =
-          f->round == 5 && (leaf_flags & PASUR_LEAF_LITERAL_BONUS0) ? f->leaf_bonus : nullptr;
-      k_leaf_util<double><<<grid_for(f->n[8]), kThreads, 0, s>>>(f->n[8], f->leaf_base, f->link,
-                                                                 V, b0, leaf);
-      st = dtype == PASUR_F32
-               ? values_t<float, double>(f, leaf, sigma_bar + r * 9, mode, res, s)
-               : values_t<double, double>(f, leaf, sigma_bar + r * 9, mode, res, s);
-    }
-    if (leaf) (void)hipFreeAsync(leaf, s);
-    if (V) (void)hipFreeAsync(V, s);
-    V = r > 0 ? res : nullptr;
-    if (st != PASUR_OK) {
-      if (V && V != out) (void)hipFreeAsync(V, s);
-      return st;
-    }
-  }
-  return PASUR_OK;
-}
-
 }  // namespace
 
 extern "C" int pasur_exploitability(const pasur_fgt *const *fgts, int n_rounds,
@@ -1478,14 +1338,8 @@ extern "C" int pasur_exploitability(const pasur_fgt *const *fgts, int n_rounds,
                                     double *d_br_a, double *d_br_b, double *d_v, void *stream) {
   PASUR_TRY(check_exploitability(fgts, n_rounds, sigma_bar, dtype, leaf_flags, d_br_a, d_br_b,
                                  d_v));
-  hipStream_t s = (hipStream_t)stream;
-  double *outs[3] = {d_br_a, d_br_b, d_v};
-  const int modes[3] = {PASUR_TV_BR_A, PASUR_TV_BR_B, PASUR_TV_EXPECT};
-  for (int m = 0; m < 3; ++m)
-    if (outs[m])
-      PASUR_TRY(composed_values(fgts, n_rounds, sigma_bar, dtype, leaf_flags, modes[m], outs[m], s));
-  PASUR_TRY_HIP(hipGetLastError());
-  return PASUR_OK;
+  return composed_values(fgts, n_rounds, sigma_bar, dtype, leaf_flags, d_br_a, d_br_b, d_v,
+                         (hipStream_t)stream);
 }
 
 extern "C" int pasur_tree_values_noalloc(const pasur_fgt *f, const double *d_leaf, int dtype,
@@ -1494,20 +1348,12 @@ extern "C" int pasur_tree_values_noalloc(const pasur_fgt *f, const double *d_lea
   PASUR_TRY(check_tree_values(f, d_leaf, dtype, sigma, mode, d_out));
   const int64_t mx = widest_level(f);
   if (mx > kNoAllocLevel) {
-    set_error("a tree level of %lld nodes exceeds the %lld-node scratch of "
-              "pasur_tree_values_noalloc (use pasur_tree_values)",
+    set_error("a tree level of %lld nodes exceeds the %lld nodes that "
+              "pasur_tree_values_noalloc takes (use pasur_tree_values)",
               (long long)mx, (long long)kNoAllocLevel);
     return PASUR_E_CAPACITY;
   }
-  double *p = nullptr;
-  PASUR_TRY(scratch_for_current_device(&p));
-  hipStream_t s = (hipStream_t)stream;
-  if (dtype == PASUR_F32)
-    values_run<float, double>(f, d_leaf, sigma, mode, d_out, p, p + kNoAllocLevel, s);
-  else
-    values_run<double, double>(f, d_leaf, sigma, mode, d_out, p, p + kNoAllocLevel, s);
-  PASUR_TRY_HIP(hipGetLastError());
-  return PASUR_OK;
+  return tree_values(f, d_leaf, PASUR_F64, dtype, sigma, mode, d_out, (hipStream_t)stream);
 }
 
 extern "C" int pasur_profile_enable(int on) {

@@ -258,6 +258,14 @@ int sweep_iterate(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_param
 // schedule on this round (PASUR_SCHED_AUTO).
 bool sweep_pays(const pasur_fgt *f);
 
+// ---- exact values (pasur_values.hip) -----------------------------------------
+// Root values of one round from an array of leaf values (leaf_dtype; FP64
+// leaves when dtype is PASUR_F64), as pasur_tree_values.  Allocates nothing.
+int tree_values(const pasur_fgt *f, const void *leaf, int leaf_dtype, int dtype,
+                void *const *sigma, int mode, double *out, hipStream_t s);
+// pasur_exploitability on checked arguments.
+int composed_values(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar, int dtype,
+                    int leaf_flags, double *br_a, double *br_b, double *v, hipStream_t s);
 
 }  // namespace pasur
 
