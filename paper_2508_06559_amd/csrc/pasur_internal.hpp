@@ -164,52 +164,8 @@ inline IterK iter_k(const pasur_cfr_params *p, int64_t t) {
   return IterK{ic.dpos, ic.dneg, ic.avg_w, ic.avg_t};
 }
 
-// ---- wave-level helpers of the chunked up sweeps ----------------------------
-// The value of lane i-1 (lane_from_below) or lane i+1 (lane_from_above) of
-// the wave, by a DPP whole-wave shift; lane 0 (resp. 63) receives 0.
-__device__ __forceinline__ double lane_from_below(double v) {
-  const long long x = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), 0x138, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ double lane_from_above(double v) {
-  const long long x = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), 0x130, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Sum of v over each sibling group of the wave (the group's lanes are
-// consecutive; pos = index within the group, k = group size), added in
-// sibling order from 0.0 exactly as the sequential loop does, and returned
-// on every lane of the group.  Each step moves values one lane; the steps
-// stop once no lane of the wave needs another (kw = largest group of the
-// wave).  Must run with all lanes of the wave active.
-__device__ __forceinline__ double group_sum(double v, int pos, int k, int kw) {
-  double acc = 0.0 + v;
-  for (int s = 1; s < kw; ++s) {
-    const double prev = lane_from_below(acc);
-    acc = pos == s ? prev + v : acc;
-  }
-  for (int s = 1; s < kw; ++s) {
-    const double next = lane_from_above(acc);
-    acc = k - 1 - pos == s ? next : acc;
-  }
-  return acc;
-}
-
-// Largest value of x over the wave (x >= 0), as a wave-uniform scalar.
-__device__ __forceinline__ int wave_max(int x) {
-  int m = x;
-  m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x111, 0xF, 0xF, false));  // row_shr:1
-  m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x112, 0xF, 0xF, false));  // row_shr:2
-  m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x114, 0xF, 0xF, false));  // row_shr:4
-  m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x118, 0xF, 0xF, false));  // row_shr:8
-  m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x142, 0xF, 0xF, false));  // row_bcast:15
-  m = max(m, __builtin_amdgcn_update_dpp(0, m, 0x143, 0xF, 0xF, false));  // row_bcast:31
-  return __builtin_amdgcn_readlane(m, 63);
-}
+// The state's arrays are there and its type is known (pasur_cfr.hip).
+int check_state(const pasur_fgt *f, const pasur_cfr_state *st);
 
 // ---- optional per-launch timing (pasur_profile_enable) ------------------------
 struct ProfRec {
@@ -305,4 +261,7 @@ struct pasur_fgt {
   int32_t *h_root_off;  // 9 * (n_roots + 1), level-major
   // structure index of the streaming schedule, built on first use
   pasur::SweepIndex *sweep;
+  // per root, what a segment's LDS layout counts (4 ints: see pasur_seg.hip),
+  // on the host; computed on first use
+  int32_t *h_root_seg;
 };

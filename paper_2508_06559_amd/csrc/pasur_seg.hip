@@ -1,0 +1,1135 @@
+// pasur_seg.hip -- the persistent segment schedule of full-width DCFR (section
+// "CFR Algorithm": CodeSnippets FindReachProbability and FindUtility, equations
+// DFCR_REG, RM and DFCR_AVG) and the batched plans that launch it.
+//
+// The subgames below different roots never interact inside a round, so one
+// workgroup owns a segment -- a run of consecutive roots of one tree -- and
+// runs all iterations on it.  A launch can cover the trees of many deals.
+//
+// The segment lives in LDS in a compact form, made when the launch starts and
+// dissolved when it ends; no iteration touches memory.  What bounds an
+// iteration is then the dependent steps between the workgroup's barriers on
+// small launches, and the FP64 instructions on large ones.  Four choices serve
+// both; none changes a result:
+//
+//  * Forced chains are not iterated.  A node of level 6 or 7 whose whole
+//    subtree is one line (each player holds one card there, so most nodes of
+//    those levels are; called passive) keeps sigma = 1 and zero regret below
+//    itself and the utility of its leaf.  Its parent's update carries along
+//    the average sums of the at most two edges below it, and nothing else of
+//    them exists in LDS: about half of a tree's nodes.
+//  * Sibling groups in classes.  The active (non-passive) nodes of a level are
+//    ordered by their number of children k, and the j-th children of the n
+//    nodes of a class lie side by side: child j of a node is slot + j * n.  The
+//    64 parents of a wave then loop over the same k, without divergence, and
+//    read consecutive LDS words.
+//  * Values first, updates later.  Going up, only utilities pass between the
+//    levels; the regret, matching and average updates of all levels run
+//    together afterwards in one pass, each parent recomputing its own utility.
+//  * One reach per node.  An edge scales its mover's reach only, so a node
+//    stores the reach of the player who moved last; the other one's is its
+//    parent's.  Two consecutive levels then do not depend on each other, and go
+//    down in one step.
+//
+// An iteration takes one barrier per level above the topmost levels (which one
+// wave runs by itself while the others update) and one after the updates.
+// Every parent's sums run over its children in child order in FP64 without
+// contraction, whatever order the nodes are stored in: the state ends bit
+// for bit as with the level-synchronous kernels.
+//
+// A segment that does not fit (a root of more than about 14,000 nodes, a node
+// of more than 63 moves) is iterated in place in global memory, one phase per
+// level.
+#pragma clang fp contract(off)
+
+#include "pasur_internal.hpp"
+
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+#include <mutex>
+#include <vector>
+
+using namespace pasur;
+
+namespace {
+
+// One (tree, state) pair of a launch.
+template <class T>
+struct ItemDesc {
+  const int32_t *off[9];     // per-root level offsets
+  const int32_t *parent[9];  // levels 1..8
+  const int32_t *cb[9];      // levels 0..7
+  T *sigma[9], *R[9], *Sbar[9], *ra[9], *rb[9], *u[9];
+  double *vacc;
+};
+
+struct Seg {
+  int32_t item, j0, j1, pad;  // roots j0 .. j1-1 of item
+};
+
+// ---- the compact form ----------------------------------------------------------
+
+// What a segment's LDS layout depends on: active nodes (levels 0..7), their
+// children (edges), those of levels 6 and 7, roots, and the tree's nodes.
+struct SegCounts {
+  int na, ne, ne67, roots;
+  int c07, c6, c7;  // nodes of levels 0..7, of level 6, of level 7
+};
+
+// Byte offsets of a segment's arrays in LDS.  While the form is made, class
+// tables and a map from tree nodes to active nodes take the edge arrays'
+// place.
+struct SegLds {
+  uint32_t b6, b7;              // passive bits of levels 6 and 7
+  uint32_t tmp;                 // = the start of the edge arrays
+  uint32_t vacc;                // double per root: running sum of root utilities
+  uint32_t sg, u, r, s;         // T per edge; u also per root, after the edges
+  uint32_t s1, s2;              // T per edge of levels 6 and 7: average sums below it
+  uint32_t x;                   // T per active node, then per root: reaches
+  uint32_t slot, up, meta, pos; // words of an active node, see below
+  uint32_t bytes;
+};
+// Words of active node i:
+//   slot: slot of its first child | distance to the next child << 16
+//   up:   its own slot as a child | active node two levels up << 16
+//   meta: its parent | number of children << 16 | level << 24
+//   pos:  16 bits, its index within its level of the segment
+// A root's slot as a child is its place in u after the edges, and its parent
+// is its second entry of x (the reach of the player who moves first).
+
+constexpr int kClasses = 64;  // children per node: 0 .. 63
+constexpr uint32_t kTableBytes = 3 * 8 * kClasses * 4;
+
+__host__ __device__ inline uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
+
+__host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t) {
+  SegLds L;
+  uint32_t p = 0;
+  auto take = [&p](uint32_t bytes) {
+    const uint32_t at = p;
+    p = align16(p + bytes);
+    return at;
+  };
+  L.b6 = take((uint32_t)((c.c6 + 63) / 64) * 8u);
+  L.b7 = take((uint32_t)((c.c7 + 63) / 64) * 8u);
+  L.tmp = p;
+  const uint32_t tmp_end = p + kTableBytes + align16(2u * (uint32_t)c.c07);
+  L.sg = take(t * (uint32_t)c.ne);
+  L.u = take(t * (uint32_t)(c.ne + c.roots));
+  L.r = take(t * (uint32_t)c.ne);
+  L.s = take(t * (uint32_t)c.ne);
+  L.s1 = take(t * (uint32_t)c.ne67);
+  L.s2 = take(t * (uint32_t)c.ne67);
+  L.x = take(t * (uint32_t)(c.na + c.roots));
+  L.vacc = take(8u * (uint32_t)c.roots);
+  if (p < tmp_end) p = tmp_end;
+  L.slot = take(4u * (uint32_t)c.na);
+  L.up = take(4u * (uint32_t)c.na);
+  L.meta = take(4u * (uint32_t)c.na);
+  L.pos = take(2u * (uint32_t)c.na);
+  L.bytes = p;
+  return L;
+}
+// Indices are held in 16 bits.
+__host__ __device__ inline bool seg_indices_fit(const SegCounts &c) {
+  return c.ne + c.roots < 65536 && c.na + c.roots < 65536 && c.c07 < 8 * 65536;
+}
+
+extern __shared__ __align__(16) unsigned char g_lds[];
+// the segment's active nodes and edges per level (first index; [8], [9]: end)
+__shared__ int g_nb[9], g_sb[10];
+__shared__ int g_sum[2][8];
+__shared__ int g_bad;
+
+template <class T>
+__device__ __forceinline__ T *lds(uint32_t off) {
+  return reinterpret_cast<T *>(g_lds + off);
+}
+
+__device__ __forceinline__ bool bit_of(uint32_t off, int i) {
+  return (lds<uint32_t>(off)[i >> 5] >> (i & 31)) & 1u;
+}
+
+// LDS accesses of a wave run in order: between steps that one wave runs by
+// itself only the compiler has to keep them so.
+__device__ __forceinline__ void wave_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Makes the compact form of roots j0 .. j1-1; false (for every thread) if it
+// does not fit in lds_bytes.  `L` is the layout, g_nb and g_sb the levels.
+template <class T, int BLOCK>
+__device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, uint32_t lds_bytes,
+                                         SegLds &L, int &na, int &ne) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NW = BLOCK / 64;
+  SegCounts c;
+  c.roots = j1 - j0;
+  c.c07 = 0;
+  bool fits = true;
+  for (int l = 0; l < 8; ++l) {
+    const int n = D.off[l][j1] - D.off[l][j0];
+    if (n > 65535) fits = false;
+    c.c07 += fits ? n : 0;
+    if (l == 6) c.c6 = n;
+    if (l == 7) c.c7 = n;
+  }
+  if (!fits) return false;
+  // where bits, tables and the map go does not depend on the other counts
+  c.na = c.ne = c.ne67 = 0;
+  L = seg_layout(c, sizeof(T));
+  if (L.bytes > lds_bytes) return false;
+  uint32_t *const count = lds<uint32_t>(L.tmp);  // per level and class: nodes
+  uint32_t *const next = count + 8 * kClasses;   // next rank within the level
+  uint32_t *const first = next + 8 * kClasses;   // first slot - first rank
+  uint16_t *const map = lds<uint16_t>(L.tmp + kTableBytes);
+  // passive nodes: one child, along an edge of sigma 1, that is a leaf of
+  // finite utility or passive itself
+  if (tid == 0) g_bad = 0;
+  for (int i = tid; i < 8 * kClasses; i += BLOCK) count[i] = 0;
+  for (int l = 7; l >= 6; --l) {
+    const int n = l == 7 ? c.c7 : c.c6, h0 = D.off[l][j0], q0 = D.off[l + 1][j0];
+    const int32_t *const cb = D.cb[l];
+    for (int i = tid; i < ((n + 63) & ~63); i += BLOCK) {
+      bool p = false;
+      if (i < n) {
+        const int32_t q = cb[h0 + i];
+        p = cb[h0 + i + 1] - q == 1 && (double)D.sigma[l + 1][q] == 1.0;
+        if (p) p = l == 7 ? isfinite((double)D.u[8][q]) : bit_of(L.b7, q - q0);
+      }
+      const unsigned long long m = __ballot(p);
+      if (lane == 0) lds<unsigned long long>(l == 7 ? L.b7 : L.b6)[i >> 6] = m;
+    }
+    __syncthreads();
+  }
+  auto active = [&](int l, int i) {
+    return l < 6 || !bit_of(l == 6 ? L.b6 : L.b7, i);
+  };
+  for (int l = 0; l < 8; ++l) {
+    const int h0 = D.off[l][j0], n = D.off[l][j1] - h0;
+    for (int i = tid; i < n; i += BLOCK)
+      if (active(l, i)) {
+        const int k = D.cb[l][h0 + i + 1] - D.cb[l][h0 + i];
+        if (k < kClasses) atomicAdd(&count[l * kClasses + k], 1u);
+        else g_bad = 1;
+      }
+  }
+  __syncthreads();
+  if (g_bad) return false;
+  // classes in order of descending k: lane i of a wave takes k = 63 - i
+  for (int l = wave; l < 8; l += NW) {
+    const int k = kClasses - 1 - lane;
+    const int n = (int)count[l * kClasses + k];
+    int nodes = n, kids = n * k;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int a = __shfl_up(nodes, d, 64), b = __shfl_up(kids, d, 64);
+      if (lane >= d) {
+        nodes += a;
+        kids += b;
+      }
+    }
+    next[l * kClasses + k] = (uint32_t)(nodes - n);
+    first[l * kClasses + k] = (uint32_t)((kids - n * k) - (nodes - n));
+    if (lane == 63) {
+      g_sum[0][l] = nodes;
+      g_sum[1][l] = kids;
+    }
+  }
+  __syncthreads();
+  for (int l = 0; l < 8; ++l) {
+    c.na += g_sum[0][l];
+    c.ne += g_sum[1][l];
+    if (l == 5 || l == 6) c.ne67 += g_sum[1][l];
+  }
+  na = c.na;
+  ne = c.ne;
+  L = seg_layout(c, sizeof(T));
+  if (L.bytes > lds_bytes || !seg_indices_fit(c)) return false;
+  if (tid == 0) {
+    int a = 0, e = 0;
+    for (int l = 0; l < 8; ++l) {
+      g_nb[l] = a;
+      g_sb[l + 1] = e;
+      a += g_sum[0][l];
+      e += g_sum[1][l];
+    }
+    g_nb[8] = a;
+    g_sb[9] = e;
+  }
+  __syncthreads();
+  uint32_t *const w_slot = lds<uint32_t>(L.slot), *const w_up = lds<uint32_t>(L.up);
+  uint32_t *const w_meta = lds<uint32_t>(L.meta);
+  uint16_t *const w_pos = lds<uint16_t>(L.pos);
+  // every active node's place and its children's slots
+  for (int l = 0, at = 0; l < 8; ++l) {
+    const int h0 = D.off[l][j0], n = D.off[l][j1] - h0;
+    for (int i = tid; i < n; i += BLOCK)
+      if (active(l, i)) {
+        const int k = D.cb[l][h0 + i + 1] - D.cb[l][h0 + i];
+        const uint32_t rank = atomicAdd(&next[l * kClasses + k], 1u);
+        const uint32_t id = (uint32_t)g_nb[l] + rank;
+        w_slot[id] = ((uint32_t)g_sb[l + 1] + first[l * kClasses + k] + rank) |
+                     (count[l * kClasses + k] << 16);
+        w_meta[id] = ((uint32_t)k << 16) | ((uint32_t)l << 24);
+        w_pos[id] = (uint16_t)i;
+        map[at + i] = (uint16_t)id;
+      }
+    at += n;
+  }
+  __syncthreads();
+  // ancestors of an active node are active
+  for (int l = 0, at = 0, up = 0, up2 = 0; l < 8; ++l) {
+    const int h0 = D.off[l][j0], n = D.off[l][j1] - h0;
+    for (int i = tid; i < n; i += BLOCK)
+      if (active(l, i)) {
+        const uint32_t id = map[at + i];
+        uint32_t slot = (uint32_t)c.ne + id, par = (uint32_t)c.na + id, up_id = 0;
+        if (l > 0) {
+          const int p0 = D.off[l - 1][j0];
+          const int32_t h = D.parent[l][h0 + i];
+          par = map[up + (h - p0)];
+          const uint32_t w = w_slot[par];
+          slot = (w & 0xFFFFu) + (uint32_t)(h0 + i - D.cb[l - 1][h]) * (w >> 16);
+          up_id = l > 1 ? map[up2 + (D.parent[l - 1][h] - D.off[l - 2][j0])]
+                        : (uint32_t)c.na + par;
+        }
+        w_up[id] = slot | (up_id << 16);
+        w_meta[id] |= par;
+      }
+    up2 = up;
+    up = at;
+    at += n;
+  }
+  __syncthreads();
+  // the state; from here on the edge arrays take the tables' place
+  T *const sg = lds<T>(L.sg), *const uu = lds<T>(L.u), *const rr = lds<T>(L.r);
+  T *const ss = lds<T>(L.s), *const s1 = lds<T>(L.s1), *const s2 = lds<T>(L.s2);
+  const int e6 = g_sb[6];
+  for (int l = 0; l < 8; ++l) {
+    const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0];
+    const int end = g_nb[l + 1];
+    for (int id = g_nb[l] + tid; id < end; id += BLOCK) {
+      const int32_t b = D.cb[l][h0 + w_pos[id]];
+      const int k = (int)(w_meta[id] >> 16) & 0xFF;
+      int e = (int)(w_slot[id] & 0xFFFFu);
+      const int step = (int)(w_slot[id] >> 16);
+      for (int j = 0; j < k; ++j, e += step) {
+        const int32_t q = b + j;
+        sg[e] = D.sigma[l + 1][q];
+        rr[e] = D.R[l + 1][q];
+        ss[e] = D.Sbar[l + 1][q];
+        T v = (T)0, a1 = (T)0, a2 = (T)0;
+        if (l == 7) {
+          v = D.u[8][q];
+        } else if (l == 6) {
+          if (bit_of(L.b7, q - q0)) {
+            const int32_t q8 = D.cb[7][q];
+            v = (T)(0.0 + (double)D.u[8][q8]);
+            a1 = D.Sbar[8][q8];
+          }
+        } else if (l == 5) {
+          if (bit_of(L.b6, q - q0)) {
+            const int32_t q7 = D.cb[6][q], q8 = D.cb[7][q7];
+            v = (T)(0.0 + (double)D.u[8][q8]);
+            a1 = D.Sbar[7][q7];
+            a2 = D.Sbar[8][q8];
+          }
+        }
+        uu[e] = v;
+        if (l == 5 || l == 6) {
+          s1[e - e6] = a1;
+          s2[e - e6] = a2;
+        }
+      }
+    }
+  }
+  for (int id = tid; id < c.roots; id += BLOCK) {
+    const int64_t j = D.off[0][j0] + w_pos[id];
+    lds<T>(L.x)[id] = D.rb[0][j];
+    lds<T>(L.x)[c.na + id] = D.ra[0][j];
+    lds<double>(L.vacc)[id] = D.vacc[j];
+  }
+  __syncthreads();
+  return true;
+}
+
+// u of active node id: the sum of sigma * u over its children, in child order.
+template <class T>
+__device__ __forceinline__ double node_value(const T *sg, const T *uu, uint32_t w_slot, int k) {
+  int e = (int)(w_slot & 0xFFFFu);
+  const int step = (int)(w_slot >> 16);
+  double uh = 0.0;
+  for (int j = 0; j < k; ++j, e += step) uh += (double)sg[e] * (double)uu[e];
+  return uh;
+}
+
+__device__ __forceinline__ double matched(double R, int rm_mode, double eps) {
+  return rm_mode == PASUR_RM_FLOOR ? fmax(R, eps) : fmax(R, 0.0);
+}
+
+__device__ __forceinline__ double next_regret(double Rq, double r, const IterK &ik, int variant) {
+  if (variant == PASUR_DCFR) {
+    const double d = Rq > 0.0 ? ik.dpos : ik.dneg;
+    return d * Rq + r;
+  }
+  if (variant == PASUR_CFR_PLUS) {
+    const double x = Rq + r;
+    return x < 0.0 ? 0.0 : x;
+  }
+  return Rq + r;
+}
+
+// Regret, matching and average updates of one active node's children, and the
+// average sums of the chains below them.
+template <class T>
+__device__ __forceinline__ void node_update(const SegLds &L, int id, int e6, const IterK &ik,
+                                            int variant, int rm_mode, double eps) {
+  T *const sg = lds<T>(L.sg), *const rr = lds<T>(L.r), *const ss = lds<T>(L.s);
+  const T *const uu = lds<T>(L.u), *const x = lds<T>(L.x);
+  const uint32_t meta = lds<uint32_t>(L.meta)[id], w = lds<uint32_t>(L.slot)[id];
+  const int k = (int)(meta >> 16) & 0xFF, level = (int)(meta >> 24);
+  const int e0 = (int)(w & 0xFFFFu), step = (int)(w >> 16);
+  const double opp = (double)x[id], own = (double)x[meta & 0xFFFFu];
+  const double sgn = (level & 1) == 0 ? 1.0 : -1.0;
+  const double uh = node_value(sg, uu, w, k);
+  double sum = 0.0;
+  for (int j = 0, e = e0; j < k; ++j, e += step) {
+    const double r = sgn * opp * ((double)uu[e] - uh);
+    const T Rs = (T)next_regret((double)rr[e], r, ik, variant);
+    rr[e] = Rs;
+    sum += matched((double)Rs, rm_mode, eps);
+  }
+  const double inv_k = sum > 0.0 ? 0.0 : 1.0 / (double)k;
+  const bool chains = level == 5 || level == 6;
+  for (int j = 0, e = e0; j < k; ++j, e += step) {
+    const double m = matched((double)rr[e], rm_mode, eps);
+    const double s_new = sum > 0.0 ? m / sum : inv_k;
+    const double add = own * (double)sg[e];
+    ss[e] = (T)(ik.avg_w * (double)ss[e] + (variant == PASUR_CFR_PLUS ? add * ik.avg_t : add));
+    sg[e] = (T)s_new;
+    if (chains) {
+      // below a passive child first the other player moves (reach opp, as
+      // inherited), then the mover of this node (the child's own reach)
+      T *const s1 = lds<T>(L.s1) + (e - e6), *const s2 = lds<T>(L.s2) + (e - e6);
+      double a1 = opp, a2 = (double)(T)add;
+      if (variant == PASUR_CFR_PLUS) {
+        a1 *= ik.avg_t;
+        a2 *= ik.avg_t;
+      }
+      *s1 = (T)(ik.avg_w * (double)*s1 + a1);
+      *s2 = (T)(ik.avg_w * (double)*s2 + a2);
+    }
+  }
+}
+
+// Reach arrays of the segment's nodes below the roots, as the last iteration's
+// way down leaves them (before its updates).
+template <class T, int BLOCK>
+__device__ __forceinline__ void seg_store_reach(const ItemDesc<T> &D, int j0, const SegLds &L) {
+  const T *const sg = lds<T>(L.sg), *const x = lds<T>(L.x);
+  for (int l = 0; l < 7; ++l) {
+    const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0], end = g_nb[l + 1];
+    T *const moved = (l & 1) == 0 ? D.ra[l + 1] : D.rb[l + 1];
+    T *const kept = (l & 1) == 0 ? D.rb[l + 1] : D.ra[l + 1];
+    for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
+      const uint32_t meta = lds<uint32_t>(L.meta)[id], w = lds<uint32_t>(L.slot)[id];
+      const int32_t b = D.cb[l][h0 + lds<uint16_t>(L.pos)[id]];
+      const int k = (int)(meta >> 16) & 0xFF;
+      const T opp = x[id];
+      const double own = (double)x[meta & 0xFFFFu];
+      int e = (int)(w & 0xFFFFu);
+      for (int j = 0; j < k; ++j, e += (int)(w >> 16)) {
+        const int32_t q = b + j;
+        const T v = (T)(own * (double)sg[e]);
+        moved[q] = v;
+        kept[q] = opp;
+        if (l == 5 && bit_of(L.b6, q - q0)) {
+          const int32_t q7 = D.cb[6][q];  // level 6's mover moves on with probability 1
+          D.rb[7][q7] = v;
+          D.ra[7][q7] = opp;
+        }
+      }
+    }
+  }
+}
+
+// A chain edge's regret after the call's iterations: each adds a regret of
+// zero (the edge is forced) to the discounted one.
+template <class T>
+__device__ __forceinline__ void chain_regret(T *R, double sgn, const IterK *ks, int n_iters,
+                                             int variant) {
+  T v = *R;
+  if (v == (T)0 && !signbit((double)v)) return;
+  for (int it = 0; it < n_iters; ++it)
+    v = (T)next_regret((double)v, sgn * 0.0, ks[it], variant);
+  *R = v;
+}
+
+// The state back into the level arrays.
+template <class T, int BLOCK>
+__device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int roots, const SegLds &L,
+                                          int na, int ne, const IterK *ks, int n_iters,
+                                          int variant) {
+  const T *const sg = lds<T>(L.sg), *const uu = lds<T>(L.u), *const rr = lds<T>(L.r);
+  const T *const ss = lds<T>(L.s), *const s1 = lds<T>(L.s1), *const s2 = lds<T>(L.s2);
+  const int e6 = g_sb[6];
+  for (int l = 0; l < 8; ++l) {
+    const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0], end = g_nb[l + 1];
+    for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
+      const uint32_t meta = lds<uint32_t>(L.meta)[id], w = lds<uint32_t>(L.slot)[id];
+      const int32_t b = D.cb[l][h0 + lds<uint16_t>(L.pos)[id]];
+      const int k = (int)(meta >> 16) & 0xFF;
+      int e = (int)(w & 0xFFFFu);
+      for (int j = 0; j < k; ++j, e += (int)(w >> 16)) {
+        const int32_t q = b + j;
+        D.sigma[l + 1][q] = sg[e];
+        D.R[l + 1][q] = rr[e];
+        D.Sbar[l + 1][q] = ss[e];
+        if (l < 7) D.u[l + 1][q] = uu[e];
+        if (l == 5 && bit_of(L.b6, q - q0)) {
+          const int32_t q7 = D.cb[6][q], q8 = D.cb[7][q7];
+          D.u[7][q7] = uu[e];
+          D.Sbar[7][q7] = s1[e - e6];
+          D.Sbar[8][q8] = s2[e - e6];
+          chain_regret(D.R[7] + q7, 1.0, ks, n_iters, variant);
+          chain_regret(D.R[8] + q8, -1.0, ks, n_iters, variant);
+        } else if (l == 6 && bit_of(L.b7, q - q0)) {
+          const int32_t q8 = D.cb[7][q];
+          D.Sbar[8][q8] = s1[e - e6];
+          chain_regret(D.R[8] + q8, -1.0, ks, n_iters, variant);
+        }
+      }
+    }
+  }
+  for (int id = threadIdx.x; id < roots; id += BLOCK) {
+    const int64_t j = D.off[0][j0] + lds<uint16_t>(L.pos)[id];
+    D.u[0][j] = uu[ne + id];
+    D.vacc[j] = lds<double>(L.vacc)[id];
+  }
+}
+
+// All iterations of one segment in its compact form.  PAPER fixes the paper's
+// variant (DCFR with the regret floor) at compile time.
+template <class T, int BLOCK, bool PAPER>
+__device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1, const SegLds &L,
+                                           int na, int ne, const IterK *__restrict__ ks,
+                                           int n_iters, int variant, int rm_mode, double eps) {
+  if (PAPER) {
+    variant = PASUR_DCFR;
+    rm_mode = PASUR_RM_FLOOR;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const T *const sg = lds<T>(L.sg);
+  T *const uu = lds<T>(L.u), *const x = lds<T>(L.x);
+  double *const vacc = lds<double>(L.vacc);
+  const uint32_t *const w_slot = lds<uint32_t>(L.slot), *const w_up = lds<uint32_t>(L.up);
+  const uint32_t *const w_meta = lds<uint32_t>(L.meta);
+  // the levels' first nodes, one per lane, read as wave-uniform scalars
+  const int nb_lane = lane <= 8 ? g_nb[lane] : na;
+  auto nb = [&](int l) { return __builtin_amdgcn_readlane(nb_lane, l); };
+  const int e6 = __builtin_amdgcn_readfirstlane(g_sb[6]);
+  int bottom = 7;  // deepest level with active nodes
+  while (bottom > 0 && nb(bottom + 1) == nb(bottom)) --bottom;
+  // levels 0 .. top-1 hold at most 64 nodes and belong to wave 0, a lane each
+  int top = 0;
+  while (top < 5 && nb(top + 1) <= 64) ++top;
+  const int n_top = nb(top);
+  const int down0 = top > 0 ? 1 : 0;         // first interval with a step down
+  const int first_down = top > 0 ? top : 1;  // its first level
+  const int n_up = bottom - top + 1, n_down = (bottom - first_down + 2) / 2;
+  const int n_int = n_up > down0 + n_down ? n_up : down0 + n_down;
+
+  auto value = [&](int id) {
+    const double uh = node_value<T>(sg, uu, w_slot[id], (int)(w_meta[id] >> 16) & 0xFF);
+    uu[w_up[id] & 0xFFFFu] = (T)uh;
+    return uh;
+  };
+  auto down = [&](int id) {
+    const uint32_t w = w_up[id];
+    x[id] = (T)((double)x[w >> 16] * (double)sg[w & 0xFFFFu]);
+  };
+
+  for (int it = 0; it < n_iters; ++it) {
+    // utilities go up from the bottom level to `top`, one level per interval,
+    // while reaches go down, two levels per interval
+    for (int iv = 0; iv < n_int; ++iv) {
+      const int ul = bottom - iv;
+      if (iv == 0 && top > 0) {
+        if (wave == 0) {
+          for (int l = 1; l < top; l += 2) {
+            if (lane >= nb(l) && lane < nb(l + 2 < top ? l + 2 : top)) down(lane);
+            wave_order();
+          }
+        } else {
+          for (int id = nb(ul) + tid - 64; id < nb(ul + 1); id += BLOCK - 64) value(id);
+        }
+      } else {
+        if (ul >= top)
+          for (int id = nb(ul) + tid; id < nb(ul + 1); id += BLOCK) {
+            const double uh = value(id);
+            if (ul == 0) vacc[id] += uh;
+          }
+        const int dl = first_down + 2 * (iv - down0);
+        if (dl <= bottom)
+          for (int id = nb(dl) + tid; id < nb(dl + 2 < 8 ? dl + 2 : 8); id += BLOCK) down(id);
+      }
+      __syncthreads();
+    }
+    if (it == n_iters - 1) {
+      seg_store_reach<T, BLOCK>(D, j0, L);
+      __syncthreads();
+    }
+    // updates of all levels; wave 0 finishes the top levels' utilities first,
+    // whose strategies no other wave changes
+    const IterK k = ks[it];
+    if (top > 0 && wave == 0) {
+      for (int l = top - 1; l >= 0; --l) {
+        if (lane >= nb(l) && lane < nb(l + 1)) {
+          const double uh = value(lane);
+          if (l == 0) vacc[lane] += uh;
+        }
+        wave_order();
+      }
+      if (lane < n_top) node_update<T>(L, lane, e6, k, variant, rm_mode, eps);
+    } else {
+      const int t = top > 0 ? tid - 64 : tid, nt = top > 0 ? BLOCK - 64 : BLOCK;
+      for (int id = n_top + t; id < na; id += nt)
+        node_update<T>(L, id, e6, k, variant, rm_mode, eps);
+    }
+    __syncthreads();
+  }
+  seg_store<T, BLOCK>(D, j0, j1 - j0, L, na, ne, ks, n_iters, variant);
+}
+
+// ---- in global memory ------------------------------------------------------------
+// Global-memory arrays addressed through a per-workgroup pointer table kept
+// in LDS, so that the 72 per-level pointers are not all live in registers.
+__shared__ void *g_ptab[8][9];
+__shared__ int g_lo[9], g_cnt[9];
+
+template <class T, int SLOT>
+struct TabArr {
+  int l;
+  __device__ __forceinline__ T &operator[](int i) const { return reinterpret_cast<T *>(g_ptab[SLOT][l])[i]; }
+};
+
+// FindUtility for the parents of level L-1, one thread each, over their
+// children in child order.
+template <class T, int L>
+__device__ __forceinline__ void up_global(double *vacc, const IterK &ik, int variant, int rm_mode,
+                                          double eps) {
+  constexpr int mover = (L - 1) & 1;
+  const TabArr<T, 0> sg{L};
+  const TabArr<T, 1> Rr{L};
+  const TabArr<T, 2> Sb{L};
+  const TabArr<T, 3> uu{L};
+  const double sgn = mover == 0 ? 1.0 : -1.0;
+  int t0 = threadIdx.x;
+  asm volatile("" : "+v"(t0));  // per-lane start stays inside the phase
+  for (int h = t0; h < g_cnt[L - 1]; h += blockDim.x) {
+    const int b = TabArr<const int32_t, 7>{L - 1}[h] - g_lo[L];
+    const int e = TabArr<const int32_t, 7>{L - 1}[h + 1] - g_lo[L];
+    const double ra = (double)TabArr<T, 4>{L - 1}[h], rb = (double)TabArr<T, 5>{L - 1}[h];
+    const double opp = mover == 0 ? rb : ra, own = mover == 0 ? ra : rb;
+    double uh = 0.0;
+    for (int q = b; q < e; ++q) uh += (double)sg[q] * (double)uu[q];
+    double sum = 0.0;
+    for (int q = b; q < e; ++q) {
+      const double r = sgn * opp * ((double)uu[q] - uh);
+      const T Rs = (T)next_regret((double)Rr[q], r, ik, variant);
+      Rr[q] = Rs;
+      sum += matched((double)Rs, rm_mode, eps);
+    }
+    const double inv_k = sum > 0.0 ? 0.0 : 1.0 / (double)(e - b);
+    for (int q = b; q < e; ++q) {
+      const double m = matched((double)Rr[q], rm_mode, eps);
+      const double s_new = sum > 0.0 ? m / sum : inv_k;
+      double add = own * (double)sg[q];
+      if (variant == PASUR_CFR_PLUS) add *= ik.avg_t;
+      Sb[q] = (T)(ik.avg_w * (double)Sb[q] + add);
+      sg[q] = (T)s_new;
+    }
+    TabArr<T, 3>{L - 1}[h] = (T)uh;
+    if (L == 1) vacc[h] += uh;
+  }
+  __syncthreads();
+}
+
+template <class T, int BLOCK, bool PAPER>
+__device__ __forceinline__ void seg_in_global(const ItemDesc<T> &D, int j0, int j1,
+                                              const IterK *__restrict__ ks, int n_iters,
+                                              int variant, int rm_mode, double eps) {
+  if (PAPER) {
+    variant = PASUR_DCFR;
+    rm_mode = PASUR_RM_FLOOR;
+  }
+  if (threadIdx.x < 9) {
+    const int l = threadIdx.x, lo = D.off[l][j0];
+    g_ptab[0][l] = l >= 1 ? (void *)(D.sigma[l] + lo) : nullptr;
+    g_ptab[1][l] = l >= 1 ? (void *)(D.R[l] + lo) : nullptr;
+    g_ptab[2][l] = l >= 1 ? (void *)(D.Sbar[l] + lo) : nullptr;
+    g_ptab[3][l] = (void *)(D.u[l] + lo);
+    g_ptab[4][l] = l <= 7 ? (void *)(D.ra[l] + lo) : nullptr;
+    g_ptab[5][l] = l <= 7 ? (void *)(D.rb[l] + lo) : nullptr;
+    g_ptab[6][l] = l >= 1 ? (void *)(D.parent[l] + lo) : nullptr;
+    g_ptab[7][l] = l <= 7 ? (void *)(D.cb[l] + lo) : nullptr;
+    g_lo[l] = lo;
+    g_cnt[l] = D.off[l][j1] - lo;
+  }
+  __syncthreads();
+  double *const vacc = D.vacc + j0;
+  for (int it = 0; it < n_iters; ++it) {
+    const IterK k = ks[it];
+    // FindReachProbability, two levels per phase: a node of the second level
+    // starts from its grandparent's reaches and applies its parent's and its
+    // own action probability, rounding to T after each level
+#pragma unroll
+    for (int l = 1; l <= 7; l += 2) {
+      const int l2 = l < 7 ? l + 1 : 0;  // second level of the phase (0: none)
+      const int n1 = g_cnt[l], n2 = l2 ? g_cnt[l2] : 0;
+      int t0 = threadIdx.x;
+      asm volatile("" : "+v"(t0));
+      for (int i = t0; i < n1 + n2; i += BLOCK) {
+        const bool second = i >= n1;
+        const int q = second ? i - n1 : i;
+        const int h1 = second ? TabArr<const int32_t, 6>{l2}[q] - g_lo[l] : q;
+        const int g = TabArr<const int32_t, 6>{l}[h1] - g_lo[l - 1];
+        double a = (double)TabArr<T, 4>{l - 1}[g], b = (double)TabArr<T, 5>{l - 1}[g];
+        const double s1 = (double)TabArr<T, 0>{l}[h1];
+        if (((l - 1) & 1) == 0) a *= s1;
+        else b *= s1;
+        a = (double)(T)a;
+        b = (double)(T)b;
+        if (second) {
+          const double s2 = (double)TabArr<T, 0>{l2}[q];
+          if ((l & 1) == 0) a *= s2;
+          else b *= s2;
+        }
+        TabArr<T, 4>{second ? l2 : l}[q] = (T)a;
+        TabArr<T, 5>{second ? l2 : l}[q] = (T)b;
+      }
+      __syncthreads();
+    }
+    up_global<T, 8>(vacc, k, variant, rm_mode, eps);
+    up_global<T, 7>(vacc, k, variant, rm_mode, eps);
+    up_global<T, 6>(vacc, k, variant, rm_mode, eps);
+    up_global<T, 5>(vacc, k, variant, rm_mode, eps);
+    up_global<T, 4>(vacc, k, variant, rm_mode, eps);
+    up_global<T, 3>(vacc, k, variant, rm_mode, eps);
+    up_global<T, 2>(vacc, k, variant, rm_mode, eps);
+    up_global<T, 1>(vacc, k, variant, rm_mode, eps);
+  }
+}
+
+// One workgroup per segment; the segment runs in LDS when its compact form
+// fits in the launch's dynamic LDS (lds_bytes), otherwise in global memory.
+template <class T, int BLOCK, bool PAPER>
+__global__ void __launch_bounds__(BLOCK)
+    k_cfr_seg(const ItemDesc<T> *__restrict__ items, const Seg *__restrict__ segs,
+              const IterK *__restrict__ ks, int n_iters, int variant, int rm_mode, double eps,
+              uint32_t lds_bytes) {
+  const Seg sg = segs[blockIdx.x];
+  const ItemDesc<T> &D = items[sg.item];
+  SegLds L;
+  int na = 0, ne = 0;
+  if (seg_load<T, BLOCK>(D, sg.j0, sg.j1, lds_bytes, L, na, ne))
+    seg_in_lds<T, BLOCK, PAPER>(D, sg.j0, sg.j1, L, na, ne, ks, n_iters, variant, rm_mode, eps);
+  else
+    seg_in_global<T, BLOCK, PAPER>(D, sg.j0, sg.j1, ks, n_iters, variant, rm_mode, eps);
+}
+
+// Per root, what the tree's structure says of its compact form on levels 6 and
+// 7: active nodes of level 6 and of level 7, and the children of either.
+__global__ void __launch_bounds__(64) k_seg_counts(const int32_t *__restrict__ off6,
+                                                   const int32_t *__restrict__ off7,
+                                                   const int32_t *__restrict__ cb6,
+                                                   const int32_t *__restrict__ cb7,
+                                                   int32_t *__restrict__ out) {
+  const int64_t j = blockIdx.x;
+  int v[4] = {0, 0, 0, 0};
+  for (int i = off6[j] + (int)threadIdx.x; i < off6[j + 1]; i += 64) {
+    const int32_t b = cb6[i], k = cb6[i + 1] - b;
+    if (k != 1 || cb7[b + 1] - cb7[b] != 1) {
+      v[0] += 1;
+      v[2] += k;
+    }
+  }
+  for (int i = off7[j] + (int)threadIdx.x; i < off7[j + 1]; i += 64) {
+    const int32_t k = cb7[i + 1] - cb7[i];
+    if (k != 1) {
+      v[1] += 1;
+      v[3] += k;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v[m] += __shfl_xor(v[m], d, 64);
+    if (threadIdx.x == 0) out[4 * j + m] = v[m];
+  }
+}
+
+constexpr uint32_t kLdsPerWorkgroup = 160 * 1024;
+// static LDS: the global-memory path's pointer table, the levels' bounds
+constexpr uint32_t kStaticLds = 1024;
+
+inline bool paper_variant(int variant, int rm_mode) {
+  return variant == PASUR_DCFR && rm_mode == PASUR_RM_FLOOR;
+}
+
+template <class T, int BLOCK>
+void *seg_kernel(bool paper) {
+  return paper ? (void *)k_cfr_seg<T, BLOCK, true> : (void *)k_cfr_seg<T, BLOCK, false>;
+}
+
+std::mutex g_counts_mu;
+
+int root_counts(pasur_fgt *f, hipStream_t s) {
+  std::lock_guard<std::mutex> lock(g_counts_mu);
+  if (f->h_root_seg) return PASUR_OK;
+  const size_t n = 4 * (size_t)f->n_roots;
+  int32_t *d = nullptr;
+  PASUR_TRY(dev_alloc(&d, (int64_t)n));
+  int32_t *h = (int32_t *)std::malloc(n * sizeof(int32_t));
+  if (!h) {
+    dev_free(d);
+    set_error("host allocation failed");
+    return PASUR_E_NOMEM;
+  }
+  k_seg_counts<<<(unsigned)f->n_roots, 64, 0, s>>>(f->root_off[6], f->root_off[7],
+                                                   f->child_begin[6], f->child_begin[7], d);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpyAsync(h, d, n * sizeof(int32_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  dev_free(d);
+  if (e != hipSuccess) {
+    std::free(h);
+    set_error("segment counts: %s", hipGetErrorString(e));
+    return PASUR_E_HIP;
+  }
+  f->h_root_seg = h;
+  return PASUR_OK;
+}
+
+// One kernel launch of a plan: consecutive segments with the same LDS size.
+struct SegLaunch {
+  int first, count, block;
+  uint32_t lds_bytes;
+};
+
+}  // namespace
+
+struct pasur_plan {
+  int dtype, block, variant, rm_mode;
+  double eps;
+  int64_t t_first, t_last;
+  int n_items, n_segs;
+  void *d_items;
+  Seg *d_segs;
+  IterK *d_ks;
+  uint32_t lds_bytes;
+  int64_t work[4];  // edges, internal nodes, roots, level-7 nodes
+  int64_t n_lds_segs;
+  std::vector<SegLaunch> launches;
+};
+
+namespace {
+
+struct SegPlan {
+  Seg seg;
+  int64_t nodes;
+  uint32_t bytes;  // of its compact form, 0: in global memory
+};
+
+// Launches of segments ordered by descending size, those in global memory
+// first.  A launch's workgroups all hold the LDS of its largest segment, so
+// segments of which more fit on a CU get a launch of their own, unless there
+// are too few of them to fill the chip; segments in global memory, the longest
+// of all, run beside the largest ones.
+void plan_launches(pasur_plan *pl, const std::vector<SegPlan> &segs, int user_block) {
+  constexpr int kCus = 256;
+  auto per_cu = [](uint32_t bytes) {
+    const int n = (int)(kLdsPerWorkgroup / (bytes + kStaticLds));
+    return bytes == 0 || n < 1 ? 1 : n > 4 ? 4 : n;
+  };
+  const int n = (int)segs.size();
+  for (int i = 0; i < n;) {
+    SegLaunch la;
+    const int c = per_cu(segs[(size_t)i].bytes);
+    int j = i;
+    la.lds_bytes = 0;
+    while (j < n && per_cu(segs[(size_t)j].bytes) == c) {
+      la.lds_bytes = std::max(la.lds_bytes, segs[(size_t)j].bytes);
+      ++j;
+    }
+    if (n - j < kCus && j < n) {
+      la.lds_bytes = std::max(la.lds_bytes, segs[(size_t)j].bytes);
+      j = n;
+    }
+    la.first = i;
+    la.count = j - i;
+    la.block = user_block ? user_block : la.count <= kCus || c == 1 ? 1024 : c == 2 ? 512 : 256;
+    pl->launches.push_back(la);
+    i = j;
+  }
+}
+
+template <class T>
+int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_state *const *states,
+               const pasur_cfr_params *p, int force_global, hipStream_t s) {
+  const int n_items = pl->n_items;
+  std::vector<ItemDesc<T>> items((size_t)n_items);
+  std::vector<SegPlan> segs;
+  const uint32_t budget = force_global ? 0u : kLdsPerWorkgroup - kStaticLds;
+  for (int64_t k = 0; k < 4; ++k) pl->work[k] = 0;
+  pl->n_lds_segs = 0;
+  for (int it = 0; it < n_items; ++it) {
+    const pasur_fgt *f = fgts[it];
+    const pasur_cfr_state *st = states[it];
+    PASUR_TRY(root_counts(const_cast<pasur_fgt *>(f), s));
+    ItemDesc<T> &D = items[(size_t)it];
+    for (int l = 0; l <= 8; ++l) {
+      D.off[l] = f->root_off[l];
+      D.parent[l] = f->parent[l];
+      D.cb[l] = l <= 7 ? f->child_begin[l] : nullptr;
+      D.sigma[l] = l >= 1 ? (T *)st->sigma[l] : nullptr;
+      D.R[l] = l >= 1 ? (T *)st->R[l] : nullptr;
+      D.Sbar[l] = l >= 1 ? (T *)st->Sbar[l] : nullptr;
+      D.ra[l] = l <= 7 ? (T *)st->reachA[l] : nullptr;
+      D.rb[l] = l <= 7 ? (T *)st->reachB[l] : nullptr;
+      D.u[l] = (T *)st->u[l];
+    }
+    D.vacc = st->vacc;
+    // Segments: runs of consecutive roots, closed when the next root would
+    // exceed seg_nodes nodes, the workgroup's thread count, or LDS.
+    const int64_t nr = f->n_roots;
+    auto level_nodes = [&](int l, int64_t j) {
+      const int32_t *o = f->h_root_off + (size_t)l * (nr + 1);
+      return o[j + 1] - o[j];
+    };
+    auto add_root = [&](SegCounts &c, int64_t &tot, int64_t j) {
+      int n[9], c07 = 0, ne = 0;
+      for (int l = 0; l <= 8; ++l) n[l] = level_nodes(l, j);
+      for (int l = 0; l <= 7; ++l) c07 += n[l];
+      for (int l = 1; l <= 6; ++l) ne += n[l];
+      const int32_t *x = f->h_root_seg + 4 * j;
+      c.na += c07 - n[6] - n[7] + x[0] + x[1];
+      c.ne += ne + x[2] + x[3];
+      c.ne67 += n[6] + x[2];
+      c.roots += 1;
+      c.c07 += c07;
+      c.c6 += n[6];
+      c.c7 += n[7];
+      tot += c07 + n[8];
+    };
+    auto bytes_of = [&](const SegCounts &c) -> uint32_t {
+      if (c.c6 > 65535 || c.c7 > 65535 || !seg_indices_fit(c)) return 0u;
+      const uint32_t b = seg_layout(c, sizeof(T)).bytes;
+      return b <= budget ? b : 0u;
+    };
+    int64_t j0 = 0;
+    while (j0 < nr) {
+      int64_t j1 = j0 + 1, tot = 0;
+      SegCounts c = {};
+      add_root(c, tot, j0);
+      uint32_t bytes = bytes_of(c);
+      while (p->seg_nodes > 0 && bytes && j1 < nr && j1 - j0 < pl->block) {
+        SegCounts c2 = c;
+        int64_t t2 = tot;
+        add_root(c2, t2, j1);
+        const uint32_t b2 = bytes_of(c2);
+        if (t2 > p->seg_nodes || !b2) break;
+        ++j1;
+        c = c2;
+        tot = t2;
+        bytes = b2;
+      }
+      if (bytes) pl->n_lds_segs += 1;
+      SegPlan sp;
+      sp.seg.item = it;
+      sp.seg.j0 = (int32_t)j0;
+      sp.seg.j1 = (int32_t)j1;
+      sp.seg.pad = 0;
+      sp.nodes = tot;
+      sp.bytes = bytes;
+      segs.push_back(sp);
+      j0 = j1;
+    }
+    for (int l = 1; l <= 8; ++l) pl->work[0] += f->n[l];
+    for (int l = 0; l <= 7; ++l) pl->work[1] += f->n[l];
+    pl->work[2] += f->n[0];
+    pl->work[3] += f->n[7];
+  }
+  // segments in global memory first, then the largest
+  std::stable_sort(segs.begin(), segs.end(), [](const SegPlan &a, const SegPlan &b) {
+    if ((a.bytes == 0) != (b.bytes == 0)) return a.bytes == 0;
+    return a.bytes ? a.bytes > b.bytes : a.nodes > b.nodes;
+  });
+  std::vector<Seg> sorted(segs.size());
+  uint32_t max_bytes = 0;
+  for (size_t i = 0; i < segs.size(); ++i) {
+    sorted[i] = segs[i].seg;
+    max_bytes = std::max(max_bytes, segs[i].bytes);
+  }
+  pl->n_segs = (int)sorted.size();
+  pl->lds_bytes = max_bytes;
+  plan_launches(pl, segs, p->block);
+  // iteration constants for t_first .. t_last, computed on the host
+  const int64_t nt = pl->t_last - pl->t_first + 1;
+  std::vector<IterK> ks((size_t)nt);
+  for (int64_t i = 0; i < nt; ++i) ks[(size_t)i] = iter_k(p, pl->t_first + i);
+  PASUR_TRY_HIP(hipMalloc(&pl->d_items, sizeof(ItemDesc<T>) * items.size()));
+  PASUR_TRY_HIP(hipMalloc((void **)&pl->d_segs, sizeof(Seg) * (sorted.size() + 1)));
+  PASUR_TRY_HIP(hipMalloc((void **)&pl->d_ks, sizeof(IterK) * ks.size()));
+  PASUR_TRY_HIP(hipMemcpyAsync(pl->d_items, items.data(), sizeof(ItemDesc<T>) * items.size(),
+                               hipMemcpyHostToDevice, s));
+  PASUR_TRY_HIP(hipMemcpyAsync(pl->d_segs, sorted.data(), sizeof(Seg) * sorted.size(),
+                               hipMemcpyHostToDevice, s));
+  PASUR_TRY_HIP(hipMemcpyAsync(pl->d_ks, ks.data(), sizeof(IterK) * ks.size(),
+                               hipMemcpyHostToDevice, s));
+  PASUR_TRY_HIP(hipStreamSynchronize(s));  // host staging vectors go out of scope
+  const bool paper = paper_variant(p->variant, p->rm_mode);
+  // The attribute is a ceiling shared by every plan of this instance, so it
+  // is raised to the whole budget (plans may be launched in any order); each
+  // launch still asks for its own lds_bytes.
+  for (const SegLaunch &la : pl->launches) {
+    void *kern = la.block == 256   ? seg_kernel<T, 256>(paper)
+                 : la.block == 512 ? seg_kernel<T, 512>(paper)
+                                   : seg_kernel<T, 1024>(paper);
+    PASUR_TRY_HIP(hipFuncSetAttribute((const void *)kern,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)(kLdsPerWorkgroup - kStaticLds)));
+  }
+  return PASUR_OK;
+}
+
+template <class T, int BLOCK>
+void plan_launch(const pasur_plan *pl, const SegLaunch &la, int64_t t0, int n_iters,
+                 hipStream_t s) {
+  auto kern = paper_variant(pl->variant, pl->rm_mode) ? k_cfr_seg<T, BLOCK, true>
+                                                      : k_cfr_seg<T, BLOCK, false>;
+  kern<<<(unsigned)la.count, BLOCK, la.lds_bytes, s>>>(
+      (const ItemDesc<T> *)pl->d_items, pl->d_segs + la.first, pl->d_ks + (t0 - pl->t_first),
+      n_iters, pl->variant, pl->rm_mode, pl->eps, la.lds_bytes);
+}
+
+}  // namespace
+
+extern "C" void pasur_plan_free(pasur_plan *pl) {
+  if (!pl) return;
+  if (pl->d_items) (void)hipFree(pl->d_items);
+  if (pl->d_segs) (void)hipFree(pl->d_segs);
+  if (pl->d_ks) (void)hipFree(pl->d_ks);
+  delete pl;
+}
+
+extern "C" int pasur_plan_create(const pasur_fgt *const *fgts,
+                                 const pasur_cfr_state *const *states, int n_items,
+                                 const pasur_cfr_params *p, int64_t t_first, int64_t t_last,
+                                 pasur_plan **out, void *stream) {
+  if (!out || !fgts || !states || !p || n_items < 1) {
+    set_error("null argument or empty batch");
+    return PASUR_E_INVAL;
+  }
+  *out = nullptr;
+  if (t_first < 1 || t_last < t_first) {
+    set_error("need 1 <= t_first <= t_last");
+    return PASUR_E_RANGE;
+  }
+  if (p->variant < 0 || p->variant > 2 || p->rm_mode < 0 || p->rm_mode > 1 ||
+      p->schedule < 0 || p->schedule > PASUR_SCHED_AUTO || p->seg_nodes < 0 ||
+      (p->block != 0 && p->block != 256 && p->block != 512 && p->block != 1024)) {
+    set_error("unknown variant, regret-matching mode, schedule, block or segment size");
+    return PASUR_E_RANGE;
+  }
+  if (p->schedule == PASUR_SCHED_LEVEL_SYNC || p->schedule == PASUR_SCHED_STREAM) {
+    set_error("plans use the persistent segment schedule");
+    return PASUR_E_RANGE;
+  }
+  if (p->flags) {
+    set_error("the snippet flags run on PASUR_SCHED_LEVEL_SYNC only, not in plans");
+    return PASUR_E_RANGE;
+  }
+  if (!states[0]) {
+    set_error("item 0 is NULL");
+    return PASUR_E_INVAL;
+  }
+  const int dtype = states[0]->dtype;
+  for (int i = 0; i < n_items; ++i) {
+    if (!fgts[i] || !states[i]) {
+      set_error("item %d is NULL", i);
+      return PASUR_E_INVAL;
+    }
+    PASUR_TRY(check_state(fgts[i], states[i]));
+    if (states[i]->dtype != dtype) {
+      set_error("all items of a plan need the same dtype");
+      return PASUR_E_INVAL;
+    }
+  }
+  pasur_plan *pl = new pasur_plan();
+  pl->dtype = dtype;
+  pl->block = p->block ? p->block : 1024;
+  pl->variant = p->variant;
+  pl->rm_mode = p->rm_mode;
+  pl->eps = p->eps;
+  pl->t_first = t_first;
+  pl->t_last = t_last;
+  pl->n_items = n_items;
+  hipStream_t s = (hipStream_t)stream;
+  const int fg = p->schedule == PASUR_SCHED_ROOT_GLOBAL;
+  int st = dtype == PASUR_F32 ? plan_build<float>(pl, fgts, states, p, fg, s)
+                              : plan_build<double>(pl, fgts, states, p, fg, s);
+  if (st) {
+    pasur_plan_free(pl);
+    return st;
+  }
+  *out = pl;
+  return PASUR_OK;
+}
+
+extern "C" int pasur_plan_iterate(const pasur_plan *pl, int64_t t0, int n_iters, void *stream) {
+  if (!pl) {
+    set_error("plan is NULL");
+    return PASUR_E_INVAL;
+  }
+  if (n_iters < 0 || t0 < pl->t_first || t0 + n_iters - 1 > pl->t_last) {
+    set_error("iterations %lld..%lld outside the plan's %lld..%lld", (long long)t0,
+              (long long)(t0 + n_iters - 1), (long long)pl->t_first, (long long)pl->t_last);
+    return PASUR_E_RANGE;
+  }
+  if (n_iters == 0) return PASUR_OK;
+  hipStream_t s = (hipStream_t)stream;
+  {
+    ProfScope ps(pl->n_lds_segs == pl->n_segs ? 2 : 3, -1, s, pl->work[0], pl->work[1],
+                 pl->work[2], pl->work[3], n_iters);
+    const bool f32 = pl->dtype == PASUR_F32;
+    for (const SegLaunch &la : pl->launches) {
+      switch (la.block) {
+        case 256: f32 ? plan_launch<float, 256>(pl, la, t0, n_iters, s) : plan_launch<double, 256>(pl, la, t0, n_iters, s); break;
+        case 512: f32 ? plan_launch<float, 512>(pl, la, t0, n_iters, s) : plan_launch<double, 512>(pl, la, t0, n_iters, s); break;
+        default: f32 ? plan_launch<float, 1024>(pl, la, t0, n_iters, s) : plan_launch<double, 1024>(pl, la, t0, n_iters, s); break;
+      }
+    }
+  }
+  PASUR_TRY_HIP(hipGetLastError());
+  return PASUR_OK;
+}
+
+extern "C" int pasur_plan_info(const pasur_plan *pl, int64_t info[8]) {
+  if (!pl || !info) {
+    set_error("null argument");
+    return PASUR_E_INVAL;
+  }
+  info[0] = pl->n_segs;
+  info[1] = pl->n_lds_segs;
+  info[2] = pl->lds_bytes;
+  info[3] = pl->block;
+  info[4] = pl->work[0];
+  info[5] = pl->work[1];
+  info[6] = pl->work[2];
+  info[7] = pl->work[3];
+  return PASUR_OK;
+}

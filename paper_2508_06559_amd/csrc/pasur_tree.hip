@@ -658,6 +658,7 @@ extern "C" void pasur_fgt_free(pasur_fgt *f) {
   dev_free(f->leaf_bonus);
   for (int l = 0; l < 9; ++l) dev_free(f->root_off[l]);
   std::free(f->h_root_off);
+  std::free(f->h_root_seg);
   sweep_index_free(f->sweep);
   delete f;
 }
