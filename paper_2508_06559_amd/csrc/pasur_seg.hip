@@ -81,22 +81,27 @@ struct SegCounts {
 // tables and a map from tree nodes to active nodes take the edge arrays'
 // place.
 struct SegLds {
-  uint32_t b6, b7;              // passive bits of levels 6 and 7
-  uint32_t tmp;                 // = the start of the edge arrays
-  uint32_t vacc;                // double per root: running sum of root utilities
-  uint32_t sg, u, r, s;         // T per edge; u also per root, after the edges
-  uint32_t s1, s2;              // T per edge of levels 6 and 7: average sums below it
-  uint32_t x;                   // T per active node, then per root: reaches
-  uint32_t slot, up, meta, pos; // words of an active node, see below
+  uint32_t b6, b7;   // passive bits of levels 6 and 7
+  uint32_t tmp;      // = the start of the edge arrays
+  uint32_t vacc;     // double per root: running sum of root utilities
+  uint32_t su, rs;   // per edge: sigma and utility, regret and average sum (pairs of T);
+                     // su also per root, after the edges
+  uint32_t chain;    // per edge of levels 6 and 7: the average sums below it (pair of T)
+  uint32_t x;        // T per active node, then per root: reaches
+  uint32_t kids, up; // words of an active node, see below
+  uint32_t pos;      // 16 bits per active node: its index within its level of the segment
   uint32_t bytes;
 };
 // Words of active node i:
-//   slot: slot of its first child | distance to the next child << 16
-//   up:   its own slot as a child | active node two levels up << 16
-//   meta: its parent | number of children << 16 | level << 24
-//   pos:  16 bits, its index within its level of the segment
-// A root's slot as a child is its place in u after the edges, and its parent
+//   kids.x: slot of its first child | distance to the next child << 16
+//   kids.y: its own slot as a child | number of children << 16 | level << 24
+//   up:     its parent | active node two levels up << 16
+// A root's slot as a child is its place in su after the edges, and its parent
 // is its second entry of x (the reach of the player who moves first).
+template <class T>
+struct alignas(2 * sizeof(T)) Pair {
+  T a, b;
+};
 
 constexpr int kClasses = 64;  // children per node: 0 .. 63
 constexpr uint32_t kTableBytes = 3 * 8 * kClasses * 4;
@@ -115,18 +120,14 @@ __host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t) {
   L.b7 = take((uint32_t)((c.c7 + 63) / 64) * 8u);
   L.tmp = p;
   const uint32_t tmp_end = p + kTableBytes + align16(2u * (uint32_t)c.c07);
-  L.sg = take(t * (uint32_t)c.ne);
-  L.u = take(t * (uint32_t)(c.ne + c.roots));
-  L.r = take(t * (uint32_t)c.ne);
-  L.s = take(t * (uint32_t)c.ne);
-  L.s1 = take(t * (uint32_t)c.ne67);
-  L.s2 = take(t * (uint32_t)c.ne67);
+  L.su = take(2 * t * (uint32_t)(c.ne + c.roots));
+  L.rs = take(2 * t * (uint32_t)c.ne);
+  L.chain = take(2 * t * (uint32_t)c.ne67);
   L.x = take(t * (uint32_t)(c.na + c.roots));
   L.vacc = take(8u * (uint32_t)c.roots);
   if (p < tmp_end) p = tmp_end;
-  L.slot = take(4u * (uint32_t)c.na);
+  L.kids = take(8u * (uint32_t)c.na);
   L.up = take(4u * (uint32_t)c.na);
-  L.meta = take(4u * (uint32_t)c.na);
   L.pos = take(2u * (uint32_t)c.na);
   L.bytes = p;
   return L;
@@ -260,8 +261,8 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
     g_sb[9] = e;
   }
   __syncthreads();
-  uint32_t *const w_slot = lds<uint32_t>(L.slot), *const w_up = lds<uint32_t>(L.up);
-  uint32_t *const w_meta = lds<uint32_t>(L.meta);
+  uint2 *const w_kids = lds<uint2>(L.kids);
+  uint32_t *const w_up = lds<uint32_t>(L.up);
   uint16_t *const w_pos = lds<uint16_t>(L.pos);
   // every active node's place and its children's slots
   for (int l = 0, at = 0; l < 8; ++l) {
@@ -271,9 +272,9 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
         const int k = D.cb[l][h0 + i + 1] - D.cb[l][h0 + i];
         const uint32_t rank = atomicAdd(&next[l * kClasses + k], 1u);
         const uint32_t id = (uint32_t)g_nb[l] + rank;
-        w_slot[id] = ((uint32_t)g_sb[l + 1] + first[l * kClasses + k] + rank) |
-                     (count[l * kClasses + k] << 16);
-        w_meta[id] = ((uint32_t)k << 16) | ((uint32_t)l << 24);
+        w_kids[id] = make_uint2(((uint32_t)g_sb[l + 1] + first[l * kClasses + k] + rank) |
+                                    (count[l * kClasses + k] << 16),
+                                ((uint32_t)k << 16) | ((uint32_t)l << 24));
         w_pos[id] = (uint16_t)i;
         map[at + i] = (uint16_t)id;
       }
@@ -291,13 +292,13 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
           const int p0 = D.off[l - 1][j0];
           const int32_t h = D.parent[l][h0 + i];
           par = map[up + (h - p0)];
-          const uint32_t w = w_slot[par];
+          const uint32_t w = w_kids[par].x;
           slot = (w & 0xFFFFu) + (uint32_t)(h0 + i - D.cb[l - 1][h]) * (w >> 16);
           up_id = l > 1 ? map[up2 + (D.parent[l - 1][h] - D.off[l - 2][j0])]
                         : (uint32_t)c.na + par;
         }
-        w_up[id] = slot | (up_id << 16);
-        w_meta[id] |= par;
+        w_kids[id].y |= slot;
+        w_up[id] = par | (up_id << 16);
       }
     up2 = up;
     up = at;
@@ -305,22 +306,21 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   }
   __syncthreads();
   // the state; from here on the edge arrays take the tables' place
-  T *const sg = lds<T>(L.sg), *const uu = lds<T>(L.u), *const rr = lds<T>(L.r);
-  T *const ss = lds<T>(L.s), *const s1 = lds<T>(L.s1), *const s2 = lds<T>(L.s2);
+  Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = lds<Pair<T>>(L.rs);
+  Pair<T> *const chain = lds<Pair<T>>(L.chain);
   const int e6 = g_sb[6];
   for (int l = 0; l < 8; ++l) {
     const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0];
     const int end = g_nb[l + 1];
     for (int id = g_nb[l] + tid; id < end; id += BLOCK) {
       const int32_t b = D.cb[l][h0 + w_pos[id]];
-      const int k = (int)(w_meta[id] >> 16) & 0xFF;
-      int e = (int)(w_slot[id] & 0xFFFFu);
-      const int step = (int)(w_slot[id] >> 16);
+      const uint2 w = w_kids[id];
+      const int k = (int)(w.y >> 16) & 0xFF;
+      int e = (int)(w.x & 0xFFFFu);
+      const int step = (int)(w.x >> 16);
       for (int j = 0; j < k; ++j, e += step) {
         const int32_t q = b + j;
-        sg[e] = D.sigma[l + 1][q];
-        rr[e] = D.R[l + 1][q];
-        ss[e] = D.Sbar[l + 1][q];
+        rs[e] = Pair<T>{D.R[l + 1][q], D.Sbar[l + 1][q]};
         T v = (T)0, a1 = (T)0, a2 = (T)0;
         if (l == 7) {
           v = D.u[8][q];
@@ -338,11 +338,8 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
             a2 = D.Sbar[8][q8];
           }
         }
-        uu[e] = v;
-        if (l == 5 || l == 6) {
-          s1[e - e6] = a1;
-          s2[e - e6] = a2;
-        }
+        su[e] = Pair<T>{D.sigma[l + 1][q], v};
+        if (l == 5 || l == 6) chain[e - e6] = Pair<T>{a1, a2};
       }
     }
   }
@@ -356,13 +353,39 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   return true;
 }
 
-// u of active node id: the sum of sigma * u over its children, in child order.
+// A node's children: slot, distance and number, from its words.
+struct Kids {
+  int e, step, k;
+  __device__ __forceinline__ Kids(uint2 w)
+      : e((int)(w.x & 0xFFFFu)), step((int)(w.x >> 16)), k((int)(w.y >> 16) & 0xFF) {}
+};
+
+// uh + the sum of sigma * u over at most K children from slot e, in child
+// order.  All K are read at once, so that LDS latency is paid once; past the
+// last child the first one is read again and counts as zero (adding zero
+// leaves the sum's bits alone: it is never -0).
+template <class T, int K>
+__device__ __forceinline__ double value_few(const Pair<T> *su, int e, int step, int k, double uh) {
+  Pair<T> p[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) p[i] = su[i < k ? e + i * step : e];
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const T s = i < k ? p[i].a : (T)0, v = i < k ? p[i].b : (T)0;
+    uh += (double)s * (double)v;
+  }
+  return uh;
+}
+
+// u of an active node.  The form is the wave's: a class's nodes are
+// neighbours, so its lanes mostly agree.
 template <class T>
-__device__ __forceinline__ double node_value(const T *sg, const T *uu, uint32_t w_slot, int k) {
-  int e = (int)(w_slot & 0xFFFFu);
-  const int step = (int)(w_slot >> 16);
+__device__ __forceinline__ double node_value(const Pair<T> *su, const Kids &n) {
+  if (!__ballot(n.k > 2)) return value_few<T, 2>(su, n.e, n.step, n.k, 0.0);
+  if (!__ballot(n.k > 4)) return value_few<T, 4>(su, n.e, n.step, n.k, 0.0);
   double uh = 0.0;
-  for (int j = 0; j < k; ++j, e += step) uh += (double)sg[e] * (double)uu[e];
+  for (int left = n.k, e = n.e; left > 0; left -= 4, e += 4 * n.step)
+    uh = value_few<T, 4>(su, e, n.step, left, uh);
   return uh;
 }
 
@@ -382,45 +405,113 @@ __device__ __forceinline__ double next_regret(double Rq, double r, const IterK &
   return Rq + r;
 }
 
-// Regret, matching and average updates of one active node's children, and the
-// average sums of the chains below them.
+// Average sums of a child (edge e, sigma^t = sg) and of the chain below it, if
+// any: there first the other player moves (reach opp, as inherited), then the
+// mover of this node (the child's own reach).  Returns the child's.
 template <class T>
-__device__ __forceinline__ void node_update(const SegLds &L, int id, int e6, const IterK &ik,
-                                            int variant, int rm_mode, double eps) {
-  T *const sg = lds<T>(L.sg), *const rr = lds<T>(L.r), *const ss = lds<T>(L.s);
-  const T *const uu = lds<T>(L.u), *const x = lds<T>(L.x);
-  const uint32_t meta = lds<uint32_t>(L.meta)[id], w = lds<uint32_t>(L.slot)[id];
-  const int k = (int)(meta >> 16) & 0xFF, level = (int)(meta >> 24);
-  const int e0 = (int)(w & 0xFFFFu), step = (int)(w >> 16);
-  const double opp = (double)x[id], own = (double)x[meta & 0xFFFFu];
-  const double sgn = (level & 1) == 0 ? 1.0 : -1.0;
-  const double uh = node_value(sg, uu, w, k);
-  double sum = 0.0;
-  for (int j = 0, e = e0; j < k; ++j, e += step) {
-    const double r = sgn * opp * ((double)uu[e] - uh);
-    const T Rs = (T)next_regret((double)rr[e], r, ik, variant);
-    rr[e] = Rs;
-    sum += matched((double)Rs, rm_mode, eps);
+__device__ __forceinline__ T average_update(Pair<T> *chain, bool chains, double opp, double own, T sg,
+                                            T sb, const IterK &ik, int variant) {
+  const double add = own * (double)sg;
+  if (chains) {
+    double a1 = opp, a2 = (double)(T)add;
+    if (variant == PASUR_CFR_PLUS) {
+      a1 *= ik.avg_t;
+      a2 *= ik.avg_t;
+    }
+    const Pair<T> c = *chain;
+    *chain = Pair<T>{(T)(ik.avg_w * (double)c.a + a1), (T)(ik.avg_w * (double)c.b + a2)};
   }
-  const double inv_k = sum > 0.0 ? 0.0 : 1.0 / (double)k;
-  const bool chains = level == 5 || level == 6;
-  for (int j = 0, e = e0; j < k; ++j, e += step) {
-    const double m = matched((double)rr[e], rm_mode, eps);
-    const double s_new = sum > 0.0 ? m / sum : inv_k;
-    const double add = own * (double)sg[e];
-    ss[e] = (T)(ik.avg_w * (double)ss[e] + (variant == PASUR_CFR_PLUS ? add * ik.avg_t : add));
-    sg[e] = (T)s_new;
-    if (chains) {
-      // below a passive child first the other player moves (reach opp, as
-      // inherited), then the mover of this node (the child's own reach)
-      T *const s1 = lds<T>(L.s1) + (e - e6), *const s2 = lds<T>(L.s2) + (e - e6);
-      double a1 = opp, a2 = (double)(T)add;
-      if (variant == PASUR_CFR_PLUS) {
-        a1 *= ik.avg_t;
-        a2 *= ik.avg_t;
+  return (T)(ik.avg_w * (double)sb + (variant == PASUR_CFR_PLUS ? add * ik.avg_t : add));
+}
+
+// The update of one active node: reaches, regret sign and arrays.
+template <class T>
+struct Update {
+  Pair<T> *su, *rs, *chain;  // chain: of edge 0 (only edges of levels 6 and 7 exist)
+  double sopp, opp, own;     // signed opponent's, opponent's and own reach
+  bool chains;
+  IterK ik;
+  int variant, rm_mode;
+  double eps;
+};
+
+// Regret, matching and average updates of the children of a node with at most
+// K of them: every child is read once and held in registers.
+template <class T, int K>
+__device__ __forceinline__ void update_few(const Update<T> &c, const Kids &n) {
+  Pair<T> p[K], r[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const int e = i < n.k ? n.e + i * n.step : n.e;
+    p[i] = c.su[e];
+    r[i] = c.rs[e];
+  }
+  double uh = 0.0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const T s = i < n.k ? p[i].a : (T)0, v = i < n.k ? p[i].b : (T)0;
+    uh += (double)s * (double)v;
+  }
+  double sum = 0.0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    r[i].a = (T)next_regret((double)r[i].a, c.sopp * ((double)p[i].b - uh), c.ik, c.variant);
+    sum += i < n.k ? matched((double)r[i].a, c.rm_mode, c.eps) : 0.0;
+  }
+  const double inv_k = sum > 0.0 ? 0.0 : 1.0 / (double)n.k;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    if (i % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // two divisions at a time: registers
+    const T s_new = (T)(sum > 0.0 ? matched((double)r[i].a, c.rm_mode, c.eps) / sum : inv_k);
+    if (i < n.k) {
+      const int e = n.e + i * n.step;
+      r[i].b = average_update<T>(c.chain + e, c.chains, c.opp, c.own, p[i].a, r[i].b, c.ik,
+                                 c.variant);
+      c.su[e].a = s_new;
+      c.rs[e] = r[i];
+    }
+  }
+}
+
+// The same for any number of children, four at a time.
+template <class T>
+__device__ __forceinline__ void update_many(const Update<T> &c, const Kids &n, double uh) {
+  double sum = 0.0;
+  for (int left = n.k, e0 = n.e; left > 0; left -= 4, e0 += 4 * n.step) {
+    T v[4], r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = i < left ? e0 + i * n.step : e0;
+      v[i] = c.su[e].b;
+      r[i] = c.rs[e].a;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const T Rs = (T)next_regret((double)r[i], c.sopp * ((double)v[i] - uh), c.ik, c.variant);
+      if (i < left) c.rs[e0 + i * n.step].a = Rs;
+      sum += i < left ? matched((double)Rs, c.rm_mode, c.eps) : 0.0;
+    }
+  }
+  const double inv_k = sum > 0.0 ? 0.0 : 1.0 / (double)n.k;
+  for (int left = n.k, e0 = n.e; left > 0; left -= 4, e0 += 4 * n.step) {
+    T s[4];
+    Pair<T> r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = i < left ? e0 + i * n.step : e0;
+      s[i] = c.su[e].a;
+      r[i] = c.rs[e];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+      const T s_new = (T)(sum > 0.0 ? matched((double)r[i].a, c.rm_mode, c.eps) / sum : inv_k);
+      if (i < left) {
+        const int e = e0 + i * n.step;
+        c.rs[e].b = average_update<T>(c.chain + e, c.chains, c.opp, c.own, s[i], r[i].b, c.ik,
+                                      c.variant);
+        c.su[e].a = s_new;
       }
-      *s1 = (T)(ik.avg_w * (double)*s1 + a1);
-      *s2 = (T)(ik.avg_w * (double)*s2 + a2);
     }
   }
 }
@@ -429,21 +520,20 @@ __device__ __forceinline__ void node_update(const SegLds &L, int id, int e6, con
 // way down leaves them (before its updates).
 template <class T, int BLOCK>
 __device__ __forceinline__ void seg_store_reach(const ItemDesc<T> &D, int j0, const SegLds &L) {
-  const T *const sg = lds<T>(L.sg), *const x = lds<T>(L.x);
+  const Pair<T> *const su = lds<Pair<T>>(L.su);
+  const T *const x = lds<T>(L.x);
   for (int l = 0; l < 7; ++l) {
     const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0], end = g_nb[l + 1];
     T *const moved = (l & 1) == 0 ? D.ra[l + 1] : D.rb[l + 1];
     T *const kept = (l & 1) == 0 ? D.rb[l + 1] : D.ra[l + 1];
     for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
-      const uint32_t meta = lds<uint32_t>(L.meta)[id], w = lds<uint32_t>(L.slot)[id];
+      const Kids n(lds<uint2>(L.kids)[id]);
       const int32_t b = D.cb[l][h0 + lds<uint16_t>(L.pos)[id]];
-      const int k = (int)(meta >> 16) & 0xFF;
       const T opp = x[id];
-      const double own = (double)x[meta & 0xFFFFu];
-      int e = (int)(w & 0xFFFFu);
-      for (int j = 0; j < k; ++j, e += (int)(w >> 16)) {
+      const double own = (double)x[lds<uint32_t>(L.up)[id] & 0xFFFFu];
+      for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
         const int32_t q = b + j;
-        const T v = (T)(own * (double)sg[e]);
+        const T v = (T)(own * (double)su[e].a);
         moved[q] = v;
         kept[q] = opp;
         if (l == 5 && bit_of(L.b6, q - q0)) {
@@ -473,32 +563,31 @@ template <class T, int BLOCK>
 __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int roots, const SegLds &L,
                                           int na, int ne, const IterK *ks, int n_iters,
                                           int variant) {
-  const T *const sg = lds<T>(L.sg), *const uu = lds<T>(L.u), *const rr = lds<T>(L.r);
-  const T *const ss = lds<T>(L.s), *const s1 = lds<T>(L.s1), *const s2 = lds<T>(L.s2);
+  const Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = lds<Pair<T>>(L.rs);
+  const Pair<T> *const chain = lds<Pair<T>>(L.chain);
   const int e6 = g_sb[6];
   for (int l = 0; l < 8; ++l) {
     const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0], end = g_nb[l + 1];
     for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
-      const uint32_t meta = lds<uint32_t>(L.meta)[id], w = lds<uint32_t>(L.slot)[id];
+      const Kids n(lds<uint2>(L.kids)[id]);
       const int32_t b = D.cb[l][h0 + lds<uint16_t>(L.pos)[id]];
-      const int k = (int)(meta >> 16) & 0xFF;
-      int e = (int)(w & 0xFFFFu);
-      for (int j = 0; j < k; ++j, e += (int)(w >> 16)) {
+      for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
         const int32_t q = b + j;
-        D.sigma[l + 1][q] = sg[e];
-        D.R[l + 1][q] = rr[e];
-        D.Sbar[l + 1][q] = ss[e];
-        if (l < 7) D.u[l + 1][q] = uu[e];
+        const Pair<T> p = su[e], r = rs[e];
+        D.sigma[l + 1][q] = p.a;
+        D.R[l + 1][q] = r.a;
+        D.Sbar[l + 1][q] = r.b;
+        if (l < 7) D.u[l + 1][q] = p.b;
         if (l == 5 && bit_of(L.b6, q - q0)) {
           const int32_t q7 = D.cb[6][q], q8 = D.cb[7][q7];
-          D.u[7][q7] = uu[e];
-          D.Sbar[7][q7] = s1[e - e6];
-          D.Sbar[8][q8] = s2[e - e6];
+          D.u[7][q7] = p.b;
+          D.Sbar[7][q7] = chain[e - e6].a;
+          D.Sbar[8][q8] = chain[e - e6].b;
           chain_regret(D.R[7] + q7, 1.0, ks, n_iters, variant);
           chain_regret(D.R[8] + q8, -1.0, ks, n_iters, variant);
         } else if (l == 6 && bit_of(L.b7, q - q0)) {
           const int32_t q8 = D.cb[7][q];
-          D.Sbar[8][q8] = s1[e - e6];
+          D.Sbar[8][q8] = chain[e - e6].a;
           chain_regret(D.R[8] + q8, -1.0, ks, n_iters, variant);
         }
       }
@@ -506,7 +595,7 @@ __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int root
   }
   for (int id = threadIdx.x; id < roots; id += BLOCK) {
     const int64_t j = D.off[0][j0] + lds<uint16_t>(L.pos)[id];
-    D.u[0][j] = uu[ne + id];
+    D.u[0][j] = su[ne + id].b;
     D.vacc[j] = lds<double>(L.vacc)[id];
   }
 }
@@ -522,15 +611,14 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
     rm_mode = PASUR_RM_FLOOR;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const T *const sg = lds<T>(L.sg);
-  T *const uu = lds<T>(L.u), *const x = lds<T>(L.x);
+  Pair<T> *const su = lds<Pair<T>>(L.su);
+  T *const x = lds<T>(L.x);
   double *const vacc = lds<double>(L.vacc);
-  const uint32_t *const w_slot = lds<uint32_t>(L.slot), *const w_up = lds<uint32_t>(L.up);
-  const uint32_t *const w_meta = lds<uint32_t>(L.meta);
+  const uint2 *const w_kids = lds<uint2>(L.kids);
+  const uint32_t *const w_up = lds<uint32_t>(L.up);
   // the levels' first nodes, one per lane, read as wave-uniform scalars
   const int nb_lane = lane <= 8 ? g_nb[lane] : na;
   auto nb = [&](int l) { return __builtin_amdgcn_readlane(nb_lane, l); };
-  const int e6 = __builtin_amdgcn_readfirstlane(g_sb[6]);
   int bottom = 7;  // deepest level with active nodes
   while (bottom > 0 && nb(bottom + 1) == nb(bottom)) --bottom;
   // levels 0 .. top-1 hold at most 64 nodes and belong to wave 0, a lane each
@@ -541,41 +629,87 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   const int first_down = top > 0 ? top : 1;  // its first level
   const int n_up = bottom - top + 1, n_down = (bottom - first_down + 2) / 2;
   const int n_int = n_up > down0 + n_down ? n_up : down0 + n_down;
+  const bool top_wave = top > 0 && wave == 0;
 
-  auto value = [&](int id) {
-    const double uh = node_value<T>(sg, uu, w_slot[id], (int)(w_meta[id] >> 16) & 0xFF);
-    uu[w_up[id] & 0xFFFFu] = (T)uh;
+  auto value = [&](uint2 w) {
+    const double uh = node_value<T>(su, Kids(w));
+    su[w.y & 0xFFFFu].b = (T)uh;
     return uh;
   };
-  auto down = [&](int id) {
-    const uint32_t w = w_up[id];
-    x[id] = (T)((double)x[w >> 16] * (double)sg[w & 0xFFFFu]);
+  auto down = [&](int id, uint32_t slot, uint32_t up) {
+    x[id] = (T)((double)x[up >> 16] * (double)su[slot & 0xFFFFu].a);
   };
+  Update<T> c;
+  c.su = su;
+  c.rs = lds<Pair<T>>(L.rs);
+  c.chain = lds<Pair<T>>(L.chain) - g_sb[6];
+  c.variant = variant;
+  c.rm_mode = rm_mode;
+  c.eps = eps;
+  auto update = [&](int id, uint2 w, uint32_t up) {
+    const int level = (int)(w.y >> 24);
+    c.opp = (double)x[id];
+    c.own = (double)x[up & 0xFFFFu];
+    c.sopp = (level & 1) == 0 ? c.opp : -c.opp;
+    c.chains = level == 5 || level == 6;
+    const Kids n(w);
+    if (!__ballot(n.k > 2)) update_few<T, 2>(c, n);
+    else if (!__ballot(n.k > 4)) update_few<T, 4>(c, n);
+    else update_many<T>(c, n, node_value<T>(su, n));
+  };
+  // This thread's first node in the updates, and in interval iv on the way up
+  // and down (possibly past the level's end); their words never change and are
+  // fetched one interval ahead.
+  const int first_update = top_wave ? tid : top > 0 ? n_top + tid - 64 : tid;
+  const int update_step = top > 0 ? BLOCK - 64 : BLOCK;
+  auto up_id = [&](int iv) {
+    return iv >= n_int ? first_update : nb(bottom - iv) + (iv == 0 && top > 0 ? tid - 64 : tid);
+  };
+  auto down_id = [&](int iv) { return nb(first_down + 2 * (iv - down0)) + tid; };
+  auto clamp = [&](int id) { return id < 0 ? 0 : id < na ? id : na - 1; };
+  const uint2 top_kids = w_kids[clamp(lane)];
+  const uint32_t top_up = w_up[clamp(lane)];
+  uint2 up_w = w_kids[clamp(up_id(0))];
+  uint2 down_w = make_uint2(0, 0);
+  if (down0 == 0) down_w = make_uint2(w_kids[clamp(down_id(0))].y, w_up[clamp(down_id(0))]);
 
+  IterK next = ks[0];
   for (int it = 0; it < n_iters; ++it) {
+    c.ik = next;
+    next = ks[it + 1 < n_iters ? it + 1 : it];
     // utilities go up from the bottom level to `top`, one level per interval,
     // while reaches go down, two levels per interval
     for (int iv = 0; iv < n_int; ++iv) {
-      const int ul = bottom - iv;
-      if (iv == 0 && top > 0) {
-        if (wave == 0) {
-          for (int l = 1; l < top; l += 2) {
-            if (lane >= nb(l) && lane < nb(l + 2 < top ? l + 2 : top)) down(lane);
-            wave_order();
-          }
-        } else {
-          for (int id = nb(ul) + tid - 64; id < nb(ul + 1); id += BLOCK - 64) value(id);
-        }
-      } else {
-        if (ul >= top)
-          for (int id = nb(ul) + tid; id < nb(ul + 1); id += BLOCK) {
-            const double uh = value(id);
-            if (ul == 0) vacc[id] += uh;
-          }
-        const int dl = first_down + 2 * (iv - down0);
-        if (dl <= bottom)
-          for (int id = nb(dl) + tid; id < nb(dl + 2 < 8 ? dl + 2 : 8); id += BLOCK) down(id);
+      const int ul = bottom - iv, dl = first_down + 2 * (iv - down0);
+      uint2 next_up = up_w, next_down = down_w;
+      if (iv + 1 >= n_int || ul - 1 >= top) next_up = w_kids[clamp(up_id(iv + 1))];
+      if (iv + 1 >= down0 && dl + 2 <= bottom) {
+        const int id = clamp(down_id(iv + 1));
+        next_down = make_uint2(w_kids[id].y, w_up[id]);
       }
+      if (iv == 0 && top_wave) {
+        for (int l = 1; l < top; l += 2) {
+          if (lane >= nb(l) && lane < nb(l + 2 < top ? l + 2 : top))
+            down(lane, top_kids.y, top_up);
+          wave_order();
+        }
+      } else if (ul >= top) {
+        const int end = nb(ul + 1), step = iv == 0 && top > 0 ? BLOCK - 64 : BLOCK;
+        int id = up_id(iv);
+        for (uint2 w = up_w; id < end; id += step, w = w_kids[clamp(id)]) {
+          const double uh = value(w);
+          if (ul == 0) vacc[id] += uh;
+        }
+      }
+      if (iv >= down0 && dl <= bottom) {
+        const int end = nb(dl + 2 < 8 ? dl + 2 : 8);
+        int id = down_id(iv);
+        for (uint2 w = down_w; id < end;
+             id += BLOCK, w = make_uint2(w_kids[clamp(id)].y, w_up[clamp(id)]))
+          down(id, w.x, w.y);
+      }
+      up_w = next_up;
+      down_w = next_down;
       __syncthreads();
     }
     if (it == n_iters - 1) {
@@ -584,20 +718,22 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
     }
     // updates of all levels; wave 0 finishes the top levels' utilities first,
     // whose strategies no other wave changes
-    const IterK k = ks[it];
-    if (top > 0 && wave == 0) {
+    const uint2 first = up_w;
+    up_w = w_kids[clamp(up_id(0))];
+    if (down0 == 0) down_w = make_uint2(w_kids[clamp(down_id(0))].y, w_up[clamp(down_id(0))]);
+    if (top_wave) {
       for (int l = top - 1; l >= 0; --l) {
         if (lane >= nb(l) && lane < nb(l + 1)) {
-          const double uh = value(lane);
+          const double uh = value(top_kids);
           if (l == 0) vacc[lane] += uh;
         }
         wave_order();
       }
-      if (lane < n_top) node_update<T>(L, lane, e6, k, variant, rm_mode, eps);
-    } else {
-      const int t = top > 0 ? tid - 64 : tid, nt = top > 0 ? BLOCK - 64 : BLOCK;
-      for (int id = n_top + t; id < na; id += nt)
-        node_update<T>(L, id, e6, k, variant, rm_mode, eps);
+    }
+    uint2 w = top_wave ? top_kids : first;
+    for (int id = first_update, end = top_wave ? n_top : na; id < end; id += update_step) {
+      update(id, w, w_up[id]);
+      w = w_kids[clamp(id + update_step)];
     }
     __syncthreads();
   }
