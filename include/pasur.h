@@ -298,8 +298,8 @@ int pasur_round_values(const pasur_fgt *fgt, const pasur_cfr_state *st,
  * d_leaf (device double, n[8]) to the roots (d_out, device double, n[0]):
  * EXPECT: sum sigma * value; BR_A: max at Alex's nodes, expectation at Bob's;
  * BR_B: min at Bob's nodes, expectation at Alex's; MINIMAX: max/min.
- * sigma (type `dtype`, levels 1..8) may be NULL for MINIMAX.  Uses
- * stream-ordered scratch memory. */
+ * sigma (type `dtype`, levels 1..8) may be NULL for MINIMAX.  One launch,
+ * which allocates nothing. */
 typedef enum { PASUR_TV_EXPECT = 0, PASUR_TV_BR_A = 1, PASUR_TV_BR_B = 2,
                PASUR_TV_MINIMAX = 3 } pasur_tv_mode;
 int pasur_tree_values(const pasur_fgt *fgt, const double *d_leaf, int dtype,
@@ -321,7 +321,7 @@ int pasur_tree_values(const pasur_fgt *fgt, const double *d_leaf, int dtype,
  * with `leaf_flags`).  Any output may be NULL (not
  * computed), not all three.  Exploitability in points per game is
  * (br_a - br_b) / 2 >= 0.  Asynchronous on `stream`; uses stream-ordered
- * scratch (a level of each round, its leaves and its roots, in double).
+ * scratch (two rounds' root values).
  * PASUR_E_INVAL for null or inconsistent trees, PASUR_E_RANGE for n_rounds
  * outside 1..6 or an unknown dtype. */
 int pasur_exploitability(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar,
@@ -330,13 +330,9 @@ int pasur_exploitability(const pasur_fgt *const *fgts, int n_rounds, void *const
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * computation and arguments as pasur_tree_values, with its two level
- * buffers in a fixed device array instead of stream-ordered allocations.
- * Allocates nothing.  Limit: every level 0..7 of the tree at most 2^21
- * (2,097,152) nodes -- larger trees get PASUR_E_CAPACITY (use
- * pasur_tree_values).  Each GPU holds one 32 MiB array for the process's
- * lifetime, shared by every call on that GPU: calls that overlap on one GPU
- * (on any streams) race and must be serialised by the caller. */
+ * computation and arguments as pasur_tree_values.  Allocates nothing.  Limit:
+ * every level 0..7 of the tree at most 2^21 (2,097,152) nodes -- larger trees
+ * get PASUR_E_CAPACITY (use pasur_tree_values). */
 int pasur_tree_values_noalloc(const pasur_fgt *fgt, const double *d_leaf, int dtype,
                               void *const sigma[9], int mode, double *d_out, void *stream);
 
@@ -528,13 +524,13 @@ int pasur_sample_parents(const pasur_fgt *fgt, int level, uint64_t seed, double 
  * discounts treat the warm start as earlier iterations. */
 int pasur_cfr_warm_init(const pasur_fgt *fgt, const pasur_cfr_state *st, int level,
                         const float *Y, float kappa_r, float kappa_s, void *stream);
-/* The warm start of a whole round in one call (after pasur_cfr_init): the
- * feature rows of every node of levels 1..max_level (one launch), the MLP
- * forward pass over all of them, and sigma / R / Sbar of those levels as in
+/* The warm start of a whole round in one call (after pasur_cfr_init): the MLP
+ * forward pass over every node of levels 1..max_level (one launch, which makes
+ * the nodes' feature rows on chip), and sigma / R / Sbar of those levels as in
  * pasur_cfr_warm_init (one launch); deeper levels keep their initial state.
- * `gt` must be the game tree `fgt` was unfolded from.  Uses stream-ordered
- * the caller's workspace when it is large enough, else stream-ordered scratch
- * (rows x 192 BF16 + rows x 2 FP32); the forward pass is pasur_mlp_infer. */
+ * `gt` must be the game tree `fgt` was unfolded from.  The network's outputs
+ * (rows x 2 FP32) go to the caller's workspace when it is large enough, else to
+ * stream-ordered scratch. */
 int pasur_warm_start_round(const pasur_gt *gt, const pasur_fgt *fgt, const pasur_cfr_state *st,
                            const pasur_mlp_weights *w, int max_level, float kappa_r,
                            float kappa_s, void *workspace, int64_t workspace_bytes,

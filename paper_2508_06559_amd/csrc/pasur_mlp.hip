@@ -635,73 +635,171 @@ struct HandCards {
   uint8_t card[8];
 };
 
-__device__ void feature_row(int32_t q, const int32_t *__restrict__ f_gt,
-                            const int32_t *__restrict__ f_sid, const uint64_t *__restrict__ pool,
-                            const uint8_t *__restrict__ hands, const int8_t *__restrict__ rs,
-                            const int8_t *__restrict__ tab, int level, const HandCards &hc,
-                            __bf16 *__restrict__ row) {
-  const int32_t g = f_gt[q];
-  const uint8_t h = hands[g];
-  uint64_t ha = 0, hb = 0;
-  for (int b = 0; b < 4; ++b) {
-    if ((h >> b) & 1) ha |= 1ull << hc.card[b];
-    if ((h >> (4 + b)) & 1) hb |= 1ull << hc.card[4 + b];
-  }
-  const uint64_t p = pool[g];
-  const __bf16 one = (__bf16)1.f, zero = (__bf16)0.f;
-  for (int c = 0; c < 52; ++c) {
-    row[c] = ((ha >> c) & 1) ? one : zero;
-    row[52 + c] = ((hb >> c) & 1) ? one : zero;
-    row[104 + c] = ((p >> c) & 1) ? one : zero;
-  }
-  const int8_t *s = tab + 4 * f_sid[q];
-  row[156] = (__bf16)((float)s[0] / 7.f);
-  row[157] = (__bf16)((float)s[1] / 7.f);
-  row[158] = (__bf16)((float)s[2] / 16.f);
-  row[159] = (__bf16)(s[3] == 1 ? 1.f : (s[3] == 2 ? -1.f : 0.f));
-  const int8_t *r = rs + 8 * (int64_t)g;  // Acl, Bcl, last picker, Apt, Asr, Bpt, Bsr
-  row[160] = (__bf16)((float)r[0] / 13.f);
-  row[161] = (__bf16)((float)r[1] / 13.f);
-  row[162] = (__bf16)(r[2] == 1 ? 1.f : (r[2] == 2 ? -1.f : 0.f));
-  row[163] = (__bf16)((float)r[3] / 10.f);
-  row[164] = (__bf16)(float)r[4];
-  row[165] = (__bf16)((float)r[5] / 10.f);
-  row[166] = (__bf16)(float)r[6];
-  for (int c = 167; c < kIn; ++c) row[c] = zero;
-  row[167 + level] = one;
-}
-
-__global__ void k_features(int64_t n, const int32_t *__restrict__ edges, const int32_t *__restrict__ f_gt,
-                           const int32_t *__restrict__ f_sid, const uint64_t *__restrict__ pool,
-                           const uint8_t *__restrict__ hands, const int8_t *__restrict__ rs,
-                           const int8_t *__restrict__ tab, int level, HandCards hc,
-                           __bf16 *__restrict__ X) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  feature_row(edges ? edges[i] : (int32_t)i, f_gt, f_sid, pool, hands, rs, tab, level, hc,
-              X + i * kIn);
-}
-
-// Feature rows of every node of levels 1..nl, level by level (row off[l-1] +
-// q for node q of level l).
-struct FeatLevels {
-  const int32_t *f_gt[9], *f_sid[9];
-  const uint64_t *pool[9];
-  const uint8_t *hands[9];
-  const int8_t *rs[9];
-  int64_t off[9];  // off[l-1] = first row of level l; off[nl] = rows
-  int nl;
+// What the rows of one level are made from: the level's FGT nodes and the
+// card states and running scores of the game tree.
+struct FeatLevel {
+  const int32_t *f_gt, *f_sid;
+  const uint64_t *pool;
+  const uint8_t *hands;
+  const uint64_t *rs;
 };
 
-__global__ void k_features_levels(FeatLevels F, const int8_t *__restrict__ tab, HandCards hc,
-                                  __bf16 *__restrict__ X) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= F.off[F.nl]) return;
-  int l = 1;
-  while (l < F.nl && i >= F.off[l]) ++l;
-  feature_row((int32_t)(i - F.off[l - 1]), F.f_gt[l], F.f_sid[l], F.pool[l], F.hands[l], F.rs[l],
-              tab, l, hc, X + i * kIn);
+// A row before it is written out: the three card masks as one string of 156
+// bits, and the columns behind them.  Any 8 columns (16 bytes) can then be
+// made by themselves, so that several threads share a row and their stores
+// run along it.
+struct FeatRow {
+  uint64_t bits[3];
+  uint16_t score[4], run[8];  // columns 156..159; 160..166 and a zero
+  int level;
+
+  static __device__ __forceinline__ uint16_t bf(float x) {
+    return __builtin_bit_cast(uint16_t, (__bf16)x);
+  }
+  static __device__ __forceinline__ float owner(int o) {
+    return o == 1 ? 1.f : (o == 2 ? -1.f : 0.f);
+  }
+  __device__ __forceinline__ void load(const FeatLevel &F, const int8_t *__restrict__ tab,
+                                       const HandCards &hc, int lev, int32_t q) {
+    const int32_t g = F.f_gt[q];
+    const uint8_t h = F.hands[g];
+    const uint64_t p = F.pool[g], r = F.rs[g];
+    const uint32_t s = *reinterpret_cast<const uint32_t *>(tab + 4 * (int64_t)F.f_sid[q]);
+    uint64_t ha = 0, hb = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if ((h >> b) & 1) ha |= 1ull << hc.card[b];
+      if ((h >> (4 + b)) & 1) hb |= 1ull << hc.card[4 + b];
+    }
+    bits[0] = ha | (hb << 52);
+    bits[1] = (hb >> 12) | (p << 40);
+    bits[2] = p >> 24;
+    auto byte = [](uint64_t w, int i) { return (int)(int8_t)((w >> (8 * i)) & 0xFF); };
+    score[0] = bf((float)byte(s, 0) / 7.f);
+    score[1] = bf((float)byte(s, 1) / 7.f);
+    score[2] = bf((float)byte(s, 2) / 16.f);
+    score[3] = bf(owner(byte(s, 3)));
+    run[0] = bf((float)byte(r, 0) / 13.f);
+    run[1] = bf((float)byte(r, 1) / 13.f);
+    run[2] = bf(owner(byte(r, 2)));
+    run[3] = bf((float)byte(r, 3) / 10.f);
+    run[4] = bf((float)byte(r, 4));
+    run[5] = bf((float)byte(r, 5) / 10.f);
+    run[6] = bf((float)byte(r, 6));
+    run[7] = 0;
+    level = lev;
+  }
+  // Columns 8 c .. 8 c + 7 as the bit patterns of 8 BF16 values (1 = 0x3F80).
+  __device__ __forceinline__ uint4 columns(int c) const {
+    uint32_t w[4];
+    if (c < 20) {
+      const uint32_t m = (uint32_t)(bits[c >> 3] >> (8 * (c & 7)));
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        w[k] = ((m >> (2 * k)) & 1u) * 0x3F80u | ((m >> (2 * k + 1)) & 1u) * 0x3F800000u;
+      if (c == 19) {
+        w[2] = (uint32_t)score[0] | ((uint32_t)score[1] << 16);
+        w[3] = (uint32_t)score[2] | ((uint32_t)score[3] << 16);
+      }
+    } else {
+      const int hot = 167 + level - 8 * c;  // the one-hot column, if among these
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        w[k] = c == 20 ? (uint32_t)run[2 * k] | ((uint32_t)run[2 * k + 1] << 16) : 0u;
+        if (hot == 2 * k) w[k] |= 0x3F80u;
+        if (hot == 2 * k + 1) w[k] |= 0x3F800000u;
+      }
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+  }
+};
+static_assert(kIn == 192, "24 groups of 8 columns per row");
+
+// Feature rows of one level's nodes edges[i] (or all in order): eight threads
+// per row, three groups of 8 columns each, so that a wave writes eight rows'
+// consecutive bytes.  Bound by the 384 B written per row; one thread per row
+// writing column by column took 98 us for 71,000 rows, a fifth of that rate.
+// X needs 2-byte alignment only: unaligned output goes value by value.
+constexpr int kFeatThreads = 256, kFeatRows = kFeatThreads / 8;
+__global__ void __launch_bounds__(kFeatThreads)
+    k_features(int64_t n, const int32_t *__restrict__ edges, FeatLevel F,
+               const int8_t *__restrict__ tab, int level, HandCards hc, uint16_t *__restrict__ X) {
+  const int64_t i = (int64_t)blockIdx.x * kFeatRows + (threadIdx.x >> 3);
+  if (i >= n) return;
+  FeatRow row;
+  row.load(F, tab, hc, level, edges ? edges[i] : (int32_t)i);
+  uint16_t *const out = X + i * kIn;
+  const bool aligned = (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int c = (int)(threadIdx.x & 7) + 8 * k;
+    const uint4 v = row.columns(c);
+    if (aligned) {
+      *reinterpret_cast<uint4 *>(out + 8 * c) = v;
+    } else {
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) out[8 * c + j] = (uint16_t)(w[j >> 1] >> (16 * (j & 1)));
+    }
+  }
 }
+
+// Network input held in memory: X [M][192], 16-byte aligned pieces.
+struct InputRows {
+  const __bf16 *X;
+  // Rows m0 .. m0+ROWS-1 into LDS rows of `stride` values by NT threads (rows
+  // past M are zero); every load is issued before the first LDS write.
+  template <int ROWS, int NT>
+  __device__ __forceinline__ void stage(__bf16 *Xs, int stride, int m0, int M, int tid) const {
+    constexpr int XP = ROWS * (kIn / 8) / NT;  // 16-byte pieces per thread
+    static_assert(ROWS * (kIn / 8) % NT == 0, "tile staging");
+    bf16x8 xv[XP];
+#pragma unroll
+    for (int i = 0; i < XP; ++i) {
+      const int e = tid + i * NT, r = e / (kIn / 8), c = (e % (kIn / 8)) * 8;
+      if (m0 + r < M) xv[i] = *reinterpret_cast<const bf16x8 *>(X + (int64_t)(m0 + r) * kIn + c);
+      else
+#pragma unroll
+        for (int j = 0; j < 8; ++j) xv[i][j] = (__bf16)0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < XP; ++i) {
+      const int e = tid + i * NT, r = e / (kIn / 8), c = (e % (kIn / 8)) * 8;
+      *reinterpret_cast<bf16x8 *>(Xs + r * stride + c) = xv[i];
+    }
+  }
+};
+
+// Network input made where it is used: the feature rows of every node of
+// levels 1..nl, level by level (row off[l-1] + q for node q of level l).  They
+// never exist in memory: some 33 bytes of a node are read instead of 384
+// written and read again.
+struct FeatureRows {
+  FeatLevel level[9];
+  int64_t off[9];  // off[l-1] = first row of level l; off[nl] = rows
+  int nl;
+  const int8_t *tab;
+  HandCards hc;
+  template <int ROWS, int NT>
+  __device__ __forceinline__ void stage(__bf16 *Xs, int stride, int m0, int M, int tid) const {
+    constexpr int PARTS = NT / ROWS, GROUPS = kIn / 8 / PARTS;
+    static_assert(NT % ROWS == 0 && (kIn / 8) % PARTS == 0, "tile staging");
+    const int r = tid / PARTS, part = tid % PARTS;
+    const int64_t i = m0 + r;
+    FeatRow row;
+    if (i < M) {
+      int l = 1;
+      while (l < nl && i >= off[l]) ++l;
+      row.load(level[l], tab, hc, l, (int32_t)(i - off[l - 1]));
+    }
+#pragma unroll
+    for (int k = 0; k < GROUPS; ++k) {
+      const int c = part + PARTS * k;
+      *reinterpret_cast<uint4 *>(Xs + r * stride + 8 * c) =
+          i < M ? row.columns(c) : make_uint4(0, 0, 0, 0);
+    }
+  }
+};
 
 // Policy / value loss gradient.  seg[p]..seg[p+1] are the rows (edges) of
 // parent p; Y[r] = (logit, value).  Policy: cross-entropy between the
@@ -938,9 +1036,9 @@ __device__ __forceinline__ void store_hidden(const __bf16 *Hs, __bf16 *__restric
 }
 
 // STORE: the training forward pass, which also writes H1 and H2 (for the
-// backward pass) from LDS as they are formed.
-template <int WAVES, int DEPTH, bool STORE>
-__global__ void __launch_bounds__(64 * WAVES) k_mlp_infer(int M, const __bf16 *__restrict__ X,
+// backward pass) from LDS as they are formed.  Input: InputRows or FeatureRows.
+template <int WAVES, int DEPTH, bool STORE, class Input>
+__global__ void __launch_bounds__(64 * WAVES) k_mlp_infer(int M, Input in,
                                                    const __bf16 *__restrict__ W1t,
                                                    const float *__restrict__ b1,
                                                    const __bf16 *__restrict__ W2t,
@@ -958,21 +1056,10 @@ __global__ void __launch_bounds__(64 * WAVES) k_mlp_infer(int M, const __bf16 *_
   constexpr int NT = 64 * WAVES;         // threads
   constexpr int TA = kHid / 16 / WAVES;  // 16-wide output tiles per wave
   constexpr int TB = IM / 16;            // 16-row tiles per workgroup
-  constexpr int XP = IM * (kIn / 8) / NT;  // 16-byte pieces of the tile per thread
-  static_assert(IM * (kIn / 8) % NT == 0 && NT >= kHid, "tile staging");
+  static_assert(NT >= kHid, "bias staging");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m0 = blockIdx.x * IM;
-  // X tile, biases and W3 -> LDS: every load issued before the first LDS
-  // write (rows past M are zero)
-  bf16x8 xv[XP];
-#pragma unroll
-  for (int i = 0; i < XP; ++i) {
-    const int e = tid + i * NT, r = e / (kIn / 8), c = (e % (kIn / 8)) * 8;
-    if (m0 + r < M) xv[i] = *reinterpret_cast<const bf16x8 *>(X + (int64_t)(m0 + r) * kIn + c);
-    else
-#pragma unroll
-      for (int j = 0; j < 8; ++j) xv[i][j] = (__bf16)0.f;
-  }
+  // biases, W3 and the X tile -> LDS
   float bv1 = 0.f, bv2 = 0.f;
   __bf16 wv[kOut];
   if (tid < kHid) {
@@ -982,11 +1069,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_mlp_infer(int M, const __bf16 *_
     for (int o = 0; o < kOut; ++o) wv[o] = W3[tid * kOut + o];
   }
   const float bo0 = b3[0], bo1 = b3[1];
-#pragma unroll
-  for (int i = 0; i < XP; ++i) {
-    const int e = tid + i * NT, r = e / (kIn / 8), c = (e % (kIn / 8)) * 8;
-    *reinterpret_cast<bf16x8 *>(Xs + r * XS + c) = xv[i];
-  }
+  in.template stage<IM, NT>(Xs, XS, m0, M, tid);
   if (tid < kHid) {
     b1s[tid] = bv1;
     b2s[tid] = bv2;
@@ -1120,8 +1203,8 @@ extern "C" int pasur_gemm_bf16(int M, int N, int K, const uint16_t *A, int64_t s
 }
 
 namespace {
-template <bool STORE>
-int fused_forward(const pasur_mlp_weights *w, const uint16_t *X, int64_t M, float *Y, uint16_t *H1,
+template <bool STORE, class Input>
+int fused_forward(const pasur_mlp_weights *w, const Input &in, int64_t M, float *Y, uint16_t *H1,
                   uint16_t *H2, hipStream_t s);
 }  // namespace
 
@@ -1136,7 +1219,7 @@ extern "C" int pasur_mlp_forward(const pasur_mlp_weights *w, const uint16_t *X, 
   if (((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(H1) |
         reinterpret_cast<uintptr_t>(H2)) & 15) == 0)
     // all three layers in the fused kernel, H1 and H2 written from LDS
-    return fused_forward<true>(w, X, M, Y, H1, H2, s);
+    return fused_forward<true>(w, InputRows{(const __bf16 *)X}, M, Y, H1, H2, s);
   const int m = (int)M;
   PASUR_TRY(pasur_gemm_bf16(m, kHid, kIn, X, kIn, 1, w->W1, kHid, 1, nullptr, H1, kHid, w->b1, 1, s));
   PASUR_TRY(pasur_gemm_bf16(m, kHid, kHid, H1, kHid, 1, w->W2, kHid, 1, nullptr, H2, kHid, w->b2, 1, s));
@@ -1356,6 +1439,13 @@ extern "C" int pasur_sgd_step(float *w, const float *g, uint16_t *w_bf16, int64_
   return PASUR_OK;
 }
 
+namespace {
+FeatLevel feat_level(const pasur_gt *gt, const pasur_fgt *fgt, int level) {
+  return FeatLevel{fgt->gt[level], fgt->sid[level], gt->pool[level], gt->hands[level],
+                   gt->rs[level]};
+}
+}  // namespace
+
 extern "C" int pasur_edge_features(const pasur_gt *gt, const pasur_fgt *fgt, int level,
                                    const int32_t *d_edges, int64_t n, uint16_t *d_X,
                                    void *stream) {
@@ -1377,9 +1467,8 @@ extern "C" int pasur_edge_features(const pasur_gt *gt, const pasur_fgt *fgt, int
   }
   HandCards hc;
   for (int b = 0; b < 8; ++b) hc.card[b] = gt->deck[4 + 8 * gt->round + b];
-  k_features<<<blocks(n), 256, 0, (hipStream_t)stream>>>(
-      n, d_edges, fgt->gt[level], fgt->sid[level], gt->pool[level], gt->hands[level],
-      (const int8_t *)gt->rs[level], fgt->score_tab, level, hc, (__bf16 *)d_X);
+  k_features<<<blocks(n, kFeatRows), kFeatThreads, 0, (hipStream_t)stream>>>(
+      n, d_edges, feat_level(gt, fgt, level), fgt->score_tab, level, hc, d_X);
   PASUR_TRY_HIP(hipGetLastError());
   return PASUR_OK;
 }
@@ -1486,8 +1575,7 @@ int64_t warm_rows(const pasur_fgt *fgt, int max_level) {
   return rows;
 }
 int64_t warm_bytes(int64_t rows) {
-  return (int64_t)align_up((size_t)rows * kIn * sizeof(__bf16), 256) +
-         (int64_t)align_up((size_t)rows * kOut * sizeof(float), 256);
+  return (int64_t)align_up((size_t)rows * kOut * sizeof(float), 256);
 }
 }  // namespace
 
@@ -1517,17 +1605,14 @@ extern "C" int pasur_warm_start_round(const pasur_gt *gt, const pasur_fgt *fgt,
     return PASUR_E_RANGE;
   }
   hipStream_t s = (hipStream_t)stream;
-  FeatLevels F;
+  FeatureRows F;
   std::memset(&F, 0, sizeof(F));
   F.nl = max_level;
+  F.tab = fgt->score_tab;
   int64_t rows = 0;
   for (int l = 1; l <= max_level; ++l) {
     F.off[l - 1] = rows;
-    F.f_gt[l] = fgt->gt[l];
-    F.f_sid[l] = fgt->sid[l];
-    F.pool[l] = gt->pool[l];
-    F.hands[l] = gt->hands[l];
-    F.rs[l] = (const int8_t *)gt->rs[l];
+    F.level[l] = feat_level(gt, fgt, l);
     rows += fgt->n[l];
   }
   F.off[max_level] = rows;
@@ -1536,28 +1621,21 @@ extern "C" int pasur_warm_start_round(const pasur_gt *gt, const pasur_fgt *fgt,
     set_error("too many rows for one forward pass");
     return PASUR_E_RANGE;
   }
-  HandCards hc;
-  for (int b = 0; b < 8; ++b) hc.card[b] = gt->deck[4 + 8 * gt->round + b];
-  __bf16 *X = nullptr;
+  for (int b = 0; b < 8; ++b) F.hc.card[b] = gt->deck[4 + 8 * gt->round + b];
   float *Y = nullptr;
   const bool own = !workspace || workspace_bytes < warm_bytes(rows);
   hipError_t e = hipSuccess;
   if (own) {
-    e = hipMallocAsync((void **)&X, sizeof(__bf16) * (size_t)rows * kIn, s);
-    if (e == hipSuccess) e = hipMallocAsync((void **)&Y, sizeof(float) * (size_t)rows * kOut, s);
+    e = hipMallocAsync((void **)&Y, sizeof(float) * (size_t)rows * kOut, s);
   } else {
-    X = (__bf16 *)workspace;
-    Y = (float *)((char *)workspace + align_up((size_t)rows * kIn * sizeof(__bf16), 256));
+    Y = (float *)workspace;
   }
   int rc = PASUR_OK;
   if (e != hipSuccess) {
     set_error("warm start workspace: %s", hipGetErrorString(e));
     rc = PASUR_E_NOMEM;
   }
-  if (!rc) {
-    k_features_levels<<<blocks(rows), 256, 0, s>>>(F, fgt->score_tab, hc, X);
-    rc = pasur_mlp_infer(w, (const uint16_t *)X, rows, Y, s);
-  }
+  if (!rc) rc = fused_forward<false>(w, F, rows, Y, nullptr, nullptr, s);
   if (!rc) {
     auto launch = [&](auto *tag) {
       using T = std::remove_pointer_t<decltype(tag)>;
@@ -1585,10 +1663,7 @@ extern "C" int pasur_warm_start_round(const pasur_gt *gt, const pasur_fgt *fgt,
       rc = PASUR_E_HIP;
     }
   }
-  if (own) {
-    (void)hipFreeAsync(X, s);
-    (void)hipFreeAsync(Y, s);
-  }
+  if (own && Y) (void)hipFreeAsync(Y, s);
   return rc;
 }
 
@@ -1610,10 +1685,10 @@ namespace {
 // The fused kernel over M > 0 rows (inference, or with STORE the training
 // forward that also writes H1 and H2): transposed weights from the caller's
 // cache, else transposed here into stream-ordered scratch.
-template <bool STORE>
-int fused_forward(const pasur_mlp_weights *w, const uint16_t *X, int64_t M, float *Y, uint16_t *H1,
+template <bool STORE, class Input>
+int fused_forward(const pasur_mlp_weights *w, const Input &in, int64_t M, float *Y, uint16_t *H1,
                   uint16_t *H2, hipStream_t s) {
-  auto kern = k_mlp_infer<kInferWaves, kInferDepth, STORE>;
+  auto kern = k_mlp_infer<kInferWaves, kInferDepth, STORE, Input>;
   // the kernel's LDS exceeds the default limit: raise it once per device
   static std::once_flag lds_once[kMaxDevices];
   static hipError_t lds_err[kMaxDevices];
@@ -1646,7 +1721,7 @@ int fused_forward(const pasur_mlp_weights *w, const uint16_t *X, int64_t M, floa
         (const __bf16 *)w->W1, Wt, (const __bf16 *)w->W2, Wt + (size_t)kIn * kHid);
   }
   kern<<<(unsigned)((M + IM - 1) / IM), 64 * kInferWaves, kInferLds, s>>>(
-      (int)M, (const __bf16 *)X, W1t, w->b1, W2t, w->b2, (const __bf16 *)w->W3, w->b3, Y,
+      (int)M, in, W1t, w->b1, W2t, w->b2, (const __bf16 *)w->W3, w->b3, Y,
       (__bf16 *)H1, (__bf16 *)H2);
   e = hipGetLastError();
   if (Wt) (void)hipFreeAsync(Wt, s);
@@ -1666,5 +1741,6 @@ extern "C" int pasur_mlp_infer(const pasur_mlp_weights *w, const uint16_t *X, in
     return PASUR_E_INVAL;
   }
   if (M == 0) return PASUR_OK;
-  return fused_forward<false>(w, X, M, Y, nullptr, nullptr, (hipStream_t)stream);
+  return fused_forward<false>(w, InputRows{(const __bf16 *)X}, M, Y, nullptr, nullptr,
+                              (hipStream_t)stream);
 }
