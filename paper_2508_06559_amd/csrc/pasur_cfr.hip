@@ -377,17 +377,7 @@ extern "C" int pasur_cfr_iterate(const pasur_fgt *f, const pasur_cfr_state *st,
     return st->dtype == PASUR_F32 ? iterate_t<float>(f, st, p, t0, n_iters, s)
                                   : iterate_t<double>(f, st, p, t0, n_iters, s);
   if (n_iters == 0) return PASUR_OK;
-  pasur_plan *pl = nullptr;
-  PASUR_TRY(pasur_plan_create(&f, &st, 1, p, t0, t0 + n_iters - 1, &pl, stream));
-  int rc = pasur_plan_iterate(pl, t0, n_iters, stream);
-  hipError_t e = hipStreamSynchronize(s);  // the plan's buffers are freed below
-  pasur_plan_free(pl);
-  if (rc) return rc;
-  if (e != hipSuccess) {
-    set_error("iterate: %s", hipGetErrorString(e));
-    return PASUR_E_HIP;
-  }
-  return PASUR_OK;
+  return seg_iterate(f, st, p, t0, n_iters, s);
 }
 
 extern "C" int pasur_average_strategy(const pasur_fgt *f, const pasur_cfr_state *st,

@@ -49,18 +49,23 @@ void dev_free(T *&p) {
   p = nullptr;
 }
 
+// Device memory for trees and their construction, from a cache of freed blocks
+// (pasur_util.hip): hipMalloc costs up to 40 ms per GB for blocks of 8 to 500 MB,
+// and building a game takes and gives back hundreds of them.  A block that goes
+// back must be idle: nothing that uses it is pending on any stream.
+int block_alloc(void **p, size_t bytes);
+void block_free(void *p);
+// The wait of a hipFree, for handles that the caller may free while work that
+// uses them is still running: an anchor is a small plain allocation, and freeing
+// it waits for the device as freeing the arrays themselves did.
+int anchor_alloc(void **a);
+void anchor_wait(void *a);
+
 // Exclusive scan of n int32 counts into out[0..n] (out[n] = total); the
 // total is returned through *total (synchronises `stream`).  Fails with
 // PASUR_E_OVERFLOW when the total exceeds INT32_MAX.
 int scan_counts(const int32_t *d_counts, int64_t n, int32_t *d_out,
                 int64_t *total, hipStream_t stream);
-
-// Stable LSD radix sort of (key, value) pairs by key; every key bit at or
-// above end_bit must be zero.  The result is in keys_out/vals_out, and
-// keys/vals are overwritten.  Synchronises `stream`.
-template <class K>
-int radix_sort_pairs(K *keys, K *keys_out, int32_t *vals, int32_t *vals_out, int64_t n,
-                     int end_bit, hipStream_t stream);
 
 // Bit masks over the 52 card indices.
 constexpr uint64_t kNumericMask = (1ull << 40) - 1;       // A..10, 40 cards
@@ -214,6 +219,11 @@ int sweep_iterate(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_param
 // schedule on this round (PASUR_SCHED_AUTO).
 bool sweep_pays(const pasur_fgt *f);
 
+// Iterations t0 .. t0+n_iters-1 of one round with the persistent segment
+// schedule (pasur_seg.hip); n_iters >= 1.  Waits for the stream.
+int seg_iterate(const pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,
+                int64_t t0, int n_iters, hipStream_t s);
+
 // ---- exact values (pasur_values.hip) -----------------------------------------
 // Root values of one round from an array of leaf values (leaf_dtype; FP64
 // leaves when dtype is PASUR_F64), as pasur_tree_values.  Allocates nothing.
@@ -237,6 +247,8 @@ struct pasur_gt {
   uint8_t *act_card[9];
   uint64_t *act_cap[9];
   uint8_t deck[52];
+  void *block[9];  // the block that holds a level's arrays
+  void *anchor;
 };
 
 // Unfolded tree of one round.
@@ -264,4 +276,7 @@ struct pasur_fgt {
   // per root, what a segment's LDS layout counts (4 ints: see pasur_seg.hip),
   // on the host; computed on first use
   int32_t *h_root_seg;
+  // the blocks behind root_off, the arrays of the levels, and next_roots
+  void *off_block, *block, *next_block;
+  void *anchor;
 };

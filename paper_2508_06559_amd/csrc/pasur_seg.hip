@@ -106,7 +106,10 @@ struct alignas(2 * sizeof(T)) Pair {
 constexpr int kClasses = 64;  // children per node: 0 .. 63
 constexpr uint32_t kTableBytes = 3 * 8 * kClasses * 4;
 
-__host__ __device__ inline uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
+template <class U>
+__host__ __device__ inline U align16(U x) {
+  return (x + 15u) & ~(U)15u;
+}
 
 __host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t) {
   SegLds L;
@@ -927,20 +930,21 @@ int root_counts(pasur_fgt *f, hipStream_t s) {
   std::lock_guard<std::mutex> lock(g_counts_mu);
   if (f->h_root_seg) return PASUR_OK;
   const size_t n = 4 * (size_t)f->n_roots;
-  int32_t *d = nullptr;
-  PASUR_TRY(dev_alloc(&d, (int64_t)n));
+  void *d = nullptr;
+  PASUR_TRY(block_alloc(&d, n * sizeof(int32_t)));
   int32_t *h = (int32_t *)std::malloc(n * sizeof(int32_t));
   if (!h) {
-    dev_free(d);
+    block_free(d);
     set_error("host allocation failed");
     return PASUR_E_NOMEM;
   }
   k_seg_counts<<<(unsigned)f->n_roots, 64, 0, s>>>(f->root_off[6], f->root_off[7],
-                                                   f->child_begin[6], f->child_begin[7], d);
+                                                   f->child_begin[6], f->child_begin[7], (int32_t *)d);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(h, d, n * sizeof(int32_t), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  dev_free(d);
+  const hipError_t e2 = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = e2;
+  block_free(d);
   if (e != hipSuccess) {
     std::free(h);
     set_error("segment counts: %s", hipGetErrorString(e));
@@ -963,6 +967,7 @@ struct pasur_plan {
   double eps;
   int64_t t_first, t_last;
   int n_items, n_segs;
+  void *mem, *anchor;  // the arrays below in one block; see anchor_alloc
   void *d_items;
   Seg *d_segs;
   IterK *d_ks;
@@ -1117,16 +1122,19 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   const int64_t nt = pl->t_last - pl->t_first + 1;
   std::vector<IterK> ks((size_t)nt);
   for (int64_t i = 0; i < nt; ++i) ks[(size_t)i] = iter_k(p, pl->t_first + i);
-  PASUR_TRY_HIP(hipMalloc(&pl->d_items, sizeof(ItemDesc<T>) * items.size()));
-  PASUR_TRY_HIP(hipMalloc((void **)&pl->d_segs, sizeof(Seg) * (sorted.size() + 1)));
-  PASUR_TRY_HIP(hipMalloc((void **)&pl->d_ks, sizeof(IterK) * ks.size()));
-  PASUR_TRY_HIP(hipMemcpyAsync(pl->d_items, items.data(), sizeof(ItemDesc<T>) * items.size(),
-                               hipMemcpyHostToDevice, s));
-  PASUR_TRY_HIP(hipMemcpyAsync(pl->d_segs, sorted.data(), sizeof(Seg) * sorted.size(),
-                               hipMemcpyHostToDevice, s));
-  PASUR_TRY_HIP(hipMemcpyAsync(pl->d_ks, ks.data(), sizeof(IterK) * ks.size(),
-                               hipMemcpyHostToDevice, s));
-  PASUR_TRY_HIP(hipStreamSynchronize(s));  // host staging vectors go out of scope
+  // one upload
+  const size_t at_segs = align16(sizeof(ItemDesc<T>) * items.size());
+  const size_t at_ks = at_segs + align16(sizeof(Seg) * sorted.size());
+  std::vector<unsigned char> stage(at_ks + sizeof(IterK) * ks.size());
+  std::memcpy(stage.data(), items.data(), sizeof(ItemDesc<T>) * items.size());
+  std::memcpy(stage.data() + at_segs, sorted.data(), sizeof(Seg) * sorted.size());
+  std::memcpy(stage.data() + at_ks, ks.data(), sizeof(IterK) * ks.size());
+  PASUR_TRY(block_alloc(&pl->mem, stage.size()));
+  pl->d_items = pl->mem;
+  pl->d_segs = (Seg *)((unsigned char *)pl->mem + at_segs);
+  pl->d_ks = (IterK *)((unsigned char *)pl->mem + at_ks);
+  PASUR_TRY_HIP(hipMemcpyAsync(pl->mem, stage.data(), stage.size(), hipMemcpyHostToDevice, s));
+  PASUR_TRY_HIP(hipStreamSynchronize(s));  // the staging vector goes out of scope
   const bool paper = paper_variant(p->variant, p->rm_mode);
   // The attribute is a ceiling shared by every plan of this instance, so it
   // is raised to the whole budget (plans may be launched in any order); each
@@ -1156,16 +1164,17 @@ void plan_launch(const pasur_plan *pl, const SegLaunch &la, int64_t t0, int n_it
 
 extern "C" void pasur_plan_free(pasur_plan *pl) {
   if (!pl) return;
-  if (pl->d_items) (void)hipFree(pl->d_items);
-  if (pl->d_segs) (void)hipFree(pl->d_segs);
-  if (pl->d_ks) (void)hipFree(pl->d_ks);
+  anchor_wait(pl->anchor);
+  block_free(pl->mem);
   delete pl;
 }
 
-extern "C" int pasur_plan_create(const pasur_fgt *const *fgts,
-                                 const pasur_cfr_state *const *states, int n_items,
-                                 const pasur_cfr_params *p, int64_t t_first, int64_t t_last,
-                                 pasur_plan **out, void *stream) {
+namespace {
+
+// anchored: the plan may be freed while launches of it are pending.
+int plan_create(const pasur_fgt *const *fgts,
+                const pasur_cfr_state *const *states, int n_items, const pasur_cfr_params *p,
+                int64_t t_first, int64_t t_last, pasur_plan **out, void *stream, bool anchored) {
   if (!out || !fgts || !states || !p || n_items < 1) {
     set_error("null argument or empty batch");
     return PASUR_E_INVAL;
@@ -1216,8 +1225,10 @@ extern "C" int pasur_plan_create(const pasur_fgt *const *fgts,
   pl->n_items = n_items;
   hipStream_t s = (hipStream_t)stream;
   const int fg = p->schedule == PASUR_SCHED_ROOT_GLOBAL;
-  int st = dtype == PASUR_F32 ? plan_build<float>(pl, fgts, states, p, fg, s)
-                              : plan_build<double>(pl, fgts, states, p, fg, s);
+  int st = anchored ? anchor_alloc(&pl->anchor) : PASUR_OK;
+  if (!st)
+    st = dtype == PASUR_F32 ? plan_build<float>(pl, fgts, states, p, fg, s)
+                            : plan_build<double>(pl, fgts, states, p, fg, s);
   if (st) {
     pasur_plan_free(pl);
     return st;
@@ -1225,6 +1236,32 @@ extern "C" int pasur_plan_create(const pasur_fgt *const *fgts,
   *out = pl;
   return PASUR_OK;
 }
+
+}  // namespace
+
+extern "C" int pasur_plan_create(const pasur_fgt *const *fgts,
+                                 const pasur_cfr_state *const *states, int n_items,
+                                 const pasur_cfr_params *p, int64_t t_first, int64_t t_last,
+                                 pasur_plan **out, void *stream) {
+  return plan_create(fgts, states, n_items, p, t_first, t_last, out, stream, true);
+}
+
+namespace pasur {
+int seg_iterate(const pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,
+                int64_t t0, int n_iters, hipStream_t s) {
+  pasur_plan *pl = nullptr;
+  PASUR_TRY(plan_create(&f, &st, 1, p, t0, t0 + n_iters - 1, &pl, s, false));
+  const int rc = pasur_plan_iterate(pl, t0, n_iters, s);
+  const hipError_t e = hipStreamSynchronize(s);  // the plan's block is idle below
+  pasur_plan_free(pl);
+  if (rc) return rc;
+  if (e != hipSuccess) {
+    set_error("iterate: %s", hipGetErrorString(e));
+    return PASUR_E_HIP;
+  }
+  return PASUR_OK;
+}
+}  // namespace pasur
 
 extern "C" int pasur_plan_iterate(const pasur_plan *pl, int64_t t0, int n_iters, void *stream) {
   if (!pl) {

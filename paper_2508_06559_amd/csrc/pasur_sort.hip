@@ -1,21 +1,23 @@
-// pasur_sort.hip -- stable LSD radix sort of (key, int32 value) pairs, used by
-// the unfolding to group leaves by their next-round root (the canonical
-// (compressed pool, score) key of section "Between-Hand Updates") and root
-// scores by their score key.
+// pasur_sort.hip -- stable LSD radix sort of (64-bit key, int32 value) pairs, used
+// by the unfolding to group leaves by their next-round root (the canonical
+// (compressed pool, score) key of section "Between-Hand Updates").
 //
-// One pass per 8-bit digit that actually varies over the keys (an AND/OR
-// reduction finds them first).  A pass is three launches:
+// Only the key bits that vary over the keys are sorted by (an AND/OR reduction
+// finds them first), eight of them per pass wherever they lie in the key: the
+// leaves of a round differ in 20 to 40 of their 60 bits, and an 8-bit window at
+// fixed places took five to eight passes for what three to five do.  A pass is:
 //   k_rs_hist     per 4096-key tile, a 256-bucket histogram in LDS, stored
 //                 digit-major: hist[d * n_tiles + tile];
-//   scan_counts   exclusive scan of that array: the first output slot of
-//                 (digit d, tile) in the sorted order;
+//   a scan        of that array: the first output slot of (digit d, tile) in
+//                 the sorted order;
 //   k_rs_scatter  per tile, the stable rank of every key within its digit
 //                 (wavefront ballots over the digit's bits give the rank
 //                 among equal digits of one wave; per-wave counts in LDS
 //                 order the waves and the tile's 16 rounds), then the tile is
 //                 reordered in LDS by digit so that each bucket's run leaves
 //                 as consecutive addresses.
-#include "pasur_internal.hpp"
+#include "pasur_sort.hpp"
+
 
 namespace pasur {
 namespace {
@@ -25,6 +27,19 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kItems = 16;
 constexpr int kTile = kBlock * kItems;
 constexpr int kBuckets = 256;
+
+// The eight key bits of a pass, lowest first (unused places repeat a bit that
+// does not vary: its digit bit is the same for all keys).
+struct Digit {
+  uint8_t bit[8];
+  template <class K>
+  __device__ __forceinline__ int operator()(K k) const {
+    int d = 0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) d |= (int)((k >> bit[b]) & 1) << b;
+    return d;
+  }
+};
 
 template <class K>
 __global__ void __launch_bounds__(kBlock) k_rs_andor(const K *__restrict__ keys, int64_t n,
@@ -66,7 +81,7 @@ __global__ void k_rs_andor_init(unsigned long long *acc) {
 
 template <class K>
 __global__ void __launch_bounds__(kBlock) k_rs_hist(const K *__restrict__ keys, int64_t n,
-                                                    int shift, int64_t n_tiles,
+                                                    Digit dig, int64_t n_tiles,
                                                     int32_t *__restrict__ hist) {
   __shared__ int32_t h[kBuckets];
   h[threadIdx.x] = 0;
@@ -75,7 +90,7 @@ __global__ void __launch_bounds__(kBlock) k_rs_hist(const K *__restrict__ keys, 
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
     const int64_t i = base + (int64_t)r * kBlock;
-    if (i < n) atomicAdd(&h[(int)((keys[i] >> shift) & 0xFF)], 1);
+    if (i < n) atomicAdd(&h[dig(keys[i])], 1);
   }
   __syncthreads();
   hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
@@ -84,7 +99,7 @@ __global__ void __launch_bounds__(kBlock) k_rs_hist(const K *__restrict__ keys, 
 template <class K>
 __global__ void __launch_bounds__(kBlock) k_rs_scatter(const K *__restrict__ keys,
                                                        const int32_t *__restrict__ vals, int64_t n,
-                                                       int shift, int64_t n_tiles,
+                                                       Digit dig, int64_t n_tiles,
                                                        const int32_t *__restrict__ off,
                                                        K *__restrict__ okeys,
                                                        int32_t *__restrict__ ovals) {
@@ -115,7 +130,7 @@ __global__ void __launch_bounds__(kBlock) k_rs_scatter(const K *__restrict__ key
     for (int q = 0; q < kWaves; ++q) wc[q][t] = 0;
     __syncthreads();
     const bool ok = r * kBlock + t < count;
-    const int d = (int)((k[r] >> shift) & 0xFF);
+    const int d = dig(k[r]);
     unsigned long long m = __ballot(ok);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -150,7 +165,7 @@ __global__ void __launch_bounds__(kBlock) k_rs_scatter(const K *__restrict__ key
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
     if (r * kBlock + t < count) {
-      const int d = (int)((k[r] >> shift) & 0xFF);
+      const int d = dig(k[r]);
       const int p = lo[d] + rank[r];
       sk[p] = k[r];
       sv[p] = v[r];
@@ -159,7 +174,7 @@ __global__ void __launch_bounds__(kBlock) k_rs_scatter(const K *__restrict__ key
   __syncthreads();
   for (int j = t; j < count; j += kBlock) {
     const K kk = sk[j];
-    const int d = (int)((kk >> shift) & 0xFF);
+    const int d = dig(kk);
     const int64_t g = (int64_t)gof[d] + (j - lo[d]);
     okeys[g] = kk;
     ovals[g] = sv[j];
@@ -170,80 +185,41 @@ unsigned grid_tiles(int64_t n) { return (unsigned)((n + kTile - 1) / kTile); }
 
 }  // namespace
 
-template <class K>
-int radix_sort_pairs(K *keys, K *keys_out, int32_t *vals, int32_t *vals_out, int64_t n,
-                     int end_bit, hipStream_t s) {
-  if (n <= 0) return PASUR_OK;
-  const int64_t n_tiles = (n + kTile - 1) / kTile;
-  unsigned long long *acc = nullptr;
-  PASUR_TRY(dev_alloc(&acc, 2));
-  k_rs_andor_init<<<1, 64, 0, s>>>(acc);
-  k_rs_andor<K><<<grid_tiles(n), kBlock, 0, s>>>(keys, n, acc);
-  unsigned long long h_acc[2] = {0, 0};
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(h_acc, acc, sizeof(h_acc), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  dev_free(acc);
-  if (e != hipSuccess) {
-    set_error("radix sort: %s", hipGetErrorString(e));
-    return PASUR_E_HIP;
-  }
-  const unsigned long long varying = h_acc[0] ^ h_acc[1];
-  int shifts[8], n_pass = 0;
-  for (int sh = 0; sh < end_bit && sh < 8 * (int)sizeof(K); sh += 8)
-    if ((varying >> sh) & 0xFF) shifts[n_pass++] = sh;
-  K *ks[2] = {keys, keys_out};
-  int32_t *vs[2] = {vals, vals_out};
-  int src = 0;
-  int st = PASUR_OK;
-  if (n_pass > 0) {
-    int32_t *hist = nullptr, *off = nullptr;
-    st = dev_alloc(&hist, n_tiles * kBuckets);
-    if (!st) st = dev_alloc(&off, n_tiles * kBuckets + 1);
-    for (int p = 0; p < n_pass && !st; ++p) {
-      k_rs_hist<K><<<grid_tiles(n), kBlock, 0, s>>>(ks[src], n, shifts[p], n_tiles, hist);
-      e = hipGetLastError();
-      if (e != hipSuccess) {
-        set_error("radix sort: %s", hipGetErrorString(e));
-        st = PASUR_E_HIP;
-        break;
-      }
-      int64_t total = 0;
-      st = scan_counts(hist, n_tiles * kBuckets, off, &total, s);
-      if (st) break;
-      k_rs_scatter<K><<<grid_tiles(n), kBlock, 0, s>>>(ks[src], vs[src], n, shifts[p], n_tiles,
-                                                       off, ks[src ^ 1], vs[src ^ 1]);
-      e = hipGetLastError();
-      if (e != hipSuccess) {
-        set_error("radix sort: %s", hipGetErrorString(e));
-        st = PASUR_E_HIP;
-      }
-      src ^= 1;
-    }
-    e = hipStreamSynchronize(s);
-    dev_free(hist);
-    dev_free(off);
-    if (!st && e != hipSuccess) {
-      set_error("radix sort: %s", hipGetErrorString(e));
-      st = PASUR_E_HIP;
-    }
-  }
-  if (!st && src == 0) {  // the sorted pairs are in the input buffers
-    e = hipMemcpyAsync(keys_out, keys, n * sizeof(K), hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(vals_out, vals, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-      set_error("radix sort: %s", hipGetErrorString(e));
-      st = PASUR_E_HIP;
-    }
-  }
-  return st;
+int64_t sort_scratch_ints(int64_t n) { return 2 * ((int64_t)grid_tiles(n) * kBuckets + 1); }
+int64_t sort_scratch_words(int64_t n) {
+  return 2 + scan_scratch((int64_t)grid_tiles(n) * kBuckets) + 1;
 }
 
-template int radix_sort_pairs<uint32_t>(uint32_t *, uint32_t *, int32_t *, int32_t *, int64_t,
-                                        int, hipStream_t);
-template int radix_sort_pairs<uint64_t>(uint64_t *, uint64_t *, int32_t *, int32_t *, int64_t,
-                                        int, hipStream_t);
+int sort_pairs(uint64_t *const keys[2], int32_t *const vals[2], int64_t n, int32_t *ints,
+               int64_t *words, int64_t *host, int *result, hipStream_t s) {
+  *result = 0;
+  if (n <= 0) return PASUR_OK;
+  const int64_t n_tiles = grid_tiles(n), n_hist = n_tiles * kBuckets;
+  unsigned long long *const acc = (unsigned long long *)words;
+  k_rs_andor_init<<<1, 64, 0, s>>>(acc);
+  k_rs_andor<uint64_t><<<grid_tiles(n), kBlock, 0, s>>>(keys[0], n, acc);
+  PASUR_TRY_HIP(hipGetLastError());
+  PASUR_TRY_HIP(hipMemcpyAsync(host, acc, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  PASUR_TRY_HIP(hipStreamSynchronize(s));
+  const uint64_t varying = (uint64_t)host[0] ^ (uint64_t)host[1];
+  const int fixed = varying == ~0ull ? 0 : __builtin_ctzll(~varying);  // a bit that does not vary
+  int32_t *const hist = ints, *const off = ints + n_hist + 1;
+  int src = 0;
+  for (uint64_t left = varying; left;) {
+    Digit dig;
+    for (int b = 0; b < 8; ++b) {
+      dig.bit[b] = (uint8_t)(left ? __builtin_ctzll(left) : fixed);
+      left &= left - 1;
+    }
+    k_rs_hist<uint64_t><<<grid_tiles(n), kBlock, 0, s>>>(keys[src], n, dig, n_tiles, hist);
+    scan_enqueue(CountsIn{hist}, OffsetsOut{off, 0}, n_hist, 1, words + 3, words + 2, s);
+    k_rs_scatter<uint64_t><<<grid_tiles(n), kBlock, 0, s>>>(
+        keys[src], vals[src], n, dig, n_tiles, off, keys[src ^ 1], vals[src ^ 1]);
+    PASUR_TRY_HIP(hipGetLastError());
+    src ^= 1;
+  }
+  *result = src;
+  return PASUR_OK;
+}
 
 }  // namespace pasur

@@ -1,10 +1,15 @@
 // pasur_tree.hip -- round game tree (move generation), the Unfolding
 // Process and the Between-Hand linkage, as level-synchronous HIP kernels.
 //
-// Every level is laid out count -> exclusive scan -> fill, one thread per
-// parent, so children land parent-major in canonical order without atomics.
-#include "pasur_internal.hpp"
-
+// Every level is laid out count -> exclusive scan -> fill, a fixed set of threads
+// per parent, so children land parent-major in canonical order without atomics.
+//
+// Small rounds are bound by what surrounds the kernels: a round's build and
+// unfolding wait for the stream 13 times (a level's size has to be known before
+// it is allocated) and allocate 14 times, against about 60 and 120 with an
+// allocation per array and a wait per scan.  Totals arrive in pinned host words
+// that the scans write.
+#include "pasur_sort.hpp"
 
 #include <algorithm>
 #include <cstdlib>
@@ -30,13 +35,6 @@ __device__ inline int points_of(uint64_t m) {
          __popcll(m & kJackMask);
 }
 
-// Mover's hand, ascending by card index.
-struct Hand {
-  uint8_t card[4];
-  uint8_t bit[4];  // hand bit (0..7) of that card
-  int k;
-};
-
 // Cards dealt to the two players in this round, per hand bit, and for each
 // player the order of his 4 hand bits by ascending card index.
 struct DealInfo {
@@ -44,112 +42,130 @@ struct DealInfo {
   uint8_t order[2][4];
 };
 
-__device__ inline Hand held_cards(const DealInfo &di, uint8_t hands, int mover) {
-  Hand h;
-  h.k = 0;
+// The hand bit of the mover's slot-th held card in ascending order, or -1.
+__device__ __forceinline__ int held_bit(const DealInfo &di, uint8_t hands, int mover, int slot) {
+  int left = slot, bit = -1;
+#pragma unroll
   for (int j = 0; j < 4; ++j) {
-    int b = 4 * mover + di.order[mover][j];
+    const int b = 4 * mover + di.order[mover][j];
     if ((hands >> b) & 1) {
-      h.card[h.k] = di.card[b];
-      h.bit[h.k] = (uint8_t)b;
-      ++h.k;
+      if (left == 0) bit = b;
+      --left;
     }
   }
-  return h;
+  return bit;
 }
 
-// Legal moves of a hand on a pool, in canonical order (card ascending, then
-// capture mask ascending), passed to emit(hand slot, card, capture mask).
+// Legal moves with card c on a pool, in canonical order (capture mask
+// ascending), passed to emit(capture mask):
 //  - numeric card: every set of pool numerics whose values complete 11,
-//    enumerated in colex order (= ascending mask) by an explicit-stack
-//    depth-first search over the pool numerics sorted by index (values are
-//    non-decreasing in index, which bounds every frame); no capture -> lay;
+//    enumerated in colex order (= ascending mask) by a depth-first search over
+//    the pool's bits: a set's cards are chosen from the highest down, the
+//    candidates of a step are the pool cards below the last chosen one, and
+//    values never decrease with the index, which ends a step early.  The
+//    chosen cards (at most 9) are a stack of 6-bit fields in one register;
+//    no capture -> lay;
 //  - Jack: all pool numerics and Jacks, or a lay if there are none;
 //  - Queen/King: one capture per same-rank pool card, else a lay.
 template <class Emit>
-__device__ inline void for_each_move(const Hand &h, uint64_t pool, Emit &&emit) {
-  uint8_t num[40];
-  int m = 0;
-  for (uint64_t pn = pool & kNumericMask; pn; pn &= pn - 1) num[m++] = (uint8_t)(__ffsll((long long)pn) - 1);
-  for (int s = 0; s < h.k; ++s) {
-    const int c = h.card[s];
-    bool found = false;
-    if (c < 40) {
-      int hh[11], tt[11], lim[11];
-      uint64_t acc = 0;
-      int d = 0;
-      hh[0] = 0;
-      tt[0] = 11 - card_value(c);
-      lim[0] = m;
-      while (true) {
-        if (hh[d] >= lim[d]) {
-          if (d == 0) break;
-          --d;
-          acc &= ~(1ull << num[hh[d]]);
-          ++hh[d];
-          continue;
-        }
-        const int v = card_value(num[hh[d]]);
-        if (v > tt[d]) {  // every later card is at least as large
-          hh[d] = lim[d];
-          continue;
-        }
-        if (v == tt[d]) {
-          emit(s, c, acc | (1ull << num[hh[d]]));
-          found = true;
-          ++hh[d];
-          continue;
-        }
-        acc |= 1ull << num[hh[d]];
-        lim[d + 1] = hh[d];
-        tt[d + 1] = tt[d] - v;
-        hh[d + 1] = 0;
-        ++d;
+__device__ __forceinline__ void for_each_move(int c, uint64_t pool, Emit &&emit) {
+  bool found = false;
+  if (c < 40) {
+    const uint64_t pn = pool & kNumericMask;
+    uint64_t acc = 0, stack = 0, m = pn;
+    int rem = 11 - card_value(c), depth = 0;
+    while (true) {
+      if (m == 0) {
+        if (depth == 0) break;
+        const int x = (int)(stack & 63);
+        stack >>= 6;
+        --depth;
+        acc &= ~(1ull << x);
+        rem += card_value(x);
+        const uint64_t below = depth ? (1ull << (stack & 63)) - 1 : ~0ull;
+        m = pn & below & ~((2ull << x) - 1);
+        continue;
       }
-    } else if (c < 44) {
-      uint64_t cap = pool & (kNumericMask | kJackMask);
-      if (cap) {
-        emit(s, c, cap);
+      const int x = __ffsll((long long)m) - 1, v = card_value(x);
+      if (v > rem) {  // every later card is at least as large
+        m = 0;
+      } else if (v == rem) {
+        emit(acc | (1ull << x));
         found = true;
-      }
-    } else {
-      for (uint64_t cap = pool & (0xFull << (c & ~3)); cap; cap &= cap - 1) {
-        emit(s, c, cap & (~cap + 1));
-        found = true;
+        m &= m - 1;
+      } else {
+        acc |= 1ull << x;
+        rem -= v;
+        stack = (stack << 6) | (uint64_t)x;
+        ++depth;
+        m = pn & ((1ull << x) - 1);
       }
     }
-    if (!found) emit(s, c, 0ull);
+  } else if (c < 44) {
+    const uint64_t cap = pool & (kNumericMask | kJackMask);
+    if (cap) {
+      emit(cap);
+      found = true;
+    }
+  } else {
+    for (uint64_t cap = pool & (0xFull << (c & ~3)); cap; cap &= cap - 1) {
+      emit(cap & (~cap + 1));
+      found = true;
+    }
   }
+  if (!found) emit(0ull);
 }
 
-__global__ void k_gt_count(int64_t n, const uint64_t *__restrict__ pool,
-                           const uint8_t *__restrict__ hands, DealInfo di, int mover,
-                           int32_t *__restrict__ counts) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  Hand h = held_cards(di, hands[i], mover);
-  int cnt = 0;
-  for_each_move(h, pool[i], [&](int, int, uint64_t) { ++cnt; });
-  counts[i] = cnt;
+// Moves per held card (16 bits each) of every node of a level; four threads per
+// node, one per card: the search is a serial walk, and early levels have few
+// nodes (one thread per node with its cards in turn and the search's state in
+// indexed arrays took 17 us for the levels of a two-round subgame).
+__global__ void __launch_bounds__(kThreads)
+    k_gt_count(int64_t n, const uint64_t *__restrict__ pool, const uint8_t *__restrict__ hands,
+               DealInfo di, int mover, uint64_t *__restrict__ counts) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = t >> 2;
+  const int slot = (int)(t & 3);
+  uint64_t cnt = 0;
+  if (i < n) {
+    const int b = held_bit(di, hands[i], mover, slot);
+    if (b >= 0) for_each_move(di.card[b], pool[i], [&](uint64_t) { ++cnt; });
+  }
+  cnt <<= 16 * slot;
+  cnt |= __shfl_xor((unsigned long long)cnt, 1, 64);
+  cnt |= __shfl_xor((unsigned long long)cnt, 2, 64);
+  if (i < n && slot == 0) counts[i] = cnt;
 }
+
+struct MovesIn {
+  using Acc = int64_t;
+  const uint64_t *counts;
+  __device__ __forceinline__ int64_t operator()(int, int64_t i) const {
+    const uint64_t c = counts[i];
+    return (int64_t)((c & 0xFFFF) + ((c >> 16) & 0xFFFF) + ((c >> 32) & 0xFFFF) + (c >> 48));
+  }
+};
 
 // ApplyActions (and the capture/Sur/clean-up scoring): children of node i
-// written at child_begin[i] + j.
-__global__ void k_gt_fill(int64_t n, int round, int ply, const uint64_t *__restrict__ pool,
-                          const uint8_t *__restrict__ hands, const uint64_t *__restrict__ rs,
-                          const int32_t *__restrict__ cb, DealInfo di,
-                          uint64_t *__restrict__ c_pool, uint8_t *__restrict__ c_hands,
-                          uint64_t *__restrict__ c_rs, int32_t *__restrict__ c_parent,
-                          uint8_t *__restrict__ c_card, uint64_t *__restrict__ c_cap) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// written at child_begin[i] + j, by four threads as in k_gt_count.
+__global__ void __launch_bounds__(kThreads)
+    k_gt_fill(int64_t n, int round, int ply, const uint64_t *__restrict__ pool,
+              const uint8_t *__restrict__ hands, const uint64_t *__restrict__ rs,
+              const int32_t *__restrict__ cb, const uint64_t *__restrict__ counts, DealInfo di,
+              uint64_t *__restrict__ c_pool, uint8_t *__restrict__ c_hands,
+              uint64_t *__restrict__ c_rs, int32_t *__restrict__ c_parent,
+              uint8_t *__restrict__ c_card, uint64_t *__restrict__ c_cap) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = t >> 2;
+  const int slot = (int)(t & 3);
   if (i >= n) return;
   const int mover = ply & 1;
-  const uint64_t p0 = pool[i];
   const uint8_t h0 = hands[i];
-  const uint64_t r0 = rs[i];
-  Hand h = held_cards(di, h0, mover);
+  const int bit = held_bit(di, h0, mover, slot);
+  if (bit < 0) return;
+  const int c = di.card[bit];
+  const uint64_t p0 = pool[i], r0 = rs[i], cnt = counts[i];
   int64_t q = cb[i];
-  for_each_move(h, p0, [&](int s, int c, uint64_t cap) {
+  for (int s = 0; s < slot; ++s) q += (int64_t)((cnt >> (16 * s)) & 0xFFFF);
+  for_each_move(c, p0, [&](uint64_t cap) {
     uint64_t p = p0;
     int8_t r[8];
 #pragma unroll
@@ -159,22 +175,35 @@ __global__ void k_gt_fill(int64_t n, int round, int ply, const uint64_t *__restr
       p |= cbit;
     } else {
       const uint64_t taken = cap | cbit;
-      r[mover] += (int8_t)__popcll(taken & kClubMask);
-      r[3 + 2 * mover] += (int8_t)points_of(taken);
+      const int8_t clubs = (int8_t)__popcll(taken & kClubMask), pts = (int8_t)points_of(taken);
+      const int8_t sur = cap == p0 && !(c >= 40 && c < 44) && round != 5 ? 1 : 0;
+      if (mover == 0) {
+        r[0] += clubs;
+        r[3] += pts;
+        r[4] += sur;
+      } else {
+        r[1] += clubs;
+        r[5] += pts;
+        r[6] += sur;
+      }
       r[2] = (int8_t)(mover + 1);
-      if (cap == p0 && !(c >= 40 && c < 44) && round != 5) r[4 + 2 * mover] += 1;
       p &= ~cap;
     }
     if (round == 5 && ply == 7 && r[2] != 0) {
-      const int w = r[2] - 1;
-      r[w] += (int8_t)__popcll(p & kClubMask);
-      r[3 + 2 * w] += (int8_t)points_of(p);
+      const int8_t clubs = (int8_t)__popcll(p & kClubMask), pts = (int8_t)points_of(p);
+      if (r[2] == 1) {
+        r[0] += clubs;
+        r[3] += pts;
+      } else {
+        r[1] += clubs;
+        r[5] += pts;
+      }
     }
     uint64_t packed = 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) packed |= (uint64_t)(uint8_t)r[k] << (8 * k);
     c_pool[q] = p;
-    c_hands[q] = (uint8_t)(h0 & ~(1u << h.bit[s]));
+    c_hands[q] = (uint8_t)(h0 & ~(1u << bit));
     c_rs[q] = packed;
     c_parent[q] = (int32_t)i;
     c_card[q] = (uint8_t)c;
@@ -185,43 +214,45 @@ __global__ void k_gt_fill(int64_t n, int round, int ply, const uint64_t *__restr
 
 // Root checks: canonical order (strictly ascending by pool, bonus, ca, cb,
 // d), valid scores, pools made of cards dealt before the round, zero pad.
+// *bad is a host word; with `keys`, also marks every root's score key in that
+// set of 2^16 bits.
 __global__ void k_check_roots(int64_t n, const pasur_root *__restrict__ roots,
-                              uint64_t dealt_before, int *__restrict__ bad) {
+                              uint64_t dealt_before, int64_t *__restrict__ bad,
+                              unsigned long long *__restrict__ keys) {
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
   const pasur_root r = roots[j];
   bool ok = (r.pool & ~dealt_before) == 0 && r.pad == 0 && r.bonus >= 0 && r.bonus <= 2;
   ok = ok && (r.bonus == 0 ? (r.ca >= 0 && r.ca <= 6 && r.cb >= 0 && r.cb <= 6)
                            : (r.ca == 0 && r.cb == 0));
+  const uint32_t kr = score_key(r.ca, r.cb, r.d, r.bonus);
   if (ok && j > 0) {
     const pasur_root p = roots[j - 1];
     const uint32_t kp = score_key(p.ca, p.cb, p.d, p.bonus);
-    const uint32_t kr = score_key(r.ca, r.cb, r.d, r.bonus);
     ok = r.pool > p.pool || (r.pool == p.pool && kr > kp);
   }
-  if (!ok) atomicOr(bad, 1);
+  if (!ok) *bad = 1;
+  if (keys) atomicOr(&keys[(kr & 0xFFFF) >> 6], 1ull << (kr & 63));
 }
 
-__global__ void k_pool_flags(int64_t n, const pasur_root *__restrict__ roots,
-                             int32_t *__restrict__ flags) {
+// 1 where a root's pool differs from the root's before it.
+struct PoolChange {
+  using Acc = int;
+  const pasur_root *roots;
+  __device__ __forceinline__ int operator()(int, int64_t j) const {
+    return j == 0 || roots[j].pool != roots[j - 1].pool ? 1 : 0;
+  }
+};
+
+// Level 0 of the game tree: the distinct pools, everything held, no points.
+__global__ void k_gt_roots(int64_t n, const pasur_root *__restrict__ roots,
+                           const int32_t *__restrict__ pos, uint64_t *__restrict__ pools,
+                           uint8_t *__restrict__ hands, uint64_t *__restrict__ rs) {
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  flags[j] = (j == 0 || roots[j].pool != roots[j - 1].pool) ? 1 : 0;
-}
-
-__global__ void k_pool_compact(int64_t n, const pasur_root *__restrict__ roots,
-                               const int32_t *__restrict__ flags, const int32_t *__restrict__ pos,
-                               uint64_t *__restrict__ pools) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  if (flags[j]) pools[pos[j]] = roots[j].pool;
-}
-
-__global__ void k_gt_root_init(int64_t n, uint8_t *__restrict__ hands, uint64_t *__restrict__ rs) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  hands[i] = 0xFF;
-  rs[i] = 0;
+  if (j >= n || pos[j + 1] == pos[j]) return;
+  pools[pos[j]] = roots[j].pool;
+  hands[pos[j]] = 0xFF;
+  rs[pos[j]] = 0;
 }
 
 int validate_deck(const uint8_t *deck) {
@@ -240,8 +271,7 @@ int validate_deck(const uint8_t *deck) {
   return PASUR_OK;
 }
 
-int check_roots(const uint8_t *deck, int round, const pasur_root *d_roots, int64_t n_roots,
-                hipStream_t stream) {
+int check_root_list(const pasur_root *d_roots, int64_t n_roots) {
   if (!d_roots || n_roots < 1) {
     set_error("need at least one root");
     return PASUR_E_INVAL;
@@ -250,49 +280,19 @@ int check_roots(const uint8_t *deck, int round, const pasur_root *d_roots, int64
     set_error("too many roots");
     return PASUR_E_OVERFLOW;
   }
-  uint64_t dealt = 0;
-  for (int i = 0; i < 4 + 8 * round; ++i) dealt |= 1ull << deck[i];
-  int *bad = nullptr;
-  PASUR_TRY(dev_alloc(&bad, 1));
-  int hbad = 0;
-  hipError_t e = hipMemsetAsync(bad, 0, sizeof(int), stream);
-  if (e == hipSuccess) {
-    k_check_roots<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, d_roots, dealt, bad);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  dev_free(bad);
-  if (e != hipSuccess) {
-    set_error("root check: %s", hipGetErrorString(e));
-    return PASUR_E_HIP;
-  }
-  if (hbad) {
-    set_error("roots must be strictly ascending by (pool, bonus, ca, cb, d), hold valid "
-              "scores and pools of cards dealt before round %d", round);
-    return PASUR_E_INVAL;
-  }
   return PASUR_OK;
 }
 
-// Distinct pools of the (sorted) roots: flags, positions, count.
-int distinct_pools(const pasur_root *d_roots, int64_t n_roots, int32_t **d_pos,
-                   int64_t *n_pools, uint64_t *d_pools /* nullable */, hipStream_t stream) {
-  int32_t *flags = nullptr;
-  PASUR_TRY(dev_alloc(&flags, n_roots));
-  int st = dev_alloc(d_pos, n_roots + 1);
-  if (st) { dev_free(flags); return st; }
-  k_pool_flags<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, d_roots, flags);
-  st = scan_counts(flags, n_roots, *d_pos, n_pools, stream);
-  if (!st && d_pools) {
-    k_pool_compact<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, d_roots, flags, *d_pos,
-                                                                d_pools);
-    hipError_t e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) { set_error("pool compaction: %s", hipGetErrorString(e)); st = PASUR_E_HIP; }
-  }
-  dev_free(flags);
-  if (st) dev_free(*d_pos);
-  return st;
+int bad_roots(int round) {
+  set_error("roots must be strictly ascending by (pool, bonus, ca, cb, d), hold valid "
+            "scores and pools of cards dealt before round %d", round);
+  return PASUR_E_INVAL;
+}
+
+uint64_t dealt_before(const uint8_t *deck, int round) {
+  uint64_t dealt = 0;
+  for (int i = 0; i < 4 + 8 * round; ++i) dealt |= 1ull << deck[i];
+  return dealt;
 }
 
 DealInfo deal_info(const uint8_t *deck, int round) {
@@ -310,17 +310,87 @@ DealInfo deal_info(const uint8_t *deck, int round) {
 
 extern "C" void pasur_gt_free(pasur_gt *g) {
   if (!g) return;
-  for (int l = 0; l < 9; ++l) {
-    dev_free(g->pool[l]);
-    dev_free(g->hands[l]);
-    dev_free(g->rs[l]);
-    dev_free(g->parent[l]);
-    dev_free(g->act_card[l]);
-    dev_free(g->act_cap[l]);
-    if (l < 8) dev_free(g->child_begin[l]);
-  }
+  anchor_wait(g->anchor);
+  for (int l = 0; l < 9; ++l) block_free(g->block[l]);
   delete g;
 }
+
+namespace {
+
+// The arrays of level l with n nodes, and room for the moves' counts.
+int alloc_level(pasur_gt *g, int l, int64_t n, uint64_t **counts) {
+  g->n[l] = n;
+  Arena a;
+  a.want(&g->pool[l], n);
+  a.want(&g->rs[l], n);
+  a.want(&g->hands[l], n);
+  if (l > 0) {
+    a.want(&g->act_cap[l], n);
+    a.want(&g->parent[l], n);
+    a.want(&g->act_card[l], n);
+  }
+  if (l < 8) {
+    a.want(&g->child_begin[l], n + 1);
+    a.want(counts, n);
+  }
+  PASUR_TRY(a.alloc());
+  g->block[l] = a.release();
+  return PASUR_OK;
+}
+
+int build_levels(pasur_gt *g, const pasur_root *d_roots, int64_t n_roots, hipStream_t stream) {
+  Arena scratch, level_words;
+  HostWords host(stream);  // its end waits for the stream before the arenas'
+  if (!host.ok()) return PASUR_E_NOMEM;
+  PASUR_TRY(anchor_alloc(&g->anchor));
+  int32_t *pos = nullptr;
+  int64_t *words = nullptr;
+  scratch.want(&pos, n_roots + 1);
+  scratch.want(&words, scan_scratch(n_roots));
+  PASUR_TRY(scratch.alloc());
+  k_check_roots<<<grid_for(n_roots), kThreads, 0, stream>>>(
+      n_roots, d_roots, dealt_before(g->deck, g->round), host.dev(0), nullptr);
+  scan_enqueue(PoolChange{d_roots}, OffsetsOut{pos, 0}, n_roots, 1, words, host.dev(1), stream);
+  PASUR_TRY(host.wait());
+  if (host[0]) return bad_roots(g->round);
+  // level 0: distinct root pools (ascending because the roots are sorted)
+  uint64_t *counts = nullptr;
+  PASUR_TRY(alloc_level(g, 0, host[1], &counts));
+  k_gt_roots<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, d_roots, pos, g->pool[0],
+                                                         g->hands[0], g->rs[0]);
+  const DealInfo di = deal_info(g->deck, g->round);
+  // scans of the levels: their scratch grows with them (every scan has ended
+  // when the next level's begins)
+  int64_t have = 0;
+  int64_t *lw = nullptr;
+  for (int l = 0; l < 8; ++l) {
+    const int64_t n = g->n[l];
+    const unsigned grid = (unsigned)((4 * n + kThreads - 1) / kThreads);
+    if (n >= kScanTile && scan_scratch(n) > have) {
+      block_free(level_words.release());
+      level_words = Arena();
+      have = 4 * scan_scratch(n);
+      level_words.want(&lw, have);
+      PASUR_TRY(level_words.alloc());
+    }
+    k_gt_count<<<grid, kThreads, 0, stream>>>(n, g->pool[l], g->hands[l], di, l & 1, counts);
+    scan_enqueue(MovesIn{counts}, OffsetsOut{g->child_begin[l], 0}, n, 1, lw, host.dev(2), stream);
+    PASUR_TRY(host.wait());
+    PASUR_TRY(total_fits(host[2]));
+    uint64_t *next_counts = nullptr;
+    PASUR_TRY(alloc_level(g, l + 1, host[2], &next_counts));
+    k_gt_fill<<<grid, kThreads, 0, stream>>>(
+        n, g->round, l, g->pool[l], g->hands[l], g->rs[l], g->child_begin[l], counts, di,
+        g->pool[l + 1], g->hands[l + 1], g->rs[l + 1], g->parent[l + 1], g->act_card[l + 1],
+        g->act_cap[l + 1]);
+    PASUR_TRY_HIP(hipGetLastError());
+    counts = next_counts;
+    (void)host.dev(0);  // the fill is pending
+  }
+  return host.wait();
+}
+
+}  // namespace
 
 extern "C" int pasur_build_round_tree(const uint8_t deck[52], int round,
                                       const pasur_root *d_roots, int64_t n_roots,
@@ -336,67 +406,12 @@ extern "C" int pasur_build_round_tree(const uint8_t deck[52], int round,
     return PASUR_E_RANGE;
   }
   PASUR_TRY(validate_deck(deck));
-  PASUR_TRY(check_roots(deck, round, d_roots, n_roots, stream));
-
+  PASUR_TRY(check_root_list(d_roots, n_roots));
   pasur_gt *g = new pasur_gt();
   std::memset(g, 0, sizeof(*g));
   g->round = round;
   std::memcpy(g->deck, deck, 52);
-  const DealInfo di = deal_info(deck, round);
-  int st = PASUR_OK;
-  int32_t *pos = nullptr, *counts = nullptr;
-  int64_t n0 = 0;
-  // level 0: distinct root pools (ascending because the roots are sorted)
-  st = distinct_pools(d_roots, n_roots, &pos, &n0, nullptr, stream);
-  if (!st) st = dev_alloc(&g->pool[0], n0);
-  if (!st) {
-    dev_free(pos);
-    st = distinct_pools(d_roots, n_roots, &pos, &n0, g->pool[0], stream);
-  }
-  dev_free(pos);
-  g->n[0] = n0;
-  if (!st) st = dev_alloc(&g->hands[0], n0);
-  if (!st) st = dev_alloc(&g->rs[0], n0);
-  if (!st) {
-    k_gt_root_init<<<grid_for(n0), kThreads, 0, stream>>>(n0, g->hands[0], g->rs[0]);
-  }
-  for (int l = 0; l < 8 && !st; ++l) {
-    const int64_t n = g->n[l];
-    st = dev_alloc(&counts, n);
-    if (!st) st = dev_alloc(&g->child_begin[l], n + 1);
-    if (st) break;
-    k_gt_count<<<grid_for(n), kThreads, 0, stream>>>(n, g->pool[l], g->hands[l], di, l & 1,
-                                                      counts);
-    int64_t total = 0;
-    st = scan_counts(counts, n, g->child_begin[l], &total, stream);
-    dev_free(counts);
-    if (st) break;
-    const int L = l + 1;
-    g->n[L] = total;
-    st = dev_alloc(&g->pool[L], total);
-    if (!st) st = dev_alloc(&g->hands[L], total);
-    if (!st) st = dev_alloc(&g->rs[L], total);
-    if (!st) st = dev_alloc(&g->parent[L], total);
-    if (!st) st = dev_alloc(&g->act_card[L], total);
-    if (!st) st = dev_alloc(&g->act_cap[L], total);
-    if (st) break;
-    k_gt_fill<<<grid_for(n), kThreads, 0, stream>>>(
-        n, round, l, g->pool[l], g->hands[l], g->rs[l], g->child_begin[l], di, g->pool[L],
-        g->hands[L], g->rs[L], g->parent[L], g->act_card[L], g->act_cap[L]);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) {
-      set_error("gt fill level %d: %s", l, hipGetErrorString(e));
-      st = PASUR_E_HIP;
-    }
-  }
-  if (!st) {
-    hipError_t e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-      set_error("gt build: %s", hipGetErrorString(e));
-      st = PASUR_E_HIP;
-    }
-  }
-  dev_free(counts);
+  const int st = build_levels(g, d_roots, n_roots, stream);
   if (st) {
     pasur_gt_free(g);
     return st;
@@ -454,34 +469,41 @@ extern "C" int pasur_gt_read(const pasur_gt *gt, int field, int level, void *hos
 // --------------------------------------------------------------------------
 namespace {
 
-__global__ void k_root_keys(int64_t n, const pasur_root *__restrict__ roots,
-                            uint32_t *__restrict__ keys) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const pasur_root r = roots[j];
-  keys[j] = score_key(r.ca, r.cb, r.d, r.bonus);
+constexpr int kKeyWords = 65536 / 64;
+
+__global__ void k_clear_words(unsigned long long *w, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) w[i] = 0;
 }
 
-__global__ void k_key_flags(int64_t n, const uint32_t *__restrict__ keys, int32_t *__restrict__ flags) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  flags[j] = (j == 0 || keys[j] != keys[j - 1]) ? 1 : 0;
+// The score table from the set of the roots' score keys (one workgroup, a
+// thread per 64 keys): ids ascend with the key; before[i] = ids below key 64 i.
+__global__ void __launch_bounds__(kKeyWords)
+    k_score_table(const unsigned long long *__restrict__ keys, int32_t *__restrict__ before,
+                  int8_t *__restrict__ tab, int64_t *__restrict__ total) {
+  __shared__ int part[kKeyWords / 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  unsigned long long m = keys[t];
+  const int n = __popcll(m), incl = wave_inclusive(n, lane);
+  if (lane == 63) part[w] = incl;
+  __syncthreads();
+  int s = incl - n;
+  for (int k = 0; k < w; ++k) s += part[k];
+  before[t] = s;
+  if (t == kKeyWords - 1) *total = s + n;
+  for (; m; m &= m - 1, ++s) {
+    int ca, cb, d, bonus;
+    score_unkey((uint32_t)(64 * t + __ffsll((long long)m) - 1), &ca, &cb, &d, &bonus);
+    tab[4 * s + 0] = (int8_t)ca;
+    tab[4 * s + 1] = (int8_t)cb;
+    tab[4 * s + 2] = (int8_t)d;
+    tab[4 * s + 3] = (int8_t)bonus;
+  }
 }
 
-__global__ void k_score_table(int64_t n, const uint32_t *__restrict__ keys,
-                              const int32_t *__restrict__ flags, const int32_t *__restrict__ pos,
-                              uint32_t *__restrict__ ukeys, int8_t *__restrict__ tab) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n || !flags[j]) return;
-  int ca, cb, d, bonus;
-  score_unkey(keys[j], &ca, &cb, &d, &bonus);
-  const int32_t s = pos[j];
-  ukeys[s] = keys[j];
-  tab[4 * s + 0] = (int8_t)ca;
-  tab[4 * s + 1] = (int8_t)cb;
-  tab[4 * s + 2] = (int8_t)d;
-  tab[4 * s + 3] = (int8_t)bonus;
-}
+struct GtChildBegin {
+  const int32_t *cb[8];
+};
 
 // Per FGT root: its GT root (index of its pool among the distinct pools),
 // its score id, and the descendant range [lo, hi) of that GT root on every
@@ -489,66 +511,98 @@ __global__ void k_score_table(int64_t n, const uint32_t *__restrict__ keys,
 // parent-major).
 __global__ void k_root_ranges(int64_t n_roots, const pasur_root *__restrict__ roots,
                               const int32_t *__restrict__ pool_pos, const uint64_t *__restrict__ gt_pool0,
-                              const uint32_t *__restrict__ ukeys, int64_t n_scores,
-                              const int32_t *const *__restrict__ gt_cb, int32_t *__restrict__ lo,
-                              int32_t *__restrict__ hi, int32_t *__restrict__ root_sid,
-                              int *__restrict__ bad) {
+                              int64_t gt_n0, const unsigned long long *__restrict__ keys,
+                              const int32_t *__restrict__ before, GtChildBegin gt,
+                              int32_t *__restrict__ lo, int32_t *__restrict__ hi,
+                              int32_t *__restrict__ root_sid, int64_t *__restrict__ bad) {
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n_roots) return;
   const pasur_root r = roots[j];
-  const int32_t g = pool_pos[j + 1] - 1;  // inclusive scan of pool-change flags
-  if (gt_pool0[g] != r.pool) atomicOr(bad, 1);
-  const uint32_t k = score_key(r.ca, r.cb, r.d, r.bonus);
-  int64_t a = 0, b = n_scores;
-  while (a < b) {
-    int64_t m = (a + b) >> 1;
-    if (ukeys[m] < k) a = m + 1; else b = m;
-  }
-  root_sid[j] = (int32_t)a;
+  // inclusive scan of pool-change flags; roots that are not the game tree's
+  // are reported and kept inside its arrays
+  int32_t g = pool_pos[j + 1] - 1;
+  if (g >= gt_n0) g = (int32_t)gt_n0 - 1;
+  if (gt_pool0[g] != r.pool) *bad = 1;
+  const uint32_t k = score_key(r.ca, r.cb, r.d, r.bonus) & 0xFFFF;
+  root_sid[j] = before[k >> 6] + __popcll(keys[k >> 6] & ((1ull << (k & 63)) - 1));
   int32_t l0 = g, h0 = g + 1;
   lo[j] = l0;
   hi[j] = h0;
   for (int l = 0; l < 8; ++l) {
-    l0 = gt_cb[l][l0];
-    h0 = gt_cb[l][h0];
+    l0 = gt.cb[l][l0];
+    h0 = gt.cb[l][h0];
     lo[(int64_t)(l + 1) * n_roots + j] = l0;
     hi[(int64_t)(l + 1) * n_roots + j] = h0;
   }
 }
 
-__global__ void k_range_sizes(int64_t n_roots, const int32_t *__restrict__ lo,
-                              const int32_t *__restrict__ hi, int32_t *__restrict__ sz) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n_roots) return;
-  sz[j] = hi[j] - lo[j];
-}
-
-// FGT node i of level l: root j (binary search in the level's root offsets),
-// GT node, score id, parent and child range.
-__global__ void k_fgt_fill(int64_t n, int level, int64_t n_roots, const int32_t *__restrict__ off,
-                           const int32_t *__restrict__ off_up, const int32_t *__restrict__ off_dn,
-                           const int32_t *__restrict__ lo, const int32_t *__restrict__ lo_up,
-                           const int32_t *__restrict__ lo_dn, const int32_t *__restrict__ root_sid,
-                           const int32_t *__restrict__ gt_parent, const int32_t *__restrict__ gt_cb,
-                           int64_t n_dn, int32_t *__restrict__ f_gt, int32_t *__restrict__ f_sid,
-                           int32_t *__restrict__ f_parent, int32_t *__restrict__ f_cb) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int64_t a = 0, b = n_roots;  // largest j with off[j] <= i
-  while (b - a > 1) {
-    int64_t m = (a + b) >> 1;
-    if (off[m] <= i) a = m; else b = m;
+// Nodes of every root's subtree on level `batch`.
+struct RangeSizes {
+  using Acc = int64_t;
+  const int32_t *lo, *hi;
+  int64_t n_roots;
+  __device__ __forceinline__ int64_t operator()(int batch, int64_t j) const {
+    return hi[batch * n_roots + j] - lo[batch * n_roots + j];
   }
-  // skip empty ranges (cannot happen for a round tree, kept for safety)
-  while (a + 1 < n_roots && off[a + 1] <= i) ++a;
-  const int64_t j = a;
+};
+
+struct FgtFill {
+  int64_t first[10];  // the levels' nodes as one range
+  int64_t n_roots;
+  const int32_t *off;  // [9][n_roots + 1] root offsets
+  const int32_t *lo;   // [9][n_roots] first GT node of a root
+  const int32_t *root_sid;
+  const int32_t *gt_parent[9], *gt_cb[8];
+  int32_t *gt[9], *sid[9], *parent[9], *cb[8];
+};
+
+// FGT node i of a level: its root (binary search in the level's root offsets,
+// between the roots of the workgroup's first and last node where these are of
+// one level: a root has hundreds of nodes on the large levels), GT node, score
+// id, parent and child range.
+__global__ void __launch_bounds__(kThreads) k_fgt_fill(FgtFill a) {
+  __shared__ int64_t bound[2];
+  auto level_of = [&](int64_t x) {
+    int l = 0;
+#pragma unroll
+    for (int k = 1; k < 9; ++k) l += x >= a.first[k] ? 1 : 0;
+    return l;
+  };
+  auto root_of = [&](const int32_t *off, int64_t i, int64_t lo, int64_t hi) {
+    while (hi - lo > 1) {  // largest j with off[j] <= i
+      const int64_t m = (lo + hi) >> 1;
+      if (off[m] <= i) lo = m; else hi = m;
+    }
+    // skip empty ranges (cannot happen for a round tree, kept for safety)
+    while (lo + 1 < a.n_roots && off[lo + 1] <= i) ++lo;
+    return lo;
+  };
+  const int64_t x0 = (int64_t)blockIdx.x * kThreads;
+  const int64_t x1 = x0 + kThreads < a.first[9] ? x0 + kThreads : a.first[9];  // end
+  const int l0 = level_of(x0);
+  const bool one_level = l0 == level_of(x1 - 1);
+  const int64_t on = a.n_roots + 1;
+  if (one_level && (threadIdx.x & 63) == 0 && threadIdx.x < 128) {
+    const int64_t x = threadIdx.x == 0 ? x0 : x1 - 1;
+    bound[threadIdx.x >> 6] = root_of(a.off + l0 * on, x - a.first[l0], 0, a.n_roots);
+  }
+  __syncthreads();
+  const int64_t x = x0 + threadIdx.x;
+  if (x >= x1) return;
+  const int l = one_level ? l0 : level_of(x);
+  const int64_t i = x - a.first[l];
+  const int32_t *const off = a.off + l * on;
+  const int64_t j = one_level ? root_of(off, i, bound[0], bound[1] + 1)
+                              : root_of(off, i, 0, a.n_roots);
+  const int32_t *const lo = a.lo + l * a.n_roots;
   const int32_t g = lo[j] + (int32_t)(i - off[j]);
-  f_gt[i] = g;
-  f_sid[i] = root_sid[j];
-  if (level > 0) f_parent[i] = off_up[j] + (gt_parent[g] - lo_up[j]);
-  if (level < 8) {
-    f_cb[i] = off_dn[j] + (gt_cb[g] - lo_dn[j]);
-    if (i == n - 1) f_cb[n] = (int32_t)n_dn;
+  a.gt[l][i] = g;
+  a.sid[l][i] = a.root_sid[j];
+  if (l > 0) a.parent[l][i] = (off - on)[j] + (a.gt_parent[l][g] - (lo - a.n_roots)[j]);
+  if (l < 8) {
+    a.cb[l][i] = (off + on)[j] + (a.gt_cb[l][g] - (lo + a.n_roots)[j]);
+    const int64_t n = a.first[l + 1] - a.first[l];
+    if (i == n - 1) a.cb[l][n] = (int32_t)(a.first[l + 2] - a.first[l + 1]);
   }
 }
 
@@ -602,25 +656,28 @@ __global__ void k_leaf_pass(int64_t n, int round, const int32_t *__restrict__ f_
   idx[i] = (int32_t)i;
 }
 
-__global__ void k_u64_flags(int64_t n, const uint64_t *__restrict__ keys, int32_t *__restrict__ flags) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  flags[j] = (j == 0 || keys[j] != keys[j - 1]) ? 1 : 0;
-}
+// 1 where a sorted key differs from the one before it.
+struct KeyChange {
+  using Acc = int;
+  const uint64_t *keys;
+  __device__ __forceinline__ int operator()(int, int64_t j) const {
+    return j == 0 || keys[j] != keys[j - 1] ? 1 : 0;
+  }
+};
 
 struct DealtCards {
   uint8_t card[52];  // cards dealt up to the end of the round, ascending
 };
 
 __global__ void k_next_roots(int64_t n, const uint64_t *__restrict__ keys,
-                             const int32_t *__restrict__ idx, const int32_t *__restrict__ flags,
-                             const int32_t *__restrict__ pos, DealtCards dc,
+                             const int32_t *__restrict__ idx, const int32_t *__restrict__ pos,
+                             DealtCards dc,
                              pasur_root *__restrict__ next, int32_t *__restrict__ link) {
   int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   const int32_t u = pos[k + 1] - 1;
   link[idx[k]] = u;
-  if (!flags[k]) return;
+  if (pos[k] != u) return;  // not the first of its key
   const uint64_t key = keys[k];
   uint64_t pool = 0;
   for (uint64_t m = key >> 16; m; m &= m - 1) pool |= 1ull << dc.card[__ffsll((long long)m) - 1];
@@ -636,27 +693,14 @@ __global__ void k_next_roots(int64_t n, const uint64_t *__restrict__ keys,
   next[u] = r;
 }
 
-__global__ void k_iota(int64_t n, int32_t *v) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) v[j] = (int32_t)j;
-}
-
 }  // namespace
 
 extern "C" void pasur_fgt_free(pasur_fgt *f) {
   if (!f) return;
-  for (int l = 0; l < 9; ++l) {
-    dev_free(f->gt[l]);
-    dev_free(f->sid[l]);
-    dev_free(f->parent[l]);
-    if (l < 8) dev_free(f->child_begin[l]);
-  }
-  dev_free(f->score_tab);
-  dev_free(f->next_roots);
-  dev_free(f->link);
-  dev_free(f->leaf_base);
-  dev_free(f->leaf_bonus);
-  for (int l = 0; l < 9; ++l) dev_free(f->root_off[l]);
+  anchor_wait(f->anchor);
+  block_free(f->off_block);
+  block_free(f->block);
+  block_free(f->next_block);
   std::free(f->h_root_off);
   std::free(f->h_root_seg);
   sweep_index_free(f->sweep);
@@ -665,156 +709,141 @@ extern "C" void pasur_fgt_free(pasur_fgt *f) {
 
 namespace {
 
-struct Scratch {
-  std::vector<void *> ptrs;
-  ~Scratch() {
-    for (void *p : ptrs)
-      if (p) (void)hipFree(p);
-  }
-  template <class T>
-  int alloc(T **p, int64_t n) {
-    int st = dev_alloc(p, n);
-    if (!st) ptrs.push_back((void *)*p);
-    return st;
-  }
-};
-
 int unfold_impl(const pasur_gt *gt, const pasur_root *d_roots, int64_t n_roots, pasur_fgt *f,
                 hipStream_t stream) {
-  Scratch s;
-  // --- score table: distinct root scores, ascending by (bonus, ca, cb, d)
-  uint32_t *keys = nullptr, *keys_sorted = nullptr, *ukeys = nullptr;
-  int32_t *iv = nullptr, *iv2 = nullptr, *flags = nullptr, *pos = nullptr;
-  PASUR_TRY(s.alloc(&keys, n_roots));
-  PASUR_TRY(s.alloc(&keys_sorted, n_roots));
-  PASUR_TRY(s.alloc(&iv, n_roots));
-  PASUR_TRY(s.alloc(&iv2, n_roots));
-  PASUR_TRY(s.alloc(&flags, n_roots));
-  PASUR_TRY(s.alloc(&pos, n_roots + 1));
-  k_root_keys<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, d_roots, keys);
-  k_iota<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, iv);
-  PASUR_TRY(radix_sort_pairs<uint32_t>(keys, keys_sorted, iv, iv2, n_roots, 16, stream));
-  k_key_flags<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, keys_sorted, flags);
-  int64_t ns = 0;
-  PASUR_TRY(scan_counts(flags, n_roots, pos, &ns, stream));
-  f->n_scores = ns;
-  PASUR_TRY(dev_alloc(&f->score_tab, 4 * ns));
-  PASUR_TRY(s.alloc(&ukeys, ns));
-  // pos is exclusive: id of a flagged position k is pos[k]
-  k_score_table<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, keys_sorted, flags, pos, ukeys,
-                                                            f->score_tab);
-  // --- GT root of every FGT root
-  int32_t *pool_pos = nullptr;
-  int64_t n_pools = 0;
-  PASUR_TRY(distinct_pools(d_roots, n_roots, &pool_pos, &n_pools, nullptr, stream));
-  s.ptrs.push_back(pool_pos);
-  if (n_pools != gt->n[0]) {
-    set_error("roots have %lld distinct pools, the game tree %lld roots", (long long)n_pools,
-              (long long)gt->n[0]);
-    return PASUR_E_INVAL;
-  }
-  // pool_pos is an exclusive scan of change flags, so pool_pos[j+1]-1 is
-  // the distinct-pool index of root j
-  int32_t *lo = nullptr, *hi = nullptr, *root_sid = nullptr;
-  int *bad = nullptr;
-  const int32_t **d_cb = nullptr;
-  PASUR_TRY(s.alloc(&lo, 9 * n_roots));
-  PASUR_TRY(s.alloc(&hi, 9 * n_roots));
-  PASUR_TRY(s.alloc(&root_sid, n_roots));
-  PASUR_TRY(s.alloc(&bad, 1));
-  PASUR_TRY(s.alloc(&d_cb, 8));
-  PASUR_TRY_HIP(hipMemcpyAsync((void *)d_cb, gt->child_begin, 8 * sizeof(int32_t *),
-                               hipMemcpyHostToDevice, stream));
-  PASUR_TRY_HIP(hipMemsetAsync(bad, 0, sizeof(int), stream));
-  k_root_ranges<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, d_roots, pool_pos,
-                                                             gt->pool[0], ukeys, ns, d_cb, lo, hi,
-                                                             root_sid, bad);
-  int hbad = 0;
-  PASUR_TRY_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, stream));
-  PASUR_TRY_HIP(hipStreamSynchronize(stream));
-  if (hbad) {
-    set_error("root pools do not match the game tree's level 0");
-    return PASUR_E_INVAL;
-  }
-  // --- per level: root offsets
-  int32_t **off = f->root_off;
-  int32_t *sz = nullptr;
-  PASUR_TRY(s.alloc(&sz, n_roots));
+  Arena kept, scratch, levels, leaves;
+  HostWords host(stream);  // its end waits for the stream before the arenas'
+  if (!host.ok()) return PASUR_E_NOMEM;
+  PASUR_TRY(anchor_alloc(&f->anchor));
+  enum { H_BAD, H_POOLS, H_SCORES, H_MISMATCH, H_LEVEL, H_SORT = H_LEVEL + 9, H_NEXT = H_SORT + 2 };
   f->n_roots = n_roots;
-  for (int l = 0; l <= 8; ++l) {
-    PASUR_TRY(dev_alloc(&off[l], n_roots + 1));
-    k_range_sizes<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, lo + (int64_t)l * n_roots,
-                                                              hi + (int64_t)l * n_roots, sz);
-    int64_t total = 0;
-    PASUR_TRY(scan_counts(sz, n_roots, off[l], &total, stream));
-    f->n[l] = total;
-  }
+  // --- roots: score ids, GT roots, descendant ranges, offsets per level
+  int32_t *off = nullptr, *pos = nullptr, *before = nullptr, *lo = nullptr, *hi = nullptr;
+  int32_t *root_sid = nullptr;
+  unsigned long long *keys = nullptr;
+  int64_t *words = nullptr;
+  kept.want(&off, 9 * (n_roots + 1));
+  kept.want(&f->score_tab, 4 * std::min<int64_t>(n_roots, 65536));
+  PASUR_TRY(kept.alloc());
+  f->off_block = kept.release();
+  for (int l = 0; l <= 8; ++l) f->root_off[l] = off + l * (n_roots + 1);
+  scratch.want(&pos, n_roots + 1);
+  scratch.want(&before, kKeyWords);
+  scratch.want(&keys, kKeyWords);
+  scratch.want(&lo, 9 * n_roots);
+  scratch.want(&hi, 9 * n_roots);
+  scratch.want(&root_sid, n_roots);
+  scratch.want(&words, scan_scratch(n_roots, 9));
+  PASUR_TRY(scratch.alloc());
   f->h_root_off = (int32_t *)std::malloc(sizeof(int32_t) * 9 * (size_t)(n_roots + 1));
   if (!f->h_root_off) {
     set_error("host allocation failed");
     return PASUR_E_NOMEM;
   }
-  for (int l = 0; l <= 8; ++l)
-    PASUR_TRY_HIP(hipMemcpy(f->h_root_off + (size_t)l * (n_roots + 1), off[l],
-                            sizeof(int32_t) * (n_roots + 1), hipMemcpyDeviceToHost));
-  // --- per level: FGT arrays
-  for (int l = 0; l <= 8; ++l) {
-    const int64_t n = f->n[l];
-    PASUR_TRY(dev_alloc(&f->gt[l], n));
-    PASUR_TRY(dev_alloc(&f->sid[l], n));
-    if (l > 0) PASUR_TRY(dev_alloc(&f->parent[l], n));
-    if (l < 8) PASUR_TRY(dev_alloc(&f->child_begin[l], n + 1));
-    k_fgt_fill<<<grid_for(n), kThreads, 0, stream>>>(
-        n, l, n_roots, off[l], l > 0 ? off[l - 1] : nullptr, l < 8 ? off[l + 1] : nullptr,
-        lo + (int64_t)l * n_roots, l > 0 ? lo + (int64_t)(l - 1) * n_roots : nullptr,
-        l < 8 ? lo + (int64_t)(l + 1) * n_roots : nullptr, root_sid,
-        l > 0 ? gt->parent[l] : nullptr, l < 8 ? gt->child_begin[l] : nullptr,
-        l < 8 ? f->n[l + 1] : 0, f->gt[l], f->sid[l], l > 0 ? f->parent[l] : nullptr,
-        l < 8 ? f->child_begin[l] : nullptr);
-    PASUR_TRY_HIP(hipGetLastError());
+  GtChildBegin gcb;
+  for (int l = 0; l < 8; ++l) gcb.cb[l] = gt->child_begin[l];
+  const unsigned grid = grid_for(n_roots);
+  k_clear_words<<<grid_for(kKeyWords), kThreads, 0, stream>>>(keys, kKeyWords);
+  k_check_roots<<<grid, kThreads, 0, stream>>>(n_roots, d_roots, dealt_before(gt->deck, gt->round),
+                                               host.dev(H_BAD), keys);
+  scan_enqueue(PoolChange{d_roots}, OffsetsOut{pos, 0}, n_roots, 1, words, host.dev(H_POOLS), stream);
+  k_score_table<<<1, kKeyWords, 0, stream>>>(keys, before, f->score_tab, host.dev(H_SCORES));
+  k_root_ranges<<<grid, kThreads, 0, stream>>>(n_roots, d_roots, pos, gt->pool[0], gt->n[0], keys,
+                                               before, gcb, lo, hi, root_sid,
+                                               host.dev(H_MISMATCH));
+  scan_enqueue(RangeSizes{lo, hi, n_roots}, OffsetsOut{off, n_roots + 1}, n_roots, 9, words,
+               host.dev(H_LEVEL), stream);
+  PASUR_TRY_HIP(hipGetLastError());
+  PASUR_TRY_HIP(hipMemcpyAsync(f->h_root_off, off, sizeof(int32_t) * 9 * (size_t)(n_roots + 1),
+                               hipMemcpyDeviceToHost, stream));
+  PASUR_TRY(host.wait());
+  if (host[H_BAD]) return bad_roots(gt->round);
+  if (host[H_POOLS] != gt->n[0]) {
+    set_error("roots have %lld distinct pools, the game tree %lld roots",
+              (long long)host[H_POOLS], (long long)gt->n[0]);
+    return PASUR_E_INVAL;
   }
-  // --- leaves: base utilities and next-round linkage
+  if (host[H_MISMATCH]) {
+    set_error("root pools do not match the game tree's level 0");
+    return PASUR_E_INVAL;
+  }
+  f->n_scores = host[H_SCORES];
+  for (int l = 0; l <= 8; ++l) {
+    PASUR_TRY(total_fits(host[H_LEVEL + l]));
+    f->n[l] = host[H_LEVEL + l];
+  }
+  // --- all arrays of the levels and leaves
   const int64_t nl = f->n[8];
-  PASUR_TRY(dev_alloc(&f->leaf_base, nl));
-  if (gt->round == 5) PASUR_TRY(dev_alloc(&f->leaf_bonus, nl));
-  uint64_t *lkeys = nullptr, *lkeys2 = nullptr;
-  int32_t *lidx = nullptr, *lidx2 = nullptr;
   const int r = gt->round;
-  uint64_t dealt = 0;
+  for (int l = 0; l <= 8; ++l) {
+    levels.want(&f->gt[l], f->n[l]);
+    levels.want(&f->sid[l], f->n[l]);
+    if (l > 0) levels.want(&f->parent[l], f->n[l]);
+    if (l < 8) levels.want(&f->child_begin[l], f->n[l] + 1);
+  }
+  levels.want(&f->leaf_base, nl);
+  if (r == 5) levels.want(&f->leaf_bonus, nl);
+  else levels.want(&f->link, nl);
+  PASUR_TRY(levels.alloc());
+  f->block = levels.release();
+  FgtFill fa;
+  fa.first[0] = 0;
+  for (int l = 0; l <= 8; ++l) {
+    fa.first[l + 1] = fa.first[l] + f->n[l];
+    fa.gt_parent[l] = gt->parent[l];
+    fa.gt[l] = f->gt[l];
+    fa.sid[l] = f->sid[l];
+    fa.parent[l] = f->parent[l];
+    if (l < 8) {
+      fa.gt_cb[l] = gt->child_begin[l];
+      fa.cb[l] = f->child_begin[l];
+    }
+  }
+  fa.n_roots = n_roots;
+  fa.off = off;
+  fa.lo = lo;
+  fa.root_sid = root_sid;
+  (void)host.dev(H_BAD);  // work is pending
+  k_fgt_fill<<<grid_for(fa.first[9]), kThreads, 0, stream>>>(fa);
+  PASUR_TRY_HIP(hipGetLastError());
+  // --- leaves: base utilities and next-round linkage
+  if (r == 5) {
+    k_leaf_pass<<<grid_for(nl), kThreads, 0, stream>>>(nl, r, f->gt[8], f->sid[8], f->score_tab,
+                                                       gt->rs[8], gt->pool[8], 0, f->leaf_base,
+                                                       f->leaf_bonus, nullptr, nullptr);
+    return host.wait();
+  }
+  const uint64_t dealt = dealt_before(gt->deck, r + 1);
   DealtCards dc;
   std::memset(&dc, 0, sizeof(dc));
-  if (r < 5) {
-    for (int i = 0; i < 4 + 8 * (r + 1); ++i) dealt |= 1ull << gt->deck[i];
-    int k = 0;
-    for (int c = 0; c < 52; ++c)
-      if ((dealt >> c) & 1) dc.card[k++] = (uint8_t)c;
-    PASUR_TRY(s.alloc(&lkeys, nl));
-    PASUR_TRY(s.alloc(&lkeys2, nl));
-    PASUR_TRY(s.alloc(&lidx, nl));
-    PASUR_TRY(s.alloc(&lidx2, nl));
-  }
+  for (int c = 0, k = 0; c < 52; ++c)
+    if ((dealt >> c) & 1) dc.card[k++] = (uint8_t)c;
+  uint64_t *lkeys[2] = {nullptr, nullptr};
+  int32_t *lidx[2] = {nullptr, nullptr}, *ints = nullptr, *lpos = nullptr;
+  int64_t *lwords = nullptr;
+  leaves.want(&lkeys[0], nl);
+  leaves.want(&lkeys[1], nl);
+  leaves.want(&lidx[0], nl);
+  leaves.want(&lidx[1], nl);
+  leaves.want(&ints, sort_scratch_ints(nl));
+  leaves.want(&lwords, std::max(sort_scratch_words(nl), scan_scratch(nl)));
+  leaves.want(&lpos, nl + 1);
+  PASUR_TRY(leaves.alloc());
   k_leaf_pass<<<grid_for(nl), kThreads, 0, stream>>>(nl, r, f->gt[8], f->sid[8], f->score_tab,
                                                      gt->rs[8], gt->pool[8], dealt, f->leaf_base,
-                                                     f->leaf_bonus, lkeys, lidx);
+                                                     nullptr, lkeys[0], lidx[0]);
   PASUR_TRY_HIP(hipGetLastError());
-  if (r < 5) {
-    const int nbits = __builtin_popcountll(dealt) + 16;
-    PASUR_TRY(radix_sort_pairs<uint64_t>(lkeys, lkeys2, lidx, lidx2, nl, nbits, stream));
-    int32_t *lflags = nullptr, *lpos = nullptr;
-    PASUR_TRY(s.alloc(&lflags, nl));
-    PASUR_TRY(s.alloc(&lpos, nl + 1));
-    k_u64_flags<<<grid_for(nl), kThreads, 0, stream>>>(nl, lkeys2, lflags);
-    int64_t nn = 0;
-    PASUR_TRY(scan_counts(lflags, nl, lpos, &nn, stream));
-    f->n_next = nn;
-    PASUR_TRY(dev_alloc(&f->next_roots, nn));
-    PASUR_TRY(dev_alloc(&f->link, nl));
-    k_next_roots<<<grid_for(nl), kThreads, 0, stream>>>(nl, lkeys2, lidx2, lflags, lpos, dc,
-                                                        f->next_roots, f->link);
-    PASUR_TRY_HIP(hipGetLastError());
-  }
-  PASUR_TRY_HIP(hipStreamSynchronize(stream));
-  return PASUR_OK;
+  int at = 0;
+  PASUR_TRY(sort_pairs(lkeys, lidx, nl, ints, lwords, host.dev(H_SORT), &at, stream));
+  scan_enqueue(KeyChange{lkeys[at]}, OffsetsOut{lpos, 0}, nl, 1, lwords, host.dev(H_NEXT), stream);
+  PASUR_TRY(host.wait());
+  f->n_next = host[H_NEXT];
+  PASUR_TRY(block_alloc(&f->next_block, (size_t)f->n_next * sizeof(pasur_root)));
+  f->next_roots = (pasur_root *)f->next_block;
+  (void)host.dev(H_BAD);
+  k_next_roots<<<grid_for(nl), kThreads, 0, stream>>>(nl, lkeys[at], lidx[at], lpos, dc,
+                                                      f->next_roots, f->link);
+  return host.wait();
 }
 
 }  // namespace
@@ -827,13 +856,12 @@ extern "C" int pasur_unfold_scores(const pasur_gt *gt, const pasur_root *d_roots
     return PASUR_E_INVAL;
   }
   *out_fgt = nullptr;
-  PASUR_TRY(check_roots(gt->deck, gt->round, d_roots, n_roots, stream));
+  PASUR_TRY(check_root_list(d_roots, n_roots));
   pasur_fgt *f = new pasur_fgt();
   std::memset(f, 0, sizeof(*f));
   f->round = gt->round;
   int st = unfold_impl(gt, d_roots, n_roots, f, stream);
   if (st) {
-    (void)hipStreamSynchronize(stream);
     pasur_fgt_free(f);
     return st;
   }

@@ -1,8 +1,10 @@
-// pasur_util.hip -- error reporting and the device-wide exclusive scan used
-// to lay out tree levels (counts -> CSR offsets).
-#include "pasur_internal.hpp"
+// pasur_util.hip -- error reporting, the cache of device memory blocks, the pinned
+// words that kernels report totals in, and the scan of an array of counts.
+#include "pasur_scan.hpp"
 
+#include <cstdlib>
 #include <cstring>
+#include <mutex>
 
 namespace pasur {
 
@@ -16,126 +18,187 @@ void set_error(const char *fmt, ...) {
 }
 
 namespace {
+// Freed blocks, at most kCacheBytes of them per device (3% of its memory) in at
+// most kCacheBlocks places; what does not fit is given back to the system, and
+// everything is when an allocation fails.  Blocks are handed out again only to
+// requests of a similar size.
+constexpr size_t kCacheBytes = (size_t)8 << 30;
+constexpr int kCacheBlocks = 512;
+struct Block {
+  void *p;
+  size_t bytes;
+  int device;
+};
+std::mutex g_block_mu;
+Block g_free[kCacheBlocks];
+int g_n_free = 0;
+// Size and device of the blocks in use, by address.
+struct Owned {
+  Block b;
+  Owned *next;
+};
+constexpr int kBuckets = 1024;
+Owned *g_owned[kBuckets];
 
-constexpr int kBlock = 256;
-constexpr int kItems = 8;
-constexpr int kTile = kBlock * kItems;
-
-// Block-wide exclusive scan of one int64 per thread (Hillis-Steele in LDS).
-__device__ int64_t block_exclusive_scan(int64_t v, int64_t *total) {
-  __shared__ int64_t buf[2][kBlock];
-  int t = threadIdx.x;
-  int cur = 0;
-  buf[cur][t] = v;
-  __syncthreads();
-  for (int off = 1; off < kBlock; off <<= 1) {
-    int64_t x = buf[cur][t];
-    if (t >= off) x += buf[cur][t - off];
-    buf[cur ^ 1][t] = x;
-    cur ^= 1;
-    __syncthreads();
-  }
-  int64_t incl = buf[cur][t];
-  *total = buf[cur][kBlock - 1];
-  __syncthreads();
-  return incl - v;
+Owned **owned_place(void *p) {
+  return &g_owned[((uintptr_t)p >> 12) % kBuckets];
 }
 
-template <class In>
-__global__ void __launch_bounds__(kBlock) k_tile_sums(const In *in, int64_t n, int64_t *sums) {
-  int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
-  int64_t s = 0;
-  for (int k = 0; k < kItems; ++k) {
-    int64_t i = base + k;
-    if (i < n) s += (int64_t)in[i];
+size_t rounded(size_t bytes) {
+  if (bytes <= 4096) return 4096;
+  if (bytes <= ((size_t)1 << 20)) {
+    size_t r = 4096;
+    while (r < bytes) r <<= 1;
+    return r;
   }
-  int64_t total;
-  (void)block_exclusive_scan(s, &total);
-  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+  const size_t two = (size_t)2 << 20;
+  return (bytes + two - 1) / two * two;
 }
 
-// out[i] = tile_off[tile] + exclusive prefix inside the tile; the last tile
-// also writes out[n] (the grand total).
-template <class In>
-__global__ void __launch_bounds__(kBlock) k_tile_scan(const In *in, int64_t n,
-                                                     const int64_t *tile_off, int64_t *out) {
-  int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
-  int64_t v[kItems];
-  int64_t s = 0;
-  for (int k = 0; k < kItems; ++k) {
-    int64_t i = base + k;
-    v[k] = i < n ? (int64_t)in[i] : 0;
-    s += v[k];
-  }
-  int64_t total;
-  int64_t pre = block_exclusive_scan(s, &total);
-  int64_t off = tile_off ? tile_off[blockIdx.x] : 0;
-  int64_t run = off + pre;
-  for (int k = 0; k < kItems; ++k) {
-    int64_t i = base + k;
-    if (i < n) out[i] = run;
-    run += v[k];
-  }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + total;
+// The smallest cached block of this device that holds `bytes` and is at most a
+// quarter larger.
+bool take_cached(size_t bytes, int device, Block *out) {
+  int best = -1;
+  for (int i = 0; i < g_n_free; ++i)
+    if (g_free[i].device == device && g_free[i].bytes >= bytes &&
+        g_free[i].bytes <= bytes + bytes / 4 &&
+        (best < 0 || g_free[i].bytes < g_free[best].bytes))
+      best = i;
+  if (best < 0) return false;
+  *out = g_free[best];
+  g_free[best] = g_free[--g_n_free];
+  return true;
 }
 
-template <class In>
-int scan_i64(const In *d_in, int64_t n, int64_t *d_out, hipStream_t stream) {
-  int64_t nt = (n + kTile - 1) / kTile;
-  if (nt <= 1) {
-    k_tile_scan<In><<<1, kBlock, 0, stream>>>(d_in, n, nullptr, d_out);
-    PASUR_TRY_HIP(hipGetLastError());
-    return PASUR_OK;
-  }
-  int64_t *sums = nullptr, *offs = nullptr;
-  PASUR_TRY(dev_alloc(&sums, nt));
-  int st = dev_alloc(&offs, nt + 1);
-  if (st) { dev_free(sums); return st; }
-  k_tile_sums<In><<<(unsigned)nt, kBlock, 0, stream>>>(d_in, n, sums);
-  st = scan_i64<int64_t>(sums, nt, offs, stream);
-  if (!st) {
-    k_tile_scan<In><<<(unsigned)nt, kBlock, 0, stream>>>(d_in, n, offs, d_out);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) { set_error("scan launch: %s", hipGetErrorString(e)); st = PASUR_E_HIP; }
-  }
-  // frees are ordered after the stream's work by the synchronisation below
-  hipError_t e = hipStreamSynchronize(stream);
-  dev_free(sums);
-  dev_free(offs);
-  if (!st && e != hipSuccess) { set_error("scan: %s", hipGetErrorString(e)); st = PASUR_E_HIP; }
-  return st;
+void release_cached(int device) {
+  for (int i = g_n_free; i-- > 0;)
+    if (g_free[i].device == device) {
+      (void)hipFree(g_free[i].p);
+      g_free[i] = g_free[--g_n_free];
+    }
 }
-
-__global__ void k_narrow(const int64_t *in, int64_t n, int32_t *out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i <= n) out[i] = (int32_t)in[i];
-}
-
 }  // namespace
+
+int block_alloc(void **p, size_t bytes) {
+  *p = nullptr;
+  int device = 0;
+  PASUR_TRY_HIP(hipGetDevice(&device));
+  Owned *o = (Owned *)std::malloc(sizeof(Owned));
+  if (!o) {
+    set_error("host allocation failed");
+    return PASUR_E_NOMEM;
+  }
+  const size_t want = rounded(bytes);
+  std::lock_guard<std::mutex> lock(g_block_mu);
+  if (!take_cached(want, device, &o->b)) {
+    void *mem = nullptr;
+    hipError_t e = hipMalloc(&mem, want);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      release_cached(device);
+      e = hipMalloc(&mem, want);
+    }
+    if (e != hipSuccess) {
+      std::free(o);
+      set_error("hipMalloc of %zu bytes failed: %s", want, hipGetErrorString(e));
+      return PASUR_E_NOMEM;
+    }
+    o->b = Block{mem, want, device};
+  }
+  Owned **at = owned_place(o->b.p);
+  o->next = *at;
+  *at = o;
+  *p = o->b.p;
+  return PASUR_OK;
+}
+
+void block_free(void *p) {
+  if (!p) return;
+  std::lock_guard<std::mutex> lock(g_block_mu);
+  Owned **at = owned_place(p);
+  while (*at && (*at)->b.p != p) at = &(*at)->next;
+  if (!*at) return;
+  Owned *o = *at;
+  *at = o->next;
+  const Block b = o->b;
+  std::free(o);
+  size_t cached = 0;
+  for (int i = 0; i < g_n_free; ++i)
+    if (g_free[i].device == b.device) cached += g_free[i].bytes;
+  if (g_n_free < kCacheBlocks && cached + b.bytes <= kCacheBytes) g_free[g_n_free++] = b;
+  else (void)hipFree(b.p);
+}
+
+int anchor_alloc(void **a) {
+  const hipError_t e = hipMalloc(a, 64);
+  if (e == hipSuccess) return PASUR_OK;
+  *a = nullptr;
+  set_error("hipMalloc: %s", hipGetErrorString(e));
+  return PASUR_E_NOMEM;
+}
+
+void anchor_wait(void *a) {
+  if (a) (void)hipFree(a);
+}
+
+namespace {
+// Free sets of words, linked through the word behind them.  A set is allocated
+// when a call finds none free, so there are as many as calls have been in flight
+// at once (256 bytes each); they stay until the process ends.
+std::mutex g_words_mu;
+int64_t *g_words = nullptr;
+int64_t *&next_of(int64_t *w) { return *reinterpret_cast<int64_t **>(w + kHostWords); }
+}  // namespace
+
+HostWords::HostWords(hipStream_t s) : w(nullptr), stream(s), pending(false) {
+  {
+    std::lock_guard<std::mutex> lock(g_words_mu);
+    if (g_words) {
+      w = g_words;
+      g_words = next_of(w);
+    }
+  }
+  if (!w) {
+    const hipError_t e = hipHostMalloc((void **)&w, (kHostWords + 1) * sizeof(int64_t),
+                                       hipHostMallocPortable | hipHostMallocMapped);
+    if (e != hipSuccess) {
+      set_error("pinned host memory: %s", hipGetErrorString(e));
+      w = nullptr;
+      return;
+    }
+  }
+  std::memset(w, 0, kHostWords * sizeof(int64_t));
+}
+
+HostWords::~HostWords() {
+  if (!w) return;
+  if (pending) (void)hipStreamSynchronize(stream);
+  std::lock_guard<std::mutex> lock(g_words_mu);
+  next_of(w) = g_words;
+  g_words = w;
+}
+
+int HostWords::wait() {
+  PASUR_TRY_HIP(hipGetLastError());
+  PASUR_TRY_HIP(hipStreamSynchronize(stream));
+  pending = false;
+  return PASUR_OK;
+}
 
 int scan_counts(const int32_t *d_counts, int64_t n, int32_t *d_out,
                 int64_t *total, hipStream_t stream) {
-  int64_t *tmp = nullptr;
-  PASUR_TRY(dev_alloc(&tmp, n + 1));
-  int st = scan_i64<int32_t>(d_counts, n, tmp, stream);
-  if (!st) {
-    hipError_t e = hipMemcpyAsync(total, tmp + n, sizeof(int64_t),
-                                  hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) { set_error("scan total: %s", hipGetErrorString(e)); st = PASUR_E_HIP; }
-  }
-  if (!st && *total > INT32_MAX) {
-    set_error("tree level of %lld nodes exceeds INT32_MAX", (long long)*total);
-    st = PASUR_E_OVERFLOW;
-  }
-  if (!st) {
-    k_narrow<<<(unsigned)((n + 1 + 255) / 256), 256, 0, stream>>>(tmp, n, d_out);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) { set_error("scan narrow: %s", hipGetErrorString(e)); st = PASUR_E_HIP; }
-  }
-  dev_free(tmp);
-  return st;
+  HostWords host(stream);
+  if (!host.ok()) return PASUR_E_NOMEM;
+  void *scratch = nullptr;
+  if (n >= kScanTile)
+    PASUR_TRY(block_alloc(&scratch, (size_t)scan_scratch(n) * sizeof(int64_t)));
+  scan_enqueue(CountsIn{d_counts}, OffsetsOut{d_out, 0}, n, 1, (int64_t *)scratch,
+               host.dev(0), stream);
+  const int st = host.wait();
+  block_free(scratch);
+  PASUR_TRY(st);
+  *total = host[0];
+  return total_fits(*total);
 }
 
 }  // namespace pasur
