@@ -137,11 +137,11 @@ __global__ void __launch_bounds__(kThreads)
 }
 
 struct MovesIn {
-  using Acc = int64_t;
+  using Acc = int;
   const uint64_t *counts;
-  __device__ __forceinline__ int64_t operator()(int, int64_t i) const {
+  __device__ __forceinline__ int operator()(int, int64_t i) const {
     const uint64_t c = counts[i];
-    return (int64_t)((c & 0xFFFF) + ((c >> 16) & 0xFFFF) + ((c >> 32) & 0xFFFF) + (c >> 48));
+    return (int)((c & 0xFFFF) + ((c >> 16) & 0xFFFF) + ((c >> 32) & 0xFFFF) + (c >> 48));
   }
 };
 
@@ -547,7 +547,8 @@ struct RangeSizes {
 };
 
 struct FgtFill {
-  int64_t first[10];  // the levels' nodes as one range
+  int64_t n[9];
+  unsigned block[10];  // first workgroup of each level
   int64_t n_roots;
   const int32_t *off;  // [9][n_roots + 1] root offsets
   const int32_t *lo;   // [9][n_roots] first GT node of a root
@@ -555,54 +556,62 @@ struct FgtFill {
   const int32_t *gt_parent[9], *gt_cb[8];
   int32_t *gt[9], *sid[9], *parent[9], *cb[8];
 };
+constexpr int kFillNodes = 4 * kThreads;  // per workgroup
 
-// FGT node i of a level: its root (binary search in the level's root offsets,
-// between the roots of the workgroup's first and last node where these are of
-// one level: a root has hundreds of nodes on the large levels), GT node, score
-// id, parent and child range.
+// FGT nodes of a level, four consecutive ones per thread (16-byte stores): the
+// root of the first (binary search in the level's root offsets, between the
+// roots of the workgroup's first and last node), then of each its GT node, score
+// id, parent and child range.  Bound by the 16 B written per node; one node per
+// thread, with a search over all roots or between the workgroup's, wrote 1.8e8
+// nodes in 2.1 ms.
 __global__ void __launch_bounds__(kThreads) k_fgt_fill(FgtFill a) {
   __shared__ int64_t bound[2];
-  auto level_of = [&](int64_t x) {
-    int l = 0;
+  int l = 0;
 #pragma unroll
-    for (int k = 1; k < 9; ++k) l += x >= a.first[k] ? 1 : 0;
-    return l;
-  };
-  auto root_of = [&](const int32_t *off, int64_t i, int64_t lo, int64_t hi) {
+  for (int k = 1; k < 9; ++k) l += blockIdx.x >= a.block[k] ? 1 : 0;
+  const int64_t n = a.n[l], on = a.n_roots + 1;
+  const int64_t i0 = (int64_t)(blockIdx.x - a.block[l]) * kFillNodes;
+  const int32_t *const off = a.off + l * on;
+  auto root_of = [&](int64_t i, int64_t lo, int64_t hi) {
     while (hi - lo > 1) {  // largest j with off[j] <= i
       const int64_t m = (lo + hi) >> 1;
       if (off[m] <= i) lo = m; else hi = m;
     }
-    // skip empty ranges (cannot happen for a round tree, kept for safety)
-    while (lo + 1 < a.n_roots && off[lo + 1] <= i) ++lo;
     return lo;
   };
-  const int64_t x0 = (int64_t)blockIdx.x * kThreads;
-  const int64_t x1 = x0 + kThreads < a.first[9] ? x0 + kThreads : a.first[9];  // end
-  const int l0 = level_of(x0);
-  const bool one_level = l0 == level_of(x1 - 1);
-  const int64_t on = a.n_roots + 1;
-  if (one_level && (threadIdx.x & 63) == 0 && threadIdx.x < 128) {
-    const int64_t x = threadIdx.x == 0 ? x0 : x1 - 1;
-    bound[threadIdx.x >> 6] = root_of(a.off + l0 * on, x - a.first[l0], 0, a.n_roots);
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < 128) {
+    const int64_t last = i0 + kFillNodes < n ? i0 + kFillNodes - 1 : n - 1;
+    bound[threadIdx.x >> 6] = root_of(threadIdx.x == 0 ? i0 : last, 0, a.n_roots);
   }
   __syncthreads();
-  const int64_t x = x0 + threadIdx.x;
-  if (x >= x1) return;
-  const int l = one_level ? l0 : level_of(x);
-  const int64_t i = x - a.first[l];
-  const int32_t *const off = a.off + l * on;
-  const int64_t j = one_level ? root_of(off, i, bound[0], bound[1] + 1)
-                              : root_of(off, i, 0, a.n_roots);
+  const int64_t i = i0 + 4 * threadIdx.x;
+  if (i >= n) return;
+  int64_t j = root_of(i, bound[0], bound[1] + 1);
   const int32_t *const lo = a.lo + l * a.n_roots;
-  const int32_t g = lo[j] + (int32_t)(i - off[j]);
-  a.gt[l][i] = g;
-  a.sid[l][i] = a.root_sid[j];
-  if (l > 0) a.parent[l][i] = (off - on)[j] + (a.gt_parent[l][g] - (lo - a.n_roots)[j]);
+  int32_t gt[4], sid[4], par[4], cb[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int64_t x = i + k < n ? i + k : n - 1;
+    while (j + 1 < a.n_roots && off[j + 1] <= x) ++j;
+    const int32_t g = lo[j] + (int32_t)(x - off[j]);
+    gt[k] = g;
+    sid[k] = a.root_sid[j];
+    par[k] = l > 0 ? (off - on)[j] + (a.gt_parent[l][g] - (lo - a.n_roots)[j]) : 0;
+    cb[k] = l < 8 ? (off + on)[j] + (a.gt_cb[l][g] - (lo + a.n_roots)[j]) : 0;
+  }
+  auto put = [&](int32_t *p, const int32_t *v) {
+    if (i + 4 <= n) {
+      *reinterpret_cast<int4 *>(p + i) = make_int4(v[0], v[1], v[2], v[3]);
+    } else {
+      for (int k = 0; i + k < n; ++k) p[i + k] = v[k];
+    }
+  };
+  put(a.gt[l], gt);
+  put(a.sid[l], sid);
+  if (l > 0) put(a.parent[l], par);
   if (l < 8) {
-    a.cb[l][i] = (off + on)[j] + (a.gt_cb[l][g] - (lo + a.n_roots)[j]);
-    const int64_t n = a.first[l + 1] - a.first[l];
-    if (i == n - 1) a.cb[l][n] = (int32_t)(a.first[l + 2] - a.first[l + 1]);
+    put(a.cb[l], cb);
+    if (i + 4 >= n) a.cb[l][n] = (int32_t)a.n[l + 1];
   }
 }
 
@@ -787,9 +796,10 @@ int unfold_impl(const pasur_gt *gt, const pasur_root *d_roots, int64_t n_roots, 
   PASUR_TRY(levels.alloc());
   f->block = levels.release();
   FgtFill fa;
-  fa.first[0] = 0;
+  fa.block[0] = 0;
   for (int l = 0; l <= 8; ++l) {
-    fa.first[l + 1] = fa.first[l] + f->n[l];
+    fa.n[l] = f->n[l];
+    fa.block[l + 1] = fa.block[l] + (unsigned)((f->n[l] + kFillNodes - 1) / kFillNodes);
     fa.gt_parent[l] = gt->parent[l];
     fa.gt[l] = f->gt[l];
     fa.sid[l] = f->sid[l];
@@ -804,7 +814,7 @@ int unfold_impl(const pasur_gt *gt, const pasur_root *d_roots, int64_t n_roots, 
   fa.lo = lo;
   fa.root_sid = root_sid;
   (void)host.dev(H_BAD);  // work is pending
-  k_fgt_fill<<<grid_for(fa.first[9]), kThreads, 0, stream>>>(fa);
+  k_fgt_fill<<<fa.block[9], kThreads, 0, stream>>>(fa);
   PASUR_TRY_HIP(hipGetLastError());
   // --- leaves: base utilities and next-round linkage
   if (r == 5) {
