@@ -9,6 +9,7 @@
 #pragma clang fp contract(off)
 
 #include "pasur_internal.hpp"
+#include "pasur_parents.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -39,68 +40,28 @@ void prof_clear() {
 constexpr int kThreads = 256;
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
 
-// The nodes of levels 0..7 of a tree as one range, level by level: one launch
-// covers all of them (a launch per level cost the small rounds eight times a
-// launch's 2 to 4 us, half of the time of a whole batched solve's set-up).
-struct AllParents {
-  const int32_t *cb[8];
-  int64_t first[9];
-};
-
-AllParents all_parents(const pasur_fgt *f) {
-  AllParents P;
-  P.first[0] = 0;
-  for (int l = 0; l < 8; ++l) {
-    P.cb[l] = f->child_begin[l];
-    P.first[l + 1] = P.first[l] + f->n[l];
-  }
-  return P;
-}
-
-__device__ __forceinline__ int level_of(const AllParents &P, int64_t i) {
-  int l = 0;
-#pragma unroll
-  for (int k = 1; k < 8; ++k) l += i >= P.first[k] ? 1 : 0;
-  return l;
-}
-
-template <class T>
-struct EdgeArrays {
-  T *a[9], *b[9], *c[9];  // levels 1..8
-};
-
-template <class T>
-EdgeArrays<T> edge_arrays(void *const a[9], void *const b[9], void *const c[9]) {
-  EdgeArrays<T> E;
-  for (int l = 0; l < 9; ++l) {
-    E.a[l] = l && a ? (T *)a[l] : nullptr;
-    E.b[l] = l && b ? (T *)b[l] : nullptr;
-    E.c[l] = l && c ? (T *)c[l] : nullptr;
-  }
-  return E;
-}
-
 // a = sigma (uniform), b = R and c = Sbar (zero) of every node's children;
-// the roots' reaches and utility sums.
+// the roots' reaches and utility sums.  Bound by the 12 B written per edge.
 template <class T>
-__global__ void k_init(AllParents P, EdgeArrays<T> E, T *__restrict__ ra, T *__restrict__ rb,
-                       double *__restrict__ vacc) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.first[8]) return;
-  const int l = level_of(P, i);
-  const int64_t h = i - P.first[l];
-  const int32_t b = P.cb[l][h], e = P.cb[l][h + 1];
-  const T s = (T)(1.0 / (double)(e - b));
-  T *const sg = E.a[l + 1], *const R = E.b[l + 1], *const S = E.c[l + 1];
-  for (int32_t q = b; q < e; ++q) {
-    sg[q] = s;
-    R[q] = (T)0;
-    S[q] = (T)0;
-  }
-  if (l == 0) {
-    ra[h] = (T)1;
-    rb[h] = (T)1;
-    vacc[h] = 0.0;
+__global__ void __launch_bounds__(kParentThreads)
+    k_init(AllParents P, EdgeArrays<T> E, T *__restrict__ ra, T *__restrict__ rb,
+           double *__restrict__ vacc) {
+  const MyParents m(P);
+  T *const sg = E.a[m.level + 1], *const R = E.b[m.level + 1], *const S = E.c[m.level + 1];
+#pragma unroll
+  for (int k = 0; k < kParentsPer; ++k) {
+    const int32_t b = m.b[k], e = m.e[k];
+    const T s = (T)(1.0 / (double)(e - b));
+    for (int32_t q = b; q < e; ++q) {
+      sg[q] = s;
+      R[q] = (T)0;
+      S[q] = (T)0;
+    }
+    if (m.level == 0 && m.h[k] < P.n[0]) {
+      ra[m.h[k]] = (T)1;
+      rb[m.h[k]] = (T)1;
+      vacc[m.h[k]] = 0.0;
+    }
   }
 }
 
@@ -176,22 +137,10 @@ __global__ void k_up(int64_t np, int mover, const int32_t *__restrict__ cb,
   if (vacc) vacc[h] += uh;
 }
 
-
-// a = Sbar, b = its normalisation over the children of every node.
-template <class T>
-__global__ void k_avg_strategy(AllParents P, EdgeArrays<T> E) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.first[8]) return;
-  const int l = level_of(P, i);
-  const int64_t h = i - P.first[l];
-  const int32_t b = P.cb[l][h], e = P.cb[l][h + 1];
-  const T *const S = E.a[l + 1];
-  T *const out = E.b[l + 1];
-  double s = 0.0;
-  for (int32_t q = b; q < e; ++q) s += (double)S[q];
-  for (int32_t q = b; q < e; ++q)
-    out[q] = (T)(s > 0.0 ? (double)S[q] / s : 1.0 / (double)(e - b));
-}
+// the average strategy: sums normalised as they are
+struct AsIs {
+  __device__ __forceinline__ double operator()(double x) const { return x; }
+};
 
 template <class T>
 __global__ void k_leaf_util(int64_t n, const int16_t *__restrict__ base,
@@ -212,7 +161,7 @@ __global__ void k_div(int64_t n, const double *__restrict__ a, double T, double 
 template <class T>
 int init_t(const pasur_fgt *f, const pasur_cfr_state *st, hipStream_t s) {
   const AllParents P = all_parents(f);
-  k_init<T><<<grid_for(P.first[8]), kThreads, 0, s>>>(
+  k_init<T><<<P.block[8], kParentThreads, 0, s>>>(
       P, edge_arrays<T>(st->sigma, st->R, st->Sbar), (T *)st->reachA[0], (T *)st->reachB[0],
       st->vacc);
   PASUR_TRY_HIP(hipGetLastError());
@@ -396,11 +345,11 @@ extern "C" int pasur_average_strategy(const pasur_fgt *f, const pasur_cfr_state 
   }
   const AllParents P = all_parents(f);
   if (st->dtype == PASUR_F32)
-    k_avg_strategy<float><<<grid_for(P.first[8]), kThreads, 0, s>>>(
-        P, edge_arrays<float>(st->Sbar, sigma_bar, nullptr));
+    k_normalise<float><<<P.block[8], kParentThreads, 0, s>>>(
+        P, edge_arrays<float>(st->Sbar, sigma_bar, nullptr), AsIs());
   else
-    k_avg_strategy<double><<<grid_for(P.first[8]), kThreads, 0, s>>>(
-        P, edge_arrays<double>(st->Sbar, sigma_bar, nullptr));
+    k_normalise<double><<<P.block[8], kParentThreads, 0, s>>>(
+        P, edge_arrays<double>(st->Sbar, sigma_bar, nullptr), AsIs());
   PASUR_TRY_HIP(hipGetLastError());
   return PASUR_OK;
 }

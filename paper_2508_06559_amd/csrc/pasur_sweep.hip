@@ -40,6 +40,7 @@
 #pragma clang fp contract(off)
 
 #include "pasur_internal.hpp"
+#include "pasur_parents.hpp"
 
 #include <algorithm>
 #include <vector>
@@ -494,25 +495,35 @@ __device__ __forceinline__ double regret_update(double Rq, double r, const IterK
 // ---- per-call set-up and tear-down -----------------------------------------
 
 // u of a passive node = its only child's utility (sigma = 1), once per call.
+// Four nodes per thread, a workgroup's width apart, so that four chains of loads
+// are in flight.
 template <class T>
-__global__ void k_sw_chain_u(int64_t n, const uint8_t *__restrict__ passive,
-                             const int32_t *__restrict__ cb, T *__restrict__ u,
-                             const T *__restrict__ u_next) {
-  SW_FOR(h, n) if (passive[h]) u[h] = (T)(0.0 + (double)u_next[cb[h]]);
+__global__ void __launch_bounds__(kBlk)
+    k_sw_chain_u(int64_t n, const uint8_t *__restrict__ passive, const int32_t *__restrict__ cb,
+                 T *__restrict__ u, const T *__restrict__ u_next) {
+  const int64_t h0 = (int64_t)blockIdx.x * (4 * kBlk) + threadIdx.x;
+  bool p[4];
+  int32_t q[4];
+  T v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int64_t h = h0 + k * kBlk;
+    p[k] = h < n && passive[h];
+    q[k] = h < n ? cb[h] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = p[k] ? u_next[q[k]] : (T)0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (p[k]) u[h0 + k * kBlk] = (T)(0.0 + (double)v[k]);
 }
 
-// sigma^{T+1} of every child of a level's parents, written back at the end
-// of a call.
-template <class T>
-__global__ void k_sw_sigma_out(int64_t n, const int32_t *__restrict__ cb,
-                               const T *__restrict__ R, T *__restrict__ sg, int rm_mode, double eps) {
-  SW_FOR(h, n) {
-    const int32_t b = cb[h], e = cb[h + 1];
-    const double sum = x_sum(R, b, e, rm_mode, eps);
-    for (int32_t q = b; q < e; ++q)
-      sg[q] = (T)sig_from<T>(rm_x((double)R[q], rm_mode, eps), sum, e - b);
-  }
-}
+// sigma^{T+1} of every edge, written back at the end of a call.
+struct MatchWeight {
+  int rm_mode;
+  double eps;
+  __device__ __forceinline__ double operator()(double R) const { return rm_x(R, rm_mode, eps); }
+};
 
 // ---- the sweeps --------------------------------------------------------------
 
@@ -1322,8 +1333,8 @@ int sweep_t(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p, 
     ProfScope ps(PK_SETUP, 0, s);
     for (int l = 7; l >= 1; --l)
       if (x.n_act[l] < f->n[l])
-        k_sw_chain_u<T><<<grid_of(f->n[l]), kBlk, 0, s>>>(f->n[l], x.passive[l],
-                                                           f->child_begin[l], u[l], u[l + 1]);
+        k_sw_chain_u<T><<<(unsigned)((f->n[l] + 4 * kBlk - 1) / (4 * kBlk)), kBlk, 0, s>>>(
+            f->n[l], x.passive[l], f->child_begin[l], u[l], u[l + 1]);
   }
   auto reach = [&](int L) {
     Reach<T> rc;
@@ -1513,10 +1524,10 @@ int sweep_t(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p, 
   }
   {
     ProfScope ps(PK_SETUP, 1, s);
-    for (int L = 1; L <= 8; ++L)
-      if (f->n[L - 1] > 0)
-        k_sw_sigma_out<T><<<grid_of(f->n[L - 1]), kBlk, 0, s>>>(f->n[L - 1], f->child_begin[L - 1],
-                                                                 R[L], sg[L], rm, eps);
+    const AllParents P = all_parents(f);
+    if (P.block[8] > 0)
+      k_normalise<T><<<P.block[8], kParentThreads, 0, s>>>(
+          P, edge_arrays<T>(st->R, st->sigma, nullptr), MatchWeight{rm, eps});
   }
   hipError_t e = hipGetLastError();
   if (buf) (void)hipFreeAsync(buf, s);
