@@ -90,14 +90,18 @@ struct SegLds {
   uint32_t x;        // T per active node, then per root: reaches
   uint32_t kids, up; // words of an active node, see below
   uint32_t pos;      // 16 bits per active node: its index within its level of the segment
+  uint32_t list;     // edges that are updated a lane each, see list_build
   uint32_t bytes;
 };
 // Words of active node i:
 //   kids.x: slot of its first child | distance to the next child << 16
 //   kids.y: its own slot as a child | number of children << 16 | level << 24
+//           | its children are in the list << 31
 //   up:     its parent | active node two levels up << 16
 // A root's slot as a child is its place in su after the edges, and its parent
-// is its second entry of x (the reach of the player who moves first).
+// is its second entry of x (the reach of the player who moves first).  After
+// the roots su has a pair of zeros, what a node reads in place of further children,
+// and a spare pair, which it writes in their place; rs and chain have a spare edge.
 template <class T>
 struct alignas(2 * sizeof(T)) Pair {
   T a, b;
@@ -105,6 +109,10 @@ struct alignas(2 * sizeof(T)) Pair {
 
 constexpr int kClasses = 64;  // children per node: 0 .. 63
 constexpr uint32_t kTableBytes = 3 * 8 * kClasses * 4;
+constexpr int kList = 512;     // capacity of the list
+constexpr uint32_t kNoEdge = 0xFFFFFFFFu;
+constexpr int kTopEdges = 224;  // take at most kList places, see list_build
+constexpr uint32_t kListed = 1u << 31;
 
 template <class U>
 __host__ __device__ inline U align16(U x) {
@@ -123,21 +131,22 @@ __host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t) {
   L.b7 = take((uint32_t)((c.c7 + 63) / 64) * 8u);
   L.tmp = p;
   const uint32_t tmp_end = p + kTableBytes + align16(2u * (uint32_t)c.c07);
-  L.su = take(2 * t * (uint32_t)(c.ne + c.roots));
-  L.rs = take(2 * t * (uint32_t)c.ne);
-  L.chain = take(2 * t * (uint32_t)c.ne67);
+  L.su = take(2 * t * (uint32_t)(c.ne + c.roots + 2));
+  L.rs = take(2 * t * (uint32_t)(c.ne + 1));
+  L.chain = take(2 * t * (uint32_t)(c.ne67 + 1));
   L.x = take(t * (uint32_t)(c.na + c.roots));
   L.vacc = take(8u * (uint32_t)c.roots);
   if (p < tmp_end) p = tmp_end;
   L.kids = take(8u * (uint32_t)c.na);
   L.up = take(4u * (uint32_t)c.na);
   L.pos = take(2u * (uint32_t)c.na);
+  L.list = take(4u * kList);
   L.bytes = p;
   return L;
 }
 // Indices are held in 16 bits.
 __host__ __device__ inline bool seg_indices_fit(const SegCounts &c) {
-  return c.ne + c.roots < 65536 && c.na + c.roots < 65536 && c.c07 < 8 * 65536;
+  return c.ne + c.roots + 2 < 65536 && c.na + c.roots < 65536 && c.c07 < 8 * 65536;
 }
 
 extern __shared__ __align__(16) unsigned char g_lds[];
@@ -145,6 +154,7 @@ extern __shared__ __align__(16) unsigned char g_lds[];
 __shared__ int g_nb[9], g_sb[10];
 __shared__ int g_sum[2][8];
 __shared__ int g_bad;
+__shared__ int g_list_top, g_list_end;  // where the list's two parts end
 
 template <class T>
 __device__ __forceinline__ T *lds(uint32_t off) {
@@ -160,6 +170,69 @@ __device__ __forceinline__ bool bit_of(uint32_t off, int i) {
 __device__ __forceinline__ void wave_order() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_wave_barrier();
+}
+
+// A node's children: slot, distance and number, from its words.
+struct Kids {
+  int e, step, k;
+  __device__ __forceinline__ Kids(uint2 w)
+      : e((int)(w.x & 0xFFFFu)), step((int)(w.x >> 16)), k((int)(w.y >> 16) & 0xFF) {}
+};
+
+// Levels 0 .. top-1: at most 64 nodes, and not more than kTopEdges children.
+__device__ __forceinline__ int top_levels() {
+  int top = 0;
+  while (top < 4 && g_nb[top + 1] <= 64 && g_sb[top + 2] <= kTopEdges) ++top;
+  return top;
+}
+
+// The list of edges that are updated a lane each instead of in a loop over a
+// node's children: first those of the top levels' nodes, whose updates every
+// other wave would wait for, then of nodes with more than four children.  An
+// entry is the parent | the child's number << 16.  The children of a node have
+// neighbouring places of one wave, so that its lanes can follow each other
+// without a barrier; a node that no longer fits in a wave begins the next.  Any
+// two neighbouring waves are then filled with more than 64 edges between them:
+// kTopEdges edges take at most kList places.  Nodes past the list's end stay with
+// update_many.  For one wave; before it, the list is kNoEdge.
+__device__ __forceinline__ void list_build(const SegLds &L) {
+  const int lane = threadIdx.x & 63;
+  uint2 *const w_kids = lds<uint2>(L.kids);
+  uint32_t *const list = lds<uint32_t>(L.list);
+  const int top = top_levels();
+  int at = 0;
+  bool room = true;
+  for (int l = 0; l < 8 && room; ++l) {
+    if (l == top) {
+      at = (at + 63) & ~63;
+      if (lane == 0) g_list_top = at;
+    }
+    const int end = g_nb[l + 1];
+    for (int id0 = g_nb[l]; id0 < end && room; id0 += 64) {
+      const int id = id0 + lane;
+      const Kids n(id < end ? w_kids[id] : make_uint2(0, 0));
+      const bool in = n.k > (l < top ? 0 : 4);
+      unsigned long long todo = __ballot(in);
+      if (!todo) break;  // of a level's nodes the widest come first
+      int mine = -1;
+      while (todo && room) {
+        const int i = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int k = __builtin_amdgcn_readlane(n.k, i);
+        if ((at & 63) + k > 64) at = (at + 63) & ~63;
+        room = at + k <= kList;
+        if (room) {
+          if (lane == i) mine = at;
+          at += k;
+        }
+      }
+      if (mine >= 0) {
+        for (int j = 0; j < n.k; ++j) list[mine + j] = (uint32_t)id | ((uint32_t)j << 16);
+        w_kids[id].y |= kListed;
+      }
+    }
+  }
+  if (lane == 0) g_list_end = at;
 }
 
 // Makes the compact form of roots j0 .. j1-1; false (for every thread) if it
@@ -346,6 +419,10 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
       }
     }
   }
+  if (tid == 0) su[c.ne + c.roots] = Pair<T>{(T)0, (T)0};
+  for (int i = tid; i < kList; i += BLOCK) lds<uint32_t>(L.list)[i] = kNoEdge;
+  __syncthreads();
+  if (wave == 0) list_build(L);
   for (int id = tid; id < c.roots; id += BLOCK) {
     const int64_t j = D.off[0][j0] + w_pos[id];
     lds<T>(L.x)[id] = D.rb[0][j];
@@ -356,44 +433,73 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   return true;
 }
 
-// A node's children: slot, distance and number, from its words.
-struct Kids {
-  int e, step, k;
-  __device__ __forceinline__ Kids(uint2 w)
-      : e((int)(w.x & 0xFFFFu)), step((int)(w.x >> 16)), k((int)(w.y >> 16) & 0xFF) {}
-};
-
-// uh + the sum of sigma * u over at most K children from slot e, in child
-// order.  All K are read at once, so that LDS latency is paid once; past the
-// last child the first one is read again and counts as zero (adding zero
-// leaves the sum's bits alone: it is never -0).
-template <class T, int K>
-__device__ __forceinline__ double value_few(const Pair<T> *su, int e, int step, int k, double uh) {
+// uh + the sum of sigma * u over K children (ALL), or at most K, from slot e, in
+// child order.  All K are read at once, so that LDS latency is paid once; past
+// the last child the pair of zeros is read (adding zero leaves the sum's bits
+// alone: it is never -0).
+template <class T, int K, bool ALL>
+__device__ __forceinline__ double value_few(const Pair<T> *su, int zero, int e, int step, int k,
+                                            double uh) {
   Pair<T> p[K];
 #pragma unroll
-  for (int i = 0; i < K; ++i) p[i] = su[i < k ? e + i * step : e];
+  for (int i = 0; i < K; ++i) p[i] = su[ALL || i < k ? e + i * step : zero];
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    const T s = i < k ? p[i].a : (T)0, v = i < k ? p[i].b : (T)0;
-    uh += (double)s * (double)v;
-  }
+  for (int i = 0; i < K; ++i) uh += (double)p[i].a * (double)p[i].b;
   return uh;
 }
 
 // u of an active node.  The form is the wave's: a class's nodes are
 // neighbours, so its lanes mostly agree.
 template <class T>
-__device__ __forceinline__ double node_value(const Pair<T> *su, const Kids &n) {
-  if (!__ballot(n.k > 2)) return value_few<T, 2>(su, n.e, n.step, n.k, 0.0);
-  if (!__ballot(n.k > 4)) return value_few<T, 4>(su, n.e, n.step, n.k, 0.0);
+__device__ __forceinline__ double node_value(const Pair<T> *su, int zero, const Kids &n) {
+  if (!__ballot(n.k != 2)) return value_few<T, 2, true>(su, zero, n.e, n.step, n.k, 0.0);
+  if (!__ballot(n.k > 4)) return value_few<T, 4, false>(su, zero, n.e, n.step, n.k, 0.0);
   double uh = 0.0;
-  for (int left = n.k, e = n.e; left > 0; left -= 4, e += 4 * n.step)
-    uh = value_few<T, 4>(su, e, n.step, left, uh);
+  for (int left = n.k, e = n.e; left > 0; left -= 8, e += 8 * n.step)
+    uh = value_few<T, 8, false>(su, zero, e, n.step, left, uh);
   return uh;
 }
 
+// (as one instruction: fmax would quiet its second operand each time)
 __device__ __forceinline__ double matched(double R, int rm_mode, double eps) {
-  return rm_mode == PASUR_RM_FLOOR ? fmax(R, eps) : fmax(R, 0.0);
+  const double low = rm_mode == PASUR_RM_FLOOR ? eps : 0.0;
+  double x;
+  asm("v_max_f64 %0, %1, %2" : "=v"(x) : "v"(R), "s"(low));
+  return x;
+}
+
+// Quotients by one divisor.  The reciprocal is refined once, as a division does
+// it, and each quotient takes the division's last three steps (multiply,
+// remainder, correction): the same operations, so the same bits, where a division
+// would not scale its operands.  That is so for divisors and numerators of
+// magnitude 2^-200 .. 2^200 and numerators of zero; `exact` says that a launch's
+// numerators are among these, and other divisors take the division itself.
+struct Quotient {
+  double den, inv;
+  bool plain;
+  __device__ __forceinline__ Quotient(double d, bool exact) : den(d) {
+    // (the exponent's bits: 1023 - 200 .. 1023 + 200)
+    plain = !(exact && (uint32_t)__double2hiint(d) - (823u << 20) < (400u << 20));
+    inv = __builtin_amdgcn_rcp(d);
+    inv = __builtin_fma(inv, __builtin_fma(-d, inv, 1.0), inv);
+    inv = __builtin_fma(inv, __builtin_fma(-d, inv, 1.0), inv);
+  }
+  __device__ __forceinline__ double of(double x) const {
+    const double q = x * inv;
+    return __builtin_fma(__builtin_fma(-den, q, x), inv, q);
+  }
+  // x over the sum, or 1 / k where the sum is not positive, by the division
+  __device__ __forceinline__ double plainly(double x, int k) const {
+    return den > 0.0 ? x / den : 1.0 / (double)k;
+  }
+};
+
+// Numerators are regrets of type T above the floor.
+template <class T>
+__device__ __forceinline__ bool exact_quotients(int rm_mode, double eps) {
+  const bool floor = rm_mode == PASUR_RM_FLOOR;
+  if (floor && eps >= 0x1p-200 && eps <= 0x1p200) return true;
+  return sizeof(T) == 4 && (!floor || eps == 0.0);
 }
 
 __device__ __forceinline__ double next_regret(double Rq, double r, const IterK &ik, int variant) {
@@ -408,72 +514,124 @@ __device__ __forceinline__ double next_regret(double Rq, double r, const IterK &
   return Rq + r;
 }
 
-// Average sums of a child (edge e, sigma^t = sg) and of the chain below it, if
-// any: there first the other player moves (reach opp, as inherited), then the
-// mover of this node (the child's own reach).  Returns the child's.
+// Average sum of a child: w * Sbar + own reach * sigma^t.
 template <class T>
-__device__ __forceinline__ T average_update(Pair<T> *chain, bool chains, double opp, double own, T sg,
-                                            T sb, const IterK &ik, int variant) {
+__device__ __forceinline__ T average_update(double own, T sg, T sb, const IterK &ik, int variant) {
   const double add = own * (double)sg;
-  if (chains) {
-    double a1 = opp, a2 = (double)(T)add;
-    if (variant == PASUR_CFR_PLUS) {
-      a1 *= ik.avg_t;
-      a2 *= ik.avg_t;
-    }
-    const Pair<T> c = *chain;
-    *chain = Pair<T>{(T)(ik.avg_w * (double)c.a + a1), (T)(ik.avg_w * (double)c.b + a2)};
-  }
   return (T)(ik.avg_w * (double)sb + (variant == PASUR_CFR_PLUS ? add * ik.avg_t : add));
+}
+
+// Average sums of the chain below a child: there first the other player moves
+// (reach opp, as inherited), then the mover of the child's parent (the child's
+// own reach).
+template <class T>
+__device__ __forceinline__ void chain_update(Pair<T> *chain, double opp, double own, T sg,
+                                             const IterK &ik, int variant) {
+  double a1 = opp, a2 = (double)(T)(own * (double)sg);
+  if (variant == PASUR_CFR_PLUS) {
+    a1 *= ik.avg_t;
+    a2 *= ik.avg_t;
+  }
+  const Pair<T> c = *chain;
+  *chain = Pair<T>{(T)(ik.avg_w * (double)c.a + a1), (T)(ik.avg_w * (double)c.b + a2)};
 }
 
 // The update of one active node: reaches, regret sign and arrays.
 template <class T>
 struct Update {
   Pair<T> *su, *rs, *chain;  // chain: of edge 0 (only edges of levels 6 and 7 exist)
+  int zero, spare;           // the pair of zeros in su (a spare one follows), rs's spare edge
+  int chain_spare;           // and chain's
   double sopp, opp, own;     // signed opponent's, opponent's and own reach
-  bool chains;
+  bool chains, exact;
   IterK ik;
   int variant, rm_mode;
   double eps;
 };
 
-// Regret, matching and average updates of the children of a node with at most
-// K of them: every child is read once and held in registers.
-template <class T, int K>
+// Regret, matching and average updates of the K children of a node (ALL), or at
+// most K, without a branch: every child is read once and held in registers, and
+// past the last one the work is done on the spare edge.
+template <class T, int K, bool ALL>
 __device__ __forceinline__ void update_few(const Update<T> &c, const Kids &n) {
   Pair<T> p[K], r[K];
+  int e[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    const int e = i < n.k ? n.e + i * n.step : n.e;
-    p[i] = c.su[e];
-    r[i] = c.rs[e];
+    const bool in = ALL || i < n.k;
+    e[i] = in ? n.e + i * n.step : c.spare;
+    p[i] = c.su[in ? e[i] : c.zero];
+    r[i] = c.rs[e[i]];
   }
   double uh = 0.0;
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    const T s = i < n.k ? p[i].a : (T)0, v = i < n.k ? p[i].b : (T)0;
-    uh += (double)s * (double)v;
-  }
-  double sum = 0.0;
+  for (int i = 0; i < K; ++i) uh += (double)p[i].a * (double)p[i].b;
+  double sum = 0.0, m[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) {
     r[i].a = (T)next_regret((double)r[i].a, c.sopp * ((double)p[i].b - uh), c.ik, c.variant);
-    sum += i < n.k ? matched((double)r[i].a, c.rm_mode, c.eps) : 0.0;
+    m[i] = matched((double)r[i].a, c.rm_mode, c.eps);
+    sum += ALL || i < n.k ? m[i] : 0.0;
   }
-  const double inv_k = sum > 0.0 ? 0.0 : 1.0 / (double)n.k;
+  const Quotient quo(sum, c.exact);
+  T s_new[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) s_new[i] = (T)quo.of(m[i]);
+  if (__ballot(quo.plain)) {  // (a branch: rare)
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      if (quo.plain) s_new[i] = (T)quo.plainly(m[i], n.k);
+  }
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    if (i % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // two divisions at a time: registers
-    const T s_new = (T)(sum > 0.0 ? matched((double)r[i].a, c.rm_mode, c.eps) / sum : inv_k);
-    if (i < n.k) {
-      const int e = n.e + i * n.step;
-      r[i].b = average_update<T>(c.chain + e, c.chains, c.opp, c.own, p[i].a, r[i].b, c.ik,
-                                 c.variant);
-      c.su[e].a = s_new;
-      c.rs[e] = r[i];
-    }
+    r[i].b = average_update<T>(c.own, p[i].a, r[i].b, c.ik, c.variant);
+    c.su[ALL || i < n.k ? e[i] : c.zero + 1].a = s_new[i];
+    c.rs[e[i]] = r[i];
   }
+  if (c.chains) {
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      chain_update<T>(c.chain + (ALL || i < n.k ? e[i] : c.chain_spare), c.opp, c.own, p[i].a, c.ik,
+                      c.variant);
+  }
+}
+
+// The sum of v over the node's children in child order, for lanes that hold one
+// child each: first is the lane of the first, k their number.
+__device__ __forceinline__ double sum_lanes(double v, int first, int k) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  double sum = 0.0;
+  for (int i = 0; __ballot(i < k); i += 8) {
+    int xl[8], xh[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      xl[m] = __builtin_amdgcn_ds_bpermute(4 * (first + i + m), lo);
+      xh[m] = __builtin_amdgcn_ds_bpermute(4 * (first + i + m), hi);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all on their way before the first is used
+#pragma unroll
+    for (int m = 0; m < 8; ++m) sum += i + m < k ? __hiloint2double(xh[m], xl[m]) : 0.0;
+  }
+  return sum;
+}
+
+// The update of child j of a node, one lane per edge of a wave that holds all of
+// the node's edges side by side.
+template <class T>
+__device__ __forceinline__ void update_edge(const Update<T> &c, const Kids &n, int j) {
+  const int e = n.e + j * n.step, first = (int)(threadIdx.x & 63) - j;
+  const Pair<T> p = c.su[e], r = c.rs[e];
+  const double uh = sum_lanes((double)p.a * (double)p.b, first, n.k);
+  const T Rs = (T)next_regret((double)r.a, c.sopp * ((double)p.b - uh), c.ik, c.variant);
+  const double m = matched((double)Rs, c.rm_mode, c.eps);
+  const double sum = sum_lanes(m, first, n.k);
+  const Quotient quo(sum, c.exact);
+  T s_new = (T)quo.of(m);
+  if (__ballot(quo.plain))  // (a branch: rare)
+    if (quo.plain) s_new = (T)quo.plainly(m, n.k);
+  c.rs[e] = Pair<T>{Rs, average_update<T>(c.own, p.a, r.b, c.ik, c.variant)};
+  c.su[e].a = s_new;
+  if (c.chains) chain_update<T>(c.chain + e, c.opp, c.own, p.a, c.ik, c.variant);
 }
 
 // The same for any number of children, four at a time.
@@ -511,9 +669,9 @@ __device__ __forceinline__ void update_many(const Update<T> &c, const Kids &n, d
       const T s_new = (T)(sum > 0.0 ? matched((double)r[i].a, c.rm_mode, c.eps) / sum : inv_k);
       if (i < left) {
         const int e = e0 + i * n.step;
-        c.rs[e].b = average_update<T>(c.chain + e, c.chains, c.opp, c.own, s[i], r[i].b, c.ik,
-                                      c.variant);
+        c.rs[e].b = average_update<T>(c.own, s[i], r[i].b, c.ik, c.variant);
         c.su[e].a = s_new;
+        if (c.chains) chain_update<T>(c.chain + e, c.opp, c.own, s[i], c.ik, c.variant);
       }
     }
   }
@@ -619,23 +777,28 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   double *const vacc = lds<double>(L.vacc);
   const uint2 *const w_kids = lds<uint2>(L.kids);
   const uint32_t *const w_up = lds<uint32_t>(L.up);
+  const uint32_t *const list = lds<uint32_t>(L.list);
+  const int n_list_top = __builtin_amdgcn_readfirstlane(g_list_top);
+  const int n_list = __builtin_amdgcn_readfirstlane(g_list_end);
   // the levels' first nodes, one per lane, read as wave-uniform scalars
   const int nb_lane = lane <= 8 ? g_nb[lane] : na;
   auto nb = [&](int l) { return __builtin_amdgcn_readlane(nb_lane, l); };
-  int bottom = 7;  // deepest level with active nodes
+  int bottom = 7;  // deepest level with active nodes (5 at least)
   while (bottom > 0 && nb(bottom + 1) == nb(bottom)) --bottom;
-  // levels 0 .. top-1 hold at most 64 nodes and belong to wave 0, a lane each
-  int top = 0;
-  while (top < 5 && nb(top + 1) <= 64) ++top;
+  // the utilities and reaches of levels 0 .. top-1 belong to wave 0, a lane each
+  const int top = __builtin_amdgcn_readfirstlane(top_levels());
   const int n_top = nb(top);
-  const int down0 = top > 0 ? 1 : 0;         // first interval with a step down
+  const int down0 = top > 0 ? 2 : 0;         // first interval with a step down
   const int first_down = top > 0 ? top : 1;  // its first level
   const int n_up = bottom - top + 1, n_down = (bottom - first_down + 2) / 2;
   const int n_int = n_up > down0 + n_down ? n_up : down0 + n_down;
   const bool top_wave = top > 0 && wave == 0;
+  // the way up begins with the first waves, which the hardware prefers, the way
+  // down and the list with the last
+  const int last_tid = (BLOCK / 64 - 1 - wave) * 64 + lane;
 
   auto value = [&](uint2 w) {
-    const double uh = node_value<T>(su, Kids(w));
+    const double uh = node_value<T>(su, ne + (j1 - j0), Kids(w));
     su[w.y & 0xFFFFu].b = (T)uh;
     return uh;
   };
@@ -649,39 +812,71 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   c.variant = variant;
   c.rm_mode = rm_mode;
   c.eps = eps;
-  auto update = [&](int id, uint2 w, uint32_t up) {
-    const int level = (int)(w.y >> 24);
+  c.zero = ne + (j1 - j0);
+  c.spare = ne;
+  c.chain_spare = __builtin_amdgcn_readfirstlane(g_sb[8]);
+  c.exact = exact_quotients<T>(rm_mode, eps);
+  auto node = [&](int id, uint2 w, uint32_t up) {
+    const int level = (int)(w.y >> 24) & 7;
     c.opp = (double)x[id];
     c.own = (double)x[up & 0xFFFFu];
     c.sopp = (level & 1) == 0 ? c.opp : -c.opp;
     c.chains = level == 5 || level == 6;
+  };
+  auto update = [&](int id, uint2 w, uint32_t up) {
+    node(id, w, up);
     const Kids n(w);
-    if (!__ballot(n.k > 2)) update_few<T, 2>(c, n);
-    else if (!__ballot(n.k > 4)) update_few<T, 4>(c, n);
-    else update_many<T>(c, n, node_value<T>(su, n));
+    if (!__ballot(n.k != 2)) update_few<T, 2, true>(c, n);
+    else if (!__ballot(n.k != 3)) update_few<T, 3, true>(c, n);
+    else if (!__ballot(n.k > 4)) update_few<T, 4, false>(c, n);
+    else update_many<T>(c, n, node_value<T>(su, c.zero, n));
   };
   // This thread's first node in the updates, and in interval iv on the way up
   // and down (possibly past the level's end); their words never change and are
-  // fetched one interval ahead.
-  const int first_update = top_wave ? tid : top > 0 ? n_top + tid - 64 : tid;
-  const int update_step = top > 0 ? BLOCK - 64 : BLOCK;
-  auto up_id = [&](int iv) {
-    return iv >= n_int ? first_update : nb(bottom - iv) + (iv == 0 && top > 0 ? tid - 64 : tid);
-  };
-  auto down_id = [&](int iv) { return nb(first_down + 2 * (iv - down0)) + tid; };
-  auto clamp = [&](int id) { return id < 0 ? 0 : id < na ? id : na - 1; };
+  // fetched one interval ahead.  Wave 0 joins the updates in their second round.
+  const int first_update = top_wave ? n_top + BLOCK - 64 + tid : top > 0 ? n_top + tid - 64 : tid;
+  auto up_id = [&](int iv) { return iv >= n_int ? first_update : nb(bottom - iv) + tid; };
+  auto down_id = [&](int iv) { return nb(first_down + 2 * (iv - down0)) + last_tid; };
+  auto clamp = [&](int id) { return id < na ? id : na - 1; };
   const uint2 top_kids = w_kids[clamp(lane)];
   const uint32_t top_up = w_up[clamp(lane)];
+  // the updates of the list's places i0, i0 + BLOCK, ... below end
+  struct Place {
+    uint32_t edge, up;
+    uint2 w;
+  };
+  auto place = [&](int i) {
+    Place p;
+    p.edge = list[i < kList ? i : kList - 1];
+    p.w = w_kids[clamp((int)(p.edge & 0xFFFFu))];
+    p.up = w_up[clamp((int)(p.edge & 0xFFFFu))];
+    return p;
+  };
+  auto update_list = [&](Place p, int i0, int end) {
+    if (i0 >= end) return;
+    __builtin_amdgcn_s_setprio(3);  // the other waves wait for these few
+    for (int i = i0; i < end;) {
+      if (p.edge != kNoEdge) {
+        node((int)(p.edge & 0xFFFFu), p.w, p.up);
+        update_edge<T>(c, Kids(p.w), (int)(p.edge >> 16));
+      }
+      i += BLOCK;
+      if (i < end) p = place(i);
+    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+  const Place top_place = place(last_tid);
   uint2 up_w = w_kids[clamp(up_id(0))];
   uint2 down_w = make_uint2(0, 0);
   if (down0 == 0) down_w = make_uint2(w_kids[clamp(down_id(0))].y, w_up[clamp(down_id(0))]);
 
+  c.ik = ks[0];
   IterK next = ks[0];
   for (int it = 0; it < n_iters; ++it) {
-    c.ik = next;
-    next = ks[it + 1 < n_iters ? it + 1 : it];
     // utilities go up from the bottom level to `top`, one level per interval,
-    // while reaches go down, two levels per interval
+    // while the top levels are updated for the iteration before (their words and
+    // utilities stay until the way up reaches them) and reaches go down, wave 0's
+    // in the second interval, then two levels per interval
     for (int iv = 0; iv < n_int; ++iv) {
       const int ul = bottom - iv, dl = first_down + 2 * (iv - down0);
       uint2 next_up = up_w, next_down = down_w;
@@ -690,16 +885,18 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
         const int id = clamp(down_id(iv + 1));
         next_down = make_uint2(w_kids[id].y, w_up[id]);
       }
-      if (iv == 0 && top_wave) {
+      if (iv == 0 && it > 0) update_list(top_place, last_tid, n_list_top);
+      if (iv == 1 && top_wave) {
         for (int l = 1; l < top; l += 2) {
           if (lane >= nb(l) && lane < nb(l + 2 < top ? l + 2 : top))
             down(lane, top_kids.y, top_up);
           wave_order();
         }
-      } else if (ul >= top) {
-        const int end = nb(ul + 1), step = iv == 0 && top > 0 ? BLOCK - 64 : BLOCK;
-        int id = up_id(iv);
-        for (uint2 w = up_w; id < end; id += step, w = w_kids[clamp(id)]) {
+      }
+      if (ul >= top) {
+        const int end = nb(ul + 1);
+        int id = nb(ul) + tid;
+        for (uint2 w = up_w; id < end; id += BLOCK, w = w_kids[clamp(id)]) {
           const double uh = value(w);
           if (ul == 0) vacc[id] += uh;
         }
@@ -719,9 +916,10 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
       seg_store_reach<T, BLOCK>(D, j0, L);
       __syncthreads();
     }
-    // updates of all levels; wave 0 finishes the top levels' utilities first,
-    // whose strategies no other wave changes
-    const uint2 first = up_w;
+    // the updates below the top levels; wave 0 finishes these levels' utilities
+    c.ik = next;
+    next = ks[it + 1 < n_iters ? it + 1 : it];
+    uint2 w = up_w;
     up_w = w_kids[clamp(up_id(0))];
     if (down0 == 0) down_w = make_uint2(w_kids[clamp(down_id(0))].y, w_up[clamp(down_id(0))]);
     if (top_wave) {
@@ -733,13 +931,15 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
         wave_order();
       }
     }
-    uint2 w = top_wave ? top_kids : first;
-    for (int id = first_update, end = top_wave ? n_top : na; id < end; id += update_step) {
-      update(id, w, w_up[id]);
-      w = w_kids[clamp(id + update_step)];
+    update_list(place(n_list_top + last_tid), n_list_top + last_tid, n_list);
+    for (int id = first_update; id < na; id += BLOCK) {
+      if (!(w.y & kListed)) update(id, w, w_up[id]);
+      w = w_kids[clamp(id + BLOCK)];
     }
     __syncthreads();
   }
+  update_list(top_place, last_tid, n_list_top);
+  __syncthreads();
   seg_store<T, BLOCK>(D, j0, j1 - j0, L, na, ne, ks, n_iters, variant);
 }
 
