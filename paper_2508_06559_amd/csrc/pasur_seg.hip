@@ -65,8 +65,10 @@ struct ItemDesc {
 };
 
 struct Seg {
-  int32_t item, j0, j1, pad;  // roots j0 .. j1-1 of item
+  int32_t item, j0, j1;  // roots j0 .. j1-1 of item
+  int32_t far, far_n;    // place and size of its far arrays in units of kFarUnit; -1: none
 };
+constexpr int kFarUnit = 256;
 
 // ---- the compact form ----------------------------------------------------------
 
@@ -79,7 +81,10 @@ struct SegCounts {
 
 // Byte offsets of a segment's arrays in LDS.  While the form is made, class
 // tables and a map from tree nodes to active nodes take the edge arrays'
-// place.
+// place.  A segment too large for this keeps rs, chain, kids, up and pos (its far
+// arrays) in device memory: each is read once per iteration or pass, in order,
+// while su and x are read at random.  That carries roots of 14,000 to 32,000
+// nodes (f32) at a fifth of the time of iterating them in place.
 struct SegLds {
   uint32_t b6, b7;   // passive bits of levels 6 and 7
   uint32_t tmp;      // = the start of the edge arrays
@@ -92,6 +97,7 @@ struct SegLds {
   uint32_t pos;      // 16 bits per active node: its index within its level of the segment
   uint32_t list;     // edges that are updated a lane each, see list_build
   uint32_t bytes;
+  uint32_t far;      // bytes of the far arrays
 };
 // Words of active node i:
 //   kids.x: slot of its first child | distance to the next child << 16
@@ -119,12 +125,18 @@ __host__ __device__ inline U align16(U x) {
   return (x + 15u) & ~(U)15u;
 }
 
-__host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t) {
+__host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t, bool far) {
   SegLds L;
-  uint32_t p = 0;
+  uint32_t p = 0, q = 0;
   auto take = [&p](uint32_t bytes) {
     const uint32_t at = p;
     p = align16(p + bytes);
+    return at;
+  };
+  auto take_far = [&](uint32_t bytes) {
+    if (!far) return take(bytes);
+    const uint32_t at = q;
+    q = align16(q + bytes);
     return at;
   };
   L.b6 = take((uint32_t)((c.c6 + 63) / 64) * 8u);
@@ -132,16 +144,17 @@ __host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t) {
   L.tmp = p;
   const uint32_t tmp_end = p + kTableBytes + align16(2u * (uint32_t)c.c07);
   L.su = take(2 * t * (uint32_t)(c.ne + c.roots + 2));
-  L.rs = take(2 * t * (uint32_t)(c.ne + 1));
-  L.chain = take(2 * t * (uint32_t)(c.ne67 + 1));
+  L.rs = take_far(2 * t * (uint32_t)(c.ne + 1));
+  L.chain = take_far(2 * t * (uint32_t)(c.ne67 + 1));
   L.x = take(t * (uint32_t)(c.na + c.roots));
   L.vacc = take(8u * (uint32_t)c.roots);
   if (p < tmp_end) p = tmp_end;
-  L.kids = take(8u * (uint32_t)c.na);
-  L.up = take(4u * (uint32_t)c.na);
-  L.pos = take(2u * (uint32_t)c.na);
+  L.kids = take_far(8u * (uint32_t)c.na);
+  L.up = take_far(4u * (uint32_t)c.na);
+  L.pos = take_far(2u * (uint32_t)c.na);
   L.list = take(4u * kList);
   L.bytes = p;
+  L.far = q;
   return L;
 }
 // Indices are held in 16 bits.
@@ -159,6 +172,12 @@ __shared__ int g_list_top, g_list_end;  // where the list's two parts end
 template <class T>
 __device__ __forceinline__ T *lds(uint32_t off) {
   return reinterpret_cast<T *>(g_lds + off);
+}
+
+// an array that may be far
+template <class T, bool FAR>
+__device__ __forceinline__ T *arr(unsigned char *far, uint32_t off) {
+  return FAR ? reinterpret_cast<T *>(far + off) : lds<T>(off);
 }
 
 __device__ __forceinline__ bool bit_of(uint32_t off, int i) {
@@ -195,9 +214,10 @@ __device__ __forceinline__ int top_levels() {
 // two neighbouring waves are then filled with more than 64 edges between them:
 // kTopEdges edges take at most kList places.  Nodes past the list's end stay with
 // update_many.  For one wave; before it, the list is kNoEdge.
-__device__ __forceinline__ void list_build(const SegLds &L) {
+template <bool FAR>
+__device__ __forceinline__ void list_build(unsigned char *far, const SegLds &L) {
   const int lane = threadIdx.x & 63;
-  uint2 *const w_kids = lds<uint2>(L.kids);
+  uint2 *const w_kids = arr<uint2, FAR>(far, L.kids);
   uint32_t *const list = lds<uint32_t>(L.list);
   const int top = top_levels();
   int at = 0;
@@ -237,9 +257,10 @@ __device__ __forceinline__ void list_build(const SegLds &L) {
 
 // Makes the compact form of roots j0 .. j1-1; false (for every thread) if it
 // does not fit in lds_bytes.  `L` is the layout, g_nb and g_sb the levels.
-template <class T, int BLOCK>
+template <class T, int BLOCK, bool FAR>
 __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, uint32_t lds_bytes,
-                                         SegLds &L, int &na, int &ne) {
+                                         unsigned char *far, int64_t far_bytes, SegLds &L, int &na,
+                                         int &ne) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int NW = BLOCK / 64;
   SegCounts c;
@@ -256,7 +277,7 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   if (!fits) return false;
   // where bits, tables and the map go does not depend on the other counts
   c.na = c.ne = c.ne67 = 0;
-  L = seg_layout(c, sizeof(T));
+  L = seg_layout(c, sizeof(T), FAR);
   if (L.bytes > lds_bytes) return false;
   uint32_t *const count = lds<uint32_t>(L.tmp);  // per level and class: nodes
   uint32_t *const next = count + 8 * kClasses;   // next rank within the level
@@ -323,8 +344,8 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   }
   na = c.na;
   ne = c.ne;
-  L = seg_layout(c, sizeof(T));
-  if (L.bytes > lds_bytes || !seg_indices_fit(c)) return false;
+  L = seg_layout(c, sizeof(T), FAR);
+  if (L.bytes > lds_bytes || L.far > far_bytes || !seg_indices_fit(c)) return false;
   if (tid == 0) {
     int a = 0, e = 0;
     for (int l = 0; l < 8; ++l) {
@@ -337,9 +358,9 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
     g_sb[9] = e;
   }
   __syncthreads();
-  uint2 *const w_kids = lds<uint2>(L.kids);
-  uint32_t *const w_up = lds<uint32_t>(L.up);
-  uint16_t *const w_pos = lds<uint16_t>(L.pos);
+  uint2 *const w_kids = arr<uint2, FAR>(far, L.kids);
+  uint32_t *const w_up = arr<uint32_t, FAR>(far, L.up);
+  uint16_t *const w_pos = arr<uint16_t, FAR>(far, L.pos);
   // every active node's place and its children's slots
   for (int l = 0, at = 0; l < 8; ++l) {
     const int h0 = D.off[l][j0], n = D.off[l][j1] - h0;
@@ -382,8 +403,8 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   }
   __syncthreads();
   // the state; from here on the edge arrays take the tables' place
-  Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = lds<Pair<T>>(L.rs);
-  Pair<T> *const chain = lds<Pair<T>>(L.chain);
+  Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = arr<Pair<T>, FAR>(far, L.rs);
+  Pair<T> *const chain = arr<Pair<T>, FAR>(far, L.chain);
   const int e6 = g_sb[6];
   for (int l = 0; l < 8; ++l) {
     const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0];
@@ -422,7 +443,7 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   if (tid == 0) su[c.ne + c.roots] = Pair<T>{(T)0, (T)0};
   for (int i = tid; i < kList; i += BLOCK) lds<uint32_t>(L.list)[i] = kNoEdge;
   __syncthreads();
-  if (wave == 0) list_build(L);
+  if (wave == 0) list_build<FAR>(far, L);
   for (int id = tid; id < c.roots; id += BLOCK) {
     const int64_t j = D.off[0][j0] + w_pos[id];
     lds<T>(L.x)[id] = D.rb[0][j];
@@ -679,8 +700,9 @@ __device__ __forceinline__ void update_many(const Update<T> &c, const Kids &n, d
 
 // Reach arrays of the segment's nodes below the roots, as the last iteration's
 // way down leaves them (before its updates).
-template <class T, int BLOCK>
-__device__ __forceinline__ void seg_store_reach(const ItemDesc<T> &D, int j0, const SegLds &L) {
+template <class T, int BLOCK, bool FAR>
+__device__ __forceinline__ void seg_store_reach(const ItemDesc<T> &D, int j0, unsigned char *far,
+                                                const SegLds &L) {
   const Pair<T> *const su = lds<Pair<T>>(L.su);
   const T *const x = lds<T>(L.x);
   for (int l = 0; l < 7; ++l) {
@@ -688,10 +710,10 @@ __device__ __forceinline__ void seg_store_reach(const ItemDesc<T> &D, int j0, co
     T *const moved = (l & 1) == 0 ? D.ra[l + 1] : D.rb[l + 1];
     T *const kept = (l & 1) == 0 ? D.rb[l + 1] : D.ra[l + 1];
     for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
-      const Kids n(lds<uint2>(L.kids)[id]);
-      const int32_t b = D.cb[l][h0 + lds<uint16_t>(L.pos)[id]];
+      const Kids n(arr<uint2, FAR>(far, L.kids)[id]);
+      const int32_t b = D.cb[l][h0 + arr<uint16_t, FAR>(far, L.pos)[id]];
       const T opp = x[id];
-      const double own = (double)x[lds<uint32_t>(L.up)[id] & 0xFFFFu];
+      const double own = (double)x[arr<uint32_t, FAR>(far, L.up)[id] & 0xFFFFu];
       for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
         const int32_t q = b + j;
         const T v = (T)(own * (double)su[e].a);
@@ -720,18 +742,18 @@ __device__ __forceinline__ void chain_regret(T *R, double sgn, const IterK *ks, 
 }
 
 // The state back into the level arrays.
-template <class T, int BLOCK>
-__device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int roots, const SegLds &L,
-                                          int na, int ne, const IterK *ks, int n_iters,
-                                          int variant) {
-  const Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = lds<Pair<T>>(L.rs);
-  const Pair<T> *const chain = lds<Pair<T>>(L.chain);
+template <class T, int BLOCK, bool FAR>
+__device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int roots,
+                                          unsigned char *far, const SegLds &L, int na, int ne,
+                                          const IterK *ks, int n_iters, int variant) {
+  const Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = arr<Pair<T>, FAR>(far, L.rs);
+  const Pair<T> *const chain = arr<Pair<T>, FAR>(far, L.chain);
   const int e6 = g_sb[6];
   for (int l = 0; l < 8; ++l) {
     const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0], end = g_nb[l + 1];
     for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
-      const Kids n(lds<uint2>(L.kids)[id]);
-      const int32_t b = D.cb[l][h0 + lds<uint16_t>(L.pos)[id]];
+      const Kids n(arr<uint2, FAR>(far, L.kids)[id]);
+      const int32_t b = D.cb[l][h0 + arr<uint16_t, FAR>(far, L.pos)[id]];
       for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
         const int32_t q = b + j;
         const Pair<T> p = su[e], r = rs[e];
@@ -755,7 +777,7 @@ __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int root
     }
   }
   for (int id = threadIdx.x; id < roots; id += BLOCK) {
-    const int64_t j = D.off[0][j0] + lds<uint16_t>(L.pos)[id];
+    const int64_t j = D.off[0][j0] + arr<uint16_t, FAR>(far, L.pos)[id];
     D.u[0][j] = su[ne + id].b;
     D.vacc[j] = lds<double>(L.vacc)[id];
   }
@@ -763,10 +785,11 @@ __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int root
 
 // All iterations of one segment in its compact form.  PAPER fixes the paper's
 // variant (DCFR with the regret floor) at compile time.
-template <class T, int BLOCK, bool PAPER>
-__device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1, const SegLds &L,
-                                           int na, int ne, const IterK *__restrict__ ks,
-                                           int n_iters, int variant, int rm_mode, double eps) {
+template <class T, int BLOCK, bool PAPER, bool FAR>
+__device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
+                                           unsigned char *far, const SegLds &L, int na, int ne,
+                                           const IterK *__restrict__ ks, int n_iters, int variant,
+                                           int rm_mode, double eps) {
   if (PAPER) {
     variant = PASUR_DCFR;
     rm_mode = PASUR_RM_FLOOR;
@@ -775,8 +798,8 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   Pair<T> *const su = lds<Pair<T>>(L.su);
   T *const x = lds<T>(L.x);
   double *const vacc = lds<double>(L.vacc);
-  const uint2 *const w_kids = lds<uint2>(L.kids);
-  const uint32_t *const w_up = lds<uint32_t>(L.up);
+  const uint2 *const w_kids = arr<uint2, FAR>(far, L.kids);
+  const uint32_t *const w_up = arr<uint32_t, FAR>(far, L.up);
   const uint32_t *const list = lds<uint32_t>(L.list);
   const int n_list_top = __builtin_amdgcn_readfirstlane(g_list_top);
   const int n_list = __builtin_amdgcn_readfirstlane(g_list_end);
@@ -807,8 +830,8 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   };
   Update<T> c;
   c.su = su;
-  c.rs = lds<Pair<T>>(L.rs);
-  c.chain = lds<Pair<T>>(L.chain) - g_sb[6];
+  c.rs = arr<Pair<T>, FAR>(far, L.rs);
+  c.chain = arr<Pair<T>, FAR>(far, L.chain) - g_sb[6];
   c.variant = variant;
   c.rm_mode = rm_mode;
   c.eps = eps;
@@ -913,7 +936,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
       __syncthreads();
     }
     if (it == n_iters - 1) {
-      seg_store_reach<T, BLOCK>(D, j0, L);
+      seg_store_reach<T, BLOCK, FAR>(D, j0, far, L);
       __syncthreads();
     }
     // the updates below the top levels; wave 0 finishes these levels' utilities
@@ -940,7 +963,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   }
   update_list(top_place, last_tid, n_list_top);
   __syncthreads();
-  seg_store<T, BLOCK>(D, j0, j1 - j0, L, na, ne, ks, n_iters, variant);
+  seg_store<T, BLOCK, FAR>(D, j0, j1 - j0, far, L, na, ne, ks, n_iters, variant);
 }
 
 // ---- in global memory ------------------------------------------------------------
@@ -1063,21 +1086,33 @@ __device__ __forceinline__ void seg_in_global(const ItemDesc<T> &D, int j0, int 
   }
 }
 
-// One workgroup per segment; the segment runs in LDS when its compact form
-// fits in the launch's dynamic LDS (lds_bytes), otherwise in global memory.
-template <class T, int BLOCK, bool PAPER>
+// One workgroup per segment; the segment runs in its compact form when that fits
+// in the launch's dynamic LDS (lds_bytes), otherwise in global memory.  FAR: some
+// segments have far arrays.
+template <class T, int BLOCK, bool PAPER, bool FAR>
 __global__ void __launch_bounds__(BLOCK)
     k_cfr_seg(const ItemDesc<T> *__restrict__ items, const Seg *__restrict__ segs,
-              const IterK *__restrict__ ks, int n_iters, int variant, int rm_mode, double eps,
-              uint32_t lds_bytes) {
+              const IterK *__restrict__ ks, unsigned char *far, int n_iters, int variant,
+              int rm_mode, double eps, uint32_t lds_bytes) {
   const Seg sg = segs[blockIdx.x];
   const ItemDesc<T> &D = items[sg.item];
   SegLds L;
   int na = 0, ne = 0;
-  if (seg_load<T, BLOCK>(D, sg.j0, sg.j1, lds_bytes, L, na, ne))
-    seg_in_lds<T, BLOCK, PAPER>(D, sg.j0, sg.j1, L, na, ne, ks, n_iters, variant, rm_mode, eps);
-  else
-    seg_in_global<T, BLOCK, PAPER>(D, sg.j0, sg.j1, ks, n_iters, variant, rm_mode, eps);
+  if (!FAR || sg.far < 0) {
+    if (seg_load<T, BLOCK, false>(D, sg.j0, sg.j1, lds_bytes, nullptr, 0, L, na, ne)) {
+      seg_in_lds<T, BLOCK, PAPER, false>(D, sg.j0, sg.j1, nullptr, L, na, ne, ks, n_iters, variant,
+                                         rm_mode, eps);
+      return;
+    }
+  } else {
+    far += (int64_t)sg.far * kFarUnit;
+    if (seg_load<T, BLOCK, true>(D, sg.j0, sg.j1, lds_bytes, far, (int64_t)sg.far_n * kFarUnit, L, na, ne)) {
+      seg_in_lds<T, BLOCK, PAPER, true>(D, sg.j0, sg.j1, far, L, na, ne, ks, n_iters, variant,
+                                        rm_mode, eps);
+      return;
+    }
+  }
+  seg_in_global<T, BLOCK, PAPER>(D, sg.j0, sg.j1, ks, n_iters, variant, rm_mode, eps);
 }
 
 // Per root, what the tree's structure says of its compact form on levels 6 and
@@ -1119,9 +1154,16 @@ inline bool paper_variant(int variant, int rm_mode) {
   return variant == PASUR_DCFR && rm_mode == PASUR_RM_FLOOR;
 }
 
-template <class T, int BLOCK>
-void *seg_kernel(bool paper) {
-  return paper ? (void *)k_cfr_seg<T, BLOCK, true> : (void *)k_cfr_seg<T, BLOCK, false>;
+template <class T>
+using SegKernel = void (*)(const ItemDesc<T> *, const Seg *, const IterK *, unsigned char *, int,
+                           int, int, double, uint32_t);
+
+template <class T>
+SegKernel<T> seg_kernel(int block, bool paper, bool far) {
+  if (far) return paper ? k_cfr_seg<T, 1024, true, true> : k_cfr_seg<T, 1024, false, true>;
+  if (block == 256) return paper ? k_cfr_seg<T, 256, true, false> : k_cfr_seg<T, 256, false, false>;
+  if (block == 512) return paper ? k_cfr_seg<T, 512, true, false> : k_cfr_seg<T, 512, false, false>;
+  return paper ? k_cfr_seg<T, 1024, true, false> : k_cfr_seg<T, 1024, false, false>;
 }
 
 std::mutex g_counts_mu;
@@ -1158,6 +1200,7 @@ int root_counts(pasur_fgt *f, hipStream_t s) {
 struct SegLaunch {
   int first, count, block;
   uint32_t lds_bytes;
+  bool far;  // some segments have far arrays (1024 threads)
 };
 
 }  // namespace
@@ -1168,6 +1211,7 @@ struct pasur_plan {
   int64_t t_first, t_last;
   int n_items, n_segs;
   void *mem, *anchor;  // the arrays below in one block; see anchor_alloc
+  void *far;           // far arrays of the launch that needs most (launches follow each other)
   void *d_items;
   Seg *d_segs;
   IterK *d_ks;
@@ -1182,40 +1226,61 @@ namespace {
 struct SegPlan {
   Seg seg;
   int64_t nodes;
-  uint32_t bytes;  // of its compact form, 0: in global memory
+  uint32_t bytes;  // of its compact form in LDS, 0: in global memory
 };
 
+// Far arrays of one launch: at most this much (a launch's segments beyond it go
+// to the next launch, which uses the same memory).
+constexpr int64_t kFarBytes = (int64_t)1 << 30;
+
 // Launches of segments ordered by descending size, those in global memory
-// first.  A launch's workgroups all hold the LDS of its largest segment, so
-// segments of which more fit on a CU get a launch of their own, unless there
-// are too few of them to fill the chip; segments in global memory, the longest
-// of all, run beside the largest ones.
-void plan_launches(pasur_plan *pl, const std::vector<SegPlan> &segs, int user_block) {
+// first, then those with far arrays.  A launch's workgroups all hold the LDS of
+// its largest segment, so segments of which more fit on a CU get a launch of
+// their own, unless there are too few of them to fill the chip; the segments of
+// the first two kinds, the longest of all, run beside the largest ones in LDS.
+// Gives far arrays their places; returns the bytes these take.
+int64_t plan_launches(pasur_plan *pl, std::vector<SegPlan> &segs, int user_block) {
   constexpr int kCus = 256;
-  auto per_cu = [](uint32_t bytes) {
-    const int n = (int)(kLdsPerWorkgroup / (bytes + kStaticLds));
-    return bytes == 0 || n < 1 ? 1 : n > 4 ? 4 : n;
+  auto per_cu = [](const SegPlan &sp) {
+    const int n = (int)(kLdsPerWorkgroup / (sp.bytes + kStaticLds));
+    return sp.bytes == 0 || sp.seg.far >= 0 || n < 1 ? 1 : n > 4 ? 4 : n;
   };
+  int64_t far_max = 0;
   const int n = (int)segs.size();
+  pl->launches.clear();
   for (int i = 0; i < n;) {
     SegLaunch la;
-    const int c = per_cu(segs[(size_t)i].bytes);
+    const int c = per_cu(segs[(size_t)i]);
     int j = i;
+    int64_t far = 0;
     la.lds_bytes = 0;
-    while (j < n && per_cu(segs[(size_t)j].bytes) == c) {
-      la.lds_bytes = std::max(la.lds_bytes, segs[(size_t)j].bytes);
-      ++j;
+    for (bool rest = false; j < n; ++j) {
+      SegPlan &sp = segs[(size_t)j];
+      if (!rest && per_cu(sp) != c) {
+        if (n - j >= kCus) break;
+        rest = true;
+      }
+      if (sp.seg.far >= 0) {
+        const int64_t need = (int64_t)sp.seg.far_n * kFarUnit;
+        if (far > 0 && far + need > kFarBytes) break;
+        sp.seg.far = (int32_t)(far / kFarUnit);
+        far += need;
+      }
+      la.lds_bytes = std::max(la.lds_bytes, sp.bytes);
     }
-    if (n - j < kCus && j < n) {
-      la.lds_bytes = std::max(la.lds_bytes, segs[(size_t)j].bytes);
-      j = n;
-    }
+    far_max = std::max(far_max, far);
     la.first = i;
     la.count = j - i;
-    la.block = user_block ? user_block : la.count <= kCus || c == 1 ? 1024 : c == 2 ? 512 : 256;
+    la.far = far > 0;
+    la.block = la.far       ? 1024
+               : user_block ? user_block
+               : la.count <= kCus || c == 1 ? 1024
+               : c == 2     ? 512
+                            : 256;
     pl->launches.push_back(la);
     i = j;
   }
+  return far_max;
 }
 
 template <class T>
@@ -1266,9 +1331,9 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
       c.c7 += n[7];
       tot += c07 + n[8];
     };
-    auto bytes_of = [&](const SegCounts &c) -> uint32_t {
+    auto bytes_of = [&](const SegCounts &c, bool far) -> uint32_t {
       if (c.c6 > 65535 || c.c7 > 65535 || !seg_indices_fit(c)) return 0u;
-      const uint32_t b = seg_layout(c, sizeof(T)).bytes;
+      const uint32_t b = seg_layout(c, sizeof(T), far).bytes;
       return b <= budget ? b : 0u;
     };
     int64_t j0 = 0;
@@ -1276,12 +1341,12 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
       int64_t j1 = j0 + 1, tot = 0;
       SegCounts c = {};
       add_root(c, tot, j0);
-      uint32_t bytes = bytes_of(c);
+      uint32_t bytes = bytes_of(c, false);
       while (p->seg_nodes > 0 && bytes && j1 < nr && j1 - j0 < pl->block) {
         SegCounts c2 = c;
         int64_t t2 = tot;
         add_root(c2, t2, j1);
-        const uint32_t b2 = bytes_of(c2);
+        const uint32_t b2 = bytes_of(c2, false);
         if (t2 > p->seg_nodes || !b2) break;
         ++j1;
         c = c2;
@@ -1293,7 +1358,15 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
       sp.seg.item = it;
       sp.seg.j0 = (int32_t)j0;
       sp.seg.j1 = (int32_t)j1;
-      sp.seg.pad = 0;
+      sp.seg.far = -1;
+      sp.seg.far_n = 0;
+      if (!bytes) {  // (a single root)
+        bytes = bytes_of(c, true);
+        if (bytes) {
+          sp.seg.far = 0;
+          sp.seg.far_n = (int32_t)((seg_layout(c, sizeof(T), true).far + kFarUnit - 1) / kFarUnit);
+        }
+      }
       sp.nodes = tot;
       sp.bytes = bytes;
       segs.push_back(sp);
@@ -1304,11 +1377,26 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
     pl->work[2] += f->n[0];
     pl->work[3] += f->n[7];
   }
-  // segments in global memory first, then the largest
-  std::stable_sort(segs.begin(), segs.end(), [](const SegPlan &a, const SegPlan &b) {
-    if ((a.bytes == 0) != (b.bytes == 0)) return a.bytes == 0;
-    return a.bytes ? a.bytes > b.bytes : a.nodes > b.nodes;
-  });
+  // segments in global memory first, then those with far arrays, then the largest
+  auto order = [&]() {
+    auto rank = [](const SegPlan &x) { return x.bytes == 0 ? 0 : x.seg.far >= 0 ? 1 : 2; };
+    std::stable_sort(segs.begin(), segs.end(), [&](const SegPlan &a, const SegPlan &b) {
+      if (rank(a) != rank(b)) return rank(a) < rank(b);
+      return rank(a) == 2 ? a.bytes > b.bytes : a.nodes > b.nodes;
+    });
+    return plan_launches(pl, segs, p->block);
+  };
+  const int64_t far_bytes = order();
+  if (far_bytes > 0 && block_alloc(&pl->far, (size_t)far_bytes) != PASUR_OK) {
+    // no memory for far arrays: in global memory
+    pl->far = nullptr;
+    for (SegPlan &sp : segs)
+      if (sp.seg.far >= 0) {
+        sp.seg.far = -1;
+        sp.bytes = 0;
+      }
+    order();
+  }
   std::vector<Seg> sorted(segs.size());
   uint32_t max_bytes = 0;
   for (size_t i = 0; i < segs.size(); ++i) {
@@ -1317,7 +1405,6 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   }
   pl->n_segs = (int)sorted.size();
   pl->lds_bytes = max_bytes;
-  plan_launches(pl, segs, p->block);
   // iteration constants for t_first .. t_last, computed on the host
   const int64_t nt = pl->t_last - pl->t_first + 1;
   std::vector<IterK> ks((size_t)nt);
@@ -1339,25 +1426,20 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   // The attribute is a ceiling shared by every plan of this instance, so it
   // is raised to the whole budget (plans may be launched in any order); each
   // launch still asks for its own lds_bytes.
-  for (const SegLaunch &la : pl->launches) {
-    void *kern = la.block == 256   ? seg_kernel<T, 256>(paper)
-                 : la.block == 512 ? seg_kernel<T, 512>(paper)
-                                   : seg_kernel<T, 1024>(paper);
-    PASUR_TRY_HIP(hipFuncSetAttribute((const void *)kern,
+  for (const SegLaunch &la : pl->launches)
+    PASUR_TRY_HIP(hipFuncSetAttribute((const void *)seg_kernel<T>(la.block, paper, la.far),
                                       hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)(kLdsPerWorkgroup - kStaticLds)));
-  }
   return PASUR_OK;
 }
 
-template <class T, int BLOCK>
+template <class T>
 void plan_launch(const pasur_plan *pl, const SegLaunch &la, int64_t t0, int n_iters,
                  hipStream_t s) {
-  auto kern = paper_variant(pl->variant, pl->rm_mode) ? k_cfr_seg<T, BLOCK, true>
-                                                      : k_cfr_seg<T, BLOCK, false>;
-  kern<<<(unsigned)la.count, BLOCK, la.lds_bytes, s>>>(
+  const bool paper = paper_variant(pl->variant, pl->rm_mode);
+  seg_kernel<T>(la.block, paper, la.far)<<<(unsigned)la.count, la.block, la.lds_bytes, s>>>(
       (const ItemDesc<T> *)pl->d_items, pl->d_segs + la.first, pl->d_ks + (t0 - pl->t_first),
-      n_iters, pl->variant, pl->rm_mode, pl->eps, la.lds_bytes);
+      (unsigned char *)pl->far, n_iters, pl->variant, pl->rm_mode, pl->eps, la.lds_bytes);
 }
 
 }  // namespace
@@ -1366,6 +1448,7 @@ extern "C" void pasur_plan_free(pasur_plan *pl) {
   if (!pl) return;
   anchor_wait(pl->anchor);
   block_free(pl->mem);
+  block_free(pl->far);
   delete pl;
 }
 
@@ -1478,13 +1561,9 @@ extern "C" int pasur_plan_iterate(const pasur_plan *pl, int64_t t0, int n_iters,
   {
     ProfScope ps(pl->n_lds_segs == pl->n_segs ? 2 : 3, -1, s, pl->work[0], pl->work[1],
                  pl->work[2], pl->work[3], n_iters);
-    const bool f32 = pl->dtype == PASUR_F32;
     for (const SegLaunch &la : pl->launches) {
-      switch (la.block) {
-        case 256: f32 ? plan_launch<float, 256>(pl, la, t0, n_iters, s) : plan_launch<double, 256>(pl, la, t0, n_iters, s); break;
-        case 512: f32 ? plan_launch<float, 512>(pl, la, t0, n_iters, s) : plan_launch<double, 512>(pl, la, t0, n_iters, s); break;
-        default: f32 ? plan_launch<float, 1024>(pl, la, t0, n_iters, s) : plan_launch<double, 1024>(pl, la, t0, n_iters, s); break;
-      }
+      if (pl->dtype == PASUR_F32) plan_launch<float>(pl, la, t0, n_iters, s);
+      else plan_launch<double>(pl, la, t0, n_iters, s);
     }
   }
   PASUR_TRY_HIP(hipGetLastError());
