@@ -255,26 +255,68 @@ __device__ __forceinline__ void list_build(unsigned char *far, const SegLds &L) 
   if (lane == 0) g_list_end = at;
 }
 
-// Makes the compact form of roots j0 .. j1-1; false (for every thread) if it
+// The level arrays of the segment's tree, from its first node on each level on:
+// a pointer table in LDS, since the 72 pointers don't fit in registers and a
+// level may differ from lane to lane.
+enum { P_SIGMA, P_R, P_SBAR, P_U, P_RA, P_RB, P_PARENT, P_CB };
+__shared__ void *g_ptab[8][9];
+__shared__ int g_lo[9], g_cnt[9];  // first node and nodes per level
+
+template <class T>
+using GlobalPtr = __attribute__((address_space(1))) T *;
+
+template <class T>
+__device__ __forceinline__ GlobalPtr<T> tab(int slot, int l) {
+  return (GlobalPtr<T>)g_ptab[slot][l];
+}
+
+template <class T>
+__device__ __forceinline__ void seg_open(const ItemDesc<T> &D, int j0, int j1) {
+  if (threadIdx.x < 9) {
+    const int l = threadIdx.x;
+    const GlobalPtr<const int32_t> off = (GlobalPtr<const int32_t>)D.off[l];
+    const int lo = off[j0];
+    g_ptab[P_SIGMA][l] = l >= 1 ? (void *)(D.sigma[l] + lo) : nullptr;
+    g_ptab[P_R][l] = l >= 1 ? (void *)(D.R[l] + lo) : nullptr;
+    g_ptab[P_SBAR][l] = l >= 1 ? (void *)(D.Sbar[l] + lo) : nullptr;
+    g_ptab[P_U][l] = (void *)(D.u[l] + lo);
+    g_ptab[P_RA][l] = l <= 7 ? (void *)(D.ra[l] + lo) : nullptr;
+    g_ptab[P_RB][l] = l <= 7 ? (void *)(D.rb[l] + lo) : nullptr;
+    g_ptab[P_PARENT][l] = l >= 1 ? (void *)(D.parent[l] + lo) : nullptr;
+    g_ptab[P_CB][l] = l <= 7 ? (void *)(D.cb[l] + lo) : nullptr;
+    g_lo[l] = lo;
+    g_cnt[l] = off[j1] - lo;
+  }
+  __syncthreads();
+}
+
+// Makes the compact form of the segment's roots; false (for every thread) if it
 // does not fit in lds_bytes.  `L` is the layout, g_nb and g_sb the levels.
+// Every pass runs over the nodes of all levels at once: what it waits for is
+// memory latency, and level by level it did so eight times (loading and storing
+// a segment of 3,900 nodes took as long as 12 iterations).
 template <class T, int BLOCK, bool FAR>
-__device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, uint32_t lds_bytes,
+__device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_bytes,
                                          unsigned char *far, int64_t far_bytes, SegLds &L, int &na,
                                          int &ne) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int NW = BLOCK / 64;
+  constexpr uint32_t kPassive = 0xFFFF;
   SegCounts c;
-  c.roots = j1 - j0;
-  c.c07 = 0;
+  int at[9];  // nodes above each level
   bool fits = true;
+  at[0] = 0;
+#pragma unroll
   for (int l = 0; l < 8; ++l) {
-    const int n = D.off[l][j1] - D.off[l][j0];
-    if (n > 65535) fits = false;
-    c.c07 += fits ? n : 0;
-    if (l == 6) c.c6 = n;
-    if (l == 7) c.c7 = n;
+    const int n = __builtin_amdgcn_readfirstlane(g_cnt[l]);
+    fits = fits && n <= 65535;
+    at[l + 1] = fits ? at[l] + n : at[l];
   }
   if (!fits) return false;
+  c.roots = at[1];
+  c.c07 = at[8];
+  c.c6 = at[7] - at[6];
+  c.c7 = at[8] - at[7];
   // where bits, tables and the map go does not depend on the other counts
   c.na = c.ne = c.ne67 = 0;
   L = seg_layout(c, sizeof(T), FAR);
@@ -283,36 +325,50 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   uint32_t *const next = count + 8 * kClasses;   // next rank within the level
   uint32_t *const first = next + 8 * kClasses;   // first slot - first rank
   uint16_t *const map = lds<uint16_t>(L.tmp + kTableBytes);
+  auto level_of = [&](int i) {
+    int l = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) l += i >= at[k] ? 1 : 0;
+    return l;
+  };
+  auto above = [&](int l) {  // at[l]
+    int v = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) v = l == k ? at[k] : v;
+    return v;
+  };
   // passive nodes: one child, along an edge of sigma 1, that is a leaf of
   // finite utility or passive itself
   if (tid == 0) g_bad = 0;
   for (int i = tid; i < 8 * kClasses; i += BLOCK) count[i] = 0;
+#pragma unroll
   for (int l = 7; l >= 6; --l) {
-    const int n = l == 7 ? c.c7 : c.c6, h0 = D.off[l][j0], q0 = D.off[l + 1][j0];
-    const int32_t *const cb = D.cb[l];
+    const int n = l == 7 ? c.c7 : c.c6, lo = g_lo[l + 1];
+    const GlobalPtr<const int32_t> cb = tab<const int32_t>(P_CB, l);
+    const GlobalPtr<const T> sg = tab<const T>(P_SIGMA, l + 1);
     for (int i = tid; i < ((n + 63) & ~63); i += BLOCK) {
       bool p = false;
       if (i < n) {
-        const int32_t q = cb[h0 + i];
-        p = cb[h0 + i + 1] - q == 1 && (double)D.sigma[l + 1][q] == 1.0;
-        if (p) p = l == 7 ? isfinite((double)D.u[8][q]) : bit_of(L.b7, q - q0);
+        const int32_t q = cb[i] - lo;
+        p = cb[i + 1] - lo - q == 1 && (double)sg[q] == 1.0;
+        if (p) p = l == 7 ? isfinite((double)tab<const T>(P_U, 8)[q]) : bit_of(L.b7, q);
       }
       const unsigned long long m = __ballot(p);
       if (lane == 0) lds<unsigned long long>(l == 7 ? L.b7 : L.b6)[i >> 6] = m;
     }
     __syncthreads();
   }
-  auto active = [&](int l, int i) {
-    return l < 6 || !bit_of(l == 6 ? L.b6 : L.b7, i);
-  };
-  for (int l = 0; l < 8; ++l) {
-    const int h0 = D.off[l][j0], n = D.off[l][j1] - h0;
-    for (int i = tid; i < n; i += BLOCK)
-      if (active(l, i)) {
-        const int k = D.cb[l][h0 + i + 1] - D.cb[l][h0 + i];
-        if (k < kClasses) atomicAdd(&count[l * kClasses + k], 1u);
-        else g_bad = 1;
-      }
+  // the active nodes' classes; the map holds their numbers of children for now
+  for (int i = tid; i < c.c07; i += BLOCK) {
+    const int l = level_of(i), j = i - above(l);
+    uint32_t k = kPassive;
+    if (l < 6 || !bit_of(l == 6 ? L.b6 : L.b7, j)) {
+      const GlobalPtr<const int32_t> cb = tab<const int32_t>(P_CB, l);
+      k = (uint32_t)(cb[j + 1] - cb[j]);
+      if (k < (uint32_t)kClasses) atomicAdd(&count[l * kClasses + k], 1u);
+      else g_bad = 1;
+    }
+    map[i] = (uint16_t)k;
   }
   __syncthreads();
   if (g_bad) return false;
@@ -362,82 +418,79 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   uint32_t *const w_up = arr<uint32_t, FAR>(far, L.up);
   uint16_t *const w_pos = arr<uint16_t, FAR>(far, L.pos);
   // every active node's place and its children's slots
-  for (int l = 0, at = 0; l < 8; ++l) {
-    const int h0 = D.off[l][j0], n = D.off[l][j1] - h0;
-    for (int i = tid; i < n; i += BLOCK)
-      if (active(l, i)) {
-        const int k = D.cb[l][h0 + i + 1] - D.cb[l][h0 + i];
-        const uint32_t rank = atomicAdd(&next[l * kClasses + k], 1u);
-        const uint32_t id = (uint32_t)g_nb[l] + rank;
-        w_kids[id] = make_uint2(((uint32_t)g_sb[l + 1] + first[l * kClasses + k] + rank) |
-                                    (count[l * kClasses + k] << 16),
-                                ((uint32_t)k << 16) | ((uint32_t)l << 24));
-        w_pos[id] = (uint16_t)i;
-        map[at + i] = (uint16_t)id;
-      }
-    at += n;
+  for (int i = tid; i < c.c07; i += BLOCK) {
+    const uint32_t k = map[i];
+    if (k == kPassive) continue;
+    const int l = level_of(i);
+    const uint32_t rank = atomicAdd(&next[l * kClasses + k], 1u);
+    const uint32_t id = (uint32_t)g_nb[l] + rank;
+    w_kids[id] = make_uint2(((uint32_t)g_sb[l + 1] + first[l * kClasses + k] + rank) |
+                                (count[l * kClasses + k] << 16),
+                            (k << 16) | ((uint32_t)l << 24));
+    w_pos[id] = (uint16_t)(i - above(l));
+    map[i] = (uint16_t)id;
   }
   __syncthreads();
-  // ancestors of an active node are active
-  for (int l = 0, at = 0, up = 0, up2 = 0; l < 8; ++l) {
-    const int h0 = D.off[l][j0], n = D.off[l][j1] - h0;
-    for (int i = tid; i < n; i += BLOCK)
-      if (active(l, i)) {
-        const uint32_t id = map[at + i];
-        uint32_t slot = (uint32_t)c.ne + id, par = (uint32_t)c.na + id, up_id = 0;
-        if (l > 0) {
-          const int p0 = D.off[l - 1][j0];
-          const int32_t h = D.parent[l][h0 + i];
-          par = map[up + (h - p0)];
-          const uint32_t w = w_kids[par].x;
-          slot = (w & 0xFFFFu) + (uint32_t)(h0 + i - D.cb[l - 1][h]) * (w >> 16);
-          up_id = l > 1 ? map[up2 + (D.parent[l - 1][h] - D.off[l - 2][j0])]
-                        : (uint32_t)c.na + par;
-        }
-        w_kids[id].y |= slot;
-        w_up[id] = par | (up_id << 16);
-      }
-    up2 = up;
-    up = at;
-    at += n;
+  // own slots and parents, written by the parents: low halves of the words
+  for (int id = tid; id < na; id += BLOCK) {
+    const uint2 w = w_kids[id];
+    const int l = (int)(w.y >> 24) & 7, k = (int)(w.y >> 16) & 0xFF;
+    if (l == 0) {
+      *reinterpret_cast<uint16_t *>(&w_kids[id].y) = (uint16_t)(c.ne + id);
+      w_up[id] = (uint32_t)(c.na + id);
+    }
+    if (l == 7) continue;
+    const int q = tab<const int32_t>(P_CB, l)[w_pos[id]] - g_lo[l + 1] + above(l + 1);
+    uint32_t e = w.x & 0xFFFFu;
+    for (int j = 0; j < k; ++j, e += w.x >> 16) {
+      const uint32_t child = map[q + j];
+      if (child == kPassive) continue;
+      *reinterpret_cast<uint16_t *>(&w_kids[child].y) = (uint16_t)e;
+      w_up[child] = (uint32_t)id;
+    }
   }
   __syncthreads();
+  // the nodes two levels up: high halves
+  for (int id = g_nb[1] + tid; id < na; id += BLOCK)
+    reinterpret_cast<uint16_t *>(w_up + id)[1] =
+        *reinterpret_cast<const uint16_t *>(w_up + *reinterpret_cast<const uint16_t *>(w_up + id));
   // the state; from here on the edge arrays take the tables' place
   Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = arr<Pair<T>, FAR>(far, L.rs);
   Pair<T> *const chain = arr<Pair<T>, FAR>(far, L.chain);
-  const int e6 = g_sb[6];
-  for (int l = 0; l < 8; ++l) {
-    const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0];
-    const int end = g_nb[l + 1];
-    for (int id = g_nb[l] + tid; id < end; id += BLOCK) {
-      const int32_t b = D.cb[l][h0 + w_pos[id]];
-      const uint2 w = w_kids[id];
-      const int k = (int)(w.y >> 16) & 0xFF;
-      int e = (int)(w.x & 0xFFFFu);
-      const int step = (int)(w.x >> 16);
-      for (int j = 0; j < k; ++j, e += step) {
-        const int32_t q = b + j;
-        rs[e] = Pair<T>{D.R[l + 1][q], D.Sbar[l + 1][q]};
-        T v = (T)0, a1 = (T)0, a2 = (T)0;
-        if (l == 7) {
-          v = D.u[8][q];
-        } else if (l == 6) {
-          if (bit_of(L.b7, q - q0)) {
-            const int32_t q8 = D.cb[7][q];
-            v = (T)(0.0 + (double)D.u[8][q8]);
-            a1 = D.Sbar[8][q8];
-          }
-        } else if (l == 5) {
-          if (bit_of(L.b6, q - q0)) {
-            const int32_t q7 = D.cb[6][q], q8 = D.cb[7][q7];
-            v = (T)(0.0 + (double)D.u[8][q8]);
-            a1 = D.Sbar[7][q7];
-            a2 = D.Sbar[8][q8];
-          }
+  const int e6 = g_sb[6], lo8 = g_lo[8], lo7 = g_lo[7];
+  for (int id = tid; id < na; id += BLOCK) {
+    const uint2 w = w_kids[id];
+    const int l = (int)(w.y >> 24) & 7, k = (int)(w.y >> 16) & 0xFF;
+    const int b = tab<const int32_t>(P_CB, l)[w_pos[id]] - g_lo[l + 1];
+    const GlobalPtr<const T> R = tab<const T>(P_R, l + 1), S = tab<const T>(P_SBAR, l + 1),
+                             sg = tab<const T>(P_SIGMA, l + 1);
+    const int step = (int)(w.x >> 16);
+    int e = (int)(w.x & 0xFFFFu);
+#pragma unroll 2
+    for (int j = 0; j < k; ++j, e += step) {
+      const int q = b + j;
+      const T r = R[q], sb = S[q], s0 = sg[q];
+      T v = (T)0, a1 = (T)0, a2 = (T)0;
+      if (l == 7) {
+        v = tab<const T>(P_U, 8)[q];
+      } else if (l == 6) {
+        if (bit_of(L.b7, q)) {
+          const int q8 = tab<const int32_t>(P_CB, 7)[q] - lo8;
+          v = (T)(0.0 + (double)tab<const T>(P_U, 8)[q8]);
+          a1 = tab<const T>(P_SBAR, 8)[q8];
         }
-        su[e] = Pair<T>{D.sigma[l + 1][q], v};
-        if (l == 5 || l == 6) chain[e - e6] = Pair<T>{a1, a2};
+      } else if (l == 5) {
+        if (bit_of(L.b6, q)) {
+          const int q7 = tab<const int32_t>(P_CB, 6)[q] - lo7;
+          const int q8 = tab<const int32_t>(P_CB, 7)[q7] - lo8;
+          v = (T)(0.0 + (double)tab<const T>(P_U, 8)[q8]);
+          a1 = tab<const T>(P_SBAR, 7)[q7];
+          a2 = tab<const T>(P_SBAR, 8)[q8];
+        }
       }
+      rs[e] = Pair<T>{r, sb};
+      su[e] = Pair<T>{s0, v};
+      if (l == 5 || l == 6) chain[e - e6] = Pair<T>{a1, a2};
     }
   }
   if (tid == 0) su[c.ne + c.roots] = Pair<T>{(T)0, (T)0};
@@ -445,10 +498,10 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, int j0, int j1, u
   __syncthreads();
   if (wave == 0) list_build<FAR>(far, L);
   for (int id = tid; id < c.roots; id += BLOCK) {
-    const int64_t j = D.off[0][j0] + w_pos[id];
-    lds<T>(L.x)[id] = D.rb[0][j];
-    lds<T>(L.x)[c.na + id] = D.ra[0][j];
-    lds<double>(L.vacc)[id] = D.vacc[j];
+    const int j = w_pos[id];
+    lds<T>(L.x)[id] = tab<const T>(P_RB, 0)[j];
+    lds<T>(L.x)[c.na + id] = tab<const T>(P_RA, 0)[j];
+    lds<double>(L.vacc)[id] = D.vacc[g_lo[0] + j];
   }
   __syncthreads();
   return true;
@@ -701,29 +754,29 @@ __device__ __forceinline__ void update_many(const Update<T> &c, const Kids &n, d
 // Reach arrays of the segment's nodes below the roots, as the last iteration's
 // way down leaves them (before its updates).
 template <class T, int BLOCK, bool FAR>
-__device__ __forceinline__ void seg_store_reach(const ItemDesc<T> &D, int j0, unsigned char *far,
-                                                const SegLds &L) {
+__device__ __forceinline__ void seg_store_reach(unsigned char *far, const SegLds &L) {
   const Pair<T> *const su = lds<Pair<T>>(L.su);
   const T *const x = lds<T>(L.x);
-  for (int l = 0; l < 7; ++l) {
-    const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0], end = g_nb[l + 1];
-    T *const moved = (l & 1) == 0 ? D.ra[l + 1] : D.rb[l + 1];
-    T *const kept = (l & 1) == 0 ? D.rb[l + 1] : D.ra[l + 1];
-    for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
-      const Kids n(arr<uint2, FAR>(far, L.kids)[id]);
-      const int32_t b = D.cb[l][h0 + arr<uint16_t, FAR>(far, L.pos)[id]];
-      const T opp = x[id];
-      const double own = (double)x[arr<uint32_t, FAR>(far, L.up)[id] & 0xFFFFu];
-      for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
-        const int32_t q = b + j;
-        const T v = (T)(own * (double)su[e].a);
-        moved[q] = v;
-        kept[q] = opp;
-        if (l == 5 && bit_of(L.b6, q - q0)) {
-          const int32_t q7 = D.cb[6][q];  // level 6's mover moves on with probability 1
-          D.rb[7][q7] = v;
-          D.ra[7][q7] = opp;
-        }
+  for (int id = threadIdx.x, end = g_nb[7]; id < end; id += BLOCK) {
+    const uint2 w = arr<uint2, FAR>(far, L.kids)[id];
+    const int l = (int)(w.y >> 24) & 7;
+    const Kids n(w);
+    const int b =
+        tab<const int32_t>(P_CB, l)[arr<uint16_t, FAR>(far, L.pos)[id]] - g_lo[l + 1];
+    const GlobalPtr<T> moved = tab<T>((l & 1) == 0 ? P_RA : P_RB, l + 1);
+    const GlobalPtr<T> kept = tab<T>((l & 1) == 0 ? P_RB : P_RA, l + 1);
+    const T opp = x[id];
+    const double own = (double)x[arr<uint32_t, FAR>(far, L.up)[id] & 0xFFFFu];
+    for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
+      const int q = b + j;
+      const T v = (T)(own * (double)su[e].a);
+      moved[q] = v;
+      kept[q] = opp;
+      if (l == 5 && bit_of(L.b6, q)) {
+        // level 6's mover moves on with probability 1
+        const int q7 = tab<const int32_t>(P_CB, 6)[q] - g_lo[7];
+        tab<T>(P_RB, 7)[q7] = v;
+        tab<T>(P_RA, 7)[q7] = opp;
       }
     }
   }
@@ -732,8 +785,8 @@ __device__ __forceinline__ void seg_store_reach(const ItemDesc<T> &D, int j0, un
 // A chain edge's regret after the call's iterations: each adds a regret of
 // zero (the edge is forced) to the discounted one.
 template <class T>
-__device__ __forceinline__ void chain_regret(T *R, double sgn, const IterK *ks, int n_iters,
-                                             int variant) {
+__device__ __forceinline__ void chain_regret(GlobalPtr<T> R, double sgn, const IterK *ks,
+                                             int n_iters, int variant) {
   T v = *R;
   if (v == (T)0 && !signbit((double)v)) return;
   for (int it = 0; it < n_iters; ++it)
@@ -743,51 +796,52 @@ __device__ __forceinline__ void chain_regret(T *R, double sgn, const IterK *ks, 
 
 // The state back into the level arrays.
 template <class T, int BLOCK, bool FAR>
-__device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int j0, int roots,
-                                          unsigned char *far, const SegLds &L, int na, int ne,
-                                          const IterK *ks, int n_iters, int variant) {
+__device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int roots, unsigned char *far,
+                                          const SegLds &L, int na, int ne, const IterK *ks,
+                                          int n_iters, int variant) {
   const Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = arr<Pair<T>, FAR>(far, L.rs);
   const Pair<T> *const chain = arr<Pair<T>, FAR>(far, L.chain);
-  const int e6 = g_sb[6];
-  for (int l = 0; l < 8; ++l) {
-    const int h0 = D.off[l][j0], q0 = D.off[l + 1][j0], end = g_nb[l + 1];
-    for (int id = g_nb[l] + (int)threadIdx.x; id < end; id += BLOCK) {
-      const Kids n(arr<uint2, FAR>(far, L.kids)[id]);
-      const int32_t b = D.cb[l][h0 + arr<uint16_t, FAR>(far, L.pos)[id]];
-      for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
-        const int32_t q = b + j;
-        const Pair<T> p = su[e], r = rs[e];
-        D.sigma[l + 1][q] = p.a;
-        D.R[l + 1][q] = r.a;
-        D.Sbar[l + 1][q] = r.b;
-        if (l < 7) D.u[l + 1][q] = p.b;
-        if (l == 5 && bit_of(L.b6, q - q0)) {
-          const int32_t q7 = D.cb[6][q], q8 = D.cb[7][q7];
-          D.u[7][q7] = p.b;
-          D.Sbar[7][q7] = chain[e - e6].a;
-          D.Sbar[8][q8] = chain[e - e6].b;
-          chain_regret(D.R[7] + q7, 1.0, ks, n_iters, variant);
-          chain_regret(D.R[8] + q8, -1.0, ks, n_iters, variant);
-        } else if (l == 6 && bit_of(L.b7, q - q0)) {
-          const int32_t q8 = D.cb[7][q];
-          D.Sbar[8][q8] = chain[e - e6].a;
-          chain_regret(D.R[8] + q8, -1.0, ks, n_iters, variant);
-        }
+  const int e6 = g_sb[6], lo8 = g_lo[8], lo7 = g_lo[7];
+  for (int id = threadIdx.x; id < na; id += BLOCK) {
+    const uint2 w = arr<uint2, FAR>(far, L.kids)[id];
+    const int l = (int)(w.y >> 24) & 7;
+    const Kids n(w);
+    const int b =
+        tab<const int32_t>(P_CB, l)[arr<uint16_t, FAR>(far, L.pos)[id]] - g_lo[l + 1];
+    const GlobalPtr<T> R = tab<T>(P_R, l + 1), S = tab<T>(P_SBAR, l + 1), sg = tab<T>(P_SIGMA, l + 1);
+    for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
+      const int q = b + j;
+      const Pair<T> p = su[e], r = rs[e];
+      sg[q] = p.a;
+      R[q] = r.a;
+      S[q] = r.b;
+      if (l < 7) tab<T>(P_U, l + 1)[q] = p.b;
+      if (l == 5 && bit_of(L.b6, q)) {
+        const int q7 = tab<const int32_t>(P_CB, 6)[q] - lo7;
+        const int q8 = tab<const int32_t>(P_CB, 7)[q7] - lo8;
+        tab<T>(P_U, 7)[q7] = p.b;
+        tab<T>(P_SBAR, 7)[q7] = chain[e - e6].a;
+        tab<T>(P_SBAR, 8)[q8] = chain[e - e6].b;
+        chain_regret<T>(tab<T>(P_R, 7) + q7, 1.0, ks, n_iters, variant);
+        chain_regret<T>(tab<T>(P_R, 8) + q8, -1.0, ks, n_iters, variant);
+      } else if (l == 6 && bit_of(L.b7, q)) {
+        const int q8 = tab<const int32_t>(P_CB, 7)[q] - lo8;
+        tab<T>(P_SBAR, 8)[q8] = chain[e - e6].a;
+        chain_regret<T>(tab<T>(P_R, 8) + q8, -1.0, ks, n_iters, variant);
       }
     }
   }
   for (int id = threadIdx.x; id < roots; id += BLOCK) {
-    const int64_t j = D.off[0][j0] + arr<uint16_t, FAR>(far, L.pos)[id];
-    D.u[0][j] = su[ne + id].b;
-    D.vacc[j] = lds<double>(L.vacc)[id];
+    const int j = arr<uint16_t, FAR>(far, L.pos)[id];
+    tab<T>(P_U, 0)[j] = su[ne + id].b;
+    D.vacc[g_lo[0] + j] = lds<double>(L.vacc)[id];
   }
 }
 
 // All iterations of one segment in its compact form.  PAPER fixes the paper's
 // variant (DCFR with the regret floor) at compile time.
 template <class T, int BLOCK, bool PAPER, bool FAR>
-__device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
-                                           unsigned char *far, const SegLds &L, int na, int ne,
+__device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsigned char *far, const SegLds &L, int na, int ne,
                                            const IterK *__restrict__ ks, int n_iters, int variant,
                                            int rm_mode, double eps) {
   if (PAPER) {
@@ -821,7 +875,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   const int last_tid = (BLOCK / 64 - 1 - wave) * 64 + lane;
 
   auto value = [&](uint2 w) {
-    const double uh = node_value<T>(su, ne + (j1 - j0), Kids(w));
+    const double uh = node_value<T>(su, ne + roots, Kids(w));
     su[w.y & 0xFFFFu].b = (T)uh;
     return uh;
   };
@@ -835,7 +889,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   c.variant = variant;
   c.rm_mode = rm_mode;
   c.eps = eps;
-  c.zero = ne + (j1 - j0);
+  c.zero = ne + roots;
   c.spare = ne;
   c.chain_spare = __builtin_amdgcn_readfirstlane(g_sb[8]);
   c.exact = exact_quotients<T>(rm_mode, eps);
@@ -936,7 +990,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
       __syncthreads();
     }
     if (it == n_iters - 1) {
-      seg_store_reach<T, BLOCK, FAR>(D, j0, far, L);
+      seg_store_reach<T, BLOCK, FAR>(far, L);
       __syncthreads();
     }
     // the updates below the top levels; wave 0 finishes these levels' utilities
@@ -963,19 +1017,16 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int j0, int j1,
   }
   update_list(top_place, last_tid, n_list_top);
   __syncthreads();
-  seg_store<T, BLOCK, FAR>(D, j0, j1 - j0, far, L, na, ne, ks, n_iters, variant);
+  seg_store<T, BLOCK, FAR>(D, roots, far, L, na, ne, ks, n_iters, variant);
 }
 
 // ---- in global memory ------------------------------------------------------------
-// Global-memory arrays addressed through a per-workgroup pointer table kept
-// in LDS, so that the 72 per-level pointers are not all live in registers.
-__shared__ void *g_ptab[8][9];
-__shared__ int g_lo[9], g_cnt[9];
-
 template <class T, int SLOT>
 struct TabArr {
   int l;
-  __device__ __forceinline__ T &operator[](int i) const { return reinterpret_cast<T *>(g_ptab[SLOT][l])[i]; }
+  __device__ __forceinline__ __attribute__((address_space(1))) T &operator[](int i) const {
+    return tab<T>(SLOT, l)[i];
+  }
 };
 
 // FindUtility for the parents of level L-1, one thread each, over their
@@ -1028,20 +1079,6 @@ __device__ __forceinline__ void seg_in_global(const ItemDesc<T> &D, int j0, int 
     variant = PASUR_DCFR;
     rm_mode = PASUR_RM_FLOOR;
   }
-  if (threadIdx.x < 9) {
-    const int l = threadIdx.x, lo = D.off[l][j0];
-    g_ptab[0][l] = l >= 1 ? (void *)(D.sigma[l] + lo) : nullptr;
-    g_ptab[1][l] = l >= 1 ? (void *)(D.R[l] + lo) : nullptr;
-    g_ptab[2][l] = l >= 1 ? (void *)(D.Sbar[l] + lo) : nullptr;
-    g_ptab[3][l] = (void *)(D.u[l] + lo);
-    g_ptab[4][l] = l <= 7 ? (void *)(D.ra[l] + lo) : nullptr;
-    g_ptab[5][l] = l <= 7 ? (void *)(D.rb[l] + lo) : nullptr;
-    g_ptab[6][l] = l >= 1 ? (void *)(D.parent[l] + lo) : nullptr;
-    g_ptab[7][l] = l <= 7 ? (void *)(D.cb[l] + lo) : nullptr;
-    g_lo[l] = lo;
-    g_cnt[l] = D.off[l][j1] - lo;
-  }
-  __syncthreads();
   double *const vacc = D.vacc + j0;
   for (int it = 0; it < n_iters; ++it) {
     const IterK k = ks[it];
@@ -1096,18 +1133,19 @@ __global__ void __launch_bounds__(BLOCK)
               int rm_mode, double eps, uint32_t lds_bytes) {
   const Seg sg = segs[blockIdx.x];
   const ItemDesc<T> &D = items[sg.item];
+  seg_open(D, sg.j0, sg.j1);
   SegLds L;
   int na = 0, ne = 0;
   if (!FAR || sg.far < 0) {
-    if (seg_load<T, BLOCK, false>(D, sg.j0, sg.j1, lds_bytes, nullptr, 0, L, na, ne)) {
-      seg_in_lds<T, BLOCK, PAPER, false>(D, sg.j0, sg.j1, nullptr, L, na, ne, ks, n_iters, variant,
+    if (seg_load<T, BLOCK, false>(D, lds_bytes, nullptr, 0, L, na, ne)) {
+      seg_in_lds<T, BLOCK, PAPER, false>(D, sg.j1 - sg.j0, nullptr, L, na, ne, ks, n_iters, variant,
                                          rm_mode, eps);
       return;
     }
   } else {
     far += (int64_t)sg.far * kFarUnit;
-    if (seg_load<T, BLOCK, true>(D, sg.j0, sg.j1, lds_bytes, far, (int64_t)sg.far_n * kFarUnit, L, na, ne)) {
-      seg_in_lds<T, BLOCK, PAPER, true>(D, sg.j0, sg.j1, far, L, na, ne, ks, n_iters, variant,
+    if (seg_load<T, BLOCK, true>(D, lds_bytes, far, (int64_t)sg.far_n * kFarUnit, L, na, ne)) {
+      seg_in_lds<T, BLOCK, PAPER, true>(D, sg.j1 - sg.j0, far, L, na, ne, ks, n_iters, variant,
                                         rm_mode, eps);
       return;
     }
