@@ -320,7 +320,7 @@ extern "C" int pasur_cfr_iterate(const pasur_fgt *f, const pasur_cfr_state *st,
                                   : iterate_t<double>(f, st, p, t0, n_iters, s);
   }
   if (p->schedule == PASUR_SCHED_STREAM ||
-      (p->schedule == PASUR_SCHED_AUTO && sweep_pays(f)))
+      (p->schedule == PASUR_SCHED_AUTO && sweep_pays(f, st->dtype, n_iters, s)))
     return sweep_iterate(const_cast<pasur_fgt *>(f), st, p, t0, n_iters, s);
   if (p->schedule == PASUR_SCHED_LEVEL_SYNC)
     return st->dtype == PASUR_F32 ? iterate_t<float>(f, st, p, t0, n_iters, s)

@@ -216,8 +216,8 @@ void sweep_index_free(SweepIndex *x);
 int sweep_iterate(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,
                   int64_t t0, int n_iters, hipStream_t s);
 // Whether the streaming schedule is expected to beat the persistent segment
-// schedule on this round (PASUR_SCHED_AUTO).
-bool sweep_pays(const pasur_fgt *f);
+// schedule on n_iters iterations of this round on stream s (PASUR_SCHED_AUTO).
+bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters, hipStream_t s);
 
 // Iterations t0 .. t0+n_iters-1 of one round with the persistent segment
 // schedule (pasur_seg.hip); n_iters >= 1.  Waits for the stream.

@@ -1267,6 +1267,12 @@ struct SegPlan {
   uint32_t bytes;  // of its compact form in LDS, 0: in global memory
 };
 
+// How many workgroups of such a segment a CU takes, up to 4.
+int per_cu(const SegPlan &sp) {
+  const int n = (int)(kLdsPerWorkgroup / (sp.bytes + kStaticLds));
+  return sp.bytes == 0 || sp.seg.far >= 0 || n < 1 ? 1 : n > 4 ? 4 : n;
+}
+
 // Far arrays of one launch: at most this much (a launch's segments beyond it go
 // to the next launch, which uses the same memory).
 constexpr int64_t kFarBytes = (int64_t)1 << 30;
@@ -1279,10 +1285,6 @@ constexpr int64_t kFarBytes = (int64_t)1 << 30;
 // Gives far arrays their places; returns the bytes these take.
 int64_t plan_launches(pasur_plan *pl, std::vector<SegPlan> &segs, int user_block) {
   constexpr int kCus = 256;
-  auto per_cu = [](const SegPlan &sp) {
-    const int n = (int)(kLdsPerWorkgroup / (sp.bytes + kStaticLds));
-    return sp.bytes == 0 || sp.seg.far >= 0 || n < 1 ? 1 : n > 4 ? 4 : n;
-  };
   int64_t far_max = 0;
   const int n = (int)segs.size();
   pl->launches.clear();
@@ -1415,13 +1417,30 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
     pl->work[2] += f->n[0];
     pl->work[3] += f->n[7];
   }
-  // segments in global memory first, then those with far arrays, then the largest
+  // Segments in global memory first, then those with far arrays, then the
+  // largest: the latter by how many a CU takes, and in buckets of 512 bytes (a
+  // comparison sort of 1e5 segments takes milliseconds).
   auto order = [&]() {
-    auto rank = [](const SegPlan &x) { return x.bytes == 0 ? 0 : x.seg.far >= 0 ? 1 : 2; };
-    std::stable_sort(segs.begin(), segs.end(), [&](const SegPlan &a, const SegPlan &b) {
-      if (rank(a) != rank(b)) return rank(a) < rank(b);
-      return rank(a) == 2 ? a.bytes > b.bytes : a.nodes > b.nodes;
+    std::vector<SegPlan> large, by_bytes(segs.size());
+    constexpr size_t kBuckets = kLdsPerWorkgroup / 512 + 1;
+    auto bucket = [](const SegPlan &sp) {
+      return (size_t)(per_cu(sp) - 1) * kBuckets + (kLdsPerWorkgroup - sp.bytes) / 512;
+    };
+    std::vector<size_t> at(4 * kBuckets + 1, 0);
+    for (const SegPlan &sp : segs) {
+      if (sp.bytes == 0 || sp.seg.far >= 0) large.push_back(sp);
+      else at[bucket(sp) + 1] += 1;
+    }
+    std::stable_sort(large.begin(), large.end(), [](const SegPlan &a, const SegPlan &b) {
+      if ((a.bytes == 0) != (b.bytes == 0)) return a.bytes == 0;
+      return a.nodes > b.nodes;
     });
+    at[0] = large.size();
+    for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+    std::copy(large.begin(), large.end(), by_bytes.begin());
+    for (const SegPlan &sp : segs)
+      if (sp.bytes != 0 && sp.seg.far < 0) by_bytes[at[bucket(sp)]++] = sp;
+    segs.swap(by_bytes);
     return plan_launches(pl, segs, p->block);
   };
   const int64_t far_bytes = order();

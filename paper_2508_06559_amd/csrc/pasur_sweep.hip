@@ -1540,15 +1540,40 @@ int sweep_t(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p, 
 
 }  // namespace
 
-bool sweep_pays(const pasur_fgt *f) {
-  // Measured on whole games (1000 iterations per round, streaming vs
-  // persistent segments): the streaming sweeps pay about 30 launches per
-  // iteration and overtake the segment kernel between 7.7e6 nodes (137 vs
-  // 112 ms, deal 1 round 5) and 9.7e6 (136 vs 146 ms, deal 1 round 6);
-  // 1.1e7: 133 vs 181 ms; 3.5e7: 231 vs 454 ms; 1.1e8: 442 vs 1372 ms.
+bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters, hipStream_t s) {
   int64_t nodes = 0;
   for (int l = 0; l <= 8; ++l) nodes += f->n[l];
-  return nodes >= (int64_t)9 * 1000 * 1000;
+  // Small rounds: each iteration's 30 launches cost more than all of its work
+  // (1.5e6 nodes, 20 iterations: streaming 1.11, segments 0.44 ms).
+  if (nodes < (int64_t)9 * 1000 * 1000) return false;
+  // Huge ones, whose large roots fill the segments' launches unevenly (20
+  // iterations, streaming vs segments: 1.5e8 nodes 17.4 vs 15.7 ms, 6.8e8
+  // 60 vs 82 ms, 1.6e9 252 vs 290 ms).
+  if (nodes >= (int64_t)250 * 1000 * 1000) return true;
+  // A segment is read and written once per call, at the cost of 10 to 15
+  // iterations of the largest rounds; a sweep's set-up is cheaper, its
+  // iteration dearer.  Measured crossovers: 1.0e7 nodes 4 iterations, 1.4e7 5,
+  // 2.9e7 8, 3.5e7 9, 1.1e8 26, 1.2e8 14, 1.5e8 13 (1.2e8 nodes, streaming vs
+  // segments: 8 iterations 5.1 vs 5.8 ms, 20 iterations 10.4 vs 9.1 ms).
+  if (n_iters < 4 + nodes / (12 * 1000 * 1000)) return true;
+  // A segment iterated in global memory is some ten times slower: roots that
+  // don't fit with far arrays must be few.
+  const int64_t cap = dtype == PASUR_F32 ? 30000 : 15000;
+  const int64_t nr = f->n_roots;
+  int64_t beyond = 0;
+  for (int64_t j = 0; j < nr; ++j) {
+    int64_t n = 0;
+    for (int l = 0; l <= 8; ++l) {
+      const int32_t *o = f->h_root_off + (size_t)l * (nr + 1) + j;
+      n += o[1] - o[0];
+    }
+    if (n > cap) beyond += n;
+  }
+  if (beyond > nodes / 100) return true;
+  // making a plan waits for the stream, which a capture does not allow
+  hipStreamCaptureStatus cap_status = hipStreamCaptureStatusNone;
+  (void)hipStreamIsCapturing(s, &cap_status);
+  return cap_status != hipStreamCaptureStatusNone;
 }
 
 int sweep_iterate(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,
