@@ -66,8 +66,11 @@ struct ItemDesc {
 
 struct Seg {
   int32_t item, j0, j1;  // roots j0 .. j1-1 of item
-  int32_t far, far_n;    // place and size of its far arrays in units of kFarUnit; -1: none
+  int32_t far, far_n;    // place and size of its far arrays in units of kFarUnit
+  int32_t form;          // where the compact form's arrays are
 };
+// LDS; "far" arrays in device memory; all arrays there; no compact form.
+enum { F_LDS, F_FAR, F_ALL_FAR, F_NONE };
 constexpr int kFarUnit = 256;
 
 // ---- the compact form ----------------------------------------------------------
@@ -125,7 +128,7 @@ __host__ __device__ inline U align16(U x) {
   return (x + 15u) & ~(U)15u;
 }
 
-__host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t, bool far) {
+__host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t, int form) {
   SegLds L;
   uint32_t p = 0, q = 0;
   auto take = [&p](uint32_t bytes) {
@@ -134,7 +137,7 @@ __host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t, boo
     return at;
   };
   auto take_far = [&](uint32_t bytes) {
-    if (!far) return take(bytes);
+    if (form == F_LDS) return take(bytes);
     const uint32_t at = q;
     q = align16(q + bytes);
     return at;
@@ -143,10 +146,11 @@ __host__ __device__ inline SegLds seg_layout(const SegCounts &c, uint32_t t, boo
   L.b7 = take((uint32_t)((c.c7 + 63) / 64) * 8u);
   L.tmp = p;
   const uint32_t tmp_end = p + kTableBytes + align16(2u * (uint32_t)c.c07);
-  L.su = take(2 * t * (uint32_t)(c.ne + c.roots + 2));
+  auto take_near = [&](uint32_t bytes) { return form == F_ALL_FAR ? take_far(bytes) : take(bytes); };
+  L.su = take_near(2 * t * (uint32_t)(c.ne + c.roots + 2));
   L.rs = take_far(2 * t * (uint32_t)(c.ne + 1));
   L.chain = take_far(2 * t * (uint32_t)(c.ne67 + 1));
-  L.x = take(t * (uint32_t)(c.na + c.roots));
+  L.x = take_near(t * (uint32_t)(c.na + c.roots));
   L.vacc = take(8u * (uint32_t)c.roots);
   if (p < tmp_end) p = tmp_end;
   L.kids = take_far(8u * (uint32_t)c.na);
@@ -174,19 +178,25 @@ __device__ __forceinline__ T *lds(uint32_t off) {
   return reinterpret_cast<T *>(g_lds + off);
 }
 
-// an array that may be far
-template <class T, bool FAR>
+// A far array, and su or x.
+template <class T, int FORM>
 __device__ __forceinline__ T *arr(unsigned char *far, uint32_t off) {
-  return FAR ? reinterpret_cast<T *>(far + off) : lds<T>(off);
+  return FORM != F_LDS ? reinterpret_cast<T *>(far + off) : lds<T>(off);
+}
+template <class T, int FORM>
+__device__ __forceinline__ T *near(unsigned char *far, uint32_t off) {
+  return FORM == F_ALL_FAR ? reinterpret_cast<T *>(far + off) : lds<T>(off);
 }
 
 __device__ __forceinline__ bool bit_of(uint32_t off, int i) {
   return (lds<uint32_t>(off)[i >> 5] >> (i & 31)) & 1u;
 }
 
-// LDS accesses of a wave run in order: between steps that one wave runs by
-// itself only the compiler has to keep them so.
+// Between steps that one wave runs by itself: LDS accesses of a wave run in
+// order, and only the compiler has to keep them so.
+template <int FORM>
 __device__ __forceinline__ void wave_order() {
+  if (FORM == F_ALL_FAR) __threadfence_block();
   asm volatile("" ::: "memory");
   __builtin_amdgcn_wave_barrier();
 }
@@ -214,10 +224,10 @@ __device__ __forceinline__ int top_levels() {
 // two neighbouring waves are then filled with more than 64 edges between them:
 // kTopEdges edges take at most kList places.  Nodes past the list's end stay with
 // update_many.  For one wave; before it, the list is kNoEdge.
-template <bool FAR>
+template <int FORM>
 __device__ __forceinline__ void list_build(unsigned char *far, const SegLds &L) {
   const int lane = threadIdx.x & 63;
-  uint2 *const w_kids = arr<uint2, FAR>(far, L.kids);
+  uint2 *const w_kids = arr<uint2, FORM>(far, L.kids);
   uint32_t *const list = lds<uint32_t>(L.list);
   const int top = top_levels();
   int at = 0;
@@ -295,7 +305,7 @@ __device__ __forceinline__ void seg_open(const ItemDesc<T> &D, int j0, int j1) {
 // Every pass runs over the nodes of all levels at once: what it waits for is
 // memory latency, and level by level it did so eight times (loading and storing
 // a segment of 3,900 nodes took as long as 12 iterations).
-template <class T, int BLOCK, bool FAR>
+template <class T, int BLOCK, int FORM>
 __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_bytes,
                                          unsigned char *far, int64_t far_bytes, SegLds &L, int &na,
                                          int &ne) {
@@ -319,7 +329,7 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
   c.c7 = at[8] - at[7];
   // where bits, tables and the map go does not depend on the other counts
   c.na = c.ne = c.ne67 = 0;
-  L = seg_layout(c, sizeof(T), FAR);
+  L = seg_layout(c, sizeof(T), FORM);
   if (L.bytes > lds_bytes) return false;
   uint32_t *const count = lds<uint32_t>(L.tmp);  // per level and class: nodes
   uint32_t *const next = count + 8 * kClasses;   // next rank within the level
@@ -400,7 +410,7 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
   }
   na = c.na;
   ne = c.ne;
-  L = seg_layout(c, sizeof(T), FAR);
+  L = seg_layout(c, sizeof(T), FORM);
   if (L.bytes > lds_bytes || L.far > far_bytes || !seg_indices_fit(c)) return false;
   if (tid == 0) {
     int a = 0, e = 0;
@@ -414,9 +424,9 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
     g_sb[9] = e;
   }
   __syncthreads();
-  uint2 *const w_kids = arr<uint2, FAR>(far, L.kids);
-  uint32_t *const w_up = arr<uint32_t, FAR>(far, L.up);
-  uint16_t *const w_pos = arr<uint16_t, FAR>(far, L.pos);
+  uint2 *const w_kids = arr<uint2, FORM>(far, L.kids);
+  uint32_t *const w_up = arr<uint32_t, FORM>(far, L.up);
+  uint16_t *const w_pos = arr<uint16_t, FORM>(far, L.pos);
   // every active node's place and its children's slots
   for (int i = tid; i < c.c07; i += BLOCK) {
     const uint32_t k = map[i];
@@ -455,8 +465,8 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
     reinterpret_cast<uint16_t *>(w_up + id)[1] =
         *reinterpret_cast<const uint16_t *>(w_up + *reinterpret_cast<const uint16_t *>(w_up + id));
   // the state; from here on the edge arrays take the tables' place
-  Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = arr<Pair<T>, FAR>(far, L.rs);
-  Pair<T> *const chain = arr<Pair<T>, FAR>(far, L.chain);
+  Pair<T> *const su = near<Pair<T>, FORM>(far, L.su), *const rs = arr<Pair<T>, FORM>(far, L.rs);
+  Pair<T> *const chain = arr<Pair<T>, FORM>(far, L.chain);
   const int e6 = g_sb[6], lo8 = g_lo[8], lo7 = g_lo[7];
   for (int id = tid; id < na; id += BLOCK) {
     const uint2 w = w_kids[id];
@@ -496,11 +506,11 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
   if (tid == 0) su[c.ne + c.roots] = Pair<T>{(T)0, (T)0};
   for (int i = tid; i < kList; i += BLOCK) lds<uint32_t>(L.list)[i] = kNoEdge;
   __syncthreads();
-  if (wave == 0) list_build<FAR>(far, L);
+  if (wave == 0) list_build<FORM>(far, L);
   for (int id = tid; id < c.roots; id += BLOCK) {
     const int j = w_pos[id];
-    lds<T>(L.x)[id] = tab<const T>(P_RB, 0)[j];
-    lds<T>(L.x)[c.na + id] = tab<const T>(P_RA, 0)[j];
+    near<T, FORM>(far, L.x)[id] = tab<const T>(P_RB, 0)[j];
+    near<T, FORM>(far, L.x)[c.na + id] = tab<const T>(P_RA, 0)[j];
     lds<double>(L.vacc)[id] = D.vacc[g_lo[0] + j];
   }
   __syncthreads();
@@ -753,20 +763,20 @@ __device__ __forceinline__ void update_many(const Update<T> &c, const Kids &n, d
 
 // Reach arrays of the segment's nodes below the roots, as the last iteration's
 // way down leaves them (before its updates).
-template <class T, int BLOCK, bool FAR>
+template <class T, int BLOCK, int FORM>
 __device__ __forceinline__ void seg_store_reach(unsigned char *far, const SegLds &L) {
-  const Pair<T> *const su = lds<Pair<T>>(L.su);
-  const T *const x = lds<T>(L.x);
+  const Pair<T> *const su = near<Pair<T>, FORM>(far, L.su);
+  const T *const x = near<T, FORM>(far, L.x);
   for (int id = threadIdx.x, end = g_nb[7]; id < end; id += BLOCK) {
-    const uint2 w = arr<uint2, FAR>(far, L.kids)[id];
+    const uint2 w = arr<uint2, FORM>(far, L.kids)[id];
     const int l = (int)(w.y >> 24) & 7;
     const Kids n(w);
     const int b =
-        tab<const int32_t>(P_CB, l)[arr<uint16_t, FAR>(far, L.pos)[id]] - g_lo[l + 1];
+        tab<const int32_t>(P_CB, l)[arr<uint16_t, FORM>(far, L.pos)[id]] - g_lo[l + 1];
     const GlobalPtr<T> moved = tab<T>((l & 1) == 0 ? P_RA : P_RB, l + 1);
     const GlobalPtr<T> kept = tab<T>((l & 1) == 0 ? P_RB : P_RA, l + 1);
     const T opp = x[id];
-    const double own = (double)x[arr<uint32_t, FAR>(far, L.up)[id] & 0xFFFFu];
+    const double own = (double)x[arr<uint32_t, FORM>(far, L.up)[id] & 0xFFFFu];
     for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
       const int q = b + j;
       const T v = (T)(own * (double)su[e].a);
@@ -795,19 +805,19 @@ __device__ __forceinline__ void chain_regret(GlobalPtr<T> R, double sgn, const I
 }
 
 // The state back into the level arrays.
-template <class T, int BLOCK, bool FAR>
+template <class T, int BLOCK, int FORM>
 __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int roots, unsigned char *far,
                                           const SegLds &L, int na, int ne, const IterK *ks,
                                           int n_iters, int variant) {
-  const Pair<T> *const su = lds<Pair<T>>(L.su), *const rs = arr<Pair<T>, FAR>(far, L.rs);
-  const Pair<T> *const chain = arr<Pair<T>, FAR>(far, L.chain);
+  const Pair<T> *const su = near<Pair<T>, FORM>(far, L.su), *const rs = arr<Pair<T>, FORM>(far, L.rs);
+  const Pair<T> *const chain = arr<Pair<T>, FORM>(far, L.chain);
   const int e6 = g_sb[6], lo8 = g_lo[8], lo7 = g_lo[7];
   for (int id = threadIdx.x; id < na; id += BLOCK) {
-    const uint2 w = arr<uint2, FAR>(far, L.kids)[id];
+    const uint2 w = arr<uint2, FORM>(far, L.kids)[id];
     const int l = (int)(w.y >> 24) & 7;
     const Kids n(w);
     const int b =
-        tab<const int32_t>(P_CB, l)[arr<uint16_t, FAR>(far, L.pos)[id]] - g_lo[l + 1];
+        tab<const int32_t>(P_CB, l)[arr<uint16_t, FORM>(far, L.pos)[id]] - g_lo[l + 1];
     const GlobalPtr<T> R = tab<T>(P_R, l + 1), S = tab<T>(P_SBAR, l + 1), sg = tab<T>(P_SIGMA, l + 1);
     for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
       const int q = b + j;
@@ -832,7 +842,7 @@ __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int roots, unsig
     }
   }
   for (int id = threadIdx.x; id < roots; id += BLOCK) {
-    const int j = arr<uint16_t, FAR>(far, L.pos)[id];
+    const int j = arr<uint16_t, FORM>(far, L.pos)[id];
     tab<T>(P_U, 0)[j] = su[ne + id].b;
     D.vacc[g_lo[0] + j] = lds<double>(L.vacc)[id];
   }
@@ -840,8 +850,8 @@ __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int roots, unsig
 
 // All iterations of one segment in its compact form.  PAPER fixes the paper's
 // variant (DCFR with the regret floor) at compile time.
-template <class T, int BLOCK, bool PAPER, bool FAR>
-__device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsigned char *far, const SegLds &L, int na, int ne,
+template <class T, int BLOCK, bool PAPER, int FORM>
+__device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, unsigned char *far, const SegLds &L, int na, int ne,
                                            const IterK *__restrict__ ks, int n_iters, int variant,
                                            int rm_mode, double eps) {
   if (PAPER) {
@@ -849,11 +859,11 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsi
     rm_mode = PASUR_RM_FLOOR;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  Pair<T> *const su = lds<Pair<T>>(L.su);
-  T *const x = lds<T>(L.x);
+  Pair<T> *const su = near<Pair<T>, FORM>(far, L.su);
+  T *const x = near<T, FORM>(far, L.x);
   double *const vacc = lds<double>(L.vacc);
-  const uint2 *const w_kids = arr<uint2, FAR>(far, L.kids);
-  const uint32_t *const w_up = arr<uint32_t, FAR>(far, L.up);
+  const uint2 *const w_kids = arr<uint2, FORM>(far, L.kids);
+  const uint32_t *const w_up = arr<uint32_t, FORM>(far, L.up);
   const uint32_t *const list = lds<uint32_t>(L.list);
   const int n_list_top = __builtin_amdgcn_readfirstlane(g_list_top);
   const int n_list = __builtin_amdgcn_readfirstlane(g_list_end);
@@ -884,8 +894,8 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsi
   };
   Update<T> c;
   c.su = su;
-  c.rs = arr<Pair<T>, FAR>(far, L.rs);
-  c.chain = arr<Pair<T>, FAR>(far, L.chain) - g_sb[6];
+  c.rs = arr<Pair<T>, FORM>(far, L.rs);
+  c.chain = arr<Pair<T>, FORM>(far, L.chain) - g_sb[6];
   c.variant = variant;
   c.rm_mode = rm_mode;
   c.eps = eps;
@@ -967,7 +977,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsi
         for (int l = 1; l < top; l += 2) {
           if (lane >= nb(l) && lane < nb(l + 2 < top ? l + 2 : top))
             down(lane, top_kids.y, top_up);
-          wave_order();
+          wave_order<FORM>();
         }
       }
       if (ul >= top) {
@@ -990,7 +1000,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsi
       __syncthreads();
     }
     if (it == n_iters - 1) {
-      seg_store_reach<T, BLOCK, FAR>(far, L);
+      seg_store_reach<T, BLOCK, FORM>(far, L);
       __syncthreads();
     }
     // the updates below the top levels; wave 0 finishes these levels' utilities
@@ -1005,7 +1015,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsi
           const double uh = value(top_kids);
           if (l == 0) vacc[lane] += uh;
         }
-        wave_order();
+        wave_order<FORM>();
       }
     }
     update_list(place(n_list_top + last_tid), n_list_top + last_tid, n_list);
@@ -1017,7 +1027,7 @@ __device__ __forceinline__ void seg_in_lds(const ItemDesc<T> &D, int roots, unsi
   }
   update_list(top_place, last_tid, n_list_top);
   __syncthreads();
-  seg_store<T, BLOCK, FAR>(D, roots, far, L, na, ne, ks, n_iters, variant);
+  seg_store<T, BLOCK, FORM>(D, roots, far, L, na, ne, ks, n_iters, variant);
 }
 
 // ---- in global memory ------------------------------------------------------------
@@ -1136,17 +1146,25 @@ __global__ void __launch_bounds__(BLOCK)
   seg_open(D, sg.j0, sg.j1);
   SegLds L;
   int na = 0, ne = 0;
-  if (!FAR || sg.far < 0) {
-    if (seg_load<T, BLOCK, false>(D, lds_bytes, nullptr, 0, L, na, ne)) {
-      seg_in_lds<T, BLOCK, PAPER, false>(D, sg.j1 - sg.j0, nullptr, L, na, ne, ks, n_iters, variant,
-                                         rm_mode, eps);
+  const int roots = sg.j1 - sg.j0;
+  if (sg.form == F_LDS) {
+    if (seg_load<T, BLOCK, F_LDS>(D, lds_bytes, nullptr, 0, L, na, ne)) {
+      seg_iterations<T, BLOCK, PAPER, F_LDS>(D, roots, nullptr, L, na, ne, ks, n_iters, variant,
+                                             rm_mode, eps);
       return;
     }
-  } else {
+  } else if (FAR && sg.form != F_NONE) {
     far += (int64_t)sg.far * kFarUnit;
-    if (seg_load<T, BLOCK, true>(D, lds_bytes, far, (int64_t)sg.far_n * kFarUnit, L, na, ne)) {
-      seg_in_lds<T, BLOCK, PAPER, true>(D, sg.j1 - sg.j0, far, L, na, ne, ks, n_iters, variant,
-                                        rm_mode, eps);
+    const int64_t far_bytes = (int64_t)sg.far_n * kFarUnit;
+    if (sg.form == F_FAR) {
+      if (seg_load<T, BLOCK, F_FAR>(D, lds_bytes, far, far_bytes, L, na, ne)) {
+        seg_iterations<T, BLOCK, PAPER, F_FAR>(D, roots, far, L, na, ne, ks, n_iters, variant,
+                                               rm_mode, eps);
+        return;
+      }
+    } else if (seg_load<T, BLOCK, F_ALL_FAR>(D, lds_bytes, far, far_bytes, L, na, ne)) {
+      seg_iterations<T, BLOCK, PAPER, F_ALL_FAR>(D, roots, far, L, na, ne, ks, n_iters, variant,
+                                                 rm_mode, eps);
       return;
     }
   }
@@ -1270,7 +1288,7 @@ struct SegPlan {
 // How many workgroups of such a segment a CU takes, up to 4.
 int per_cu(const SegPlan &sp) {
   const int n = (int)(kLdsPerWorkgroup / (sp.bytes + kStaticLds));
-  return sp.bytes == 0 || sp.seg.far >= 0 || n < 1 ? 1 : n > 4 ? 4 : n;
+  return sp.seg.form != F_LDS || n < 1 ? 1 : n > 4 ? 4 : n;
 }
 
 // Far arrays of one launch: at most this much (a launch's segments beyond it go
@@ -1300,7 +1318,7 @@ int64_t plan_launches(pasur_plan *pl, std::vector<SegPlan> &segs, int user_block
         if (n - j >= kCus) break;
         rest = true;
       }
-      if (sp.seg.far >= 0) {
+      if (sp.seg.far_n > 0) {
         const int64_t need = (int64_t)sp.seg.far_n * kFarUnit;
         if (far > 0 && far + need > kFarBytes) break;
         sp.seg.far = (int32_t)(far / kFarUnit);
@@ -1371,9 +1389,9 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
       c.c7 += n[7];
       tot += c07 + n[8];
     };
-    auto bytes_of = [&](const SegCounts &c, bool far) -> uint32_t {
+    auto bytes_of = [&](const SegCounts &c, int form) -> uint32_t {
       if (c.c6 > 65535 || c.c7 > 65535 || !seg_indices_fit(c)) return 0u;
-      const uint32_t b = seg_layout(c, sizeof(T), far).bytes;
+      const uint32_t b = seg_layout(c, sizeof(T), form).bytes;
       return b <= budget ? b : 0u;
     };
     int64_t j0 = 0;
@@ -1381,12 +1399,12 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
       int64_t j1 = j0 + 1, tot = 0;
       SegCounts c = {};
       add_root(c, tot, j0);
-      uint32_t bytes = bytes_of(c, false);
+      uint32_t bytes = bytes_of(c, F_LDS);
       while (p->seg_nodes > 0 && bytes && j1 < nr && j1 - j0 < pl->block) {
         SegCounts c2 = c;
         int64_t t2 = tot;
         add_root(c2, t2, j1);
-        const uint32_t b2 = bytes_of(c2, false);
+        const uint32_t b2 = bytes_of(c2, F_LDS);
         if (t2 > p->seg_nodes || !b2) break;
         ++j1;
         c = c2;
@@ -1398,15 +1416,14 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
       sp.seg.item = it;
       sp.seg.j0 = (int32_t)j0;
       sp.seg.j1 = (int32_t)j1;
-      sp.seg.far = -1;
-      sp.seg.far_n = 0;
-      if (!bytes) {  // (a single root)
-        bytes = bytes_of(c, true);
-        if (bytes) {
-          sp.seg.far = 0;
-          sp.seg.far_n = (int32_t)((seg_layout(c, sizeof(T), true).far + kFarUnit - 1) / kFarUnit);
-        }
-      }
+      sp.seg.far = sp.seg.far_n = 0;
+      sp.seg.form = F_LDS;
+      while (!bytes && sp.seg.form != F_NONE && !force_global)  // (a single root)
+        if (++sp.seg.form != F_NONE) bytes = bytes_of(c, sp.seg.form);
+      if (!bytes) sp.seg.form = F_NONE;
+      else if (sp.seg.form != F_LDS)
+        sp.seg.far_n =
+            (int32_t)((seg_layout(c, sizeof(T), sp.seg.form).far + kFarUnit - 1) / kFarUnit);
       sp.nodes = tot;
       sp.bytes = bytes;
       segs.push_back(sp);
@@ -1428,18 +1445,17 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
     };
     std::vector<size_t> at(4 * kBuckets + 1, 0);
     for (const SegPlan &sp : segs) {
-      if (sp.bytes == 0 || sp.seg.far >= 0) large.push_back(sp);
+      if (sp.seg.form != F_LDS) large.push_back(sp);
       else at[bucket(sp) + 1] += 1;
     }
     std::stable_sort(large.begin(), large.end(), [](const SegPlan &a, const SegPlan &b) {
-      if ((a.bytes == 0) != (b.bytes == 0)) return a.bytes == 0;
-      return a.nodes > b.nodes;
+      return a.seg.form != b.seg.form ? a.seg.form > b.seg.form : a.nodes > b.nodes;
     });
     at[0] = large.size();
     for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
     std::copy(large.begin(), large.end(), by_bytes.begin());
     for (const SegPlan &sp : segs)
-      if (sp.bytes != 0 && sp.seg.far < 0) by_bytes[at[bucket(sp)]++] = sp;
+      if (sp.seg.form == F_LDS) by_bytes[at[bucket(sp)]++] = sp;
     segs.swap(by_bytes);
     return plan_launches(pl, segs, p->block);
   };
@@ -1448,8 +1464,9 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
     // no memory for far arrays: in global memory
     pl->far = nullptr;
     for (SegPlan &sp : segs)
-      if (sp.seg.far >= 0) {
-        sp.seg.far = -1;
+      if (sp.seg.far_n > 0) {
+        sp.seg.far_n = 0;
+        sp.seg.form = F_NONE;
         sp.bytes = 0;
       }
     order();
