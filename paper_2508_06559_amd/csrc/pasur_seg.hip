@@ -356,15 +356,28 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
     const int n = l == 7 ? c.c7 : c.c6, lo = g_lo[l + 1];
     const GlobalPtr<const int32_t> cb = tab<const int32_t>(P_CB, l);
     const GlobalPtr<const T> sg = tab<const T>(P_SIGMA, l + 1);
-    for (int i = tid; i < ((n + 63) & ~63); i += BLOCK) {
-      bool p = false;
-      if (i < n) {
-        const int32_t q = cb[i] - lo;
-        p = cb[i + 1] - lo - q == 1 && (double)sg[q] == 1.0;
-        if (p) p = l == 7 ? isfinite((double)tab<const T>(P_U, 8)[q]) : bit_of(L.b7, q);
+    for (int i0 = tid; i0 < ((n + 63) & ~63); i0 += 4 * BLOCK) {
+      int q[4];
+      T s1[4];
+      bool p[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int i = i0 + m * BLOCK < n ? i0 + m * BLOCK : n - 1;
+        q[m] = cb[i] - lo;
+        p[m] = cb[i + 1] - lo - q[m] == 1;
       }
-      const unsigned long long m = __ballot(p);
-      if (lane == 0) lds<unsigned long long>(l == 7 ? L.b7 : L.b6)[i >> 6] = m;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {  // (a node without children: any place will do)
+        s1[m] = sg[p[m] ? q[m] : 0];
+        if (l == 7) p[m] = p[m] && isfinite((double)tab<const T>(P_U, 8)[p[m] ? q[m] : 0]);
+        else p[m] = p[m] && bit_of(L.b7, q[m]);
+      }
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int i = i0 + m * BLOCK;
+        const unsigned long long w = __ballot(i < n && p[m] && (double)s1[m] == 1.0);
+        if (lane == 0 && i < n) lds<unsigned long long>(l == 7 ? L.b7 : L.b6)[i >> 6] = w;
+      }
     }
     __syncthreads();
   }
@@ -476,31 +489,49 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
                              sg = tab<const T>(P_SIGMA, l + 1);
     const int step = (int)(w.x >> 16);
     int e = (int)(w.x & 0xFFFFu);
-#pragma unroll 2
-    for (int j = 0; j < k; ++j, e += step) {
-      const int q = b + j;
-      const T r = R[q], sb = S[q], s0 = sg[q];
-      T v = (T)0, a1 = (T)0, a2 = (T)0;
-      if (l == 7) {
-        v = tab<const T>(P_U, 8)[q];
-      } else if (l == 6) {
-        if (bit_of(L.b7, q)) {
-          const int q8 = tab<const int32_t>(P_CB, 7)[q] - lo8;
-          v = (T)(0.0 + (double)tab<const T>(P_U, 8)[q8]);
-          a1 = tab<const T>(P_SBAR, 8)[q8];
-        }
-      } else if (l == 5) {
-        if (bit_of(L.b6, q)) {
-          const int q7 = tab<const int32_t>(P_CB, 6)[q] - lo7;
-          const int q8 = tab<const int32_t>(P_CB, 7)[q7] - lo8;
-          v = (T)(0.0 + (double)tab<const T>(P_U, 8)[q8]);
-          a1 = tab<const T>(P_SBAR, 7)[q7];
-          a2 = tab<const T>(P_SBAR, 8)[q8];
-        }
+    for (int j = 0; j < k; j += 2, e += 2 * step) {  // two children at a time
+      int q[2], q7[2], q8[2];
+      T r[2], sb[2], s0[2], v[2], a1[2], a2[2];
+      bool p[2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        q[m] = b + (j + m < k ? j + m : j);
+        r[m] = R[q[m]];
+        sb[m] = S[q[m]];
+        s0[m] = sg[q[m]];
+        p[m] = l == 5 ? bit_of(L.b6, q[m]) : l == 6 ? bit_of(L.b7, q[m]) : false;
+        q7[m] = q8[m] = q[m];
+        v[m] = a1[m] = a2[m] = (T)0;
       }
-      rs[e] = Pair<T>{r, sb};
-      su[e] = Pair<T>{s0, v};
-      if (l == 5 || l == 6) chain[e - e6] = Pair<T>{a1, a2};
+      if (l == 5) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          if (p[m]) q7[m] = tab<const int32_t>(P_CB, 6)[q[m]] - lo7;
+      }
+      if (l == 5 || l == 6) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          if (p[m]) q8[m] = tab<const int32_t>(P_CB, 7)[q7[m]] - lo8;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          if (p[m]) {
+            v[m] = (T)(0.0 + (double)tab<const T>(P_U, 8)[q8[m]]);
+            a1[m] = l == 5 ? tab<const T>(P_SBAR, 7)[q7[m]] : tab<const T>(P_SBAR, 8)[q8[m]];
+            if (l == 5) a2[m] = tab<const T>(P_SBAR, 8)[q8[m]];
+          }
+      }
+      if (l == 7) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) v[m] = tab<const T>(P_U, 8)[q[m]];
+      }
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        if (j + m >= k) break;
+        const int em = e + m * step;
+        rs[em] = Pair<T>{r[m], sb[m]};
+        su[em] = Pair<T>{s0[m], v[m]};
+        if (l == 5 || l == 6) chain[em - e6] = Pair<T>{a1[m], a2[m]};
+      }
     }
   }
   if (tid == 0) su[c.ne + c.roots] = Pair<T>{(T)0, (T)0};
@@ -793,15 +824,14 @@ __device__ __forceinline__ void seg_store_reach(unsigned char *far, const SegLds
 }
 
 // A chain edge's regret after the call's iterations: each adds a regret of
-// zero (the edge is forced) to the discounted one.
+// zero (the edge is forced) to the discounted one.  False: it stays.
 template <class T>
-__device__ __forceinline__ void chain_regret(GlobalPtr<T> R, double sgn, const IterK *ks,
-                                             int n_iters, int variant) {
-  T v = *R;
-  if (v == (T)0 && !signbit((double)v)) return;
+__device__ __forceinline__ bool chain_regret(T &v, double sgn, const IterK *ks, int n_iters,
+                                             int variant) {
+  if (v == (T)0 && !signbit((double)v)) return false;
   for (int it = 0; it < n_iters; ++it)
     v = (T)next_regret((double)v, sgn * 0.0, ks[it], variant);
-  *R = v;
+  return true;
 }
 
 // The state back into the level arrays.
@@ -819,25 +849,51 @@ __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int roots, unsig
     const int b =
         tab<const int32_t>(P_CB, l)[arr<uint16_t, FORM>(far, L.pos)[id]] - g_lo[l + 1];
     const GlobalPtr<T> R = tab<T>(P_R, l + 1), S = tab<T>(P_SBAR, l + 1), sg = tab<T>(P_SIGMA, l + 1);
-    for (int j = 0, e = n.e; j < n.k; ++j, e += n.step) {
-      const int q = b + j;
-      const Pair<T> p = su[e], r = rs[e];
-      sg[q] = p.a;
-      R[q] = r.a;
-      S[q] = r.b;
-      if (l < 7) tab<T>(P_U, l + 1)[q] = p.b;
-      if (l == 5 && bit_of(L.b6, q)) {
-        const int q7 = tab<const int32_t>(P_CB, 6)[q] - lo7;
-        const int q8 = tab<const int32_t>(P_CB, 7)[q7] - lo8;
-        tab<T>(P_U, 7)[q7] = p.b;
-        tab<T>(P_SBAR, 7)[q7] = chain[e - e6].a;
-        tab<T>(P_SBAR, 8)[q8] = chain[e - e6].b;
-        chain_regret<T>(tab<T>(P_R, 7) + q7, 1.0, ks, n_iters, variant);
-        chain_regret<T>(tab<T>(P_R, 8) + q8, -1.0, ks, n_iters, variant);
-      } else if (l == 6 && bit_of(L.b7, q)) {
-        const int q8 = tab<const int32_t>(P_CB, 7)[q] - lo8;
-        tab<T>(P_SBAR, 8)[q8] = chain[e - e6].a;
-        chain_regret<T>(tab<T>(P_R, 8) + q8, -1.0, ks, n_iters, variant);
+    for (int j = 0, e = n.e; j < n.k; j += 2, e += 2 * n.step) {  // two children at a time
+      int q[2], q7[2], q8[2];
+      T r7[2], r8[2];
+      bool p[2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        q[m] = b + (j + m < n.k ? j + m : j);
+        p[m] = j + m < n.k && (l == 5 ? bit_of(L.b6, q[m]) : l == 6 ? bit_of(L.b7, q[m]) : false);
+        q7[m] = q8[m] = q[m];
+        r7[m] = r8[m] = (T)0;
+      }
+      if (l == 5) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          if (p[m]) q7[m] = tab<const int32_t>(P_CB, 6)[q[m]] - lo7;
+      }
+      if (l == 5 || l == 6) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          if (p[m]) q8[m] = tab<const int32_t>(P_CB, 7)[q7[m]] - lo8;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          if (p[m]) {
+            r8[m] = tab<T>(P_R, 8)[q8[m]];
+            if (l == 5) r7[m] = tab<T>(P_R, 7)[q7[m]];
+          }
+      }
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        if (j + m >= n.k) break;
+        const int em = e + m * n.step;
+        const Pair<T> s2 = su[em], r = rs[em];
+        sg[q[m]] = s2.a;
+        R[q[m]] = r.a;
+        S[q[m]] = r.b;
+        if (l < 7) tab<T>(P_U, l + 1)[q[m]] = s2.b;
+        if (!p[m]) continue;
+        const Pair<T> ch = chain[em - e6];
+        if (l == 5) {
+          tab<T>(P_U, 7)[q7[m]] = s2.b;
+          tab<T>(P_SBAR, 7)[q7[m]] = ch.a;
+          if (chain_regret<T>(r7[m], 1.0, ks, n_iters, variant)) tab<T>(P_R, 7)[q7[m]] = r7[m];
+        }
+        tab<T>(P_SBAR, 8)[q8[m]] = l == 5 ? ch.b : ch.a;
+        if (chain_regret<T>(r8[m], -1.0, ks, n_iters, variant)) tab<T>(P_R, 8)[q8[m]] = r8[m];
       }
     }
   }
