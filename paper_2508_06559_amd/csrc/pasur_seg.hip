@@ -382,16 +382,27 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
     __syncthreads();
   }
   // the active nodes' classes; the map holds their numbers of children for now
-  for (int i = tid; i < c.c07; i += BLOCK) {
-    const int l = level_of(i), j = i - above(l);
-    uint32_t k = kPassive;
-    if (l < 6 || !bit_of(l == 6 ? L.b6 : L.b7, j)) {
-      const GlobalPtr<const int32_t> cb = tab<const int32_t>(P_CB, l);
-      k = (uint32_t)(cb[j + 1] - cb[j]);
-      if (k < (uint32_t)kClasses) atomicAdd(&count[l * kClasses + k], 1u);
+  for (int i0 = tid; i0 < c.c07; i0 += 4 * BLOCK) {
+    int l[4];
+    uint32_t k[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int i = i0 + m * BLOCK < c.c07 ? i0 + m * BLOCK : i0;
+      l[m] = level_of(i);
+      const int j = i - above(l[m]);
+      const GlobalPtr<const int32_t> cb = tab<const int32_t>(P_CB, l[m]);
+      k[m] = (uint32_t)(cb[j + 1] - cb[j]);
+      if (l[m] >= 6 && bit_of(l[m] == 6 ? L.b6 : L.b7, j)) l[m] = 8;
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int i = i0 + m * BLOCK;
+      if (i >= c.c07) break;
+      map[i] = (uint16_t)(l[m] < 8 ? k[m] : kPassive);
+      if (l[m] == 8) continue;
+      if (k[m] < (uint32_t)kClasses) atomicAdd(&count[l[m] * kClasses + k[m]], 1u);
       else g_bad = 1;
     }
-    map[i] = (uint16_t)k;
   }
   __syncthreads();
   if (g_bad) return false;
@@ -455,21 +466,32 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
   }
   __syncthreads();
   // own slots and parents, written by the parents: low halves of the words
-  for (int id = tid; id < na; id += BLOCK) {
-    const uint2 w = w_kids[id];
-    const int l = (int)(w.y >> 24) & 7, k = (int)(w.y >> 16) & 0xFF;
-    if (l == 0) {
-      *reinterpret_cast<uint16_t *>(&w_kids[id].y) = (uint16_t)(c.ne + id);
-      w_up[id] = (uint32_t)(c.na + id);
+  for (int id0 = tid; id0 < na; id0 += 2 * BLOCK) {
+    uint2 w[2];
+    int l[2], q[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int id = id0 + m * BLOCK < na ? id0 + m * BLOCK : id0;
+      w[m] = w_kids[id];
+      l[m] = (int)(w[m].y >> 24) & 7;
+      q[m] = tab<const int32_t>(P_CB, l[m])[w_pos[id]] - g_lo[l[m] + 1] + above(l[m] + 1);
     }
-    if (l == 7) continue;
-    const int q = tab<const int32_t>(P_CB, l)[w_pos[id]] - g_lo[l + 1] + above(l + 1);
-    uint32_t e = w.x & 0xFFFFu;
-    for (int j = 0; j < k; ++j, e += w.x >> 16) {
-      const uint32_t child = map[q + j];
-      if (child == kPassive) continue;
-      *reinterpret_cast<uint16_t *>(&w_kids[child].y) = (uint16_t)e;
-      w_up[child] = (uint32_t)id;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int id = id0 + m * BLOCK, k = (int)(w[m].y >> 16) & 0xFF;
+      if (id >= na) break;
+      if (l[m] == 0) {
+        *reinterpret_cast<uint16_t *>(&w_kids[id].y) = (uint16_t)(c.ne + id);
+        w_up[id] = (uint32_t)(c.na + id);
+      }
+      if (l[m] == 7) continue;
+      uint32_t e = w[m].x & 0xFFFFu;
+      for (int j = 0; j < k; ++j, e += w[m].x >> 16) {
+        const uint32_t child = map[q[m] + j];
+        if (child == kPassive) continue;
+        *reinterpret_cast<uint16_t *>(&w_kids[child].y) = (uint16_t)e;
+        w_up[child] = (uint32_t)id;
+      }
     }
   }
   __syncthreads();
@@ -481,56 +503,58 @@ __device__ __forceinline__ bool seg_load(const ItemDesc<T> &D, uint32_t lds_byte
   Pair<T> *const su = near<Pair<T>, FORM>(far, L.su), *const rs = arr<Pair<T>, FORM>(far, L.rs);
   Pair<T> *const chain = arr<Pair<T>, FORM>(far, L.chain);
   const int e6 = g_sb[6], lo8 = g_lo[8], lo7 = g_lo[7];
-  for (int id = tid; id < na; id += BLOCK) {
-    const uint2 w = w_kids[id];
-    const int l = (int)(w.y >> 24) & 7, k = (int)(w.y >> 16) & 0xFF;
-    const int b = tab<const int32_t>(P_CB, l)[w_pos[id]] - g_lo[l + 1];
-    const GlobalPtr<const T> R = tab<const T>(P_R, l + 1), S = tab<const T>(P_SBAR, l + 1),
-                             sg = tab<const T>(P_SIGMA, l + 1);
-    const int step = (int)(w.x >> 16);
-    int e = (int)(w.x & 0xFFFFu);
-    for (int j = 0; j < k; j += 2, e += 2 * step) {  // two children at a time
-      int q[2], q7[2], q8[2];
-      T r[2], sb[2], s0[2], v[2], a1[2], a2[2];
-      bool p[2];
+  for (int id0 = tid; id0 < na; id0 += 2 * BLOCK) {
+    // two nodes, and two children of each, at a time
+    int lev[2], kids[2], b[2], e0[2], step[2];
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        q[m] = b + (j + m < k ? j + m : j);
-        r[m] = R[q[m]];
-        sb[m] = S[q[m]];
-        s0[m] = sg[q[m]];
-        p[m] = l == 5 ? bit_of(L.b6, q[m]) : l == 6 ? bit_of(L.b7, q[m]) : false;
-        q7[m] = q8[m] = q[m];
+    for (int u = 0; u < 2; ++u) {
+      const bool in = id0 + u * BLOCK < na;
+      const int id = in ? id0 + u * BLOCK : id0;
+      const uint2 w = w_kids[id];
+      lev[u] = (int)(w.y >> 24) & 7;
+      kids[u] = in ? (int)(w.y >> 16) & 0xFF : 0;
+      e0[u] = (int)(w.x & 0xFFFFu);
+      step[u] = (int)(w.x >> 16);
+      b[u] = tab<const int32_t>(P_CB, lev[u])[w_pos[id]] - g_lo[lev[u] + 1];
+    }
+    for (int j = 0; j < kids[0] || j < kids[1]; j += 2) {
+      int q[4], q7[4], q8[4];
+      T r[4], sb[4], s0[4], v[4], a1[4], a2[4];
+      bool in[4], p[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int u = m / 2, l = lev[u];
+        in[m] = j + m % 2 < kids[u];
+        q[m] = b[u] + (in[m] ? j + m % 2 : 0);
+        r[m] = tab<const T>(P_R, l + 1)[q[m]];
+        sb[m] = tab<const T>(P_SBAR, l + 1)[q[m]];
+        s0[m] = tab<const T>(P_SIGMA, l + 1)[q[m]];
         v[m] = a1[m] = a2[m] = (T)0;
-      }
-      if (l == 5) {
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-          if (p[m]) q7[m] = tab<const int32_t>(P_CB, 6)[q[m]] - lo7;
-      }
-      if (l == 5 || l == 6) {
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-          if (p[m]) q8[m] = tab<const int32_t>(P_CB, 7)[q7[m]] - lo8;
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-          if (p[m]) {
-            v[m] = (T)(0.0 + (double)tab<const T>(P_U, 8)[q8[m]]);
-            a1[m] = l == 5 ? tab<const T>(P_SBAR, 7)[q7[m]] : tab<const T>(P_SBAR, 8)[q8[m]];
-            if (l == 5) a2[m] = tab<const T>(P_SBAR, 8)[q8[m]];
-          }
-      }
-      if (l == 7) {
-#pragma unroll
-        for (int m = 0; m < 2; ++m) v[m] = tab<const T>(P_U, 8)[q[m]];
+        if (l == 7) v[m] = tab<const T>(P_U, 8)[q[m]];
+        p[m] = in[m] && (l == 5 ? bit_of(L.b6, q[m]) : l == 6 && bit_of(L.b7, q[m]));
+        q7[m] = q8[m] = q[m];
       }
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        if (j + m >= k) break;
-        const int em = e + m * step;
-        rs[em] = Pair<T>{r[m], sb[m]};
-        su[em] = Pair<T>{s0[m], v[m]};
-        if (l == 5 || l == 6) chain[em - e6] = Pair<T>{a1[m], a2[m]};
+      for (int m = 0; m < 4; ++m)
+        if (p[m] && lev[m / 2] == 5) q7[m] = tab<const int32_t>(P_CB, 6)[q[m]] - lo7;
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (p[m]) q8[m] = tab<const int32_t>(P_CB, 7)[q7[m]] - lo8;
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (p[m]) {
+          v[m] = (T)(0.0 + (double)tab<const T>(P_U, 8)[q8[m]]);
+          a2[m] = tab<const T>(P_SBAR, 8)[q8[m]];
+          if (lev[m / 2] == 5) a1[m] = tab<const T>(P_SBAR, 7)[q7[m]];
+        }
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int u = m / 2, l = lev[u], e = e0[u] + (j + m % 2) * step[u];
+        if (!in[m]) continue;
+        rs[e] = Pair<T>{r[m], sb[m]};
+        su[e] = Pair<T>{s0[m], v[m]};
+        if (l == 5) chain[e - e6] = Pair<T>{a1[m], a2[m]};
+        if (l == 6) chain[e - e6] = Pair<T>{a2[m], (T)0};
       }
     }
   }
@@ -842,51 +866,56 @@ __device__ __forceinline__ void seg_store(const ItemDesc<T> &D, int roots, unsig
   const Pair<T> *const su = near<Pair<T>, FORM>(far, L.su), *const rs = arr<Pair<T>, FORM>(far, L.rs);
   const Pair<T> *const chain = arr<Pair<T>, FORM>(far, L.chain);
   const int e6 = g_sb[6], lo8 = g_lo[8], lo7 = g_lo[7];
-  for (int id = threadIdx.x; id < na; id += BLOCK) {
-    const uint2 w = arr<uint2, FORM>(far, L.kids)[id];
-    const int l = (int)(w.y >> 24) & 7;
-    const Kids n(w);
-    const int b =
-        tab<const int32_t>(P_CB, l)[arr<uint16_t, FORM>(far, L.pos)[id]] - g_lo[l + 1];
-    const GlobalPtr<T> R = tab<T>(P_R, l + 1), S = tab<T>(P_SBAR, l + 1), sg = tab<T>(P_SIGMA, l + 1);
-    for (int j = 0, e = n.e; j < n.k; j += 2, e += 2 * n.step) {  // two children at a time
-      int q[2], q7[2], q8[2];
-      T r7[2], r8[2];
-      bool p[2];
+  for (int id0 = threadIdx.x; id0 < na; id0 += 2 * BLOCK) {
+    // two nodes, and two children of each, at a time
+    int lev[2], kids[2], b[2], e0[2], step[2];
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        q[m] = b + (j + m < n.k ? j + m : j);
-        p[m] = j + m < n.k && (l == 5 ? bit_of(L.b6, q[m]) : l == 6 ? bit_of(L.b7, q[m]) : false);
-        q7[m] = q8[m] = q[m];
+    for (int u = 0; u < 2; ++u) {
+      const bool in = id0 + u * BLOCK < na;
+      const int id = in ? id0 + u * BLOCK : id0;
+      const uint2 w = arr<uint2, FORM>(far, L.kids)[id];
+      const Kids n(w);
+      lev[u] = (int)(w.y >> 24) & 7;
+      kids[u] = in ? n.k : 0;
+      e0[u] = n.e;
+      step[u] = n.step;
+      b[u] = tab<const int32_t>(P_CB, lev[u])[arr<uint16_t, FORM>(far, L.pos)[id]] - g_lo[lev[u] + 1];
+    }
+    for (int j = 0; j < kids[0] || j < kids[1]; j += 2) {
+      int q[4], q7[4], q8[4];
+      T r7[4], r8[4];
+      bool in[4], p[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int u = m / 2, l = lev[u];
+        in[m] = j + m % 2 < kids[u];
+        q[m] = q7[m] = q8[m] = b[u] + (in[m] ? j + m % 2 : 0);
+        p[m] = in[m] && (l == 5 ? bit_of(L.b6, q[m]) : l == 6 && bit_of(L.b7, q[m]));
         r7[m] = r8[m] = (T)0;
       }
-      if (l == 5) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
-          if (p[m]) q7[m] = tab<const int32_t>(P_CB, 6)[q[m]] - lo7;
-      }
-      if (l == 5 || l == 6) {
+      for (int m = 0; m < 4; ++m)
+        if (p[m] && lev[m / 2] == 5) q7[m] = tab<const int32_t>(P_CB, 6)[q[m]] - lo7;
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
-          if (p[m]) q8[m] = tab<const int32_t>(P_CB, 7)[q7[m]] - lo8;
+      for (int m = 0; m < 4; ++m)
+        if (p[m]) q8[m] = tab<const int32_t>(P_CB, 7)[q7[m]] - lo8;
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
-          if (p[m]) {
-            r8[m] = tab<T>(P_R, 8)[q8[m]];
-            if (l == 5) r7[m] = tab<T>(P_R, 7)[q7[m]];
-          }
-      }
+      for (int m = 0; m < 4; ++m)
+        if (p[m]) {
+          r8[m] = tab<T>(P_R, 8)[q8[m]];
+          if (lev[m / 2] == 5) r7[m] = tab<T>(P_R, 7)[q7[m]];
+        }
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        if (j + m >= n.k) break;
-        const int em = e + m * n.step;
-        const Pair<T> s2 = su[em], r = rs[em];
-        sg[q[m]] = s2.a;
-        R[q[m]] = r.a;
-        S[q[m]] = r.b;
+      for (int m = 0; m < 4; ++m) {
+        const int u = m / 2, l = lev[u], e = e0[u] + (j + m % 2) * step[u];
+        if (!in[m]) continue;
+        const Pair<T> s2 = su[e], r = rs[e];
+        tab<T>(P_SIGMA, l + 1)[q[m]] = s2.a;
+        tab<T>(P_R, l + 1)[q[m]] = r.a;
+        tab<T>(P_SBAR, l + 1)[q[m]] = r.b;
         if (l < 7) tab<T>(P_U, l + 1)[q[m]] = s2.b;
         if (!p[m]) continue;
-        const Pair<T> ch = chain[em - e6];
+        const Pair<T> ch = chain[e - e6];
         if (l == 5) {
           tab<T>(P_U, 7)[q7[m]] = s2.b;
           tab<T>(P_SBAR, 7)[q7[m]] = ch.a;
