@@ -22,16 +22,16 @@
 //  - frontier (default): one persistent launch for all iterations.  Roots
 //    are independent, so each workgroup takes a run of consecutive roots and
 //    runs every iteration on them alone.  Per pass it keeps, for each level,
-//    the list of its reached nodes (the frontier) in global scratch: the
-//    reached nodes of level l + 1 are appended while level l draws (one LDS
-//    counter per level, reserved once per wave), and the up sweep visits the
-//    frontiers only.  Work per pass is proportional to the reached nodes
+//    the list of its reached nodes (the frontier) in LDS, and what does not
+//    fit there in global scratch: the reached nodes of level l + 1 are
+//    appended while level l draws, and the up sweep visits the frontiers only.  Work per pass is proportional to the reached nodes
 //    (about one opponent action in k per opponent level), not the tree.
 //  - level: one launch per level and direction with one thread per node of
 //    the level, reading the previous level's picks (no compaction).
 // Arithmetic is FP64 in registers with the state stored as float or double,
 // in the same order as the definition above.
 #include "pasur_internal.hpp"
+#include "pasur_scan.hpp"
 
 #include <cmath>
 
@@ -149,30 +149,39 @@ struct alignas(4 * sizeof(T)) EsRec {
   T sg, R, Sb, u;
 };
 
+// The nodes of levels 0..8, level by level, kBlock to a workgroup: one launch
+// (nine of them cost a small round 60 us a call).
 template <class T>
-__global__ void k_es_pack(int64_t n, const T *sg, const T *R, const T *Sb, const T *u,
-                          EsRec<T> *rec) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  EsRec<T> x;
-  x.sg = sg ? sg[i] : (T)0;
-  x.R = R ? R[i] : (T)0;
-  x.Sb = Sb ? Sb[i] : (T)0;
-  x.u = u[i];
-  rec[i] = x;
-}
+struct EsPack {
+  T *sg[9], *R[9], *Sb[9], *u[9];
+  EsRec<T> *rec[9];
+  int64_t n[9];
+  unsigned block[10];
+};
 
-template <class T>
-__global__ void k_es_unpack(int64_t n, const EsRec<T> *rec, T *sg, T *R, T *Sb, T *u) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const EsRec<T> x = rec[i];
-  if (sg) {
-    sg[i] = x.sg;
-    R[i] = x.R;
-    Sb[i] = x.Sb;
+template <class T, bool PACK>
+__global__ void __launch_bounds__(kBlock) k_es_pack(EsPack<T> a) {
+  int l = 0;
+#pragma unroll
+  for (int k = 1; k < 9; ++k) l += blockIdx.x >= a.block[k] ? 1 : 0;
+  const int64_t i = (int64_t)(blockIdx.x - a.block[l]) * kBlock + threadIdx.x;
+  if (i >= a.n[l]) return;
+  if (PACK) {
+    EsRec<T> x;
+    x.sg = l ? a.sg[l][i] : (T)0;
+    x.R = l ? a.R[l][i] : (T)0;
+    x.Sb = l ? a.Sb[l][i] : (T)0;
+    x.u = a.u[l][i];
+    a.rec[l][i] = x;
+  } else {
+    const EsRec<T> x = a.rec[l][i];
+    if (l) {
+      a.sg[l][i] = x.sg;
+      a.R[l][i] = x.R;
+      a.Sb[l][i] = x.Sb;
+    }
+    a.u[l][i] = x.u;
   }
-  u[i] = x.u;
 }
 
 struct EsSegArgs {
@@ -189,54 +198,29 @@ struct EsSegArgs {
   unsigned long long *stats;   // optional: visits and kept children, see pasur_es_iterate
 };
 
-// Exclusive offset of this lane's k items in a wave-wide reservation of
-// *counter (LDS); every lane of the wave must call it.
-__device__ __forceinline__ int wave_reserve(int k, int *counter) {
-  int x = k;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(x, d, 64);
-    if ((int)(threadIdx.x & 63) >= d) x += y;
-  }
-  const int total = __shfl(x, 63, 64);
-  int base = 0;
-  if ((threadIdx.x & 63) == 63 && total > 0) base = atomicAdd(counter, total);
-  base = __shfl(base, 63, 64);
-  return base + x - k;
-}
+// Reached nodes of one pass whose data is held in LDS, over all levels; those
+// past them are in the global lists.  A pass over a root of 4096 nodes reaches
+// some 150.
+constexpr int kFrontier = 512;
 
-// Down step of reached node h of level l on records (as down_node): returns
-// the first kept child, the number kept in *k, the number of children in
-// *kids and the entry's choice in *ch.
 template <class T>
-__device__ __forceinline__ int32_t rec_down(const EsSegArgs &a, int l, int p, uint64_t base,
-                                            int64_t h, int *k, int *kids, int32_t *ch) {
-  const int32_t b = a.cb[l][h], e = a.cb[l][h + 1];
-  *kids = e - b;
-  if ((l & 1) == p) {
-    *ch = kAll;
-    *k = e - b;
-    return b;
-  }
-  EsRec<T> *rc = reinterpret_cast<EsRec<T> *>(a.rec[l + 1]);
-  int j = 0;
-  if (e - b > 1)
-    j = choose_by(splitmix_uniform(a.seed, base + (uint64_t)h), e - b, PASUR_PLAY_SIGMA_BAR,
-                  [rc, b](int c) { return (double)rc[b + c].sg; });
-  for (int c = b; c < e; ++c) rc[c].Sb = (T)((double)rc[c].Sb + (double)rc[c].sg);
-  *ch = b + j;
-  *k = 1;
-  return b + j;
-}
+struct EsLds {
+  int h[kFrontier];          // the node
+  int child[kFrontier];      // its first kept child
+  uint32_t next[kFrontier];  // where its kept children begin in the next level's list
+                             // | number of children << 16, 0 for a node of the opponent
+  T sg[kFrontier], R[kFrontier], u[kFrontier];
+};
 
-// Up step of reached node h of level l on records (as up_node).
+// Up step of reached node h of level l on records (as up_node); returns its value.
 template <class T>
-__device__ __forceinline__ void rec_up(const EsSegArgs &a, int l, int p, int64_t h, int32_t ch) {
+__device__ __forceinline__ T rec_up(const EsSegArgs &a, int l, int p, int64_t h, int32_t ch) {
   EsRec<T> *rc = reinterpret_cast<EsRec<T> *>(a.rec[l + 1]);
   EsRec<T> *rl = reinterpret_cast<EsRec<T> *>(a.rec[l]);
   if (ch != kAll) {
-    rl[h].u = rc[ch].u;
-    return;
+    const T u = rc[ch].u;
+    rl[h].u = u;
+    return u;
   }
   const int32_t b = a.cb[l][h], e = a.cb[l][h + 1];
   double acc = 0.0;
@@ -257,61 +241,175 @@ __device__ __forceinline__ void rec_up(const EsSegArgs &a, int l, int p, int64_t
                                                  : fmax((double)rc[c].R, 0.0);
     rc[c].sg = (T)(sum > 0.0 ? x / sum : inv_k);
   }
+  return uh;
 }
 
-template <class T, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_es_frontier(EsSegArgs a) {
-  __shared__ int cnt[9];
-  __shared__ int64_t seg[9];  // where this workgroup's frontier of each level starts
+// A wave per run of roots.  A pass is a chain of dependent loads, two levels of
+// them per level of the tree: what a node's up step needs is read in its down
+// step, beside the loads that the way down waits for, and kept in LDS, so that
+// the way up waits for the leaves alone (a pass over one tree of 7,000 nodes,
+// with the lists and the values in memory: 20 us).
+template <class T>
+__global__ __launch_bounds__(64) void k_es_frontier(EsSegArgs a) {
+  __shared__ EsLds<T> s;
+  __shared__ int start[9];    // where a level's entries begin
+  __shared__ int64_t seg[9];  // where this wave's part of a level's global list begins
+  const int lane = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * a.roots_per_wg;
   const int64_t r1 = r0 + a.roots_per_wg < a.n_roots ? r0 + a.roots_per_wg : a.n_roots;
-  if (threadIdx.x < 9) seg[threadIdx.x] = a.off[threadIdx.x] + a.root_off[threadIdx.x][r0];
+  if (lane < 9) seg[lane] = a.off[lane] + a.root_off[lane][r0];
+  auto order = [] {  // LDS accesses of a wave run in order
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  };
+  order();
   unsigned long long n_trav = 0, e_trav = 0, n_opp = 0, e_opp = 0;
   for (int64_t it = 0; it < a.n_iters; ++it) {
     const uint64_t t = (uint64_t)(a.t0 + it + 1);
     for (int p = 0; p < 2; ++p) {
       const uint64_t pass_base = (2 * (t - 1) + (uint64_t)p) * a.N;
-      __syncthreads();  // the previous pass has finished with the counters
-      if (threadIdx.x < 9) cnt[threadIdx.x] = 0;
-      __syncthreads();
-#pragma unroll
+      int from = 0, m = (int)(r1 - r0);  // the level's entries
+#pragma unroll 1
       for (int l = 0; l < 8; ++l) {
         const uint64_t base = pass_base + (uint64_t)a.off[l];
-        const int m = l == 0 ? (int)(r1 - r0) : cnt[l];
-        for (int i0 = 0; i0 < m; i0 += BLOCK) {
-          const int i = i0 + (int)threadIdx.x;
-          int k = 0, kids = 0;
+        const int32_t *const cb = a.cb[l];
+        const EsRec<T> *const rl = reinterpret_cast<const EsRec<T> *>(a.rec[l]);
+        EsRec<T> *const rc = reinterpret_cast<EsRec<T> *>(a.rec[l + 1]);
+        const bool own = (l & 1) == p;
+        const bool near = from + m <= kFrontier;
+        if (!near) __threadfence_block();  // the list's end is in memory
+        if (lane == 0) start[l] = from;
+        int next = 0;  // entries of the next level
+        for (int i0 = 0; i0 < m; i0 += 64) {
+          const int i = i0 + lane, e = from + i;
+          int k = 0;
           int32_t first = 0;
           if (i < m) {
-            const int64_t h = l == 0 ? r0 + i : (int64_t)a.front[seg[l] + i];
-            int32_t ch;
-            first = rec_down<T>(a, l, p, base, h, &k, &kids, &ch);
-            a.choice[seg[l] + i] = ch;
-            if ((l & 1) == p) {
+            const int64_t h =
+                l == 0 ? r0 + i : (int64_t)(e < kFrontier ? s.h[e] : a.front[seg[l] + i]);
+            const int32_t b = cb[h];
+            const int kids = cb[h + 1] - b;
+            if (l > 0 && !own) {  // the mover above is the updated player
+              const EsRec<T> x = rl[h];
+              if (e < kFrontier) {
+                s.sg[e] = x.sg;
+                s.R[e] = x.R;
+              }
+            }
+            first = b;
+            k = kids;
+            if (own) {
               ++n_trav;
               e_trav += kids;
             } else {
+              EsRec<T> x[4];  // the first children's records
+#pragma unroll
+              for (int j = 0; j < 4; ++j) x[j] = rc[b + (j < kids ? j : 0)];
+              if (kids > 1)
+                first += choose_by(splitmix_uniform(a.seed, base + (uint64_t)h), kids,
+                                   PASUR_PLAY_SIGMA_BAR, [&](int j) {
+                                     return (double)(j == 0   ? x[0].sg
+                                                     : j == 1 ? x[1].sg
+                                                     : j == 2 ? x[2].sg
+                                                     : j == 3 ? x[3].sg
+                                                              : rc[b + j].sg);
+                                   });
+#pragma unroll
+              for (int j = 0; j < 4; ++j)
+                if (j < kids) rc[b + j].Sb = (T)((double)x[j].Sb + (double)x[j].sg);
+              for (int j = 4; j < kids; ++j)
+                rc[b + j].Sb = (T)((double)rc[b + j].Sb + (double)rc[b + j].sg);
+              k = 1;
               ++n_opp;
               e_opp += kids;
             }
           }
-          if (l < 7) {
-            const int pos = wave_reserve(k, &cnt[l + 1]);
-            int32_t *dst = a.front + seg[l + 1] + pos;
-            for (int j = 0; j < k; ++j) dst[j] = first + j;
+          const int upto = wave_inclusive<int>(k, lane);
+          if (i < m) {
+            const int at = next + upto - k;
+            if (e < kFrontier) {
+              s.h[e] = (int)(l == 0 ? r0 + i : (int64_t)s.h[e]);
+              s.child[e] = first;
+              s.next[e] = ((uint32_t)at & 0xFFFFu) | (own ? (uint32_t)k << 16 : 0u);
+            } else {
+              a.choice[seg[l] + i] = own ? kAll : first;
+            }
+            if (l < 7)
+              for (int j = 0; j < k; ++j) {
+                const int to = from + m + at + j;
+                if (to < kFrontier) s.h[to] = first + j;
+                else a.front[seg[l + 1] + at + j] = first + j;
+              }
           }
+          next += wave_last(upto);
+          order();
         }
-        __syncthreads();
+        from += m;
+        m = next;
       }
-#pragma unroll
-      for (int l = 7; l >= 0; --l) {
-        const int m = l == 0 ? (int)(r1 - r0) : cnt[l];
-        for (int i = (int)threadIdx.x; i < m; i += BLOCK) {
-          const int64_t h = l == 0 ? r0 + i : (int64_t)a.front[seg[l] + i];
-          rec_up<T>(a, l, p, h, a.choice[seg[l] + i]);
+      const int total = from;
+      order();
+      if (total <= kFrontier) {
+#pragma unroll 1
+        for (int l = 7; l >= 0; --l) {
+          const int e0 = start[l], end = l < 7 ? start[l + 1] : total;
+          EsRec<T> *const rl = reinterpret_cast<EsRec<T> *>(a.rec[l]);
+          EsRec<T> *const rc = reinterpret_cast<EsRec<T> *>(a.rec[l + 1]);
+          for (int e = e0 + lane; e < end; e += 64) {
+            const int b = s.child[e], h = s.h[e], k = (int)(s.next[e] >> 16);
+            const int c0 = end + (int)(s.next[e] & 0xFFFFu);  // its children's entries
+            T uh;
+            if (k == 0) {
+              uh = l < 7 ? s.u[c0] : rc[b].u;
+            } else if (l < 7) {
+              double acc = 0.0;
+              for (int j = 0; j < k; ++j) acc += (double)s.sg[c0 + j] * (double)s.u[c0 + j];
+              uh = (T)acc;
+              const double v = (double)uh;
+              double sum = 0.0;
+              for (int j = 0; j < k; ++j) {
+                const double w = (double)s.u[c0 + j];
+                const T r = (T)((double)s.R[c0 + j] + (p == 0 ? w - v : v - w));
+                s.R[c0 + j] = r;
+                rc[b + j].R = r;
+                sum += a.rm_mode == PASUR_RM_FLOOR ? fmax((double)r, a.eps) : fmax((double)r, 0.0);
+              }
+              const double inv_k = 1.0 / (double)k;
+              for (int j = 0; j < k; ++j) {
+                const double r = (double)s.R[c0 + j];
+                const double x = a.rm_mode == PASUR_RM_FLOOR ? fmax(r, a.eps) : fmax(r, 0.0);
+                rc[b + j].sg = (T)(sum > 0.0 ? x / sum : inv_k);
+              }
+            } else {
+              uh = rec_up<T>(a, l, p, h, kAll);
+            }
+            s.u[e] = uh;
+            if (l < 7 || k == 0) rl[h].u = uh;
+          }
+          order();
         }
-        __syncthreads();
+      } else {
+        // the lists' end, and so values of children, are in memory
+        __threadfence_block();
+#pragma unroll 1
+        for (int l = 7; l >= 0; --l) {
+          const int e0 = start[l], end = l < 7 ? start[l + 1] : total;
+          for (int e = e0 + lane; e < end; e += 64) {
+            int64_t h;
+            int32_t ch;
+            if (e < kFrontier) {
+              h = s.h[e];
+              ch = (s.next[e] >> 16) != 0 ? kAll : s.child[e];
+            } else {
+              h = l == 0 ? r0 + e : (int64_t)a.front[seg[l] + (e - e0)];
+              ch = a.choice[seg[l] + (e - e0)];
+            }
+            rec_up<T>(a, l, p, h, ch);
+          }
+          __threadfence_block();
+        }
       }
+      __threadfence_block();  // before the next pass reads the records
     }
   }
   if (a.stats) {
@@ -345,7 +443,6 @@ void fill_levels(EsLevel lv[8], const pasur_fgt *f, const pasur_cfr_state *st, c
   }
 }
 
-constexpr int kFrontierBlock = 64;
 constexpr int64_t kNodesPerWorkgroup = 4096;
 
 template <class T>
@@ -364,15 +461,20 @@ int es_run(const pasur_fgt *f, const pasur_cfr_state *st, int64_t t0, int64_t n_
     EsRec<T> *recs = reinterpret_cast<EsRec<T> *>(ws);
     int64_t roff = 0;
     EsSegArgs a;
+    EsPack<T> pk;
+    pk.block[0] = 0;
     for (int l = 0; l < 9; ++l) {
       a.rec[l] = recs + roff;
-      const int64_t n = f->n[l];
-      if (n > 0)
-        k_es_pack<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(
-            n, l > 0 ? (const T *)st->sigma[l] : nullptr, l > 0 ? (const T *)st->R[l] : nullptr,
-            l > 0 ? (const T *)st->Sbar[l] : nullptr, (const T *)st->u[l], recs + roff);
-      roff += n;
+      pk.sg[l] = (T *)st->sigma[l];
+      pk.R[l] = (T *)st->R[l];
+      pk.Sb[l] = (T *)st->Sbar[l];
+      pk.u[l] = (T *)st->u[l];
+      pk.rec[l] = recs + roff;
+      pk.n[l] = f->n[l];
+      pk.block[l + 1] = pk.block[l] + (unsigned)((f->n[l] + kBlock - 1) / kBlock);
+      roff += f->n[l];
     }
+    k_es_pack<T, true><<<pk.block[9], kBlock, 0, s>>>(pk);
     int32_t *lists = reinterpret_cast<int32_t *>(recs + roff);
     for (int l = 0; l < 8; ++l) a.cb[l] = f->child_begin[l];
     for (int l = 0; l < 9; ++l) {
@@ -395,14 +497,8 @@ int es_run(const pasur_fgt *f, const pasur_cfr_state *st, int64_t t0, int64_t n_
     a.roots_per_wg = (int)(per < 1 ? 1 : per > f->n_roots ? f->n_roots : per);
     a.stats = stats;
     const unsigned grid = (unsigned)((f->n_roots + a.roots_per_wg - 1) / a.roots_per_wg);
-    k_es_frontier<T, kFrontierBlock><<<grid, kFrontierBlock, 0, s>>>(a);
-    for (int l = 0; l < 9; ++l) {
-      const int64_t n = f->n[l];
-      if (n > 0)
-        k_es_unpack<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(
-            n, reinterpret_cast<const EsRec<T> *>(a.rec[l]), l > 0 ? (T *)st->sigma[l] : nullptr,
-            l > 0 ? (T *)st->R[l] : nullptr, l > 0 ? (T *)st->Sbar[l] : nullptr, (T *)st->u[l]);
-    }
+    k_es_frontier<T><<<grid, 64, 0, s>>>(a);
+    k_es_pack<T, false><<<pk.block[9], kBlock, 0, s>>>(pk);
     PASUR_TRY_HIP(hipGetLastError());
     return PASUR_OK;
   }
