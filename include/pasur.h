@@ -281,6 +281,17 @@ int pasur_plan_iterate(const pasur_plan *plan, int64_t t0, int n_iters, void *st
 /* info: segments, LDS-resident segments, dynamic LDS bytes, threads per
  * workgroup, edges, internal nodes, roots, level-7 nodes. */
 int pasur_plan_info(const pasur_plan *plan, int64_t info[8]);
+/* pasur_leaf_utilities (no flags; d_V_next[i] may be NULL for round 5) and
+ * pasur_cfr_init of n_items (tree, state) pairs of one dtype, in one launch per
+ * eight; d_V_next may be NULL if every tree is a round 5.  Asynchronous. */
+int pasur_batch_begin(const pasur_fgt *const *fgts, const pasur_cfr_state *const *states,
+                      const double *const *d_V_next, int n_items, void *stream);
+/* pasur_average_strategy into sigma_bar[9 * i + l] (l = 1..8) and
+ * pasur_round_values (PASUR_V_ITERATE_MEAN over T iterations) into d_V[i], in
+ * one launch per eight.  Asynchronous. */
+int pasur_batch_end(const pasur_fgt *const *fgts, const pasur_cfr_state *const *states,
+                    void *const *sigma_bar, int64_t T, double *const *d_V, int n_items,
+                    void *stream);
 void pasur_plan_free(pasur_plan *plan);
 
 /* Normalise (CodeSnippet CFR): sigma_bar = Sbar / sum over siblings, uniform

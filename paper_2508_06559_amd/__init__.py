@@ -97,6 +97,8 @@ def lib():
         L.pasur_gt_get_view.argtypes = [vp, vp]
         L.pasur_fgt_get_view.argtypes = [vp, vp]
         L.pasur_sgd_step.argtypes = [vp, vp, vp, i64, C.c_float, vp]
+        L.pasur_batch_begin.argtypes = [vp, vp, vp, i32, vp]
+        L.pasur_batch_end.argtypes = [vp, vp, vp, i64, vp, i32, vp]
         L.pasur_plan_create.argtypes = [vp, vp, i32, vp, i64, i64, C.POINTER(vp), vp]
         L.pasur_plan_iterate.argtypes = [vp, i64, i32, vp]
         L.pasur_plan_info.argtypes = [vp, vp]
@@ -422,6 +424,38 @@ def sgd_step(w, g, wb, lr, stream=None):
     """pasur_sgd_step on torch tensors (wb: int16 BF16 bit patterns or None)."""
     _check(lib().pasur_sgd_step(_p(w), _p(g), _p(wb), w.numel(), lr, _stream(stream)),
            "pasur_sgd_step")
+
+
+class BatchEnds:
+    """What surrounds the iterations of a batch: leaf utilities and the
+    initial states before, average strategies and mean values after
+    (pasur_batch_begin, pasur_batch_end), a launch per eight trees."""
+
+    def __init__(self, states: Sequence[CfrState]):
+        n = len(states)
+        self.states = list(states)
+        self.fg = (C.c_void_p * n)(*[st.fgt.h for st in states])
+        self.sp = (C.c_void_p * n)(*[C.addressof(st.c) for st in states])
+        self.sb = (C.c_void_p * (9 * n))()
+        for i, st in enumerate(states):
+            self.sb[9 * i:9 * i + 9] = st.sb_ptrs[:]
+
+    def begin(self, V_next, stream=None):
+        """V_next: per item the next round's root values, or None (round 5)."""
+        n = len(self.states)
+        vn = (C.c_void_p * n)(*[None if v is None else v.data_ptr() for v in V_next])
+        _check(lib().pasur_batch_begin(self.fg, self.sp, vn, n, _stream(stream)),
+               "pasur_batch_begin")
+        for st in self.states:
+            st.t = 1
+            st.es_t = 0
+
+    def end(self, V, stream=None):
+        """V: per item where its roots' values go."""
+        n = len(self.states)
+        v = (C.c_void_p * n)(*[x.data_ptr() for x in V])
+        _check(lib().pasur_batch_end(self.fg, self.sp, self.sb, self.states[0].t - 1, v, n,
+                                     _stream(stream)), "pasur_batch_end")
 
 
 class Plan:

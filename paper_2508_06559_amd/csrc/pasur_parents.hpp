@@ -39,11 +39,11 @@ struct MyParents {
   int64_t h[kParentsPer];
   int32_t b[kParentsPer], e[kParentsPer];
 
-  __device__ __forceinline__ explicit MyParents(const AllParents &P) {
+  __device__ __forceinline__ MyParents(const AllParents &P, unsigned block) {
     level = 0;
 #pragma unroll
-    for (int k = 1; k < 8; ++k) level += blockIdx.x >= P.block[k] ? 1 : 0;
-    const int64_t h0 = (int64_t)(blockIdx.x - P.block[level]) * (kParentThreads * kParentsPer);
+    for (int k = 1; k < 8; ++k) level += block >= P.block[k] ? 1 : 0;
+    const int64_t h0 = (int64_t)(block - P.block[level]) * (kParentThreads * kParentsPer);
     const int32_t *const cb = P.cb[level];
 #pragma unroll
     for (int k = 0; k < kParentsPer; ++k) {
@@ -75,12 +75,8 @@ EdgeArrays<T> edge_arrays(void *const a[9], void *const b[9], void *const c[9]) 
 // 1 / children where the sum is not positive.  The first kAhead children of all
 // of a thread's parents are read before any is used.
 template <class T, class Weight>
-__global__ void __launch_bounds__(kParentThreads)
-    k_normalise(AllParents P, EdgeArrays<T> E, Weight w) {
+__device__ __forceinline__ void normalise(const MyParents &m, const T *in, T *out, Weight w) {
   constexpr int kAhead = 2;
-  const MyParents m(P);
-  const T *const in = E.a[m.level + 1];
-  T *const out = E.b[m.level + 1];
   T v[kParentsPer][kAhead];
 #pragma unroll
   for (int k = 0; k < kParentsPer; ++k)
@@ -101,6 +97,13 @@ __global__ void __launch_bounds__(kParentThreads)
     for (int32_t q = b + kAhead; q < e; ++q)
       out[q] = (T)(s > 0.0 ? w((double)in[q]) / s : 1.0 / (double)(e - b));
   }
+}
+
+template <class T, class Weight>
+__global__ void __launch_bounds__(kParentThreads)
+    k_normalise(AllParents P, EdgeArrays<T> E, Weight w) {
+  const MyParents m(P, blockIdx.x);
+  normalise<T>(m, E.a[m.level + 1], E.b[m.level + 1], w);
 }
 
 }  // namespace pasur

@@ -14,7 +14,7 @@ from typing import List, Optional
 
 from . import (PASUR_F32, PASUR_F64, PLAY_SIGMA_BAR, RM_FLOOR, SCHED_STREAM, V_ITERATE_MEAN,
                V_SIGMA_BAR, ES_FRONTIER, CfrParams, FGT_CHILD_BEGIN, FGT_LINK, FGT_NEXT_ROOTS, ROOT_DTYPE, CfrState,
-               es_iterate, exploitability, selfplay, Plan, UnfoldedTree,
+               es_iterate, exploitability, selfplay, BatchEnds, Plan, UnfoldedTree,
                average_strategy, build_round_tree, cfr_init, cfr_iterate, leaf_utilities,
                paper_params, round_values, roots_to_device, unfold_scores, _torch)
 
@@ -209,6 +209,8 @@ class BatchSolver:
             for rr in sv.rounds:
                 rr.state = CfrState(rr.fgt, dtype)
                 rr.V = torch.empty(rr.fgt.n[0], dtype=torch.float64, device="cuda")
+        self.ends = [BatchEnds([sv.rounds[k].state for sv in self.deals])
+                     for k in range(self.n_rounds)]
         self.plans = []
         self.set_params(params)
 
@@ -241,16 +243,16 @@ class BatchSolver:
 
     def _backward(self, stream=None):
         for k in range(self.n_rounds - 1, -1, -1):
-            for sv in self.deals:
-                rr = sv.rounds[k]
-                V = None if k == self.n_rounds - 1 else sv.rounds[k + 1].V
-                leaf_utilities(rr.fgt, V, rr.state.dtype, rr.state.u[8], stream)
-                cfr_init(rr.state, stream)
+            self.ends[k].begin([sv.rounds[k + 1].V if k + 1 < self.n_rounds else None
+                                for sv in self.deals], stream)
             if self.plans[k] is not None:
                 self.plans[k].iterate(1, self.iters, stream)
             for sv, st in zip(self.deals, self.streamed[k]):
                 if st:
                     cfr_iterate(sv.rounds[k].state, self.iters, self.stream_params[k], stream=stream)
+            if self.value_mode == V_ITERATE_MEAN:
+                self.ends[k].end([sv.rounds[k].V for sv in self.deals], stream)
+                continue
             for sv in self.deals:
                 rr = sv.rounds[k]
                 average_strategy(rr.state, stream)
