@@ -40,27 +40,44 @@ void prof_clear() {
 constexpr int kThreads = 256;
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
 
-// sigma uniform, R and Sbar zero for the children of a thread's parents; the
-// roots' reaches and utility sums.  Bound by the 12 B written per edge.
+// Zeros in p[b] .. p[e-1] by a workgroup, 16 bytes per thread and store.
+template <class T>
+__device__ __forceinline__ void zero_range(T *p, int64_t b, int64_t e) {
+  constexpr int kPer = 16 / (int)sizeof(T);
+  const int64_t lead = ((16 - (int64_t)(reinterpret_cast<uintptr_t>(p + b) & 15)) & 15) / (int)sizeof(T);
+  const int64_t b16 = b + lead < e ? b + lead : e, n16 = (e - b16) / kPer;
+  int4 *const q = reinterpret_cast<int4 *>(p + b16);
+  for (int64_t i = threadIdx.x; i < n16; i += kParentThreads) q[i] = make_int4(0, 0, 0, 0);
+  const int64_t tail = b16 + n16 * kPer;
+  if ((int64_t)threadIdx.x < b16 - b) p[b + threadIdx.x] = (T)0;
+  if ((int64_t)threadIdx.x < e - tail) p[tail + threadIdx.x] = (T)0;
+}
+
+// sigma uniform, R and Sbar zero for the children of a workgroup's parents (their
+// children are neighbours); the roots' reaches and utility sums.  Bound by the
+// 12 B written per edge (6.8e8 nodes: 3.0 ms with R and Sbar written child by
+// child beside sigma).
 template <class T>
 __device__ __forceinline__ void init_children(const AllParents &P, const MyParents &m,
                                               const EdgeArrays<T> &E, T *ra, T *rb, double *vacc) {
-  T *const sg = E.a[m.level + 1], *const R = E.b[m.level + 1], *const S = E.c[m.level + 1];
+  T *const sg = E.a[m.level + 1];
 #pragma unroll
   for (int k = 0; k < kParentsPer; ++k) {
     const int32_t b = m.b[k], e = m.e[k];
     const T s = (T)(1.0 / (double)(e - b));
-    for (int32_t q = b; q < e; ++q) {
-      sg[q] = s;
-      R[q] = (T)0;
-      S[q] = (T)0;
-    }
+    for (int32_t q = b; q < e; ++q) sg[q] = s;
     if (m.level == 0 && m.h[k] < P.n[0]) {
       ra[m.h[k]] = (T)1;
       rb[m.h[k]] = (T)1;
       vacc[m.h[k]] = 0.0;
     }
   }
+  const int64_t h0 = m.h[0] - (int)threadIdx.x;
+  int64_t h1 = h0 + kParentThreads * kParentsPer;
+  if (h1 > P.n[m.level]) h1 = P.n[m.level];
+  const int64_t b = P.cb[m.level][h0], e = P.cb[m.level][h1];
+  zero_range(E.b[m.level + 1], b, e);
+  zero_range(E.c[m.level + 1], b, e);
 }
 
 template <class T>
