@@ -207,7 +207,8 @@ typedef enum { PASUR_RM_FLOOR = 0, PASUR_RM_POSITIVE = 1 } pasur_rm_mode;
  * as noted for STREAM):
  * ROOT: one persistent workgroup per segment (a run of consecutive roots,
  *   see seg_nodes) runs all iterations on that segment's subtrees, its state
- *   held in LDS when it fits (else in global memory);
+ *   held in LDS when it fits (else partly or wholly in device memory that the
+ *   plan holds, at most 1 GiB, or in place where there is none);
  * LEVEL_SYNC: one launch per level and sweep direction;
  * ROOT_GLOBAL: the persistent schedule with state always in global memory;
  * STREAM: one coalesced launch per level and sweep direction that streams
@@ -264,11 +265,12 @@ int pasur_cfr_iterate(const pasur_fgt *fgt, const pasur_cfr_state *st,
                       void *stream);
 /* ---- a12: batched solve -------------------------------------------------------
  * A plan gathers n_items (unfolded tree, solver state) pairs -- e.g. one
- * round of many deals -- into one persistent launch of the segment schedule
- * and uploads everything the launch needs: item descriptors, the segment
+ * round of many deals -- into persistent launches of the segment schedule (one
+ * per class of segments by how many fit on a compute unit)
+ * and uploads everything they need: item descriptors, the segment
  * list (longest first) and the DCFR constants of iterations
  * t_first..t_last (computed on the host).  pasur_plan_iterate only enqueues
- * one kernel, so it can be captured into a HIP graph; it runs iterations
+ * kernels, so it can be captured into a HIP graph; it runs iterations
  * t0..t0+n_iters-1 (within the plan's range) on every item, with results
  * bit-identical to pasur_cfr_iterate on each item.  Items keep their own
  * caller-owned arrays, which must outlive the plan.  All items share one

@@ -460,7 +460,7 @@ class BatchEnds:
 
 class Plan:
     """pasur_plan: a batch of (unfolded tree, solver state) items iterated by
-    one persistent launch per call (a12).  Keeps the items alive."""
+    persistent launches (a12).  Keeps the items alive."""
 
     def __init__(self, states: Sequence[CfrState], params: Optional[CfrParams] = None,
                  t_first: int = 1, t_last: int = 1000, stream=None):

@@ -183,7 +183,7 @@ def _initial_pool(deck) -> int:
 class BatchSolver:
     """Many deals solved together (a12): every round of every deal is built
     and unfolded as in SubgameSolver; the backward solve then runs one
-    persistent launch per round over the trees of all deals (a plan), with
+    plan per round (persistent launches) over the trees of all deals, with
     per-deal leaf utilities, initialisation, average strategies and round
     values around it.  ``capture()`` records the whole backward solve into a
     HIP graph (torch.cuda.CUDAGraph) so that ``replay()`` is one graph launch.
