@@ -130,7 +130,7 @@ constexpr int kClasses = 64;  // children per node: 0 .. 63
 constexpr uint32_t kTableBytes = 3 * 8 * kClasses * 4;
 constexpr int kList = 512;     // capacity of the list
 constexpr uint32_t kNoEdge = 0xFFFFFFFFu;
-constexpr int kTopEdges = 224;  // take at most kList places, see list_build
+constexpr int kTopEdges = 64;  // one wave updates them
 constexpr uint32_t kListed = 1u << 31;
 
 template <class U>
@@ -218,10 +218,10 @@ struct Kids {
       : e((int)(w.x & 0xFFFFu)), step((int)(w.x >> 16)), k((int)(w.y >> 16) & 0xFF) {}
 };
 
-// Levels 0 .. top-1: at most 64 nodes, and not more than kTopEdges children.
+// Levels 0 .. top-1: at most kTopEdges children (and so fewer nodes).
 __device__ __forceinline__ int top_levels() {
   int top = 0;
-  while (top < 4 && g_nb[top + 1] <= 64 && g_sb[top + 2] <= kTopEdges) ++top;
+  while (top < 4 && g_sb[top + 2] <= kTopEdges) ++top;
   return top;
 }
 
@@ -230,10 +230,9 @@ __device__ __forceinline__ int top_levels() {
 // other wave would wait for, then of nodes with more than four children.  An
 // entry is the parent | the child's number << 16.  The children of a node have
 // neighbouring places of one wave, so that its lanes can follow each other
-// without a barrier; a node that no longer fits in a wave begins the next.  Any
-// two neighbouring waves are then filled with more than 64 edges between them:
-// kTopEdges edges take at most kList places.  Nodes past the list's end stay with
-// update_many.  For one wave; before it, the list is kNoEdge.
+// without a barrier; a node that no longer fits in a wave begins the next.  Nodes
+// past the list's end stay with update_many.  For one wave; before it, the list
+// is kNoEdge.
 template <int FORM>
 __device__ __forceinline__ void list_build(unsigned char *far, const SegLds &L) {
   const int lane = threadIdx.x & 63;
@@ -977,13 +976,13 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
   // the utilities and reaches of levels 0 .. top-1 belong to wave 0, a lane each
   const int top = __builtin_amdgcn_readfirstlane(top_levels());
   const int n_top = nb(top);
-  const int down0 = top > 0 ? 2 : 0;         // first interval with a step down
+  const int down0 = top > 0 ? 1 : 0;         // first interval with a step down
   const int first_down = top > 0 ? top : 1;  // its first level
   const int n_up = bottom - top + 1, n_down = (bottom - first_down + 2) / 2;
   const int n_int = n_up > down0 + n_down ? n_up : down0 + n_down;
   const bool top_wave = top > 0 && wave == 0;
   // the way up begins with the first waves, which the hardware prefers, the way
-  // down and the list with the last
+  // down and the list's second part with the last
   const int last_tid = (BLOCK / 64 - 1 - wave) * 64 + lane;
 
   auto value = [&](uint2 w) {
@@ -1024,7 +1023,9 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
   // and down (possibly past the level's end); their words never change and are
   // fetched one interval ahead.  Wave 0 joins the updates in their second round.
   const int first_update = top_wave ? n_top + BLOCK - 64 + tid : top > 0 ? n_top + tid - 64 : tid;
-  auto up_id = [&](int iv) { return iv >= n_int ? first_update : nb(bottom - iv) + tid; };
+  auto up_id = [&](int iv) {
+    return iv >= n_int ? first_update : nb(bottom - iv) + (iv == 0 && top > 0 ? last_tid : tid);
+  };
   auto down_id = [&](int iv) { return nb(first_down + 2 * (iv - down0)) + last_tid; };
   auto clamp = [&](int id) { return id < na ? id : na - 1; };
   const uint2 top_kids = w_kids[clamp(lane)];
@@ -1054,18 +1055,18 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
     }
     __builtin_amdgcn_s_setprio(0);
   };
-  const Place top_place = place(last_tid);
+  const Place top_place = place(lane);
   uint2 up_w = w_kids[clamp(up_id(0))];
   uint2 down_w = make_uint2(0, 0);
   if (down0 == 0) down_w = make_uint2(w_kids[clamp(down_id(0))].y, w_up[clamp(down_id(0))]);
 
-  c.ik = ks[0];
   IterK next = ks[0];
   for (int it = 0; it < n_iters; ++it) {
+    c.ik = next;
+    next = ks[it + 1 < n_iters ? it + 1 : it];
     // utilities go up from the bottom level to `top`, one level per interval,
-    // while the top levels are updated for the iteration before (their words and
-    // utilities stay until the way up reaches them) and reaches go down, wave 0's
-    // in the second interval, then two levels per interval
+    // while reaches go down, wave 0's in the first interval, then two levels per
+    // interval
     for (int iv = 0; iv < n_int; ++iv) {
       const int ul = bottom - iv, dl = first_down + 2 * (iv - down0);
       uint2 next_up = up_w, next_down = down_w;
@@ -1074,8 +1075,7 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
         const int id = clamp(down_id(iv + 1));
         next_down = make_uint2(w_kids[id].y, w_up[id]);
       }
-      if (iv == 0 && it > 0) update_list(top_place, last_tid, n_list_top);
-      if (iv == 1 && top_wave) {
+      if (iv == 0 && top_wave) {
         for (int l = 1; l < top; l += 2) {
           if (lane >= nb(l) && lane < nb(l + 2 < top ? l + 2 : top))
             down(lane, top_kids.y, top_up);
@@ -1084,7 +1084,7 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
       }
       if (ul >= top) {
         const int end = nb(ul + 1);
-        int id = nb(ul) + tid;
+        int id = up_id(iv);
         for (uint2 w = up_w; id < end; id += BLOCK, w = w_kids[clamp(id)]) {
           const double uh = value(w);
           if (ul == 0) vacc[id] += uh;
@@ -1105,9 +1105,8 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
       seg_store_reach<T, BLOCK, FORM>(far, L);
       __syncthreads();
     }
-    // the updates below the top levels; wave 0 finishes these levels' utilities
-    c.ik = next;
-    next = ks[it + 1 < n_iters ? it + 1 : it];
+    // the updates; wave 0 finishes the top levels' utilities first, whose
+    // strategies no other wave changes, and then updates these levels
     uint2 w = up_w;
     up_w = w_kids[clamp(up_id(0))];
     if (down0 == 0) down_w = make_uint2(w_kids[clamp(down_id(0))].y, w_up[clamp(down_id(0))]);
@@ -1119,6 +1118,7 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
         }
         wave_order<FORM>();
       }
+      update_list(top_place, lane, n_list_top);
     }
     update_list(place(n_list_top + last_tid), n_list_top + last_tid, n_list);
     for (int id = first_update; id < na; id += BLOCK) {
@@ -1127,8 +1127,6 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
     }
     __syncthreads();
   }
-  update_list(top_place, last_tid, n_list_top);
-  __syncthreads();
   seg_store<T, BLOCK, FORM>(D, roots, far, L, na, ne, ks, n_iters, variant);
 }
 
