@@ -74,6 +74,7 @@ def lib():
         L = C.CDLL(LIB_PATH)
         vp, i64, i32 = C.c_void_p, C.c_int64, C.c_int
         L.pasur_last_error.restype = C.c_char_p
+        L.pasur_release_cache.restype = None
         L.pasur_build_round_tree.argtypes = [vp, i32, vp, i64, C.POINTER(vp), vp]
         L.pasur_gt_sizes.argtypes = [vp, vp]
         L.pasur_gt_read.argtypes = [vp, i32, i32, vp]
@@ -286,14 +287,22 @@ class CfrState:
         tdt = torch.float32 if dtype == PASUR_F32 else torch.float64
         n = fgt.n
         dev = torch.device("cuda")
-        self.sigma = [None] + [torch.empty(n[l], dtype=tdt, device=dev) for l in range(1, 9)]
-        self.R = [None] + [torch.empty(n[l], dtype=tdt, device=dev) for l in range(1, 9)]
-        self.Sbar = [None] + [torch.empty(n[l], dtype=tdt, device=dev) for l in range(1, 9)]
-        self.reachA = [torch.empty(n[l], dtype=tdt, device=dev) for l in range(8)] + [None]
-        self.reachB = [torch.empty(n[l], dtype=tdt, device=dev) for l in range(8)] + [None]
-        self.u = [torch.empty(n[l], dtype=tdt, device=dev) for l in range(9)]
+
+        def empty(n_l):
+            try:
+                return torch.empty(n_l, dtype=tdt, device=dev)
+            except torch.OutOfMemoryError:  # the library keeps some of what freed trees held
+                lib().pasur_release_cache()
+                return torch.empty(n_l, dtype=tdt, device=dev)
+
+        self.sigma = [None] + [empty(n[l]) for l in range(1, 9)]
+        self.R = [None] + [empty(n[l]) for l in range(1, 9)]
+        self.Sbar = [None] + [empty(n[l]) for l in range(1, 9)]
+        self.reachA = [empty(n[l]) for l in range(8)] + [None]
+        self.reachB = [empty(n[l]) for l in range(8)] + [None]
+        self.u = [empty(n[l]) for l in range(9)]
         self.vacc = torch.zeros(n[0], dtype=torch.float64, device=dev)
-        self.sigma_bar = [None] + [torch.empty(n[l], dtype=tdt, device=dev) for l in range(1, 9)]
+        self.sigma_bar = [None] + [empty(n[l]) for l in range(1, 9)]
         st = _State()
         st.dtype = dtype
         for name in ("sigma", "R", "Sbar", "reachA", "reachB", "u"):

@@ -30,11 +30,21 @@ void set_error(const char *fmt, ...);
     if (s_ != PASUR_OK) return s_;                                            \
   } while (0)
 
+// Gives the cached blocks of the current device back (below); a failed
+// allocation of any kind is tried again after it.
+void blocks_release();
+hipError_t malloc_async(void **p, size_t bytes, hipStream_t s);  // hipMallocAsync
+
 template <class T>
 int dev_alloc(T **p, int64_t n) {
   *p = nullptr;
   size_t bytes = (size_t)(n > 0 ? n : 1) * sizeof(T);
   hipError_t e = hipMalloc((void **)p, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    blocks_release();
+    e = hipMalloc((void **)p, bytes);
+  }
   if (e != hipSuccess) {
     set_error("hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
     *p = nullptr;

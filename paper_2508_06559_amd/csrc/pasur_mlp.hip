@@ -1254,7 +1254,7 @@ int backward_workspace(hipStream_t s, size_t bytes, void **out) {
     if (ws.first) (void)hipFreeAsync(ws.first, s);
     ws = std::make_pair(nullptr, (size_t)0);
     void *p = nullptr;
-    const hipError_t e = hipMallocAsync(&p, bytes, s);
+    const hipError_t e = malloc_async(&p, bytes, s);
     if (e != hipSuccess) {
       set_error("MLP backward workspace (%zu bytes): %s", bytes, hipGetErrorString(e));
       return PASUR_E_NOMEM;
@@ -1626,7 +1626,7 @@ extern "C" int pasur_warm_start_round(const pasur_gt *gt, const pasur_fgt *fgt,
   const bool own = !workspace || workspace_bytes < warm_bytes(rows);
   hipError_t e = hipSuccess;
   if (own) {
-    e = hipMallocAsync((void **)&Y, sizeof(float) * (size_t)rows * kOut, s);
+    e = malloc_async((void **)&Y, sizeof(float) * (size_t)rows * kOut, s);
   } else {
     Y = (float *)workspace;
   }
@@ -1710,7 +1710,7 @@ int fused_forward(const pasur_mlp_weights *w, const Input &in, int64_t M, float 
   const __bf16 *W1t = (const __bf16 *)w->W1t, *W2t = (const __bf16 *)w->W2t;
   hipError_t e = hipSuccess;
   if (!W1t || !W2t) {
-    e = hipMallocAsync((void **)&Wt, sizeof(__bf16) * (size_t)(kIn + kHid) * kHid, s);
+    e = malloc_async((void **)&Wt, sizeof(__bf16) * (size_t)(kIn + kHid) * kHid, s);
     if (e != hipSuccess) {
       set_error("MLP fused forward workspace: %s", hipGetErrorString(e));
       return PASUR_E_NOMEM;

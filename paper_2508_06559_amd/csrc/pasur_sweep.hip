@@ -1326,7 +1326,7 @@ int sweep_t(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p, 
   unsigned char *buf = nullptr;
   Tail<T> tl;
   if (S) {
-    PASUR_TRY_HIP(hipMallocAsync((void **)&buf, tail_bytes<T>(x), s));
+    PASUR_TRY_HIP(malloc_async((void **)&buf, tail_bytes<T>(x), s));
     tail_carve<T>(x, buf, tl);
   }
   {

@@ -19,9 +19,10 @@ void set_error(const char *fmt, ...) {
 
 namespace {
 // Freed blocks, at most kCacheBytes of them per device (3% of its memory) in at
-// most kCacheBlocks places; what does not fit is given back to the system, and
-// everything is when an allocation fails.  Blocks are handed out again only to
-// requests of a similar size.
+// most kCacheBlocks places; what does not fit is given back to the system, as is
+// what comes back when an eighth of the device or less is free, and everything
+// when an allocation fails or the caller asks for it.  Blocks are handed out
+// again only to requests of a similar size.
 constexpr size_t kCacheBytes = (size_t)8 << 30;
 constexpr int kCacheBlocks = 512;
 struct Block {
@@ -125,8 +126,28 @@ void block_free(void *p) {
   size_t cached = 0;
   for (int i = 0; i < g_n_free; ++i)
     if (g_free[i].device == b.device) cached += g_free[i].bytes;
-  if (g_n_free < kCacheBlocks && cached + b.bytes <= kCacheBytes) g_free[g_n_free++] = b;
+  bool keep = g_n_free < kCacheBlocks && cached + b.bytes <= kCacheBytes;
+  if (keep && b.bytes >= ((size_t)64 << 20)) {
+    size_t free_bytes = 0, total = 0;
+    keep = hipMemGetInfo(&free_bytes, &total) == hipSuccess && free_bytes > total / 8;
+  }
+  if (keep) g_free[g_n_free++] = b;
   else (void)hipFree(b.p);
+}
+
+void blocks_release() {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return;
+  std::lock_guard<std::mutex> lock(g_block_mu);
+  release_cached(device);
+}
+
+hipError_t malloc_async(void **p, size_t bytes, hipStream_t s) {
+  const hipError_t e = hipMallocAsync(p, bytes, s);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  blocks_release();
+  return hipMallocAsync(p, bytes, s);
 }
 
 int anchor_alloc(void **a) {
@@ -205,3 +226,4 @@ int scan_counts(const int32_t *d_counts, int64_t n, int32_t *d_out,
 
 extern "C" const char *pasur_last_error(void) { return pasur::g_err; }
 extern "C" int pasur_version(void) { return 1; }
+extern "C" void pasur_release_cache(void) { pasur::blocks_release(); }

@@ -237,7 +237,7 @@ int composed(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar,
   for (int r = 1; r < n_rounds; ++r) most = std::max(most, fgts[r]->n[0]);
   double *buf = nullptr;
   if (most > 0) {
-    const hipError_t e = hipMallocAsync((void **)&buf, 2 * NM * most * sizeof(double), s);
+    const hipError_t e = malloc_async((void **)&buf, 2 * NM * most * sizeof(double), s);
     if (e != hipSuccess) {
       set_error("hipMallocAsync: %s", hipGetErrorString(e));
       return PASUR_E_NOMEM;
