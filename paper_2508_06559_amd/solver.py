@@ -42,7 +42,9 @@ class SubgameSolver:
         self.rounds: List[RoundResult] = []
         d_roots = roots_to_device(roots)
         self._root_tensor = d_roots
+        self.torch = torch
         ptr, n = d_roots.data_ptr(), len(roots)
+        self._fork()
         for r in range(start_round, 6):
             gt = build_round_tree(self.deck, r, ptr, n, stream)
             fgt = unfold_scores(gt, ptr, n, stream)
@@ -52,13 +54,23 @@ class SubgameSolver:
             self.rounds.append(RoundResult(r, fgt, gt=gt))
             if r < 5:
                 ptr, n = fgt.next_roots_device()
-        self.torch = torch
 
     def sizes(self):
         return [rr.fgt.n for rr in self.rounds]
 
     def edges(self) -> int:
         return sum(rr.fgt.edges() for rr in self.rounds)
+
+    def _fork(self):
+        """What the caller's stream holds (new tensors' memory) comes first."""
+        if self.stream is not None:
+            self.stream.wait_stream(self.torch.cuda.current_stream())
+
+    def _join(self):
+        """The caller's stream waits for the solver's: the library's calls only
+        enqueue work, and returned tensors are read on the caller's stream."""
+        if self.stream is not None:
+            self.torch.cuda.current_stream().wait_stream(self.stream)
 
     def solve(self, iters: int, params=None, value_mode: int = V_ITERATE_MEAN,
               round_events=None, on_round=None):
@@ -73,6 +85,7 @@ class SubgameSolver:
         for rr in reversed(self.rounds):
             st = rr.state if rr.state is not None else CfrState(rr.fgt, self.dtype)
             rr.state = st
+            self._fork()
             leaf_utilities(rr.fgt, V, self.dtype, st.u[8], self.stream, self.literal_bonus0)
             cfr_init(st, self.stream)
             if round_events is not None:
@@ -86,8 +99,10 @@ class SubgameSolver:
                 on_round(rr.round)
             average_strategy(st, self.stream)
             rr.V = torch.empty(rr.fgt.n[0], dtype=torch.float64, device="cuda")
+            self._fork()
             round_values(st, value_mode, rr.V, self.stream)
             V = rr.V
+        self._join()
         return self.rounds[0].V
 
     def solve_es(self, iters: int, seed: int, rm_mode: int = RM_FLOOR, eps: float = 1e-8,
@@ -101,13 +116,16 @@ class SubgameSolver:
         for rr in reversed(self.rounds):
             st = rr.state if rr.state is not None else CfrState(rr.fgt, self.dtype)
             rr.state = st
+            self._fork()
             leaf_utilities(rr.fgt, V, self.dtype, st.u[8], self.stream, self.literal_bonus0)
             cfr_init(st, self.stream)
             es_iterate(st, iters, seed, rm_mode, eps, schedule=schedule, stream=self.stream)
             average_strategy(st, self.stream)
             rr.V = torch.empty(rr.fgt.n[0], dtype=torch.float64, device="cuda")
+            self._fork()
             round_values(st, V_SIGMA_BAR, rr.V, self.stream)
             V = rr.V
+        self._join()
         return self.rounds[0].V
 
     def exploitability(self):
@@ -118,8 +136,10 @@ class SubgameSolver:
         torch = self.torch
         n0 = self.rounds[0].fgt.n[0]
         out = [torch.empty(n0, dtype=torch.float64, device="cuda") for _ in range(3)]
+        self._fork()
         exploitability([rr.fgt for rr in self.rounds], [rr.state.sigma_bar for rr in self.rounds],
                        self.dtype, out[0], out[1], out[2], self.stream, self.literal_bonus0)
+        self._join()
         return tuple(out)
 
     def selfplay(self, n_games: int, seed: int, policy_a: int = PLAY_SIGMA_BAR,
@@ -132,8 +152,10 @@ class SubgameSolver:
         torch = self.torch
         margin = torch.empty(max(n_games, 1), dtype=torch.int32, device="cuda")
         sb = strategies if strategies is not None else [rr.state.sigma_bar for rr in self.rounds]
+        self._fork()
         selfplay([rr.fgt for rr in self.rounds], sb, self.dtype, root, n_games, seed, policy_a,
                  policy_b, margin, self.stream)
+        self._join()
         return margin[:n_games]
 
     def free(self):

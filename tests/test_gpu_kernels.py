@@ -271,6 +271,28 @@ def test_exploitability_outputs_one_at_a_time(which):
     s.free()
 
 
+def test_results_of_a_solver_with_its_own_stream():
+    """Solves and best responses on a stream of the solver's own: what they return
+    is read on the caller's stream without waiting."""
+    pa = require_gpu()
+    import torch
+    deck, roots = playout(pa, 101, 3)
+    ref = pa.SubgameSolver(deck, 3, roots)
+    s = pa.SubgameSolver(deck, 3, roots, stream=torch.cuda.Stream())
+    for iters in (3, 40, 10):
+        want = [float(ref.solve(iters)[0])] + [float(x[0]) for x in ref.exploitability()]
+        for _ in range(3):
+            V = s.solve(iters)
+            got = [float(V[0])]
+            a, b, v = s.exploitability()
+            assert float(((a - b) / 2).max()) >= 0.0
+            assert got + [float(x[0]) for x in (a, b, v)] == want
+            m = s.selfplay(1000, 7)
+            assert int(m.sum()) == int(ref.selfplay(1000, 7).sum())
+    s.free()
+    ref.free()
+
+
 @pytest.mark.parametrize("n", [1, 7, 31, 32, 33, 257])
 def test_feature_rows_at_any_offset(n):
     """Rows of 384 bytes to aligned and unaligned places, all edges in order or
