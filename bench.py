@@ -43,19 +43,19 @@ METRIC = "CFR node-updates/s at 1 GPU; secs to exploitability 1e-3, warm-start v
 # counter summaries under profiles/).  Valid only while the kernel's source
 # file is unchanged (sha256 recorded with the counters).
 TRAFFIC = {
-    # k_cfr_seg, two-round subgame of deal 1 (average of its two launches)
-    "two-round": {"source": "paper_2508_06559_amd/csrc/pasur_cfr.hip",
-                  "sha256": "8a5ddb5c77265daad665dce4f88b4a8561c5daf99c8fbfcfc7c9ae652406889c",
-                  "bytes": 4.60e6},
-    # k_cfr_seg, the batched solve's largest launch (round 6 of all 64 deals)
-    "batched": {"source": "paper_2508_06559_amd/csrc/pasur_cfr.hip",
-                "sha256": "8a5ddb5c77265daad665dce4f88b4a8561c5daf99c8fbfcfc7c9ae652406889c",
-                "bytes": 1.226e12},
-    # the full game's dominant streaming kernel (average over its launches)
+    # k_cfr_seg: not counted since its state is iterated in the compact form
+    "two-round": {"source": "paper_2508_06559_amd/csrc/pasur_seg.hip", "sha256": None, "bytes": None},
+    "batched": {"source": "paper_2508_06559_amd/csrc/pasur_seg.hip", "sha256": None, "bytes": None},
+    # the full game's dominant streaming kernel (one of round 6's launches)
     "full-game": {"source": "paper_2508_06559_amd/csrc/pasur_sweep.hip",
-                  "sha256": "b709966b880899046598e783d0007aaedb0aeb2b4c2c72f3c58875b6926fa956",
-                  "bytes": 2.134e9},
+                  "sha256": "00091aad91bd74f519c7e61583ef271ae96578b86d799baaeeee6acee9f7377a",
+                  "bytes": 5.198e9},
 }
+
+
+def streamed(nodes, iters):
+    """Whether the automatic schedule streams a round (its root sizes aside)."""
+    return nodes >= 9_000_000 and (nodes >= 250_000_000 or iters < 4 + nodes // 12_000_000)
 
 
 def counted_traffic(args, workload="two-round"):
@@ -462,7 +462,7 @@ def bench_full(args):
         ms_r = round_ms[5 - r] if len(round_ms) == 6 else None
         b_r, t_r, lds_r = round_alg.get(r, (0.0, 0.0, None))
         rounds.append({"round": r + 1, "nodes": int(sum(n)), "edges": int(e_r),
-                       "schedule": (("stream" if sum(n) >= 9_000_000 else "persistent segments")
+                       "schedule": (("stream" if streamed(sum(n), iters) else "persistent segments")
                                     if args.sched == "auto" else args.sched),
                        "dcfr_ms": ms_r,
                        "node_updates_per_s": e_r * iters / (ms_r * 1e-3) if ms_r else None,
