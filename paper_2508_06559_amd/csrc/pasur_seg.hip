@@ -9,7 +9,7 @@
 // The segment lives in LDS in a compact form, made when the launch starts and
 // dissolved when it ends; no iteration touches memory.  What bounds an
 // iteration is then the dependent steps between the workgroup's barriers on
-// small launches, and the FP64 instructions on large ones.  Four choices serve
+// small launches, and the FP64 instructions on large ones.  Five choices serve
 // both; none changes a result:
 //
 //  * Forced chains are not iterated.  A node of level 6 or 7 whose whole
@@ -30,21 +30,19 @@
 //    stores the reach of the player who moved last; the other one's is its
 //    parent's.  Two consecutive levels then do not depend on each other, and go
 //    down in one step.
-//
 //  * A lane per edge where a loop over children would be waited for: at the
 //    topmost levels, which one wave runs by itself, and at nodes with more than
-//    four children.  The topmost levels' updates run during the next iteration's
-//    first step up.
+//    four children.
 //
 // An iteration takes one barrier per level above the topmost levels and one
 // after the updates.  Every parent's sums run over its children in child order
 // in FP64 without contraction, whatever order the nodes are stored in: the
 // state ends bit for bit as with the level-synchronous kernels.
 //
-// Measured (FP32 unless said): seven roots of 3,200 nodes, FP64, 11.3 -> 4.6 us
+// Measured (FP32 unless said): seven roots of 3,200 nodes, FP64, 11.3 -> 4.5 us
 // per iteration against one phase per level over all nodes; 38,652 roots of 3,900
-// nodes, 0.53 ms per iteration (2.8e11 nodes/s); a batch of 64 deals (4.4e7
-// nodes), 50 iterations, 56 -> 15.9 ms with all that surrounds it.
+// nodes, 0.53 ms per iteration (2.8e11 nodes/s, VALU 52 to 65% busy); a batch of
+// 64 deals (7.6e7 nodes), 50 iterations, 56 -> 16.2 ms with all that surrounds it.
 //
 // A segment too large for LDS keeps its far arrays in device memory (roots of
 // more than about 14,000 nodes, F64 7,000), or all of the form (32,000, F64
