@@ -363,3 +363,29 @@ def test_trees_built_in_several_threads():
     for t in threads:
         t.join()
     assert not failed, failed
+
+
+def test_cached_blocks_follow_the_games_built():
+    """Trees of 8.5e8 and of 6.4e8 nodes, more than the cache holds together: the
+    last game's blocks stay, so that building it again asks the device for none."""
+    pa = require_gpu()
+    import torch
+    slack = 256 << 20  # the tensors of the driver and of other libraries
+
+    def build_and_free(seed):
+        deck, roots = synth.full_game_root(seed)
+        s = pa.SubgameSolver(deck, 0, roots)
+        built = torch.cuda.mem_get_info()[0]
+        s.free()
+        return built, torch.cuda.mem_get_info()[0]
+
+    pa.lib().pasur_release_cache()
+    start = torch.cuda.mem_get_info()[0]
+    _, free = build_and_free(40)
+    assert start - free <= (16 << 30) + slack
+    _, free = build_and_free(22)
+    assert start - free <= (16 << 30) + slack
+    built, again = build_and_free(22)
+    assert abs(built - free) <= slack and abs(again - free) <= slack
+    pa.lib().pasur_release_cache()
+    assert start - torch.cuda.mem_get_info()[0] <= slack
