@@ -1,14 +1,16 @@
 // pasur_play.hip -- self-play with average strategies: the paper's way of
-// estimating a deal's fair value (section "Experimental Evaluation").  One
-// thread per game walks the unfolded trees of a solved subgame from a root:
-// at each decision the player to move samples one child (inverse CDF of the
-// average strategy, or uniformly at random); at a round's last level the
+// estimating a deal's fair value (section "Experimental Evaluation").  A
+// thread walks the unfolded trees of a solved subgame from a root, for one game
+// or several: at each decision the player to move samples one child (inverse CDF
+// of the average strategy, or uniformly at random); at a round's last level the
 // game adds the leaf's round points and continues at the linked next-round
 // root.  Random numbers come from a counter-based SplitMix64 stream, so any
 // game can be replayed on its own.
 #include "pasur_internal.hpp"
 
+#include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 using namespace pasur;
 
@@ -21,33 +23,78 @@ struct PlayRound {
   const void *sbar[9];
   const int32_t *link;
   const int16_t *base;
+  int32_t n[9];  // nodes per level
 };
 
 struct PlayArgs {
   PlayRound r[kMaxRounds];
   int n_rounds, dtype, policy[2], root;
   uint64_t seed;
-  int64_t n_games;
+  int64_t first, n_games;  // games first .. n_games - 1
 };
 
-// kGamesPerThread games per thread, g, g + stride, ... (stride = threads in
-// the grid), stepped together so that their dependent gathers overlap (one
-// game per thread: 19.3 ms per three matchups of 2^24 full games; two 17.7,
-// four 16.2, eight 15.5).  A thread's games past the last one are played
-// (indices stay valid) and their margins dropped.
-constexpr int kGamesPerThread = 8;
-
+// The strategy at a node's first four children, in one load where the level does
+// not end before.
 template <class T>
+struct First {
+  T p[4];
+  __device__ __forceinline__ void load(const T *sb, int32_t b, int k, int32_t n) {
+    if (b + 4 <= n) {
+      __builtin_memcpy(p, sb + b, sizeof(p));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) p[c] = c < k ? sb[b + c] : (T)0;
+    }
+  }
+};
+
+// choose_by with the first four probabilities in registers, the others at rest[c].
+template <class T>
+__device__ __forceinline__ int choose_first(double u, const First<T> &f, const T *rest, int k) {
+  const int uni = min((int)(u * (double)k), k - 1);
+  double total = 0.0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (c < k) total += (double)f.p[c];
+  for (int c = 4; c < k; ++c) total += (double)rest[c];
+  if (!(total > 0.0)) return uni;
+  const double x = u * total;
+  double acc = 0.0;
+  int last = 0, pick = -1;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (c < k && pick < 0) {
+      const double pc = (double)f.p[c];
+      acc += pc;
+      if (pc > 0.0) last = c;
+      if (acc > x) pick = c;
+    }
+  for (int c = 4; c < k && pick < 0; ++c) {
+    const double pc = (double)rest[c];
+    acc += pc;
+    if (pc > 0.0) last = c;
+    if (acc > x) pick = c;
+  }
+  return pick < 0 ? last : pick;
+}
+
+// G games per thread, g, g + stride, ... (stride = threads in the grid), stepped
+// together so that their dependent gathers overlap; T = void where both players
+// are uniform.  A thread's games past the last one are played (indices stay
+// valid) and their margins dropped.  Bound by the chain of two dependent gathers
+// per decision: 2^20 games of a game of 3.4e7 nodes with one average strategy, 286
+// us with eight games per thread and a load per child and per end of the range,
+// 195 with four and the wide loads; 2700 games of three rounds 110 us, 18 with one.
+template <class T, int G>
 __global__ void k_selfplay(PlayArgs a, int32_t *__restrict__ margin) {
-  constexpr int G = kGamesPerThread;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g0 >= a.n_games) return;
+  if (g0 >= a.n_games - a.first) return;
   int64_t g[G];
   int32_t q[G], m[G];
 #pragma unroll
   for (int i = 0; i < G; ++i) {
-    g[i] = g0 + i * stride;
+    g[i] = a.first + g0 + i * stride;
     q[i] = a.root;
     m[i] = 0;
   }
@@ -57,18 +104,42 @@ __global__ void k_selfplay(PlayArgs a, int32_t *__restrict__ margin) {
       int32_t b[G], e[G];
 #pragma unroll
       for (int i = 0; i < G; ++i) {
-        b[i] = R.cb[l][q[i]];
-        e[i] = R.cb[l][q[i] + 1];
+        int32_t be[2];
+        __builtin_memcpy(be, R.cb[l] + q[i], sizeof(be));
+        b[i] = be[0];
+        e[i] = be[1];
       }
+      if constexpr (std::is_void<T>::value) {
 #pragma unroll
-      for (int i = 0; i < G; ++i) {
-        const int k = e[i] - b[i];
-        int c = 0;
-        if (k > 1) {
-          const double u = splitmix_uniform(a.seed, (uint64_t)g[i] * 64u + (uint64_t)(r * 8 + l));
-          c = choose<T>(u, reinterpret_cast<const T *>(R.sbar[l + 1]) + b[i], k, a.policy[l & 1]);
+        for (int i = 0; i < G; ++i) {
+          const int k = e[i] - b[i];
+          q[i] = b[i];
+          if (k > 1) {
+            const double u =
+                splitmix_uniform(a.seed, (uint64_t)g[i] * 64u + (uint64_t)(r * 8 + l));
+            q[i] += min((int)(u * (double)k), k - 1);
+          }
         }
-        q[i] = b[i] + c;
+      } else {
+        const T *const sb = reinterpret_cast<const T *>(R.sbar[l + 1]);
+        const bool uniform = a.policy[l & 1] == PASUR_PLAY_UNIFORM;
+        First<T> f[G];
+        if (!uniform) {
+#pragma unroll
+          for (int i = 0; i < G; ++i)
+            if (e[i] - b[i] > 1) f[i].load(sb, b[i], e[i] - b[i], R.n[l + 1]);
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+          const int k = e[i] - b[i];
+          int c = 0;
+          if (k > 1) {
+            const double u =
+                splitmix_uniform(a.seed, (uint64_t)g[i] * 64u + (uint64_t)(r * 8 + l));
+            c = uniform ? min((int)(u * (double)k), k - 1) : choose_first(u, f[i], sb + b[i], k);
+          }
+          q[i] = b[i] + c;
+        }
       }
     }
 #pragma unroll
@@ -80,6 +151,20 @@ __global__ void k_selfplay(PlayArgs a, int32_t *__restrict__ margin) {
 #pragma unroll
   for (int i = 0; i < G; ++i)
     if (g[i] < a.n_games) margin[g[i]] = m[i];
+}
+
+// A launch's threads stay below 2^32.
+template <class T, int G>
+int play(PlayArgs a, int32_t *d_margin, hipStream_t s) {
+  constexpr int64_t kGames = (int64_t)1 << 31;
+  const int64_t n_games = a.n_games;
+  for (a.first = 0; a.first < n_games; a.first += kGames) {
+    a.n_games = std::min(n_games, a.first + kGames);
+    const int64_t threads = (a.n_games - a.first + G - 1) / G;
+    k_selfplay<T, G><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(a, d_margin);
+    PASUR_TRY_HIP(hipGetLastError());
+  }
+  return PASUR_OK;
 }
 
 }  // namespace
@@ -141,6 +226,7 @@ extern "C" int pasur_selfplay(const pasur_fgt *const *fgts, int n_rounds,
     }
     a.r[r].link = f->link;
     a.r[r].base = f->leaf_base;
+    for (int l = 0; l <= 8; ++l) a.r[r].n[l] = (int32_t)f->n[l];
   }
   if (root < 0 || root >= fgts[0]->n[0]) {
     set_error("root %d outside 0..%lld", root, (long long)fgts[0]->n[0] - 1);
@@ -155,12 +241,18 @@ extern "C" int pasur_selfplay(const pasur_fgt *const *fgts, int n_rounds,
   a.seed = seed;
   a.n_games = n_games;
   hipStream_t s = (hipStream_t)stream;
-  const int64_t threads = (n_games + kGamesPerThread - 1) / kGamesPerThread;
-  const unsigned grid = (unsigned)((threads + 255) / 256);
+  // One game per thread while that leaves no game waiting for another's steps: up
+  // to 2^19 games all threads run at once (eight waves per SIMD).  Beyond that more
+  // games per thread keep more loads in flight.  2^18, 2^20, 2^24 games of a game of
+  // 3.4e7 nodes, one side by its average strategy: 1 game per thread 62, 221, 3450
+  // us, 4 games 91, 204, 3160, 8 games 161, 229, 2920 (with FP64 averages 294, 444,
+  // 6810: spills).  Uniform players' games spread over the whole tree and need no
+  // strategies: 1 game per thread 62, 301, 5900 us, 4 games 71, 260, 5290, 8 games
+  // 99, 204, 4910.
+  if (policy_a == PASUR_PLAY_UNIFORM && policy_b == PASUR_PLAY_UNIFORM)
+    return n_games <= (1 << 18) ? play<void, 1>(a, d_margin, s) : play<void, 8>(a, d_margin, s);
+  const bool one = n_games <= (1 << 19);
   if (dtype == PASUR_F32)
-    k_selfplay<float><<<grid, 256, 0, s>>>(a, d_margin);
-  else
-    k_selfplay<double><<<grid, 256, 0, s>>>(a, d_margin);
-  PASUR_TRY_HIP(hipGetLastError());
-  return PASUR_OK;
+    return one ? play<float, 1>(a, d_margin, s) : play<float, 4>(a, d_margin, s);
+  return one ? play<double, 1>(a, d_margin, s) : play<double, 4>(a, d_margin, s);
 }

@@ -389,3 +389,25 @@ def test_cached_blocks_follow_the_games_built():
     assert abs(built - free) <= slack and abs(again - free) <= slack
     pa.lib().pasur_release_cache()
     assert start - torch.cuda.mem_get_info()[0] <= slack
+
+
+# one game per thread up to 2^18 games of two uniform players and 2^19 others,
+# several beyond: the same game under its number in both
+@pytest.mark.parametrize("dtype_name", ["PASUR_F32", "PASUR_F64"])
+@pytest.mark.parametrize("start", [4, 5])
+def test_games_do_not_depend_on_their_number(start, dtype_name):
+    pa = require_gpu()
+    import torch
+    deck, roots = playout(pa, 102, start)
+    s = pa.SubgameSolver(deck, start, roots, dtype=getattr(pa, dtype_name))
+    s.solve(30)
+    S, U = pa.PLAY_SIGMA_BAR, pa.PLAY_UNIFORM
+    for pol, line in (((S, S), 1 << 19), ((S, U), 1 << 19), ((U, S), 1 << 19), ((U, U), 1 << 18)):
+        want = s.selfplay(line, 3, *pol)
+        for n in (1, 257, line - 1, line + 1, 2 * line + 255):
+            got = s.selfplay(n, 3, *pol)
+            assert got.shape == (n,)
+            m = min(n, line)
+            assert torch.equal(got[:m], want[:m]), (pol, n)
+        assert len(torch.unique(want)) > (pol != (S, S)), pol
+    s.free()
