@@ -851,7 +851,7 @@ def bench_selfplay(args):
                                   f"({sum(sum(x) for x in sizes)} nodes, {iters} DCFR iterations per "
                                   f"round): {n} games per matchup, 3 matchups per step",
                       "state": args.state, "matchups": stats},
-           "roofline": {"bound": "hbm", "kernel": "k_selfplay (one thread per game, dependent "
+           "roofline": {"bound": "hbm", "kernel": "k_selfplay (dependent "
                                                   "child-begin gathers down one path)",
                         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": achieved / HBM_PEAK_GBS, "traffic": None,
