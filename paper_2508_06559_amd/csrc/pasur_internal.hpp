@@ -69,7 +69,11 @@ void block_free(void *p);
 // uses them is still running: an anchor is a small plain allocation, and freeing
 // it waits for the device as freeing the arrays themselves did.
 int anchor_alloc(void **a);
-void anchor_wait(void *a);
+// Frees the anchor (NULL: the blocks are idle) and gives the n blocks (at most
+// kRetired, NULLs among them) back.  Where the wait is refused, as while another
+// thread captures a stream, they are set aside until a later one succeeds.
+constexpr int kRetired = 9;
+void blocks_retire(void *anchor, void *const *blocks, int n);
 
 // Exclusive scan of n int32 counts into out[0..n] (out[n] = total); the
 // total is returned through *total (synchronises `stream`).  Fails with

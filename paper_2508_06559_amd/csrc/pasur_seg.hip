@@ -1340,7 +1340,7 @@ int root_counts(pasur_fgt *f, hipStream_t s) {
   if (e == hipSuccess) e = hipMemcpyAsync(h, d, n * sizeof(int32_t), hipMemcpyDeviceToHost, s);
   const hipError_t e2 = hipStreamSynchronize(s);
   if (e == hipSuccess) e = e2;
-  block_free(d);
+  if (e2 == hipSuccess) block_free(d);  // (else it may be in use)
   if (e != hipSuccess) {
     std::free(h);
     set_error("segment counts: %s", hipGetErrorString(e));
@@ -1593,7 +1593,12 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   pl->d_segs = (Seg *)((unsigned char *)pl->mem + at_segs);
   pl->d_ks = (IterK *)((unsigned char *)pl->mem + at_ks);
   PASUR_TRY_HIP(hipMemcpyAsync(pl->mem, stage.data(), stage.size(), hipMemcpyHostToDevice, s));
-  PASUR_TRY_HIP(hipStreamSynchronize(s));  // the staging vector goes out of scope
+  const hipError_t e = hipStreamSynchronize(s);  // the staging vector goes out of scope
+  if (e != hipSuccess) {
+    pl->mem = nullptr;  // may be in use: not handed out again
+    set_error("plan upload: %s", hipGetErrorString(e));
+    return PASUR_E_HIP;
+  }
   const bool paper = paper_variant(p->variant, p->rm_mode);
   // The attribute is a ceiling shared by every plan of this instance, so it
   // is raised to the whole budget (plans may be launched in any order); each
@@ -1618,9 +1623,8 @@ void plan_launch(const pasur_plan *pl, const SegLaunch &la, int64_t t0, int n_it
 
 extern "C" void pasur_plan_free(pasur_plan *pl) {
   if (!pl) return;
-  anchor_wait(pl->anchor);
-  block_free(pl->mem);
-  block_free(pl->far);
+  void *const blocks[] = {pl->mem, pl->far};
+  blocks_retire(pl->anchor, blocks, 2);
   delete pl;
 }
 
@@ -1707,7 +1711,8 @@ int seg_iterate(const pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_p
   pasur_plan *pl = nullptr;
   PASUR_TRY(plan_create(&f, &st, 1, p, t0, t0 + n_iters - 1, &pl, s, false));
   const int rc = pasur_plan_iterate(pl, t0, n_iters, s);
-  const hipError_t e = hipStreamSynchronize(s);  // the plan's block is idle below
+  const hipError_t e = hipStreamSynchronize(s);  // the plan's blocks are idle below
+  if (e != hipSuccess) pl->mem = pl->far = nullptr;  // or may be in use: not handed out again
   pasur_plan_free(pl);
   if (rc) return rc;
   if (e != hipSuccess) {

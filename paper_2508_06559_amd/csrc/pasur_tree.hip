@@ -310,8 +310,7 @@ DealInfo deal_info(const uint8_t *deck, int round) {
 
 extern "C" void pasur_gt_free(pasur_gt *g) {
   if (!g) return;
-  anchor_wait(g->anchor);
-  for (int l = 0; l < 9; ++l) block_free(g->block[l]);
+  blocks_retire(g->anchor, g->block, 9);
   delete g;
 }
 
@@ -706,10 +705,8 @@ __global__ void k_next_roots(int64_t n, const uint64_t *__restrict__ keys,
 
 extern "C" void pasur_fgt_free(pasur_fgt *f) {
   if (!f) return;
-  anchor_wait(f->anchor);
-  block_free(f->off_block);
-  block_free(f->block);
-  block_free(f->next_block);
+  void *const blocks[] = {f->off_block, f->block, f->next_block};
+  blocks_retire(f->anchor, blocks, 3);
   std::free(f->h_root_off);
   std::free(f->h_root_seg);
   sweep_index_free(f->sweep);

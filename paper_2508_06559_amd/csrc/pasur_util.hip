@@ -104,12 +104,43 @@ bool make_room(size_t bytes, int device) {
   }
   return g_n_free < kCacheBlocks && cached + bytes <= kCacheBytes;
 }
+
+// Blocks whose handles are gone but whose idleness is not known.
+struct Retired {
+  void *anchor, *blocks[kRetired];
+  int n;
+  Retired *next;
+};
+Retired *g_retired = nullptr;
+
+bool anchor_wait(void *a) {
+  if (!a || hipFree(a) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Waits once more for the device on behalf of blocks that were set aside.
+void retire_again() {
+  Retired *r;
+  {
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    r = g_retired;
+    g_retired = nullptr;
+  }
+  while (r) {
+    Retired *const next = r->next;
+    blocks_retire(r->anchor, r->blocks, r->n);
+    std::free(r);
+    r = next;
+  }
+}
 }  // namespace
 
 int block_alloc(void **p, size_t bytes) {
   *p = nullptr;
   int device = 0;
   PASUR_TRY_HIP(hipGetDevice(&device));
+  retire_again();
   Owned *o = (Owned *)std::malloc(sizeof(Owned));
   if (!o) {
     set_error("host allocation failed");
@@ -160,6 +191,7 @@ void block_free(void *p) {
 }
 
 void blocks_release() {
+  retire_again();
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess) return;
   std::lock_guard<std::mutex> lock(g_block_mu);
@@ -182,8 +214,19 @@ int anchor_alloc(void **a) {
   return PASUR_E_NOMEM;
 }
 
-void anchor_wait(void *a) {
-  if (a) (void)hipFree(a);
+void blocks_retire(void *anchor, void *const *blocks, int n) {
+  if (anchor_wait(anchor)) {
+    for (int i = 0; i < n; ++i) block_free(blocks[i]);
+    return;
+  }
+  Retired *r = (Retired *)std::malloc(sizeof(Retired));
+  if (!r) return;  // their memory stays unused
+  r->anchor = anchor;
+  r->n = n;
+  std::memcpy(r->blocks, blocks, (size_t)n * sizeof(void *));
+  std::lock_guard<std::mutex> lock(g_block_mu);
+  r->next = g_retired;
+  g_retired = r;
 }
 
 namespace {

@@ -1,0 +1,64 @@
+"""Device memory that freed trees and plans leave to later ones: it is idle when
+it is handed out again, and it is not kept where it is needed.  The library's
+host code runs over a HIP runtime without a device (fake_hip.c)."""
+import fake_hip
+
+
+def test_blocks_of_a_handle_wait_for_a_failed_free(tmp_path):
+    """The wait for the device that comes before a tree's blocks go back is refused,
+    as while another thread captures: nobody gets these blocks until it has
+    succeeded."""
+    fake_hip.run("""
+        st, g = fake_hip.build_round(fake, L, 7)
+        assert st == 0, L.pasur_last_error()
+        fake.pending = 1   # a caller's work on the tree
+        fake.free_status = 900
+        L.pasur_gt_free(g)
+        fake.free_status = 0
+        before = fake.mallocs
+        fake.pending = 1   # it still runs, and the wait is refused again
+        fake.free_status = 900
+        st, h = fake_hip.build_round(fake, L, 7)
+        assert st == 0
+        assert fake.mallocs - before >= 9, fake.mallocs - before
+        # once a wait succeeds they are handed out again
+        fake.free_status = 0
+        L.pasur_gt_free(h)
+        before = fake.mallocs
+        st, a = fake_hip.build_round(fake, L, 7)
+        st, b = fake_hip.build_round(fake, L, 7)
+        assert fake.mallocs - before == 2, fake.mallocs - before   # their anchors
+    """, tmp_path)
+
+
+def test_blocks_of_a_plan_wait_for_a_failed_wait(tmp_path):
+    """A call whose own wait for the stream fails does not leave its memory to
+    others."""
+    fake_hip.run("""
+        import paper_2508_06559_amd as pa
+        st, g = fake_hip.build_round(fake, L, 7)
+        st, f = fake_hip.unfold(fake, L, g, 7)
+        assert st == 0, L.pasur_last_error()
+        one = (C.c_double * 64)()
+        s = pa._State()
+        for name in ("sigma", "R", "Sbar", "reachA", "reachB", "u"):
+            for l in range(9):
+                getattr(s, name)[l] = C.addressof(one)
+        s.vacc = C.addressof(one)
+        p = pa.paper_params(pa.SCHED_ROOT)
+        run = lambda: L.pasur_cfr_iterate(f, C.byref(s), C.byref(p), 1, 2, None)
+        assert run() == 0
+        before = fake.mallocs
+        assert run() == 0
+        assert fake.mallocs == before   # the first call's memory again
+        syncs = [0]
+        def fail(): # the second wait, behind the launch, fails
+            syncs[0] += 1
+            fake.sync_status = 0 if syncs[0] < 2 else 719
+        hook = fake_hip.HOOK(fail)
+        fake.in_sync = C.cast(hook, C.c_void_p)
+        assert run() != 0
+        fake.in_sync, fake.sync_status = None, 0
+        assert run() == 0
+        assert fake.mallocs > before, "memory of the failed call handed out again"
+    """, tmp_path)
