@@ -25,6 +25,8 @@ class HostWords {
   }
   int64_t operator[](int k) const { return w[k]; }
   int wait();
+  // Nothing that writes them is pending: the last wait has succeeded.
+  bool idle() const { return !pending; }
 
  private:
   int64_t *w;  // kHostWords words, zero at first, then a link of the free list

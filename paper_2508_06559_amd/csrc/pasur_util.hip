@@ -267,9 +267,11 @@ HostWords::~HostWords() {
 }
 
 int HostWords::wait() {
-  PASUR_TRY_HIP(hipGetLastError());
-  PASUR_TRY_HIP(hipStreamSynchronize(stream));
+  // whatever an earlier call left to report, what is enqueued has to end first
+  const hipError_t earlier = hipGetLastError(), e = hipStreamSynchronize(stream);
+  PASUR_TRY_HIP(e);
   pending = false;
+  PASUR_TRY_HIP(earlier);
   return PASUR_OK;
 }
 
@@ -283,7 +285,7 @@ int scan_counts(const int32_t *d_counts, int64_t n, int32_t *d_out,
   scan_enqueue(CountsIn{d_counts}, OffsetsOut{d_out, 0}, n, 1, (int64_t *)scratch,
                host.dev(0), stream);
   const int st = host.wait();
-  block_free(scratch);
+  if (host.idle()) block_free(scratch);  // (else it may be in use)
   PASUR_TRY(st);
   *total = host[0];
   return total_fits(*total);

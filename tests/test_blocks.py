@@ -62,3 +62,32 @@ def test_blocks_of_a_plan_wait_for_a_failed_wait(tmp_path):
         assert run() == 0
         assert fake.mallocs > before, "memory of the failed call handed out again"
     """, tmp_path)
+
+
+def test_scan_scratch_is_kept_until_its_scan_has_ended(tmp_path):
+    """An error that an earlier, unrelated call left behind comes up in the middle of
+    a scan: its scratch does not go back while its kernels may run."""
+    fake_hip.run("""
+        n = 5000   # more than a tile, so that a scan has scratch
+        st, g = fake_hip.build_round(fake, L, n)
+        st, f = fake_hip.unfold(fake, L, g, n)
+        assert st == 0, L.pasur_last_error()
+        L.pasur_release_cache()
+        seg, edges = (C.c_int32 * (n + 1))(), (C.c_int32 * n)()
+        a, b = C.c_int64(), C.c_int64()
+        sample = lambda: L.pasur_sample_parents(f, 8, 1, 0.5, seg, edges, C.byref(a), C.byref(b), None)
+        # another thread releases the cache while the call waits
+        def release():
+            assert not fake.freed_pending
+            L.pasur_release_cache()
+        hook = fake_hip.HOOK(release)
+        fake.pending = fake.freed_pending = 0
+        fake.in_sync = C.cast(hook, C.c_void_p)
+        fake.last_error = 1
+        assert sample() != 0
+        assert fake.freed_pending == 0, "scratch given back while its scan is pending"
+        fake.in_sync = None
+        for k in range(31): fake.words[k] = 1
+        assert sample() == 0, L.pasur_last_error()
+        assert fake.freed_pending == 0
+    """, tmp_path)
