@@ -357,6 +357,7 @@ int build_levels(pasur_gt *g, const pasur_root *d_roots, int64_t n_roots, hipStr
   PASUR_TRY(alloc_level(g, 0, host[1], &counts));
   k_gt_roots<<<grid_for(n_roots), kThreads, 0, stream>>>(n_roots, d_roots, pos, g->pool[0],
                                                          g->hands[0], g->rs[0]);
+  (void)host.dev(0);  // and reads the scratch until it has ended
   const DealInfo di = deal_info(g->deck, g->round);
   // scans of the levels: their scratch grows with them (every scan has ended
   // when the next level's begins)

@@ -91,3 +91,16 @@ def test_scan_scratch_is_kept_until_its_scan_has_ended(tmp_path):
         assert sample() == 0, L.pasur_last_error()
         assert fake.freed_pending == 0
     """, tmp_path)
+
+
+def test_build_that_runs_out_of_memory_waits_for_its_kernels(tmp_path):
+    """No memory for the first level's scan: the roots' scratch, which the kernel
+    before it reads, goes back only after that kernel has ended."""
+    fake_hip.run("""
+        n = 5000
+        fake.failing_after, fake.failing_mallocs = 3, 2   # anchor, scratch, level 0; then none
+        st, g = fake_hip.build_round(fake, L, n)
+        assert st == -5 and not g.value, L.pasur_last_error()
+        assert fake.launches > 0 and fake.failing_mallocs == 0
+        assert fake.freed_pending == 0, "memory given back while a kernel is pending"
+    """, tmp_path)
