@@ -46,6 +46,7 @@ int dev_alloc(T **p, int64_t n) {
     e = hipMalloc((void **)p, bytes);
   }
   if (e != hipSuccess) {
+    (void)hipGetLastError();
     set_error("hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
     *p = nullptr;
     return PASUR_E_NOMEM;

@@ -157,6 +157,7 @@ int block_alloc(void **p, size_t bytes) {
       e = hipMalloc(&mem, want);
     }
     if (e != hipSuccess) {
+      (void)hipGetLastError();
       std::free(o);
       set_error("hipMalloc of %zu bytes failed: %s", want, hipGetErrorString(e));
       return PASUR_E_NOMEM;
@@ -206,13 +207,7 @@ hipError_t malloc_async(void **p, size_t bytes, hipStream_t s) {
   return hipMallocAsync(p, bytes, s);
 }
 
-int anchor_alloc(void **a) {
-  const hipError_t e = hipMalloc(a, 64);
-  if (e == hipSuccess) return PASUR_OK;
-  *a = nullptr;
-  set_error("hipMalloc: %s", hipGetErrorString(e));
-  return PASUR_E_NOMEM;
-}
+int anchor_alloc(void **a) { return dev_alloc((int64_t **)a, 8); }
 
 void blocks_retire(void *anchor, void *const *blocks, int n) {
   if (anchor_wait(anchor)) {

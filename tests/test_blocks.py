@@ -104,3 +104,20 @@ def test_build_that_runs_out_of_memory_waits_for_its_kernels(tmp_path):
         assert fake.launches > 0 and fake.failing_mallocs == 0
         assert fake.freed_pending == 0, "memory given back while a kernel is pending"
     """, tmp_path)
+
+
+def test_anchors_are_allocated_from_released_memory(tmp_path):
+    """The device is full but for what the library keeps: it gives that back for a
+    handle's anchor too, and a failed allocation leaves no error behind."""
+    fake_hip.run("""
+        st, g = fake_hip.build_round(fake, L, 7)
+        L.pasur_gt_free(g)
+        frees = fake.frees
+        fake.failing_mallocs = 1
+        st, g = fake_hip.build_round(fake, L, 7)
+        assert st == 0, L.pasur_last_error()
+        assert fake.frees - frees >= 9   # the cached blocks
+        fake.failing_mallocs = 2
+        st, h = fake_hip.build_round(fake, L, 7)
+        assert st == -5 and fake.last_error == 0
+    """, tmp_path)
