@@ -105,6 +105,17 @@ bool make_room(size_t bytes, int device) {
   return g_n_free < kCacheBlocks && cached + bytes <= kCacheBytes;
 }
 
+// More than an eighth of that device's memory is free.
+bool room_on(int device) {
+  int current = 0;
+  if (hipGetDevice(&current) != hipSuccess) return false;
+  if (current != device && hipSetDevice(device) != hipSuccess) return false;
+  size_t free_bytes = 0, total = 0;
+  const bool room = hipMemGetInfo(&free_bytes, &total) == hipSuccess && free_bytes > total / 8;
+  if (current != device) (void)hipSetDevice(current);
+  return room;
+}
+
 // Blocks whose handles are gone but whose idleness is not known.
 struct Retired {
   void *anchor, *blocks[kRetired];
@@ -181,12 +192,7 @@ void block_free(void *p) {
   *at = o->next;
   const Block b = o->b;
   std::free(o);
-  bool keep = true;
-  if (b.bytes >= ((size_t)64 << 20)) {
-    size_t free_bytes = 0, total = 0;
-    keep = hipMemGetInfo(&free_bytes, &total) == hipSuccess && free_bytes > total / 8;
-  }
-  keep = keep && make_room(b.bytes, b.device);
+  const bool keep = (b.bytes < ((size_t)64 << 20) || room_on(b.device)) && make_room(b.bytes, b.device);
   if (keep) g_free[g_n_free++] = b;
   else (void)hipFree(b.p);
 }

@@ -121,3 +121,22 @@ def test_anchors_are_allocated_from_released_memory(tmp_path):
         st, h = fake_hip.build_round(fake, L, 7)
         assert st == -5 and fake.last_error == 0
     """, tmp_path)
+
+
+def test_a_block_is_kept_by_what_its_own_device_has_free(tmp_path):
+    """A tree of device 0, freed while device 1 is current, and the other way
+    round."""
+    fake_hip.run("""
+        for full, current, kept in ((1, 1, True), (0, 1, False), (1, 0, True)):
+            fake.device = 0
+            L.pasur_release_cache()
+            st, g = fake_hip.build_round(fake, L, 2 << 20)   # blocks of 88 MB
+            assert st == 0
+            fake.free_bytes[0] = fake.free_bytes[1] = 1 << 40
+            fake.free_bytes[full] = 1 << 30
+            fake.device = current
+            frees = fake.frees
+            L.pasur_gt_free(g)
+            assert fake.device == current
+            assert (fake.frees - frees == 1) == kept, (full, current, fake.frees - frees)
+    """, tmp_path)
