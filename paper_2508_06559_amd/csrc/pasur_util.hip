@@ -33,6 +33,7 @@ struct Block {
   size_t bytes;
   int device;
 };
+// Held for the lists alone: freeing waits for the device, and allocating may.
 std::mutex g_block_mu;
 Block g_free[kCacheBlocks];
 int g_n_free = 0;
@@ -78,17 +79,30 @@ bool take_cached(size_t bytes, int device, Block *out) {
   return true;
 }
 
+// Blocks on their way back to the system: taken off the list under the lock,
+// freed at the end, when it is no longer held.
+struct Outgoing {
+  void *p[kCacheBlocks];
+  int n = 0;
+  void take(int i) {
+    p[n++] = g_free[i].p;
+    remove_cached(i);
+  }
+  ~Outgoing() {
+    for (int i = 0; i < n; ++i) (void)hipFree(p[i]);
+  }
+};
+
 void release_cached(int device) {
+  Outgoing out;
+  std::lock_guard<std::mutex> lock(g_block_mu);
   for (int i = g_n_free; i-- > 0;)
-    if (g_free[i].device == device) {
-      (void)hipFree(g_free[i].p);
-      remove_cached(i);
-    }
+    if (g_free[i].device == device) out.take(i);
 }
 
-// Gives back the device's oldest blocks until one of `bytes` has room; false if it
+// Takes off the device's oldest blocks until one of `bytes` has room; false if it
 // cannot have any.
-bool make_room(size_t bytes, int device) {
+bool make_room(size_t bytes, int device, Outgoing &out) {
   if (bytes > kCacheBytes) return false;
   size_t cached = 0;
   for (int i = 0; i < g_n_free; ++i)
@@ -99,8 +113,7 @@ bool make_room(size_t bytes, int device) {
       continue;
     }
     cached -= g_free[i].bytes;
-    (void)hipFree(g_free[i].p);
-    remove_cached(i);
+    out.take(i);
   }
   return g_n_free < kCacheBlocks && cached + bytes <= kCacheBytes;
 }
@@ -158,8 +171,12 @@ int block_alloc(void **p, size_t bytes) {
     return PASUR_E_NOMEM;
   }
   const size_t want = rounded(bytes);
-  std::lock_guard<std::mutex> lock(g_block_mu);
-  if (!take_cached(want, device, &o->b)) {
+  bool cached;
+  {
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    cached = take_cached(want, device, &o->b);
+  }
+  if (!cached) {
     void *mem = nullptr;
     hipError_t e = hipMalloc(&mem, want);
     if (e != hipSuccess) {
@@ -175,6 +192,7 @@ int block_alloc(void **p, size_t bytes) {
     }
     o->b = Block{mem, want, device};
   }
+  std::lock_guard<std::mutex> lock(g_block_mu);
   Owned **at = owned_place(o->b.p);
   o->next = *at;
   *at = o;
@@ -184,24 +202,31 @@ int block_alloc(void **p, size_t bytes) {
 
 void block_free(void *p) {
   if (!p) return;
-  std::lock_guard<std::mutex> lock(g_block_mu);
-  Owned **at = owned_place(p);
-  while (*at && (*at)->b.p != p) at = &(*at)->next;
-  if (!*at) return;
-  Owned *o = *at;
-  *at = o->next;
-  const Block b = o->b;
-  std::free(o);
-  const bool keep = (b.bytes < ((size_t)64 << 20) || room_on(b.device)) && make_room(b.bytes, b.device);
-  if (keep) g_free[g_n_free++] = b;
-  else (void)hipFree(b.p);
+  Block b;
+  {
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    Owned **at = owned_place(p);
+    while (*at && (*at)->b.p != p) at = &(*at)->next;
+    if (!*at) return;
+    Owned *o = *at;
+    *at = o->next;
+    b = o->b;
+    std::free(o);
+  }
+  bool keep = b.bytes < ((size_t)64 << 20) || room_on(b.device);
+  if (keep) {
+    Outgoing out;
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    keep = make_room(b.bytes, b.device, out);
+    if (keep) g_free[g_n_free++] = b;
+  }
+  if (!keep) (void)hipFree(b.p);
 }
 
 void blocks_release() {
   retire_again();
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess) return;
-  std::lock_guard<std::mutex> lock(g_block_mu);
   release_cached(device);
 }
 

@@ -140,3 +140,41 @@ def test_a_block_is_kept_by_what_its_own_device_has_free(tmp_path):
             assert fake.device == current
             assert (fake.frees - frees == 1) == kept, (full, current, fake.frees - frees)
     """, tmp_path)
+
+
+def test_frees_do_not_hold_up_other_threads(tmp_path):
+    """A free waits for the device: meanwhile other threads allocate, free and
+    release."""
+    fake_hip.run("""
+        import threading
+        done = []
+        def other():
+            st, g = fake_hip.build_round(fake, L, 7)
+            L.pasur_gt_free(g)
+            L.pasur_release_cache()
+            done.append(st)
+        def hook():
+            fake.in_free = None
+            t = threading.Thread(target=other, daemon=True)
+            t.start()
+            t.join(10)
+        h = fake_hip.HOOK(hook)
+        def in_next_free(f):
+            del done[:]
+            fake.in_free = C.cast(h, C.c_void_p)
+            f()
+            assert done == [0], "a free held the lock"
+        st, g = fake_hip.build_round(fake, L, 7)
+        L.pasur_gt_free(g)
+        in_next_free(L.pasur_release_cache)
+        # no room: the block itself is freed
+        st, g = fake_hip.build_round(fake, L, 2 << 20)
+        def full():   # the anchor's wait is over: the next free is a block's
+            fake.free_bytes[0] = 0
+            fake.in_free = C.cast(h, C.c_void_p)
+        first = fake_hip.HOOK(full)
+        del done[:]
+        fake.in_free = C.cast(first, C.c_void_p)
+        L.pasur_gt_free(g)
+        assert done == [0], "a block's free held the lock"
+    """, tmp_path)
