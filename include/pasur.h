@@ -72,7 +72,8 @@ typedef struct pasur_fgt pasur_fgt; /* unfolded (full) game tree of a round */
 const char *pasur_last_error(void);
 /* Gives the device memory of freed trees that the library keeps for the next
  * ones (up to 16 GiB on the current device) back to the system.  The library does
- * so itself when an allocation of its own fails. */
+ * so itself when an allocation of its own fails; before an allocation of the
+ * caller's own that may need that memory, the caller does. */
 void pasur_release_cache(void);
 int pasur_version(void);
 

@@ -152,6 +152,29 @@ def _torch():
     return torch
 
 
+def release_cache():
+    """pasur_release_cache: the device memory that the library keeps of freed
+    trees (up to 16 GiB) goes back to the system.  The package's own tensors ask
+    for it when they find no room; a program's other allocations, which cannot,
+    call this first where memory is short."""
+    lib().pasur_release_cache()
+
+
+def on_device(make):
+    """make(), which allocates device tensors; once more after release_cache() if
+    there is no room."""
+    try:
+        return make()
+    except _torch().OutOfMemoryError:
+        release_cache()
+        return make()
+
+
+def device_empty(shape, dtype):
+    """torch.empty on the GPU, through on_device."""
+    return on_device(lambda: _torch().empty(shape, dtype=dtype, device="cuda"))
+
+
 def _stream(stream=None):
     torch = _torch()
     s = stream if stream is not None else torch.cuda.current_stream()
@@ -168,7 +191,7 @@ def roots_to_device(roots) -> "torch.Tensor":
         a = np.zeros(len(roots), ROOT_DTYPE)
         for i, r in enumerate(roots):
             a[i] = (r.pool, r.ca, r.cb, r.d, r.bonus, 0)
-    return torch.from_numpy(a.view(np.uint8).copy()).cuda()
+    return on_device(lambda: torch.from_numpy(a.view(np.uint8).copy()).cuda())
 
 
 class GameTree:
@@ -286,14 +309,9 @@ class CfrState:
         self.dtype = dtype
         tdt = torch.float32 if dtype == PASUR_F32 else torch.float64
         n = fgt.n
-        dev = torch.device("cuda")
 
         def empty(n_l):
-            try:
-                return torch.empty(n_l, dtype=tdt, device=dev)
-            except torch.OutOfMemoryError:  # the library keeps some of what freed trees held
-                lib().pasur_release_cache()
-                return torch.empty(n_l, dtype=tdt, device=dev)
+            return device_empty(n_l, tdt)
 
         self.sigma = [None] + [empty(n[l]) for l in range(1, 9)]
         self.R = [None] + [empty(n[l]) for l in range(1, 9)]
@@ -301,7 +319,7 @@ class CfrState:
         self.reachA = [empty(n[l]) for l in range(8)] + [None]
         self.reachB = [empty(n[l]) for l in range(8)] + [None]
         self.u = [empty(n[l]) for l in range(9)]
-        self.vacc = torch.zeros(n[0], dtype=torch.float64, device=dev)
+        self.vacc = device_empty(n[0], torch.float64).zero_()
         self.sigma_bar = [None] + [empty(n[l]) for l in range(1, 9)]
         st = _State()
         st.dtype = dtype
@@ -632,7 +650,7 @@ def es_iterate(st: CfrState, n_iters: int, seed: int, rm_mode: int = RM_FLOOR, e
     torch = _torch()
     nb = es_workspace_bytes(st.fgt, st.dtype)
     if st.es_ws is None or st.es_ws.numel() < max(nb, 1):
-        st.es_ws = torch.empty(max(nb, 1), dtype=torch.uint8, device="cuda")
+        st.es_ws = device_empty(max(nb, 1), torch.uint8)
     t = st.es_t if t0 is None else t0
     _check(lib().pasur_es_iterate(st.fgt.h, C.byref(st.c), t, n_iters, seed & ((1 << 64) - 1),
                                   rm_mode, eps, schedule, roots_per_wg, _p(st.es_ws), st.es_ws.numel(),

@@ -22,8 +22,8 @@ import numpy as np
 
 from . import (FGT_PARENT, INFOSET_MLP, INFOSET_WIDTH, PASUR_F32, PASUR_F64, MlpGrads, MlpWeights,
                CfrState, adam_step_multi, average_strategy, infoset_rows,
-               cfr_init, cfr_iterate, cfr_warm_init, edge_features, gather_f32, leaf_utilities,
-               mlp_backward, mlp_forward, mlp_infer, mlp_loss, paper_params, round_values, sample_parents,
+               cfr_init, cfr_iterate, cfr_warm_init, device_empty, edge_features, gather_f32, leaf_utilities,
+               mlp_backward, mlp_forward, mlp_infer, mlp_loss, on_device, paper_params, round_values, sample_parents,
                shift_i32, mlp_transpose, warm_start_round as _warm_start_round,
                warm_start_workspace_bytes, _torch)
 from .solver import SubgameSolver
@@ -60,11 +60,12 @@ class WarmStartMLP:
         init = [rng.normal(0, math.sqrt(2.0 / N_IN), shapes[0]), np.zeros(N_HID),
                 rng.normal(0, math.sqrt(2.0 / N_HID), shapes[2]), np.zeros(N_HID),
                 rng.normal(0, math.sqrt(1.0 / N_HID), shapes[4]), np.zeros(N_OUT)]
-        self.master = [torch.tensor(a, dtype=torch.float32, device="cuda") for a in init]
-        self.bf = {k: torch.from_numpy(_bf16_bits(init[k]).copy()).cuda() for k in (0, 2, 4)}
-        self.m = [torch.zeros_like(t) for t in self.master]
-        self.v = [torch.zeros_like(t) for t in self.master]
-        self.g = [torch.zeros_like(t) for t in self.master]
+        self.master = on_device(lambda: [torch.tensor(a, dtype=torch.float32, device="cuda") for a in init])
+        self.bf = on_device(lambda: {k: torch.from_numpy(_bf16_bits(init[k]).copy()).cuda()
+                                     for k in (0, 2, 4)})
+        self.m = on_device(lambda: [torch.zeros_like(t) for t in self.master])
+        self.v = on_device(lambda: [torch.zeros_like(t) for t in self.master])
+        self.g = on_device(lambda: [torch.zeros_like(t) for t in self.master])
         self.step = 0
         self._bufs = {}
         self._version = 0      # bumped whenever the BF16 weights change
@@ -75,9 +76,10 @@ class WarmStartMLP:
     def set_weights(self, W: Sequence[np.ndarray]):
         """Load FP32 weights (W1, b1, W2, b2, W3, b3) and their BF16 copies."""
         torch = self.torch
-        self.master = [torch.tensor(np.asarray(a), dtype=torch.float32, device="cuda") for a in W]
-        self.bf = {k: torch.from_numpy(_bf16_bits(np.asarray(W[k], np.float32)).copy()).cuda()
-                   for k in (0, 2, 4)}
+        self.master = on_device(lambda: [torch.tensor(np.asarray(a), dtype=torch.float32, device="cuda")
+                                         for a in W])
+        self.bf = on_device(lambda: {k: torch.from_numpy(_bf16_bits(np.asarray(W[k], np.float32))
+                                                         .copy()).cuda() for k in (0, 2, 4)})
         self._version += 1
 
     def weights(self) -> MlpWeights:
@@ -90,8 +92,8 @@ class WarmStartMLP:
         when the weights changed since they were made."""
         torch = self.torch
         if self._wt is None:
-            self._wt = (torch.empty((N_HID, N_IN), dtype=torch.int16, device="cuda"),
-                        torch.empty((N_HID, N_HID), dtype=torch.int16, device="cuda"))
+            self._wt = (device_empty((N_HID, N_IN), torch.int16),
+                        device_empty((N_HID, N_HID), torch.int16))
         if self._tversion != self._version:
             mlp_transpose(self.weights(), self._wt[0], self._wt[1])
             self._tversion = self._version
@@ -103,7 +105,7 @@ class WarmStartMLP:
         """A reused device buffer of at least nbytes (grown by doubling)."""
         if self._ws is None or self._ws.numel() < nbytes:
             cap = max(nbytes, 2 * (self._ws.numel() if self._ws is not None else 0))
-            self._ws = self.torch.empty(cap, dtype=self.torch.uint8, device="cuda")
+            self._ws = device_empty(cap, self.torch.uint8)
         return self._ws
 
     def grads(self) -> MlpGrads:
@@ -116,10 +118,10 @@ class WarmStartMLP:
         if M > cap:
             cap = max(M, 2 * cap)
             self._bufs = {"cap": cap,
-                          "H1": torch.empty((cap, N_HID), dtype=torch.int16, device="cuda"),
-                          "H2": torch.empty((cap, N_HID), dtype=torch.int16, device="cuda"),
-                          "Y": torch.empty((cap, N_OUT), dtype=torch.float32, device="cuda"),
-                          "dY": torch.empty((cap, N_OUT), dtype=torch.float32, device="cuda")}
+                          "H1": device_empty((cap, N_HID), torch.int16),
+                          "H2": device_empty((cap, N_HID), torch.int16),
+                          "Y": device_empty((cap, N_OUT), torch.float32),
+                          "dY": device_empty((cap, N_OUT), torch.float32)}
         return self._bufs
 
     def forward(self, X, M: int):
@@ -137,7 +139,7 @@ class WarmStartMLP:
         # so that the step allocates nothing for them)
         w = self.infer_weights()
         mlp_forward(w, u.X, u.n_rows, b["H1"], b["H2"], b["Y"])
-        loss = torch.empty((u.n_par, 2), dtype=torch.float32, device="cuda")
+        loss = device_empty((u.n_par, 2), torch.float32)
         mlp_loss(b["Y"], u.tsig, u.tval, u.seg, u.n_par, u.n_rows, value_weight, b["dY"], loss)
         mlp_backward(w, u.X, b["H1"], b["H2"], b["dY"], u.n_rows, self.grads())
         self.step += 1
@@ -172,8 +174,8 @@ def make_units(solver: SubgameSolver, seed: int, parents_per_level: int = 400,
         f, st = rr.fgt, rr.state
         parts = []
         for l in range(1, 9):
-            seg = torch.empty(f.n[l - 1] + 1, dtype=torch.int32, device="cuda")
-            edges = torch.empty(f.n[l], dtype=torch.int32, device="cuda")
+            seg = device_empty(f.n[l - 1] + 1, torch.int32)
+            edges = device_empty(f.n[l], torch.int32)
             keep = min(1.0, parents_per_level / max(1, f.n[l - 1]))
             npar, ne = sample_parents(f, l, (seed << 8) ^ (rr.round << 4) ^ l, keep, seg, edges)
             if npar:
@@ -182,10 +184,10 @@ def make_units(solver: SubgameSolver, seed: int, parents_per_level: int = 400,
         pars = sum(p[3] for p in parts)
         if rows == 0:
             continue
-        X = torch.empty((rows, N_IN), dtype=torch.int16, device="cuda")
-        tsig = torch.empty(rows, dtype=torch.float32, device="cuda")
-        tval = torch.empty(rows, dtype=torch.float32, device="cuda")
-        useg = torch.empty(pars + 1, dtype=torch.int32, device="cuda")
+        X = device_empty((rows, N_IN), torch.int16)
+        tsig = device_empty(rows, torch.float32)
+        tval = device_empty(rows, torch.float32)
+        useg = device_empty(pars + 1, torch.int32)
         off = poff = 0
         for l, seg, edges, npar, ne in parts:
             features_into(rr, l, edges, ne, X[off:], features)
@@ -216,9 +218,9 @@ def warm_start_round_by_level(model: WarmStartMLP, rr, kappa_r: float, kappa_s: 
     f = rr.fgt
     for l in range(1, 9):
         n = f.n[l]
-        X = torch.empty((n, N_IN), dtype=torch.int16, device="cuda")
+        X = device_empty((n, N_IN), torch.int16)
         features_into(rr, l, None, n, X, features)
-        Y = torch.empty((n, N_OUT), dtype=torch.float32, device="cuda")
+        Y = device_empty((n, N_OUT), torch.float32)
         mlp_infer(model.weights(), X, n, Y)
         cfr_warm_init(rr.state, l, Y, kappa_r, kappa_s)
 
@@ -276,7 +278,7 @@ def solve_built(sv: SubgameSolver, iters: int, model: Optional[WarmStartMLP] = N
         cfr_iterate(rr.state, iters, params, t0=t0)
         average_strategy(rr.state)
         if fresh_state or rr.V is None:
-            rr.V = torch.empty(rr.fgt.n[0], dtype=torch.float64, device="cuda")
+            rr.V = device_empty(rr.fgt.n[0], torch.float64)
         # round value: mean of the iterate values of the iterations run (the
         # paper's g_UTL / NUM_ITER); vacc holds exactly `iters` terms
         rr.state.t = 1 + iters
@@ -424,16 +426,16 @@ def infoset_dataset(problems, iters: int, parents_per_level: int = 600, seed0: i
         for rr in sv.rounds:
             f, st = rr.fgt, rr.state
             for l in range(1, 9):
-                seg = torch.empty(f.n[l - 1] + 1, dtype=torch.int32, device="cuda")
-                edges = torch.empty(f.n[l], dtype=torch.int32, device="cuda")
+                seg = device_empty(f.n[l - 1] + 1, torch.int32)
+                edges = device_empty(f.n[l], torch.int32)
                 keep = min(1.0, parents_per_level / max(1, f.n[l - 1]))
                 npar, ne = sample_parents(f, l, ((seed0 + k) << 8) ^ (rr.round << 4) ^ l, keep,
                                           seg, edges)
                 if not ne:
                     continue
-                R = torch.empty((ne, INFOSET_WIDTH), dtype=torch.int8, device="cuda")
+                R = device_empty((ne, INFOSET_WIDTH), torch.int8)
                 infoset_rows(rr.gt, f, l, edges, ne, R)
-                t = torch.empty(ne, dtype=torch.float32, device="cuda")
+                t = device_empty(ne, torch.float32)
                 gather_f32(st.sigma_bar[l], st.dtype, edges, ne, t)
                 sg = seg[: npar + 1].cpu().numpy()
                 g = np.repeat(np.arange(npar), np.diff(sg)) + gid
@@ -463,7 +465,7 @@ def tree_profile_exploitability(deck, roots, tree) -> float:
         rr.state = CfrState(f, PASUR_F32)
         for l in range(1, 9):
             n = f.n[l]
-            R = torch.empty((n, INFOSET_WIDTH), dtype=torch.int8, device="cuda")
+            R = device_empty((n, INFOSET_WIDTH), torch.int8)
             infoset_rows(rr.gt, f, l, None, n, R)
             p = np.maximum(tree.predict(R.cpu().numpy().astype(np.float32)), 0.0)
             par = f.read(FGT_PARENT, l).astype(np.int64)

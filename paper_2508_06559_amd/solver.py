@@ -15,7 +15,7 @@ from typing import List, Optional
 from . import (PASUR_F32, PASUR_F64, PLAY_SIGMA_BAR, RM_FLOOR, SCHED_STREAM, V_ITERATE_MEAN,
                V_SIGMA_BAR, ES_FRONTIER, CfrParams, FGT_CHILD_BEGIN, FGT_LINK, FGT_NEXT_ROOTS, ROOT_DTYPE, CfrState,
                es_iterate, exploitability, selfplay, BatchEnds, Plan, UnfoldedTree,
-               average_strategy, build_round_tree, cfr_init, cfr_iterate, leaf_utilities,
+               average_strategy, build_round_tree, cfr_init, cfr_iterate, device_empty, leaf_utilities,
                paper_params, round_values, roots_to_device, unfold_scores, _torch)
 
 
@@ -98,7 +98,7 @@ class SubgameSolver:
             if on_round is not None:
                 on_round(rr.round)
             average_strategy(st, self.stream)
-            rr.V = torch.empty(rr.fgt.n[0], dtype=torch.float64, device="cuda")
+            rr.V = device_empty(rr.fgt.n[0], torch.float64)
             self._fork()
             round_values(st, value_mode, rr.V, self.stream)
             V = rr.V
@@ -121,7 +121,7 @@ class SubgameSolver:
             cfr_init(st, self.stream)
             es_iterate(st, iters, seed, rm_mode, eps, schedule=schedule, stream=self.stream)
             average_strategy(st, self.stream)
-            rr.V = torch.empty(rr.fgt.n[0], dtype=torch.float64, device="cuda")
+            rr.V = device_empty(rr.fgt.n[0], torch.float64)
             self._fork()
             round_values(st, V_SIGMA_BAR, rr.V, self.stream)
             V = rr.V
@@ -135,7 +135,7 @@ class SubgameSolver:
         Exploitability (points per game) is (BR_A - BR_B) / 2."""
         torch = self.torch
         n0 = self.rounds[0].fgt.n[0]
-        out = [torch.empty(n0, dtype=torch.float64, device="cuda") for _ in range(3)]
+        out = [device_empty(n0, torch.float64) for _ in range(3)]
         self._fork()
         exploitability([rr.fgt for rr in self.rounds], [rr.state.sigma_bar for rr in self.rounds],
                        self.dtype, out[0], out[1], out[2], self.stream, self.literal_bonus0)
@@ -150,7 +150,7 @@ class SubgameSolver:
         `strategies[r][l]` (per round, levels 1..8, the solver's dtype: any
         per-edge strategy, e.g. a network's prediction) when given."""
         torch = self.torch
-        margin = torch.empty(max(n_games, 1), dtype=torch.int32, device="cuda")
+        margin = device_empty(max(n_games, 1), torch.int32)
         sb = strategies if strategies is not None else [rr.state.sigma_bar for rr in self.rounds]
         self._fork()
         selfplay([rr.fgt for rr in self.rounds], sb, self.dtype, root, n_games, seed, policy_a,
@@ -230,7 +230,7 @@ class BatchSolver:
         for sv in self.deals:
             for rr in sv.rounds:
                 rr.state = CfrState(rr.fgt, dtype)
-                rr.V = torch.empty(rr.fgt.n[0], dtype=torch.float64, device="cuda")
+                rr.V = device_empty(rr.fgt.n[0], torch.float64)
         self.ends = [BatchEnds([sv.rounds[k].state for sv in self.deals])
                      for k in range(self.n_rounds)]
         self.plans = []

@@ -1,6 +1,8 @@
 """Device memory that freed trees and plans leave to later ones: it is idle when
 it is handed out again, and it is not kept where it is needed.  The library's
 host code runs over a HIP runtime without a device (fake_hip.c)."""
+import pytest
+
 import fake_hip
 
 
@@ -178,3 +180,33 @@ def test_frees_do_not_hold_up_other_threads(tmp_path):
         L.pasur_gt_free(g)
         assert done == [0], "a block's free held the lock"
     """, tmp_path)
+
+
+def test_tensors_are_allocated_from_released_memory(monkeypatch):
+    """The package's tensors find no room while the library keeps freed trees'
+    memory: it is given back, and the allocation tried again, once."""
+    import torch
+
+    import paper_2508_06559_amd as pa
+    log = []
+
+    class Torch:
+        OutOfMemoryError = torch.OutOfMemoryError
+        full = 1
+
+        @classmethod
+        def empty(cls, shape, dtype, device):
+            log.append("empty")
+            if cls.full:
+                raise torch.OutOfMemoryError("full")
+            return (shape, dtype, device)
+
+    monkeypatch.setattr(pa, "_torch", lambda: Torch)
+    monkeypatch.setattr(pa, "release_cache", lambda: (log.append("release"), setattr(Torch, "full", 0)))
+    assert pa.device_empty(3, torch.int8) == (3, torch.int8, "cuda")
+    assert log == ["empty", "release", "empty"]
+    Torch.full = 1
+    monkeypatch.setattr(pa, "release_cache", lambda: log.append("release"))
+    with pytest.raises(torch.OutOfMemoryError):
+        pa.device_empty(3, torch.int8)
+    assert log == ["empty", "release", "empty"] + ["empty", "release", "empty"]
