@@ -459,19 +459,19 @@ class BatchEnds:
     (pasur_batch_begin, pasur_batch_end), a launch per eight trees."""
 
     def __init__(self, states: Sequence[CfrState]):
-        n = len(states)
         self.states = list(states)
-        self.fg = (C.c_void_p * n)(*[st.fgt.h for st in states])
-        self.sp = (C.c_void_p * n)(*[C.addressof(st.c) for st in states])
-        self.sb = (C.c_void_p * (9 * n))()
-        for i, st in enumerate(states):
-            self.sb[9 * i:9 * i + 9] = st.sb_ptrs[:]
+
+    def _items(self):
+        """Trees (NULL for one that has been freed since) and states."""
+        n = len(self.states)
+        return ((C.c_void_p * n)(*[st.fgt.h for st in self.states]),
+                (C.c_void_p * n)(*[C.addressof(st.c) for st in self.states]))
 
     def begin(self, V_next, stream=None):
         """V_next: per item the next round's root values, or None (round 5)."""
         n = len(self.states)
         vn = (C.c_void_p * n)(*[None if v is None else v.data_ptr() for v in V_next])
-        _check(lib().pasur_batch_begin(self.fg, self.sp, vn, n, _stream(stream)),
+        _check(lib().pasur_batch_begin(*self._items(), vn, n, _stream(stream)),
                "pasur_batch_begin")
         for st in self.states:
             st.t = 1
@@ -481,8 +481,14 @@ class BatchEnds:
         """V: per item where its roots' values go."""
         n = len(self.states)
         v = (C.c_void_p * n)(*[x.data_ptr() for x in V])
-        _check(lib().pasur_batch_end(self.fg, self.sp, self.sb, self.states[0].t - 1, v, n,
-                                     _stream(stream)), "pasur_batch_end")
+        sb = (C.c_void_p * (9 * n))()
+        for i, st in enumerate(self.states):
+            sb[9 * i:9 * i + 9] = st.sb_ptrs[:]
+        t = self.states[0].t
+        if any(st.t != t for st in self.states):
+            raise ValueError("the states of a batch have run different numbers of iterations")
+        _check(lib().pasur_batch_end(*self._items(), sb, t - 1, v, n, _stream(stream)),
+               "pasur_batch_end")
 
 
 class Plan:
