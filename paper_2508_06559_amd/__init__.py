@@ -470,6 +470,8 @@ class BatchEnds:
     def begin(self, V_next, stream=None):
         """V_next: per item the next round's root values, or None (round 5)."""
         n = len(self.states)
+        if n == 0:
+            return
         vn = (C.c_void_p * n)(*[None if v is None else v.data_ptr() for v in V_next])
         _check(lib().pasur_batch_begin(*self._items(), vn, n, _stream(stream)),
                "pasur_batch_begin")
@@ -480,6 +482,8 @@ class BatchEnds:
     def end(self, V, stream=None):
         """V: per item where its roots' values go."""
         n = len(self.states)
+        if n == 0:
+            return
         v = (C.c_void_p * n)(*[x.data_ptr() for x in V])
         sb = (C.c_void_p * (9 * n))()
         for i, st in enumerate(self.states):

@@ -58,3 +58,14 @@ def test_batch_with_a_freed_tree_is_refused(tmp_path):
             assert "item 1 is NULL" in str(e)
         assert fake.launches == launches
     """, tmp_path)
+
+
+def test_empty_batch_is_solved(monkeypatch):
+    import torch
+
+    import paper_2508_06559_amd as pa
+    monkeypatch.setattr(pa.solver, "_torch", lambda: torch)
+    b = pa.BatchSolver([], 4, 5)
+    b.solve()
+    assert b.deals == [] and b.edges() == 0 and b.exploitability() == []
+    b.free()
