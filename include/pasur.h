@@ -319,8 +319,8 @@ int pasur_round_values(const pasur_fgt *fgt, const pasur_cfr_state *st,
  * d_leaf (device double, n[8]) to the roots (d_out, device double, n[0]):
  * EXPECT: sum sigma * value; BR_A: max at Alex's nodes, expectation at Bob's;
  * BR_B: min at Bob's nodes, expectation at Alex's; MINIMAX: max/min.
- * sigma (type `dtype`, levels 1..8) may be NULL for MINIMAX.  One launch,
- * which allocates nothing. */
+ * sigma (type `dtype`, levels 1..8) may be NULL for MINIMAX.  Uses
+ * stream-ordered scratch where a root is so large that it is split. */
 typedef enum { PASUR_TV_EXPECT = 0, PASUR_TV_BR_A = 1, PASUR_TV_BR_B = 2,
                PASUR_TV_MINIMAX = 3 } pasur_tv_mode;
 int pasur_tree_values(const pasur_fgt *fgt, const double *d_leaf, int dtype,
@@ -342,7 +342,8 @@ int pasur_tree_values(const pasur_fgt *fgt, const double *d_leaf, int dtype,
  * with `leaf_flags`).  Any output may be NULL (not
  * computed), not all three.  Exploitability in points per game is
  * (br_a - br_b) / 2 >= 0.  Asynchronous on `stream`; uses stream-ordered
- * scratch (two rounds' root values).
+ * scratch (two rounds' root values, a level of rounds with roots so large that
+ * they are split).
  * PASUR_E_INVAL for null or inconsistent trees, PASUR_E_RANGE for n_rounds
  * outside 1..6 or an unknown dtype. */
 int pasur_exploitability(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar,
@@ -353,7 +354,9 @@ int pasur_exploitability(const pasur_fgt *const *fgts, int n_rounds, void *const
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * computation and arguments as pasur_tree_values.  Allocates nothing.  Limit:
  * every level 0..7 of the tree at most 2^21 (2,097,152) nodes -- larger trees
- * get PASUR_E_CAPACITY (use pasur_tree_values). */
+ * get PASUR_E_CAPACITY (use pasur_tree_values).  The scratch of a tree whose roots
+ * are split is the tree's own: calls on one tree that overlap (on any streams)
+ * race and must be serialised by the caller. */
 int pasur_tree_values_noalloc(const pasur_fgt *fgt, const double *d_leaf, int dtype,
                               void *const sigma[9], int mode, double *d_out, void *stream);
 

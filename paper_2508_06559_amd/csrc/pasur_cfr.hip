@@ -417,12 +417,6 @@ void prof_events(hipEvent_t *a, hipEvent_t *b) {
 
 namespace {
 
-int64_t widest_level(const pasur_fgt *f) {
-  int64_t mx = 1;
-  for (int l = 0; l <= 7; ++l) mx = f->n[l] > mx ? f->n[l] : mx;
-  return mx;
-}
-
 int check_tree_values(const pasur_fgt *f, const double *d_leaf, int dtype, void *const sigma[9],
                       int mode, double *d_out) {
   if (!f || !d_leaf || !d_out) {
@@ -446,9 +440,6 @@ int check_tree_values(const pasur_fgt *f, const double *d_leaf, int dtype, void 
   }
   return PASUR_OK;
 }
-
-// Widest level pasur_tree_values_noalloc takes.
-constexpr int64_t kNoAllocLevel = (int64_t)1 << 21;
 
 }  // namespace
 
@@ -630,13 +621,13 @@ extern "C" int pasur_round_values(const pasur_fgt *f, const pasur_cfr_state *st,
     set_error("sigma_bar is NULL");
     return PASUR_E_INVAL;
   }
-  return tree_values(f, st->u[8], st->dtype, st->dtype, sigma_bar, PASUR_TV_EXPECT, d_V, s);
+  return tree_values(f, st->u[8], st->dtype, st->dtype, sigma_bar, PASUR_TV_EXPECT, d_V, true, s);
 }
 
 extern "C" int pasur_tree_values(const pasur_fgt *f, const double *d_leaf, int dtype,
                                  void *const sigma[9], int mode, double *d_out, void *stream) {
   PASUR_TRY(check_tree_values(f, d_leaf, dtype, sigma, mode, d_out));
-  return tree_values(f, d_leaf, PASUR_F64, dtype, sigma, mode, d_out, (hipStream_t)stream);
+  return tree_values(f, d_leaf, PASUR_F64, dtype, sigma, mode, d_out, true, (hipStream_t)stream);
 }
 
 namespace {
@@ -706,14 +697,14 @@ extern "C" int pasur_tree_values_noalloc(const pasur_fgt *f, const double *d_lea
                                          void *const sigma[9], int mode, double *d_out,
                                          void *stream) {
   PASUR_TRY(check_tree_values(f, d_leaf, dtype, sigma, mode, d_out));
-  const int64_t mx = widest_level(f);
+  const int64_t mx = widest_level(f->n);
   if (mx > kNoAllocLevel) {
     set_error("a tree level of %lld nodes exceeds the %lld nodes that "
               "pasur_tree_values_noalloc takes (use pasur_tree_values)",
               (long long)mx, (long long)kNoAllocLevel);
     return PASUR_E_CAPACITY;
   }
-  return tree_values(f, d_leaf, PASUR_F64, dtype, sigma, mode, d_out, (hipStream_t)stream);
+  return tree_values(f, d_leaf, PASUR_F64, dtype, sigma, mode, d_out, false, (hipStream_t)stream);
 }
 
 extern "C" int pasur_profile_enable(int on) {

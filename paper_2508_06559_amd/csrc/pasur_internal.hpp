@@ -241,9 +241,24 @@ int seg_iterate(const pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_p
 
 // ---- exact values (pasur_values.hip) -----------------------------------------
 // Root values of one round from an array of leaf values (leaf_dtype; FP64
-// leaves when dtype is PASUR_F64), as pasur_tree_values.  Allocates nothing.
+// leaves when dtype is PASUR_F64), as pasur_tree_values.  alloc: a tree with a
+// value_stop() takes stream-ordered scratch, else its own.
 int tree_values(const pasur_fgt *f, const void *leaf, int leaf_dtype, int dtype,
-                void *const *sigma, int mode, double *out, hipStream_t s);
+                void *const *sigma, int mode, double *out, bool alloc, hipStream_t s);
+// Where some root is too large for one workgroup, the level (1 to 5) down from
+// which the roots' nodes fit one each, those of that level to 6 being evaluated
+// before; 0: a workgroup per root from the leaves.  root_off: 9 levels of
+// n_roots + 1 offsets.
+int value_stop(const int64_t n[9], int64_t n_roots, const int32_t *root_off);
+// Nodes of a tree's levels value_stop .. 6, whose values are passed on.
+int64_t split_nodes(const pasur_fgt *f);
+// The widest of levels 0..7, and the widest that pasur_tree_values_noalloc takes.
+inline int64_t widest_level(const int64_t n[9]) {
+  int64_t mx = 1;
+  for (int l = 0; l <= 7; ++l) mx = n[l] > mx ? n[l] : mx;
+  return mx;
+}
+constexpr int64_t kNoAllocLevel = (int64_t)1 << 21;
 // pasur_exploitability on checked arguments.
 int composed_values(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar, int dtype,
                     int leaf_flags, double *br_a, double *br_b, double *v, hipStream_t s);
@@ -291,6 +306,10 @@ struct pasur_fgt {
   // per root, what a segment's LDS layout counts (4 ints: see pasur_seg.hip),
   // on the host; computed on first use
   int32_t *h_root_seg;
+  // split_ws: a double per node of split_nodes(), where pasur_tree_values_noalloc
+  // takes the tree
+  int value_stop;
+  double *split_ws;
   // the blocks behind root_off, the arrays of the levels, and next_roots
   void *off_block, *block, *next_block;
   void *anchor;

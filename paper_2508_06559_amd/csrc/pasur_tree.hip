@@ -788,6 +788,9 @@ int unfold_impl(const pasur_gt *gt, const pasur_root *d_roots, int64_t n_roots, 
     if (l > 0) levels.want(&f->parent[l], f->n[l]);
     if (l < 8) levels.want(&f->child_begin[l], f->n[l] + 1);
   }
+  f->value_stop = value_stop(f->n, n_roots, f->h_root_off);
+  if (f->value_stop && widest_level(f->n) <= kNoAllocLevel)
+    levels.want(&f->split_ws, split_nodes(f));
   levels.want(&f->leaf_base, nl);
   if (r == 5) levels.want(&f->leaf_bonus, nl);
   else levels.want(&f->link, nl);

@@ -15,6 +15,12 @@
 // 3.3 ms of kernels on a game of 1.8e8 nodes, and 97 ms with the allocation
 // and release of those buffers.
 //
+// A root too large for one workgroup beside the others is split: every node of
+// level 6 is evaluated by a thread of its own, then the nodes of the levels above
+// one level a launch, until the roots' nodes fit a workgroup each (one root of
+// 6.2e6 nodes: 88 ms in one workgroup, 0.14 split; from level 5 or 7 on 0.20 and
+// 0.15).
+//
 // Sums run in child order from 0.0 in FP64, one node at a time, whatever the
 // base level is.  Contraction of a*b+c into fma is switched off.
 #pragma clang fp contract(off)
@@ -61,11 +67,13 @@ template <class T, class Leaf, int NM>
 struct ValueArgs {
   const int32_t *cb[8];
   const T *sigma[9];       // levels 1..8, may be NULL where no mode reads them
-  const int32_t *off[9];   // root offsets per level
+  const int32_t *off[6];   // root offsets per level
   Leaf leaf;
   int mode[NM];
-  double *out[NM];         // value of root j at out[m][j * stride], NULL: not wanted
+  double *out[NM];         // value of root or node j at out[m][j * stride], NULL: not wanted
   int64_t stride;
+  const double *part;      // given values of level `base`, the NM of a node side by
+  int base;                // side, or NULL: from the leaves
 };
 
 enum { V_SUM, V_MAX, V_MIN };
@@ -86,6 +94,11 @@ struct Node {
     if (NM == 3)
       return m == 0 && mover == 0 ? V_MAX : m == 1 && mover == 1 ? V_MIN : V_SUM;
     return value_kind(a.mode[m], mover);
+  }
+  // Some value needs the strategy at these nodes.
+  template <class Args>
+  static __device__ __forceinline__ bool weighs(const Args &a, int mover) {
+    return NM > 1 || kind(a, 0, mover) == V_SUM;
   }
   template <class Args>
   __device__ __forceinline__ void start(const Args &a, int mover) {
@@ -114,7 +127,7 @@ __device__ __forceinline__ void value_of(const ValueArgs<T, Leaf, NM> &a, int32_
     a.leaf.get(h, out, NM);
   } else {
     const int32_t b = a.cb[L][h], e = a.cb[L][h + 1];
-    const T *sg = a.sigma[L + 1];
+    const T *sg = Node<NM>::weighs(a, L & 1) ? a.sigma[L + 1] : nullptr;
     Node<NM> n;
     n.start(a, L & 1);
     for (int32_t q = b; q < e; ++q) {
@@ -139,24 +152,54 @@ __device__ __forceinline__ void base_level(const ValueArgs<T, Leaf, NM> &a, int3
   }
 }
 
+// A thread per node of level L, from the leaves.
+template <int L, class T, class Leaf, int NM>
+__global__ void __launch_bounds__(256) k_values_leaves(ValueArgs<T, Leaf, NM> a, int64_t n) {
+  const int64_t h = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (h >= n) return;
+  double v[NM];
+  value_of<L>(a, (int32_t)h, v);
+#pragma unroll
+  for (int m = 0; m < NM; ++m) a.out[m][h * a.stride] = v[m];
+}
+
+// A thread per node of level a.base - 1, from the given values of its children.
+template <class T, class Leaf, int NM>
+__global__ void __launch_bounds__(256) k_values_level(ValueArgs<T, Leaf, NM> a, int64_t n) {
+  const int64_t h = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (h >= n) return;
+  const int l = a.base - 1;
+  const int32_t b = a.cb[l][h], e = a.cb[l][h + 1];
+  const T *sg = Node<NM>::weighs(a, l & 1) ? a.sigma[l + 1] : nullptr;
+  Node<NM> v;
+  v.start(a, l & 1);
+  for (int32_t q = b; q < e; ++q)
+    v.add(a, l & 1, sg ? (double)sg[q] : 0.0, a.part + (int64_t)NM * q);
+#pragma unroll
+  for (int m = 0; m < NM; ++m) a.out[m][h * a.stride] = v.v[m];
+}
+
 // One workgroup per root.  The base level is the deepest of levels 1..5 whose
 // nodes below the root fit in CAP entries of LDS (deeper: more threads with
-// shorter loops; level 6 and below are mostly single-child chains).  A level
-// is then reduced in place: every thread holds its parents' values in
-// registers across the barrier that ends the reading of their children.
+// shorter loops; level 6 and below are mostly single-child chains), or that of the
+// given values.  A level is then reduced in place: every thread holds its parents'
+// values in registers across the barrier that ends the reading of their children.
 template <class T, class Leaf, int NM, int BLOCK, int CAP>
 __global__ void __launch_bounds__(BLOCK) k_values_roots(ValueArgs<T, Leaf, NM> a) {
   __shared__ double lds[NM * CAP];
   const int64_t j = blockIdx.x;
-  int32_t h0 = a.off[5][j];
-  int n = a.off[5][j + 1] - h0, l = 5;
-  while (l > 1 && n > CAP) {
+  int l = a.part ? a.base : 5;
+  int32_t h0 = a.off[l][j];
+  int n = a.off[l][j + 1] - h0;
+  while (!a.part && l > 1 && n > CAP) {
     --l;
     h0 = a.off[l][j];
     n = a.off[l][j + 1] - h0;
   }
   if (n <= CAP) {
-    switch (l) {
+    if (a.part) {
+      for (int i = threadIdx.x; i < NM * n; i += BLOCK) lds[i] = a.part[(int64_t)NM * h0 + i];
+    } else switch (l) {
       case 5: base_level<5, BLOCK>(a, h0, n, lds); break;
       case 4: base_level<4, BLOCK>(a, h0, n, lds); break;
       case 3: base_level<3, BLOCK>(a, h0, n, lds); break;
@@ -169,7 +212,7 @@ __global__ void __launch_bounds__(BLOCK) k_values_roots(ValueArgs<T, Leaf, NM> a
       const int32_t c0 = h0;
       h0 = a.off[l][j];
       n = a.off[l][j + 1] - h0;
-      const T *sg = a.sigma[l + 1];
+      const T *sg = Node<NM>::weighs(a, l & 1) ? a.sigma[l + 1] : nullptr;
       Node<NM> v[PER];
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
@@ -202,29 +245,46 @@ __global__ void __launch_bounds__(BLOCK) k_values_roots(ValueArgs<T, Leaf, NM> a
   }
 }
 
+constexpr int kWide = 4096;
+constexpr int kFlat = 6;  // the level whose nodes a split round evaluates from the leaves
+
 // Few roots leave most CUs without a workgroup: there a root gets 1024 threads
 // and room for a wide base level.  With many, small workgroups of 24 KB of LDS
 // (three modes) keep six of them on a CU.
 constexpr int64_t kFewRoots = 1024;
 
+// split: room for split_nodes(f) * NM values.
 template <class T, class Leaf, int NM>
 int launch(const pasur_fgt *f, const Leaf &leaf, void *const *sigma, const int *mode,
-           double *const *out, int64_t stride, hipStream_t s) {
+           double *const *out, int64_t stride, double *split, hipStream_t s) {
   ValueArgs<T, Leaf, NM> a;
   for (int l = 0; l < 8; ++l) a.cb[l] = f->child_begin[l];
   a.sigma[0] = nullptr;
   for (int l = 1; l < 9; ++l) a.sigma[l] = sigma ? (const T *)sigma[l] : nullptr;
-  for (int l = 0; l < 9; ++l) a.off[l] = f->root_off[l];
+  for (int l = 0; l < 6; ++l) a.off[l] = f->root_off[l];
   a.leaf = leaf;
-  for (int m = 0; m < NM; ++m) {
-    a.mode[m] = mode[m];
-    a.out[m] = out[m];
+  for (int m = 0; m < NM; ++m) a.mode[m] = mode[m];
+  a.part = nullptr;
+  a.base = 0;
+  if (f->value_stop) {
+    a.stride = NM;
+    for (int l = kFlat; l >= f->value_stop; --l) {
+      const unsigned grid = (unsigned)((f->n[l] + 255) / 256);
+      for (int m = 0; m < NM; ++m) a.out[m] = split + m;
+      if (l == kFlat) k_values_leaves<kFlat, T, Leaf, NM><<<grid, 256, 0, s>>>(a, f->n[l]);
+      else k_values_level<T, Leaf, NM><<<grid, 256, 0, s>>>(a, f->n[l]);
+      a.part = split;
+      a.base = l;
+      split += NM * f->n[l];
+    }
   }
   a.stride = stride;
-  if (f->n[0] <= kFewRoots)
-    k_values_roots<T, Leaf, NM, 1024, 4096><<<(unsigned)f->n[0], 1024, 0, s>>>(a);
+  for (int m = 0; m < NM; ++m) a.out[m] = out[m];
+  const unsigned grid = (unsigned)f->n[0];
+  if (a.part || f->n[0] <= kFewRoots)
+    k_values_roots<T, Leaf, NM, 1024, kWide><<<grid, 1024, 0, s>>>(a);
   else
-    k_values_roots<T, Leaf, NM, 256, 1024><<<(unsigned)f->n[0], 256, 0, s>>>(a);
+    k_values_roots<T, Leaf, NM, 256, 1024><<<grid, 256, 0, s>>>(a);
   PASUR_TRY_HIP(hipGetLastError());
   return PASUR_OK;
 }
@@ -232,12 +292,16 @@ int launch(const pasur_fgt *f, const Leaf &leaf, void *const *sigma, const int *
 template <class T, int NM>
 int composed(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar, int leaf_flags,
              const int *mode, double *const *outs, hipStream_t s) {
-  // the root values of rounds 1.., the NM values of a root side by side
-  int64_t most = 0;
-  for (int r = 1; r < n_rounds; ++r) most = std::max(most, fgts[r]->n[0]);
+  // the root values of rounds 1.., the NM values of a root side by side, and
+  // those of split rounds
+  int64_t most = 0, split = 0;
+  for (int r = 0; r < n_rounds; ++r) {
+    if (r > 0) most = std::max(most, fgts[r]->n[0]);
+    split = std::max(split, split_nodes(fgts[r]));
+  }
   double *buf = nullptr;
-  if (most > 0) {
-    const hipError_t e = malloc_async((void **)&buf, 2 * NM * most * sizeof(double), s);
+  if (most + split > 0) {
+    const hipError_t e = malloc_async((void **)&buf, NM * (2 * most + split) * sizeof(double), s);
     if (e != hipSuccess) {
       set_error("hipMallocAsync: %s", hipGetErrorString(e));
       return PASUR_E_NOMEM;
@@ -256,24 +320,66 @@ int composed(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar,
     double *res = buf + (r & 1) * NM * most;
     double *out[NM];
     for (int m = 0; m < NM; ++m) out[m] = r > 0 ? res + m : outs[m];
-    st = launch<T, LeafRound, NM>(f, leaf, sigma_bar + r * 9, mode, out, r > 0 ? NM : 1, s);
+    st = launch<T, LeafRound, NM>(f, leaf, sigma_bar + r * 9, mode, out, r > 0 ? NM : 1,
+                                  buf + 2 * NM * most, s);
     V = res;
   }
   if (buf) (void)hipFreeAsync(buf, s);
   return st;
 }
 
+int values_of_leaves(const pasur_fgt *f, const void *leaf, int leaf_dtype, int dtype,
+                     void *const *sigma, int mode, double *out, double *split, hipStream_t s) {
+  const LeafArray<double> ld{(const double *)leaf};
+  if (dtype == PASUR_F64)
+    return launch<double, LeafArray<double>, 1>(f, ld, sigma, &mode, &out, 1, split, s);
+  if (leaf_dtype == PASUR_F64)
+    return launch<float, LeafArray<double>, 1>(f, ld, sigma, &mode, &out, 1, split, s);
+  return launch<float, LeafArray<float>, 1>(f, LeafArray<float>{(const float *)leaf}, sigma, &mode,
+                                            &out, 1, split, s);
+}
+
 }  // namespace
 
+int64_t split_nodes(const pasur_fgt *f) {
+  int64_t n = 0;
+  if (f->value_stop)
+    for (int l = f->value_stop; l <= kFlat; ++l) n += f->n[l];
+  return n;
+}
+
+int value_stop(const int64_t n[9], int64_t n_roots, const int32_t *root_off) {
+  // Leaves of the largest root, a third of its nodes: a workgroup takes 24 us for
+  // 6,000 nodes, 100 us for 60,000 and 5.8 ms for 700,000; the chip takes 1e11
+  // nodes a second.  A root of more is worth some launches of 5 us if the round's
+  // other roots don't take as long.
+  auto widest = [&](int l) {
+    const int32_t *const o = root_off + l * (n_roots + 1);
+    int32_t w = 0;
+    for (int64_t j = 0; j < n_roots; ++j) w = std::max(w, o[j + 1] - o[j]);
+    return w;
+  };
+  const int32_t most = widest(8);
+  if (most <= 3500 + n[8] / (most > 60000 ? 800 : 160)) return 0;
+  int l = 5;
+  while (l > 1 && widest(l) > kWide) --l;
+  return l;
+}
+
 int tree_values(const pasur_fgt *f, const void *leaf, int leaf_dtype, int dtype,
-                void *const *sigma, int mode, double *out, hipStream_t s) {
+                void *const *sigma, int mode, double *out, bool alloc, hipStream_t s) {
   if (f->n[0] == 0) return PASUR_OK;
-  const LeafArray<double> ld{(const double *)leaf};
-  if (dtype == PASUR_F64) return launch<double, LeafArray<double>, 1>(f, ld, sigma, &mode, &out, 1, s);
-  if (leaf_dtype == PASUR_F64)
-    return launch<float, LeafArray<double>, 1>(f, ld, sigma, &mode, &out, 1, s);
-  return launch<float, LeafArray<float>, 1>(f, LeafArray<float>{(const float *)leaf}, sigma, &mode,
-                                            &out, 1, s);
+  double *split = f->split_ws;
+  if (f->value_stop && alloc) {
+    const hipError_t e = malloc_async((void **)&split, (size_t)split_nodes(f) * sizeof(double), s);
+    if (e != hipSuccess) {
+      set_error("hipMallocAsync: %s", hipGetErrorString(e));
+      return PASUR_E_NOMEM;
+    }
+  }
+  const int st = values_of_leaves(f, leaf, leaf_dtype, dtype, sigma, mode, out, split, s);
+  if (f->value_stop && alloc) (void)hipFreeAsync(split, s);
+  return st;
 }
 
 int composed_values(const pasur_fgt *const *fgts, int n_rounds, void *const *sigma_bar, int dtype,
