@@ -1132,13 +1132,18 @@ __device__ __forceinline__ void seg_iterations(const ItemDesc<T> &D, int roots, 
 template <class T, int SLOT>
 struct TabArr {
   int l;
-  __device__ __forceinline__ __attribute__((address_space(1))) T &operator[](int i) const {
-    return tab<T>(SLOT, l)[i];
+  __device__ __forceinline__ T &operator[](int i) const {
+    return reinterpret_cast<T *>(g_ptab[SLOT][l])[i];
   }
 };
 
 // FindUtility for the parents of level L-1, one thread each, over their
-// children in child order.
+// children in child order.  Through flat pointers and with a plain fmax the
+// compiler keeps more of the loops' loads in flight (one root of 2.5e6 nodes, 20
+// iterations: 147 ms; with global pointers 155, with `matched` as well 166).
+__device__ __forceinline__ double low_max(double R, int rm_mode, double eps) {
+  return rm_mode == PASUR_RM_FLOOR ? fmax(R, eps) : fmax(R, 0.0);
+}
 template <class T, int L>
 __device__ __forceinline__ void up_global(double *vacc, const IterK &ik, int variant, int rm_mode,
                                           double eps) {
@@ -1155,23 +1160,19 @@ __device__ __forceinline__ void up_global(double *vacc, const IterK &ik, int var
     const int e = TabArr<const int32_t, 7>{L - 1}[h + 1] - g_lo[L];
     const double ra = (double)TabArr<T, 4>{L - 1}[h], rb = (double)TabArr<T, 5>{L - 1}[h];
     const double opp = mover == 0 ? rb : ra, own = mover == 0 ? ra : rb;
-    double uh = 0.0;
+    double uh = 0.0, sum = 0.0;
     for (int q = b; q < e; ++q) uh += (double)sg[q] * (double)uu[q];
-    double sum = 0.0;
     for (int q = b; q < e; ++q) {
       const double r = sgn * opp * ((double)uu[q] - uh);
       const T Rs = (T)next_regret((double)Rr[q], r, ik, variant);
       Rr[q] = Rs;
-      sum += matched((double)Rs, rm_mode, eps);
+      sum += low_max((double)Rs, rm_mode, eps);
     }
     const double inv_k = sum > 0.0 ? 0.0 : 1.0 / (double)(e - b);
     for (int q = b; q < e; ++q) {
-      const double m = matched((double)Rr[q], rm_mode, eps);
-      const double s_new = sum > 0.0 ? m / sum : inv_k;
-      double add = own * (double)sg[q];
-      if (variant == PASUR_CFR_PLUS) add *= ik.avg_t;
-      Sb[q] = (T)(ik.avg_w * (double)Sb[q] + add);
-      sg[q] = (T)s_new;
+      const double m = low_max((double)Rr[q], rm_mode, eps);
+      Sb[q] = average_update<T>(own, sg[q], Sb[q], ik, variant);
+      sg[q] = (T)(sum > 0.0 ? m / sum : inv_k);
     }
     TabArr<T, 3>{L - 1}[h] = (T)uh;
     if (L == 1) vacc[h] += uh;
