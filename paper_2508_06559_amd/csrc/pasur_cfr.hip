@@ -487,9 +487,21 @@ extern "C" int pasur_cfr_iterate(const pasur_fgt *f, const pasur_cfr_state *st,
     return st->dtype == PASUR_F32 ? iterate_t<float>(f, st, p, t0, n_iters, s)
                                   : iterate_t<double>(f, st, p, t0, n_iters, s);
   }
-  if (p->schedule == PASUR_SCHED_STREAM ||
-      (p->schedule == PASUR_SCHED_AUTO && sweep_pays(f, st->dtype, n_iters, s)))
-    return sweep_iterate(const_cast<pasur_fgt *>(f), st, p, t0, n_iters, s);
+  if (p->schedule == PASUR_SCHED_STREAM || (p->schedule == PASUR_SCHED_AUTO && large_round(f))) {
+    pasur_fgt *const tree = const_cast<pasur_fgt *>(f);
+    if (p->schedule == PASUR_SCHED_AUTO && n_iters > 0) {
+      hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+      bool capturing = true;
+      if (hipStreamIsCapturing(s, &status) == hipSuccess)
+        capturing = status != hipStreamCaptureStatusNone;
+      else
+        (void)hipGetLastError();  // another capture forbids to ask
+      bool segs = !capturing && !sweep_pays(f, st->dtype, n_iters), done = false;
+      if (segs) PASUR_TRY(seg_enqueue(tree, st, p, t0, n_iters, capturing, &done, s));
+      if (done) return PASUR_OK;
+    }
+    return sweep_iterate(tree, st, p, t0, n_iters, s);
+  }
   if (p->schedule == PASUR_SCHED_LEVEL_SYNC)
     return st->dtype == PASUR_F32 ? iterate_t<float>(f, st, p, t0, n_iters, s)
                                   : iterate_t<double>(f, st, p, t0, n_iters, s);

@@ -66,6 +66,11 @@ void dev_free(T *&p) {
 // back must be idle: nothing that uses it is pending on any stream.
 int block_alloc(void **p, size_t bytes);
 void block_free(void *p);
+// Scratch of the work that the caller enqueues on s: given back behind that work,
+// while it is pending, to be had by later work on s at once and by others when it
+// has ended.  Not while s is being captured.
+int block_alloc_on(void **p, size_t bytes, hipStream_t s);
+void block_free_on(void *p, hipStream_t s);
 // The wait of a hipFree, for handles that the caller may free while work that
 // uses them is still running: an anchor is a small plain allocation, and freeing
 // it waits for the device as freeing the arrays themselves did.
@@ -230,14 +235,27 @@ void sweep_index_free(SweepIndex *x);
 // launches (PASUR_SCHED_STREAM); same arguments as pasur_cfr_iterate.
 int sweep_iterate(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,
                   int64_t t0, int n_iters, hipStream_t s);
-// Whether the streaming schedule is expected to beat the persistent segment
-// schedule on n_iters iterations of this round on stream s (PASUR_SCHED_AUTO).
-bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters, hipStream_t s);
+// Rounds of as many nodes, whose calls PASUR_SCHED_AUTO only enqueues, and whether
+// the streaming schedule is expected to beat the persistent segment schedule on
+// n_iters iterations of one.
+bool large_round(const pasur_fgt *f);
+bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters);
 
 // Iterations t0 .. t0+n_iters-1 of one round with the persistent segment
 // schedule (pasur_seg.hip); n_iters >= 1.  Waits for the stream.
 int seg_iterate(const pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,
                 int64_t t0, int n_iters, hipStream_t s);
+// The same without a wait, with a segment index of the tree that its first call
+// builds (seg_ready: there is one for this type, as a capture needs).  Sets *done,
+// or leaves it false where there is no memory for the segments' far arrays.
+struct SegIndex;
+constexpr int kSegIndexes = 6;  // of one tree
+// The blocks of a tree's indexes, into p[0 .. n-1]; returns how many.
+int seg_index_blocks(const SegIndex *x, void **p, int n);
+void seg_index_free(SegIndex *x);
+bool seg_ready(const pasur_fgt *f, int dtype);
+int seg_enqueue(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p, int64_t t0,
+                int n_iters, bool capturing, bool *done, hipStream_t s);
 
 // ---- exact values (pasur_values.hip) -----------------------------------------
 // Root values of one round from an array of leaf values (leaf_dtype; FP64
@@ -306,6 +324,8 @@ struct pasur_fgt {
   // per root, what a segment's LDS layout counts (4 ints: see pasur_seg.hip),
   // on the host; computed on first use
   int32_t *h_root_seg;
+  // the segments of the tree by itself, one index after another, built on first use
+  pasur::SegIndex *seg_index;
   // split_ws: a double per node of split_nodes(), where pasur_tree_values_noalloc
   // takes the tree
   int value_stop;

@@ -1400,11 +1400,11 @@ constexpr int64_t kFarBytes = (int64_t)1 << 30;
 // their own, unless there are too few of them to fill the chip; the segments of
 // the first two kinds, the longest of all, run beside the largest ones in LDS.
 // Gives far arrays their places; returns the bytes these take.
-int64_t plan_launches(pasur_plan *pl, std::vector<SegPlan> &segs, int user_block) {
+int64_t plan_launches(std::vector<SegLaunch> &launches, std::vector<SegPlan> &segs, int user_block) {
   constexpr int kCus = 256;
   int64_t far_max = 0;
   const int n = (int)segs.size();
-  pl->launches.clear();
+  launches.clear();
   for (int i = 0; i < n;) {
     SegLaunch la;
     const int c = per_cu(segs[(size_t)i]);
@@ -1434,10 +1434,157 @@ int64_t plan_launches(pasur_plan *pl, std::vector<SegPlan> &segs, int user_block
                : la.count <= kCus || c == 1 ? 1024
                : c == 2     ? 512
                             : 256;
-    pl->launches.push_back(la);
+    launches.push_back(la);
     i = j;
   }
   return far_max;
+}
+
+// Orders segments for their launches: those in global memory first, then those
+// with far arrays, then the largest, these by how many a CU takes, and in buckets
+// of 512 bytes (a comparison sort of 1e5 segments takes milliseconds).  Returns the
+// bytes of far arrays.
+int64_t order_segments(std::vector<SegLaunch> &launches, std::vector<SegPlan> &segs,
+                       int user_block) {
+  std::vector<SegPlan> large, by_bytes(segs.size());
+  constexpr size_t kBuckets = kLdsPerWorkgroup / 512 + 1;
+  auto bucket = [](const SegPlan &sp) {
+    return (size_t)(per_cu(sp) - 1) * kBuckets + (kLdsPerWorkgroup - sp.bytes) / 512;
+  };
+  std::vector<size_t> at(4 * kBuckets + 1, 0);
+  for (const SegPlan &sp : segs) {
+    if (sp.seg.form != F_LDS) large.push_back(sp);
+    else at[bucket(sp) + 1] += 1;
+  }
+  std::stable_sort(large.begin(), large.end(), [](const SegPlan &a, const SegPlan &b) {
+    return a.seg.form != b.seg.form ? a.seg.form > b.seg.form : a.nodes > b.nodes;
+  });
+  at[0] = large.size();
+  for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+  std::copy(large.begin(), large.end(), by_bytes.begin());
+  for (const SegPlan &sp : segs)
+    if (sp.seg.form == F_LDS) by_bytes[at[bucket(sp)]++] = sp;
+  segs.swap(by_bytes);
+  return plan_launches(launches, segs, user_block);
+}
+
+template <class T>
+ItemDesc<T> item_desc(const pasur_fgt *f, const pasur_cfr_state *st) {
+  ItemDesc<T> D;
+  for (int l = 0; l <= 8; ++l) {
+    D.off[l] = f->root_off[l];
+    D.parent[l] = f->parent[l];
+    D.cb[l] = l <= 7 ? f->child_begin[l] : nullptr;
+    D.sigma[l] = l >= 1 ? (T *)st->sigma[l] : nullptr;
+    D.R[l] = l >= 1 ? (T *)st->R[l] : nullptr;
+    D.Sbar[l] = l >= 1 ? (T *)st->Sbar[l] : nullptr;
+    D.ra[l] = l <= 7 ? (T *)st->reachA[l] : nullptr;
+    D.rb[l] = l <= 7 ? (T *)st->reachB[l] : nullptr;
+    D.u[l] = (T *)st->u[l];
+  }
+  D.vacc = st->vacc;
+  return D;
+}
+
+// The segments of one tree (item `it` of its plan), whose root counts are there,
+// appended: runs of consecutive roots, closed when the next root would exceed
+// seg_nodes nodes, `block` roots, or LDS.  t: bytes of the state's type.
+void tree_segments(const pasur_fgt *f, int it, uint32_t t, int seg_nodes, int block,
+                   bool force_global, std::vector<SegPlan> &segs) {
+  const uint32_t budget = force_global ? 0u : kLdsPerWorkgroup - kStaticLds;
+  const int64_t nr = f->n_roots;
+  auto level_nodes = [&](int l, int64_t j) {
+    const int32_t *o = f->h_root_off + (size_t)l * (nr + 1);
+    return o[j + 1] - o[j];
+  };
+  auto add_root = [&](SegCounts &c, int64_t &tot, int64_t j) {
+    int n[9], c07 = 0, ne = 0;
+    for (int l = 0; l <= 8; ++l) n[l] = level_nodes(l, j);
+    for (int l = 0; l <= 7; ++l) c07 += n[l];
+    for (int l = 1; l <= 6; ++l) ne += n[l];
+    const int32_t *x = f->h_root_seg + 4 * j;
+    c.na += c07 - n[6] - n[7] + x[0] + x[1];
+    c.ne += ne + x[2] + x[3];
+    c.ne67 += n[6] + x[2];
+    c.roots += 1;
+    c.c07 += c07;
+    c.c6 += n[6];
+    c.c7 += n[7];
+    tot += c07 + n[8];
+  };
+  auto bytes_of = [&](const SegCounts &c, int form) -> uint32_t {
+    if (c.c6 > 65535 || c.c7 > 65535 || !seg_indices_fit(c)) return 0u;
+    const uint32_t b = seg_layout(c, t, form).bytes;
+    return b <= budget ? b : 0u;
+  };
+  int64_t j0 = 0;
+  while (j0 < nr) {
+    int64_t j1 = j0 + 1, tot = 0;
+    SegCounts c = {};
+    add_root(c, tot, j0);
+    uint32_t bytes = bytes_of(c, F_LDS);
+    while (seg_nodes > 0 && bytes && j1 < nr && j1 - j0 < block) {
+      SegCounts c2 = c;
+      int64_t t2 = tot;
+      add_root(c2, t2, j1);
+      const uint32_t b2 = bytes_of(c2, F_LDS);
+      if (t2 > seg_nodes || !b2) break;
+      ++j1;
+      c = c2;
+      tot = t2;
+      bytes = b2;
+    }
+    SegPlan sp;
+    sp.seg.item = it;
+    sp.seg.j0 = (int32_t)j0;
+    sp.seg.j1 = (int32_t)j1;
+    sp.seg.far = sp.seg.far_n = 0;
+    sp.seg.form = F_LDS;
+    while (!bytes && sp.seg.form != F_NONE && !force_global)  // (a single root)
+      if (++sp.seg.form != F_NONE) bytes = bytes_of(c, sp.seg.form);
+    if (!bytes) sp.seg.form = F_NONE;
+    else if (sp.seg.form != F_LDS)
+      sp.seg.far_n = (int32_t)((seg_layout(c, t, sp.seg.form).far + kFarUnit - 1) / kFarUnit);
+    sp.nodes = tot;
+    sp.bytes = bytes;
+    segs.push_back(sp);
+    j0 = j1;
+  }
+}
+
+int64_t lds_segments(const std::vector<SegPlan> &segs) {
+  return std::count_if(segs.begin(), segs.end(),
+                       [](const SegPlan &sp) { return sp.seg.form == F_LDS; });
+}
+
+void add_work(int64_t work[4], const pasur_fgt *f) {
+  for (int l = 1; l <= 8; ++l) work[0] += f->n[l];
+  for (int l = 0; l <= 7; ++l) work[1] += f->n[l];
+  work[2] += f->n[0];
+  work[3] += f->n[7];
+}
+
+// The attribute is a ceiling shared by every launch of this instance, so it is
+// raised to the whole budget (plans may be launched in any order); each launch
+// still asks for its own lds_bytes.
+template <class T>
+int allow_lds(const std::vector<SegLaunch> &launches, bool paper) {
+  for (const SegLaunch &la : launches)
+    PASUR_TRY_HIP(hipFuncSetAttribute((const void *)seg_kernel<T>(la.block, paper, la.far),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)(kLdsPerWorkgroup - kStaticLds)));
+  return PASUR_OK;
+}
+
+template <class T>
+void launch_segments(const std::vector<SegLaunch> &launches, const void *items, const Seg *segs,
+                     const IterK *ks, void *far, int n_iters, int variant, int rm_mode, double eps,
+                     hipStream_t s) {
+  const bool paper = paper_variant(variant, rm_mode);
+  for (const SegLaunch &la : launches)
+    seg_kernel<T>(la.block, paper, la.far)<<<(unsigned)la.count, la.block, la.lds_bytes, s>>>(
+        (const ItemDesc<T> *)items, segs + la.first, ks, (unsigned char *)far, n_iters, variant,
+        rm_mode, eps, la.lds_bytes);
 }
 
 template <class T>
@@ -1446,119 +1593,15 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   const int n_items = pl->n_items;
   std::vector<ItemDesc<T>> items((size_t)n_items);
   std::vector<SegPlan> segs;
-  const uint32_t budget = force_global ? 0u : kLdsPerWorkgroup - kStaticLds;
   for (int64_t k = 0; k < 4; ++k) pl->work[k] = 0;
-  pl->n_lds_segs = 0;
   for (int it = 0; it < n_items; ++it) {
-    const pasur_fgt *f = fgts[it];
-    const pasur_cfr_state *st = states[it];
-    PASUR_TRY(root_counts(const_cast<pasur_fgt *>(f), s));
-    ItemDesc<T> &D = items[(size_t)it];
-    for (int l = 0; l <= 8; ++l) {
-      D.off[l] = f->root_off[l];
-      D.parent[l] = f->parent[l];
-      D.cb[l] = l <= 7 ? f->child_begin[l] : nullptr;
-      D.sigma[l] = l >= 1 ? (T *)st->sigma[l] : nullptr;
-      D.R[l] = l >= 1 ? (T *)st->R[l] : nullptr;
-      D.Sbar[l] = l >= 1 ? (T *)st->Sbar[l] : nullptr;
-      D.ra[l] = l <= 7 ? (T *)st->reachA[l] : nullptr;
-      D.rb[l] = l <= 7 ? (T *)st->reachB[l] : nullptr;
-      D.u[l] = (T *)st->u[l];
-    }
-    D.vacc = st->vacc;
-    // Segments: runs of consecutive roots, closed when the next root would
-    // exceed seg_nodes nodes, the workgroup's thread count, or LDS.
-    const int64_t nr = f->n_roots;
-    auto level_nodes = [&](int l, int64_t j) {
-      const int32_t *o = f->h_root_off + (size_t)l * (nr + 1);
-      return o[j + 1] - o[j];
-    };
-    auto add_root = [&](SegCounts &c, int64_t &tot, int64_t j) {
-      int n[9], c07 = 0, ne = 0;
-      for (int l = 0; l <= 8; ++l) n[l] = level_nodes(l, j);
-      for (int l = 0; l <= 7; ++l) c07 += n[l];
-      for (int l = 1; l <= 6; ++l) ne += n[l];
-      const int32_t *x = f->h_root_seg + 4 * j;
-      c.na += c07 - n[6] - n[7] + x[0] + x[1];
-      c.ne += ne + x[2] + x[3];
-      c.ne67 += n[6] + x[2];
-      c.roots += 1;
-      c.c07 += c07;
-      c.c6 += n[6];
-      c.c7 += n[7];
-      tot += c07 + n[8];
-    };
-    auto bytes_of = [&](const SegCounts &c, int form) -> uint32_t {
-      if (c.c6 > 65535 || c.c7 > 65535 || !seg_indices_fit(c)) return 0u;
-      const uint32_t b = seg_layout(c, sizeof(T), form).bytes;
-      return b <= budget ? b : 0u;
-    };
-    int64_t j0 = 0;
-    while (j0 < nr) {
-      int64_t j1 = j0 + 1, tot = 0;
-      SegCounts c = {};
-      add_root(c, tot, j0);
-      uint32_t bytes = bytes_of(c, F_LDS);
-      while (p->seg_nodes > 0 && bytes && j1 < nr && j1 - j0 < pl->block) {
-        SegCounts c2 = c;
-        int64_t t2 = tot;
-        add_root(c2, t2, j1);
-        const uint32_t b2 = bytes_of(c2, F_LDS);
-        if (t2 > p->seg_nodes || !b2) break;
-        ++j1;
-        c = c2;
-        tot = t2;
-        bytes = b2;
-      }
-      if (bytes) pl->n_lds_segs += 1;
-      SegPlan sp;
-      sp.seg.item = it;
-      sp.seg.j0 = (int32_t)j0;
-      sp.seg.j1 = (int32_t)j1;
-      sp.seg.far = sp.seg.far_n = 0;
-      sp.seg.form = F_LDS;
-      while (!bytes && sp.seg.form != F_NONE && !force_global)  // (a single root)
-        if (++sp.seg.form != F_NONE) bytes = bytes_of(c, sp.seg.form);
-      if (!bytes) sp.seg.form = F_NONE;
-      else if (sp.seg.form != F_LDS)
-        sp.seg.far_n =
-            (int32_t)((seg_layout(c, sizeof(T), sp.seg.form).far + kFarUnit - 1) / kFarUnit);
-      sp.nodes = tot;
-      sp.bytes = bytes;
-      segs.push_back(sp);
-      j0 = j1;
-    }
-    for (int l = 1; l <= 8; ++l) pl->work[0] += f->n[l];
-    for (int l = 0; l <= 7; ++l) pl->work[1] += f->n[l];
-    pl->work[2] += f->n[0];
-    pl->work[3] += f->n[7];
+    PASUR_TRY(root_counts(const_cast<pasur_fgt *>(fgts[it]), s));
+    items[(size_t)it] = item_desc<T>(fgts[it], states[it]);
+    tree_segments(fgts[it], it, sizeof(T), p->seg_nodes, pl->block, force_global, segs);
+    add_work(pl->work, fgts[it]);
   }
-  // Segments in global memory first, then those with far arrays, then the
-  // largest: the latter by how many a CU takes, and in buckets of 512 bytes (a
-  // comparison sort of 1e5 segments takes milliseconds).
-  auto order = [&]() {
-    std::vector<SegPlan> large, by_bytes(segs.size());
-    constexpr size_t kBuckets = kLdsPerWorkgroup / 512 + 1;
-    auto bucket = [](const SegPlan &sp) {
-      return (size_t)(per_cu(sp) - 1) * kBuckets + (kLdsPerWorkgroup - sp.bytes) / 512;
-    };
-    std::vector<size_t> at(4 * kBuckets + 1, 0);
-    for (const SegPlan &sp : segs) {
-      if (sp.seg.form != F_LDS) large.push_back(sp);
-      else at[bucket(sp) + 1] += 1;
-    }
-    std::stable_sort(large.begin(), large.end(), [](const SegPlan &a, const SegPlan &b) {
-      return a.seg.form != b.seg.form ? a.seg.form > b.seg.form : a.nodes > b.nodes;
-    });
-    at[0] = large.size();
-    for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
-    std::copy(large.begin(), large.end(), by_bytes.begin());
-    for (const SegPlan &sp : segs)
-      if (sp.seg.form == F_LDS) by_bytes[at[bucket(sp)]++] = sp;
-    segs.swap(by_bytes);
-    return plan_launches(pl, segs, p->block);
-  };
-  const int64_t far_bytes = order();
+  pl->n_lds_segs = lds_segments(segs);
+  const int64_t far_bytes = order_segments(pl->launches, segs, p->block);
   if (far_bytes > 0 && block_alloc(&pl->far, (size_t)far_bytes) != PASUR_OK) {
     // no memory for far arrays: in global memory
     pl->far = nullptr;
@@ -1568,7 +1611,7 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
         sp.seg.form = F_NONE;
         sp.bytes = 0;
       }
-    order();
+    (void)order_segments(pl->launches, segs, p->block);
   }
   std::vector<Seg> sorted(segs.size());
   uint32_t max_bytes = 0;
@@ -1600,24 +1643,7 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
     set_error("plan upload: %s", hipGetErrorString(e));
     return PASUR_E_HIP;
   }
-  const bool paper = paper_variant(p->variant, p->rm_mode);
-  // The attribute is a ceiling shared by every plan of this instance, so it
-  // is raised to the whole budget (plans may be launched in any order); each
-  // launch still asks for its own lds_bytes.
-  for (const SegLaunch &la : pl->launches)
-    PASUR_TRY_HIP(hipFuncSetAttribute((const void *)seg_kernel<T>(la.block, paper, la.far),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)(kLdsPerWorkgroup - kStaticLds)));
-  return PASUR_OK;
-}
-
-template <class T>
-void plan_launch(const pasur_plan *pl, const SegLaunch &la, int64_t t0, int n_iters,
-                 hipStream_t s) {
-  const bool paper = paper_variant(pl->variant, pl->rm_mode);
-  seg_kernel<T>(la.block, paper, la.far)<<<(unsigned)la.count, la.block, la.lds_bytes, s>>>(
-      (const ItemDesc<T> *)pl->d_items, pl->d_segs + la.first, pl->d_ks + (t0 - pl->t_first),
-      (unsigned char *)pl->far, n_iters, pl->variant, pl->rm_mode, pl->eps, la.lds_bytes);
+  return allow_lds<T>(pl->launches, paper_variant(p->variant, p->rm_mode));
 }
 
 }  // namespace
@@ -1724,6 +1750,183 @@ int seg_iterate(const pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_p
 }
 }  // namespace pasur
 
+// ---- one tree, without waiting ---------------------------------------------------
+namespace {
+// Bytes from the host behind the arguments of a kernel, which copies them (no
+// pinned memory to keep until a copy has ended, and a graph keeps them).
+struct PutBytes {
+  uint4 b[224];
+};
+__global__ void __launch_bounds__(256) k_put(PutBytes a, int n, uint4 *__restrict__ out) {
+  if ((int)threadIdx.x < n) out[threadIdx.x] = a.b[threadIdx.x];
+}
+
+// (their constants pass through the host's memory and kernel arguments)
+constexpr int kSegIters = 1 << 20;
+
+void put(unsigned char *to, const unsigned char *from, size_t bytes, hipStream_t s) {
+  for (size_t at = 0; at < bytes; at += sizeof(PutBytes)) {
+    PutBytes a;
+    const size_t n = std::min(bytes - at, sizeof(a));
+    std::memcpy(&a, from + at, n);
+    k_put<<<1, 256, 0, s>>>(a, (int)((n + 15) / 16), (uint4 *)(to + at));
+  }
+}
+
+}  // namespace
+
+namespace pasur {
+// The segments of a tree by itself, for one state type and one choice of
+// workgroup and segment size.  Never changed once it is on the tree's list.
+struct SegIndex {
+  int dtype, block, seg_nodes;
+  std::vector<SegLaunch> launches;
+  void *mem;  // the segments, on the device
+  int64_t far_bytes, n_segs, n_lds_segs;
+  SegIndex *next;
+};
+
+int seg_index_blocks(const SegIndex *x, void **p, int n) {
+  int k = 0;
+  for (; x && k < n; x = x->next) p[k++] = x->mem;
+  return k;
+}
+
+void seg_index_free(SegIndex *x) {
+  while (x) {
+    SegIndex *const next = x->next;
+    delete x;
+    x = next;
+  }
+}
+}  // namespace pasur
+
+namespace {
+// The tree's index for these, or else (any) for this type; g_counts_mu is held.
+const SegIndex *find_index(const pasur_fgt *f, int dtype, int block, int seg_nodes, bool any) {
+  for (const SegIndex *x = f->seg_index; x; x = x->next)
+    if (x->dtype == dtype && (any || (x->block == block && x->seg_nodes == seg_nodes))) return x;
+  return nullptr;
+}
+
+int build_index(pasur_fgt *f, int dtype, int block, int seg_nodes, hipStream_t s) {
+  std::vector<SegPlan> segs;
+  tree_segments(f, 0, dtype == PASUR_F32 ? 4 : 8, seg_nodes, block ? block : 1024, false, segs);
+  SegIndex *const x = new SegIndex();
+  x->dtype = dtype;
+  x->block = block;
+  x->seg_nodes = seg_nodes;
+  x->n_segs = (int64_t)segs.size();
+  x->n_lds_segs = lds_segments(segs);
+  x->far_bytes = order_segments(x->launches, segs, block);
+  std::vector<Seg> sorted(segs.size());
+  for (size_t i = 0; i < segs.size(); ++i) sorted[i] = segs[i].seg;
+  x->mem = nullptr;
+  int st = block_alloc(&x->mem, sizeof(Seg) * sorted.size());
+  if (!st) {
+    hipError_t e = hipMemcpyAsync(x->mem, sorted.data(), sizeof(Seg) * sorted.size(),
+                                  hipMemcpyHostToDevice, s);
+    const hipError_t e2 = hipStreamSynchronize(s);  // `sorted` goes out of scope
+    if (e == hipSuccess) e = e2;
+    if (e != hipSuccess) {
+      set_error("segment index: %s", hipGetErrorString(e));
+      st = PASUR_E_HIP;
+      if (e2 == hipSuccess) block_free(x->mem);  // (else it may be in use)
+    }
+  }
+  if (st) {
+    delete x;
+    return st;
+  }
+  std::lock_guard<std::mutex> lock(g_counts_mu);
+  // another thread may have been faster: what it put there stays
+  const SegIndex *const there = find_index(f, dtype, block, seg_nodes, false);
+  int n = 0;
+  for (const SegIndex *y = f->seg_index; y; y = y->next) ++n;
+  if (there || n == kSegIndexes) {
+    block_free(x->mem);
+    delete x;
+    return PASUR_OK;
+  }
+  x->next = f->seg_index;
+  f->seg_index = x;
+  return PASUR_OK;
+}
+
+template <class T>
+int enqueue(const pasur_fgt *f, const SegIndex &x, const pasur_cfr_state *st,
+            const pasur_cfr_params *p, int64_t t0, int n_iters, bool capturing, bool *done,
+            hipStream_t s) {
+  const bool paper = paper_variant(p->variant, p->rm_mode);
+  PASUR_TRY(allow_lds<T>(x.launches, paper));
+  // far arrays, the item, the iterations' constants
+  const ItemDesc<T> D = item_desc<T>(f, st);
+  std::vector<unsigned char> stage(align16(sizeof(D)) + sizeof(IterK) * (size_t)n_iters);
+  std::memcpy(stage.data(), &D, sizeof(D));
+  IterK *const ks = (IterK *)(stage.data() + align16(sizeof(D)));
+  for (int i = 0; i < n_iters; ++i) ks[i] = iter_k(p, t0 + i);
+  const size_t far_bytes = align16((size_t)x.far_bytes), bytes = far_bytes + stage.size() + 16;
+  void *mem = nullptr;
+  if (capturing) {
+    if (hipMallocAsync(&mem, bytes, s) != hipSuccess) {
+      (void)hipGetLastError();
+      return PASUR_OK;
+    }
+  } else if (block_alloc_on(&mem, bytes, s) != PASUR_OK) {
+    return PASUR_OK;
+  }
+  unsigned char *const at = (unsigned char *)mem + far_bytes;
+  put(at, stage.data(), stage.size(), s);
+  int64_t work[4] = {0, 0, 0, 0};
+  add_work(work, f);
+  {
+    ProfScope ps(x.n_lds_segs == x.n_segs ? 2 : 3, -1, s, work[0], work[1], work[2], work[3],
+                 n_iters);
+    launch_segments<T>(x.launches, at, (const Seg *)x.mem, (const IterK *)(at + align16(sizeof(D))),
+                       mem, n_iters, p->variant, p->rm_mode, p->eps, s);
+  }
+  const hipError_t e = hipGetLastError();
+  if (capturing) (void)hipFreeAsync(mem, s);
+  else block_free_on(mem, s);
+  *done = true;
+  PASUR_TRY_HIP(e);
+  return PASUR_OK;
+}
+}  // namespace
+
+namespace pasur {
+bool seg_ready(const pasur_fgt *f, int dtype) {
+  std::lock_guard<std::mutex> lock(g_counts_mu);
+  return find_index(f, dtype, 0, 0, true) != nullptr;
+}
+
+int seg_enqueue(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p, int64_t t0,
+                int n_iters, bool capturing, bool *done, hipStream_t s) {
+  if (n_iters > kSegIters) return PASUR_OK;
+  const SegIndex *x;
+  {
+    std::lock_guard<std::mutex> lock(g_counts_mu);
+    x = find_index(f, st->dtype, p->block, p->seg_nodes, false);
+    if (!x && capturing) x = find_index(f, st->dtype, 0, 0, true);
+  }
+  if (!x && !capturing) {
+    PASUR_TRY(root_counts(f, s));
+    // for both types, so that a later call may be captured whatever its state's
+    for (int dtype : {PASUR_F32, PASUR_F64}) {
+      if (dtype != st->dtype && seg_ready(f, dtype)) continue;
+      PASUR_TRY(build_index(f, dtype, p->block, p->seg_nodes, s));
+    }
+    std::lock_guard<std::mutex> lock(g_counts_mu);
+    // (a tree's list has room for kSegIndexes: any has the same results)
+    x = find_index(f, st->dtype, p->block, p->seg_nodes, false);
+    if (!x) x = find_index(f, st->dtype, 0, 0, true);
+  }
+  if (!x) return PASUR_OK;
+  return st->dtype == PASUR_F32 ? enqueue<float>(f, *x, st, p, t0, n_iters, capturing, done, s)
+                                : enqueue<double>(f, *x, st, p, t0, n_iters, capturing, done, s);
+}
+}  // namespace pasur
+
 extern "C" int pasur_plan_iterate(const pasur_plan *pl, int64_t t0, int n_iters, void *stream) {
   if (!pl) {
     set_error("plan is NULL");
@@ -1739,10 +1942,13 @@ extern "C" int pasur_plan_iterate(const pasur_plan *pl, int64_t t0, int n_iters,
   {
     ProfScope ps(pl->n_lds_segs == pl->n_segs ? 2 : 3, -1, s, pl->work[0], pl->work[1],
                  pl->work[2], pl->work[3], n_iters);
-    for (const SegLaunch &la : pl->launches) {
-      if (pl->dtype == PASUR_F32) plan_launch<float>(pl, la, t0, n_iters, s);
-      else plan_launch<double>(pl, la, t0, n_iters, s);
-    }
+    const IterK *const ks = pl->d_ks + (t0 - pl->t_first);
+    if (pl->dtype == PASUR_F32)
+      launch_segments<float>(pl->launches, pl->d_items, pl->d_segs, ks, pl->far, n_iters,
+                             pl->variant, pl->rm_mode, pl->eps, s);
+    else
+      launch_segments<double>(pl->launches, pl->d_items, pl->d_segs, ks, pl->far, n_iters,
+                              pl->variant, pl->rm_mode, pl->eps, s);
   }
   PASUR_TRY_HIP(hipGetLastError());
   return PASUR_OK;

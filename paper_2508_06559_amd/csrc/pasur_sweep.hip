@@ -1540,12 +1540,20 @@ int sweep_t(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p, 
 
 }  // namespace
 
-bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters, hipStream_t s) {
+namespace {
+int64_t nodes_of(const pasur_fgt *f) {
   int64_t nodes = 0;
   for (int l = 0; l <= 8; ++l) nodes += f->n[l];
-  // Small rounds: each iteration's 30 launches cost more than all of its work
-  // (1.5e6 nodes, 20 iterations: streaming 1.11, segments 0.44 ms).
-  if (nodes < (int64_t)9 * 1000 * 1000) return false;
+  return nodes;
+}
+}  // namespace
+
+// In small rounds each iteration's 30 launches cost more than all of its work
+// (1.5e6 nodes, 20 iterations: streaming 1.11, segments 0.44 ms).
+bool large_round(const pasur_fgt *f) { return nodes_of(f) >= (int64_t)9 * 1000 * 1000; }
+
+bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters) {
+  const int64_t nodes = nodes_of(f);
   // Huge ones, whose large roots fill the segments' launches unevenly (20
   // iterations, streaming vs segments: 1.5e8 nodes 17.4 vs 15.7 ms, 6.8e8
   // 60 vs 82 ms, 1.6e9 252 vs 290 ms).
@@ -1569,11 +1577,7 @@ bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters, hipStream_t s) {
     }
     if (n > cap) beyond += n;
   }
-  if (beyond > nodes / 100) return true;
-  // making a plan waits for the stream, which a capture does not allow
-  hipStreamCaptureStatus cap_status = hipStreamCaptureStatusNone;
-  (void)hipStreamIsCapturing(s, &cap_status);
-  return cap_status != hipStreamCaptureStatusNone;
+  return beyond > nodes / 100;
 }
 
 int sweep_iterate(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,

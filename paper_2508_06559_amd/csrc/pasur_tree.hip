@@ -706,11 +706,14 @@ __global__ void k_next_roots(int64_t n, const uint64_t *__restrict__ keys,
 
 extern "C" void pasur_fgt_free(pasur_fgt *f) {
   if (!f) return;
-  void *const blocks[] = {f->off_block, f->block, f->next_block};
-  blocks_retire(f->anchor, blocks, 3);
+  // (one segment index per state type and per choice of block and seg_nodes)
+  void *blocks[kRetired] = {f->off_block, f->block, f->next_block};
+  const int n = 3 + seg_index_blocks(f->seg_index, blocks + 3, kRetired - 3);
+  blocks_retire(f->anchor, blocks, n);
   std::free(f->h_root_off);
   std::free(f->h_root_seg);
   sweep_index_free(f->sweep);
+  seg_index_free(f->seg_index);
   delete f;
 }
 

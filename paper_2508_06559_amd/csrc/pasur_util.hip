@@ -129,6 +129,18 @@ bool room_on(int device) {
   return room;
 }
 
+// An idle block goes to the cache or to the system.
+void give_back(const Block &b) {
+  bool keep = b.bytes < ((size_t)64 << 20) || room_on(b.device);
+  if (keep) {
+    Outgoing out;
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    keep = make_room(b.bytes, b.device, out);
+    if (keep) g_free[g_n_free++] = b;
+  }
+  if (!keep) (void)hipFree(b.p);
+}
+
 // Blocks whose handles are gone but whose idleness is not known.
 struct Retired {
   void *anchor, *blocks[kRetired];
@@ -141,6 +153,68 @@ bool anchor_wait(void *a) {
   if (!a || hipFree(a) == hipSuccess) return true;
   (void)hipGetLastError();
   return false;
+}
+
+// Blocks that go back when the work enqueued before an event has ended.
+struct Pending {
+  Block b;
+  hipStream_t stream;
+  hipEvent_t ended;
+  Pending *next;
+};
+Pending *g_pending = nullptr;
+
+// Gives pending blocks back whose work has ended, or all of them (wait).
+void pending_again(bool wait) {
+  Pending *list;
+  {
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    list = g_pending;
+    g_pending = nullptr;
+  }
+  while (list) {
+    Pending *const p = list;
+    list = p->next;
+    if ((wait ? hipEventSynchronize(p->ended) : hipEventQuery(p->ended)) == hipSuccess) {
+      (void)hipEventDestroy(p->ended);
+      give_back(p->b);
+      std::free(p);
+      continue;
+    }
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    p->next = g_pending;
+    g_pending = p;
+  }
+}
+
+// A pending block of this stream that holds `bytes` and is at most a quarter
+// larger: what follows on the stream may have it at once.
+bool take_pending(size_t bytes, int device, hipStream_t s, Block *out) {
+  Pending *p;
+  {
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    Pending **at = &g_pending;
+    while (*at && !((*at)->stream == s && (*at)->b.device == device && (*at)->b.bytes >= bytes &&
+                    (*at)->b.bytes <= bytes + bytes / 4))
+      at = &(*at)->next;
+    p = *at;
+    if (!p) return false;
+    *at = p->next;
+  }
+  // (of this stream, or of an earlier one of the same name)
+  const bool ok = hipStreamWaitEvent(s, p->ended, 0) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    p->next = g_pending;
+    g_pending = p;
+    return false;
+  }
+  *out = p->b;
+  (void)hipEventDestroy(p->ended);
+  std::free(p);
+  return true;
 }
 
 // Waits once more for the device on behalf of blocks that were set aside.
@@ -160,7 +234,8 @@ void retire_again() {
 }
 }  // namespace
 
-int block_alloc(void **p, size_t bytes) {
+namespace {
+int alloc(void **p, size_t bytes, bool on_stream, hipStream_t s) {
   *p = nullptr;
   int device = 0;
   PASUR_TRY_HIP(hipGetDevice(&device));
@@ -176,11 +251,18 @@ int block_alloc(void **p, size_t bytes) {
     std::lock_guard<std::mutex> lock(g_block_mu);
     cached = take_cached(want, device, &o->b);
   }
+  if (!cached && on_stream) cached = take_pending(want, device, s, &o->b);
+  if (!cached) {
+    pending_again(false);
+    std::lock_guard<std::mutex> lock(g_block_mu);
+    cached = take_cached(want, device, &o->b);
+  }
   if (!cached) {
     void *mem = nullptr;
     hipError_t e = hipMalloc(&mem, want);
     if (e != hipSuccess) {
       (void)hipGetLastError();
+      pending_again(true);
       release_cached(device);
       e = hipMalloc(&mem, want);
     }
@@ -200,31 +282,52 @@ int block_alloc(void **p, size_t bytes) {
   return PASUR_OK;
 }
 
+// Takes a block off the list of those in use.
+bool disown(void *p, Block *b) {
+  std::lock_guard<std::mutex> lock(g_block_mu);
+  Owned **at = owned_place(p);
+  while (*at && (*at)->b.p != p) at = &(*at)->next;
+  if (!*at) return false;
+  Owned *o = *at;
+  *at = o->next;
+  *b = o->b;
+  std::free(o);
+  return true;
+}
+}  // namespace
+
+int block_alloc(void **p, size_t bytes) { return alloc(p, bytes, false, nullptr); }
+int block_alloc_on(void **p, size_t bytes, hipStream_t s) { return alloc(p, bytes, true, s); }
+
 void block_free(void *p) {
-  if (!p) return;
   Block b;
-  {
-    std::lock_guard<std::mutex> lock(g_block_mu);
-    Owned **at = owned_place(p);
-    while (*at && (*at)->b.p != p) at = &(*at)->next;
-    if (!*at) return;
-    Owned *o = *at;
-    *at = o->next;
-    b = o->b;
-    std::free(o);
+  if (p && disown(p, &b)) give_back(b);
+}
+
+void block_free_on(void *p, hipStream_t s) {
+  Block b;
+  if (!p || !disown(p, &b)) return;
+  Pending *const n = (Pending *)std::malloc(sizeof(Pending));
+  hipEvent_t ended = nullptr;
+  if (!n || hipEventCreateWithFlags(&ended, hipEventDisableTiming) != hipSuccess ||
+      hipEventRecord(ended, s) != hipSuccess) {
+    // when its work ends isn't known: the memory stays unused
+    (void)hipGetLastError();
+    if (ended) (void)hipEventDestroy(ended);
+    std::free(n);
+    return;
   }
-  bool keep = b.bytes < ((size_t)64 << 20) || room_on(b.device);
-  if (keep) {
-    Outgoing out;
-    std::lock_guard<std::mutex> lock(g_block_mu);
-    keep = make_room(b.bytes, b.device, out);
-    if (keep) g_free[g_n_free++] = b;
-  }
-  if (!keep) (void)hipFree(b.p);
+  n->b = b;
+  n->stream = s;
+  n->ended = ended;
+  std::lock_guard<std::mutex> lock(g_block_mu);
+  n->next = g_pending;
+  g_pending = n;
 }
 
 void blocks_release() {
   retire_again();
+  pending_again(false);
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess) return;
   release_cached(device);

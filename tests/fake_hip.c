@@ -21,6 +21,8 @@ struct {
   int pending;          /* launches since the last wait */
   int freed_pending;    /* hipFrees of memory while work was pending */
   int mallocs, frees, host_mallocs, syncs, launches, mallocs_async, frees_async;
+  int unfinished;       /* events have not ended yet */
+  int event_waits;      /* hipStreamWaitEvents */
   int64_t free_bytes[2], total_bytes[2];  /* per device */
   int64_t words[31];    /* what the kernels report in the library's host words */
   void (*in_sync)(void);  /* called before a wait ends */
@@ -123,6 +125,25 @@ int hipFuncSetAttribute(const void *f, int a, int v) {
 }
 int hipEventCreate(void **e) {
   *e = malloc(1);
+  return 0;
+}
+int hipEventCreateWithFlags(void **e, unsigned flags) {
+  (void)flags;
+  return hipEventCreate(e);
+}
+int hipEventDestroy(void *e) {
+  free(e);
+  return 0;
+}
+int hipEventQuery(void *e) {
+  (void)e;
+  return fake.unfinished ? 600 : 0;
+}
+int hipStreamWaitEvent(void *s, void *e, unsigned flags) {
+  (void)s;
+  (void)e;
+  (void)flags;
+  ++fake.event_waits;
   return 0;
 }
 int hipEventRecord(void *e, void *s) {

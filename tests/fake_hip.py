@@ -15,7 +15,8 @@ class Fake(C.Structure):
     _fields_ = ([(n, C.c_int) for n in
                  ("free_status", "sync_status", "last_error", "failing_mallocs", "failing_after",
                   "device", "capturing", "pending", "freed_pending", "mallocs", "frees",
-                  "host_mallocs", "syncs", "launches", "mallocs_async", "frees_async")] +
+                  "host_mallocs", "syncs", "launches", "mallocs_async", "frees_async",
+                  "unfinished", "event_waits")] +
                 [("free_bytes", C.c_int64 * 2), ("total_bytes", C.c_int64 * 2),
                  ("words", C.c_int64 * 31), ("in_sync", C.c_void_p), ("in_free", C.c_void_p)])
 

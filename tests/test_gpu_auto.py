@@ -1,0 +1,93 @@
+"""PASUR_SCHED_AUTO on large rounds: enqueued without a wait, captured and
+replayed, side by side on several streams.  The schedules run the same operations
+in the same order: states are compared bit for bit."""
+import threading
+
+import pytest
+
+import synth
+from gpu_common import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def game(pa):
+    """The whole game of deal 1: rounds 4 and 6 have 1.4e7 and 9.7e6 nodes."""
+    deck, roots = synth.full_game_root(1)
+    return pa.SubgameSolver(deck, 0, roots)
+
+
+def fresh(pa, torch, rr, dtype):
+    st = pa.CfrState(rr.fgt, dtype)
+    V = None
+    if rr.round < 5:
+        g = torch.Generator(device="cuda").manual_seed(3)
+        V = torch.empty(rr.fgt.n_next, dtype=torch.float64, device="cuda").uniform_(-9, 9, generator=g)
+    pa.leaf_utilities(rr.fgt, V, dtype, st.u[8])
+    pa.cfr_init(st)
+    return st
+
+
+def tensors(st):
+    return st.sigma[1:] + st.R[1:] + st.u + [st.vacc]
+
+
+def test_auto_returns_before_its_work_is_done():
+    """20 iterations of 1.4e7 nodes behind 50 ms of other work, on a tree whose first
+    call is over."""
+    pa = require_gpu()
+    import torch
+    s = game(pa)
+    rr = s.rounds[3]
+    pa.cfr_iterate(fresh(pa, torch, rr, pa.PASUR_F32), 20)
+    ref = fresh(pa, torch, rr, pa.PASUR_F32)
+    pa.cfr_iterate(ref, 20, pa.paper_params(pa.SCHED_ROOT))
+    pa.cfr_iterate(ref, 20, pa.paper_params(pa.SCHED_ROOT))
+    st = fresh(pa, torch, rr, pa.PASUR_F32)
+    torch.cuda.synchronize()
+    torch.cuda._sleep(100_000_000)
+    pa.cfr_iterate(st, 20)
+    pa.cfr_iterate(st, 20)
+    assert not torch.cuda.current_stream().query()
+    torch.cuda.synchronize()
+    for a, b in zip(tensors(st) + st.Sbar[1:], tensors(ref) + ref.Sbar[1:]):
+        assert torch.equal(a, b)
+    s.free()
+
+
+def test_auto_on_two_streams_and_from_two_threads():
+    """Roots of up to 26,000 nodes, whose far arrays are scratch of the call: calls
+    on states of their own that run at the same time."""
+    pa = require_gpu()
+    import torch
+    s = game(pa)
+    rr = s.rounds[3]
+    ref = fresh(pa, torch, rr, pa.PASUR_F32)
+    for _ in range(3):
+        pa.cfr_iterate(ref, 10)
+    states = [fresh(pa, torch, rr, pa.PASUR_F32) for _ in range(4)]
+    streams = [torch.cuda.Stream() for _ in states]
+    torch.cuda.synchronize()
+    for _ in range(3):  # two streams, one thread
+        for st, q in list(zip(states, streams))[:2]:
+            pa.cfr_iterate(st, 10, stream=q)
+    failed = []
+
+    def work(st, q):
+        try:
+            for _ in range(3):
+                pa.cfr_iterate(st, 10, stream=q)
+        except Exception as e:  # noqa: BLE001
+            failed.append(repr(e))
+
+    threads = [threading.Thread(target=work, args=x) for x in list(zip(states, streams))[2:]]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for st in states:
+        for a, b in zip(tensors(st) + st.Sbar[1:], tensors(ref) + ref.Sbar[1:]):
+            assert torch.equal(a, b)
+    s.free()
