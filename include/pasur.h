@@ -228,12 +228,13 @@ typedef enum { PASUR_RM_FLOOR = 0, PASUR_RM_POSITIVE = 1 } pasur_rm_mode;
  *   leave them);
  * ROOT and ROOT_GLOBAL wait for the stream.  STREAM, and AUTO on rounds of 9e6
  * nodes or more, only enqueue work, but for the first call on a tree, which builds
- * an index of it and waits.
+ * an index of it and waits; after such a call on a tree they may be captured.
  * AUTO: ROOT for rounds of fewer than 9e6 nodes and, unless many of their
  *   nodes are below roots of more than 30,000 (F64: 15,000) nodes, for calls of
  *   at least 4 + nodes / 1.2e7 iterations on rounds of fewer than 2.5e8 nodes;
- *   else, and where the stream is being captured, STREAM.  In what STREAM notes of
- *   Sbar, AUTO's calls on one state are what each of them took. */
+ *   else STREAM; a call that is captured takes the one whose index is there.  In
+ *   what STREAM notes of Sbar, AUTO's calls on one state are what each of them
+ *   took. */
 typedef enum { PASUR_SCHED_ROOT = 0, PASUR_SCHED_LEVEL_SYNC = 1,
                PASUR_SCHED_ROOT_GLOBAL = 2, PASUR_SCHED_STREAM = 3,
                PASUR_SCHED_AUTO = 4 } pasur_schedule;

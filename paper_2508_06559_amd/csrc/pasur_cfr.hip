@@ -496,7 +496,9 @@ extern "C" int pasur_cfr_iterate(const pasur_fgt *f, const pasur_cfr_state *st,
         capturing = status != hipStreamCaptureStatusNone;
       else
         (void)hipGetLastError();  // another capture forbids to ask
-      bool segs = !capturing && !sweep_pays(f, st->dtype, n_iters), done = false;
+      // a capture takes the schedule whose index an earlier call has built
+      bool segs = !sweep_pays(f, st->dtype, n_iters), done = false;
+      if (capturing) segs = seg_ready(f, st->dtype) && (segs || !f->sweep);
       if (segs) PASUR_TRY(seg_enqueue(tree, st, p, t0, n_iters, capturing, &done, s));
       if (done) return PASUR_OK;
     }

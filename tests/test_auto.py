@@ -36,6 +36,24 @@ def test_auto_only_enqueues_on_large_rounds(tmp_path):
     """, tmp_path)
 
 
+def test_auto_is_captured_after_any_call_on_the_tree(tmp_path):
+    """Whatever that call's state type and iterations: a capture may neither wait
+    nor allocate."""
+    for first in ("f32, 20", "f64, 20", "f32, 2", "f64, 2"):
+        fake_hip.run(SETUP + f"""
+        assert run({first}) == 0, L.pasur_last_error()
+        fake.capturing = 1
+        syncs, mallocs, launches = fake.syncs, fake.mallocs, fake.launches
+        for s in (f32, f64):
+            for iters in (2, 20, 300):
+                assert run(s, iters, 8) == 0, L.pasur_last_error()
+                assert (fake.syncs, fake.mallocs) == (syncs, mallocs), (s.dtype, iters)
+        assert fake.launches > launches
+        assert fake.mallocs_async == fake.frees_async
+        fake.capturing = 0
+        """, tmp_path)
+
+
 def test_scratch_of_enqueued_calls_is_not_shared(tmp_path):
     """A later call on the same stream follows the first one; a call on another
     stream has scratch of its own until the first one's work has ended."""

@@ -32,6 +32,46 @@ def tensors(st):
     return st.sigma[1:] + st.R[1:] + st.u + [st.vacc]
 
 
+# the call before the capture, and the captured one: segments or streaming sweeps
+# (three iterations), of either state type
+@pytest.mark.parametrize("before,captured", [((12, "F32"), (12, "F32")), ((12, "F32"), (9, "F64")),
+                                             ((2, "F32"), (12, "F64")), ((12, "F64"), (2, "F32"))])
+@pytest.mark.parametrize("k", [5, 3])
+def test_auto_captured_after_a_warm_up(k, before, captured):
+    pa = require_gpu()
+    import torch
+    s = game(pa)
+    rr = s.rounds[k]
+    n0, t0 = before[0], getattr(pa, "PASUR_" + before[1])
+    n1, t1 = captured[0], getattr(pa, "PASUR_" + captured[1])
+    print(f"[auto] round {k + 1}, {before} then {captured}", flush=True)
+    pa.cfr_iterate(fresh(pa, torch, rr, t0), n0)
+    ref = fresh(pa, torch, rr, t1)
+    pa.cfr_iterate(ref, n1, pa.paper_params(pa.SCHED_LEVEL_SYNC))
+    want = [t.clone() for t in tensors(ref)]
+    st = fresh(pa, torch, rr, t1)
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            pa.cfr_init(st, side)
+            pa.cfr_iterate(st, n1, stream=side)
+    torch.cuda.current_stream().wait_stream(side)
+    other = fresh(pa, torch, rr, t0)
+    for i in range(4):
+        for t in tensors(st)[:-1]:
+            if t is not st.u[8]:
+                t.fill_(0.25)
+        if i % 2:  # eager work between the replays
+            pa.cfr_iterate(other, n0)
+            torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for j, (a, b) in enumerate(zip(tensors(st), want)):
+            assert torch.equal(a, b), (i, j)
+    s.free()
+
+
 def test_auto_returns_before_its_work_is_done():
     """20 iterations of 1.4e7 nodes behind 50 ms of other work, on a tree whose first
     call is over."""
