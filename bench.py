@@ -53,11 +53,6 @@ TRAFFIC = {
 }
 
 
-def streamed(nodes, iters):
-    """Whether the automatic schedule streams a round (its root sizes aside)."""
-    return nodes >= 9_000_000 and (nodes >= 250_000_000 or iters < 4 + nodes // 12_000_000)
-
-
 def counted_traffic(args, workload="two-round"):
     """HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE counters (copy
     calibrated), valid only for the kernel source they were taken on."""
@@ -412,7 +407,7 @@ def bench_full(args):
     # warm-up, the timed steps record every launch.
     pa.profile_enable(True)
     per_all = None
-    round_alg = {}
+    round_alg, round_sched = {}, {}
     for w in range(args.warmup):
         sizes, ex, V0 = step(on_round=mark if w == 0 else None)
         log(f"[bench] warmup {w + 1}/{args.warmup} done, exploitability {ex:.3e}")
@@ -425,6 +420,8 @@ def bench_full(args):
             part = [x for x in recs_all[prev:cnt] if x[0] != 8]
             b = sum(x[1] for x in part)
             t = sum(x[2] for x in part)
+            ran = {x[0] for x in part}
+            round_sched[r] = "persistent segments" if ran & {2, 3} else "stream"
             lds = sum(x[1] for x in part if x[0] == 2)  # k_cfr_seg, every segment in LDS
             seg = sum(x[1] for x in part if x[0] in (2, 3))
             round_alg[r] = (b, t, lds / seg if seg else None)
@@ -462,8 +459,8 @@ def bench_full(args):
         ms_r = round_ms[5 - r] if len(round_ms) == 6 else None
         b_r, t_r, lds_r = round_alg.get(r, (0.0, 0.0, None))
         rounds.append({"round": r + 1, "nodes": int(sum(n)), "edges": int(e_r),
-                       "schedule": (("stream" if streamed(sum(n), iters) else "persistent segments")
-                                    if args.sched == "auto" else args.sched),
+                       # as the first warm-up step's launches show it
+                       "schedule": round_sched.get(r, args.sched) if args.sched == "auto" else args.sched,
                        "dcfr_ms": ms_r,
                        "node_updates_per_s": e_r * iters / (ms_r * 1e-3) if ms_r else None,
                        # algorithmic bytes of the round's sweep launches over

@@ -229,9 +229,10 @@ typedef enum { PASUR_RM_FLOOR = 0, PASUR_RM_POSITIVE = 1 } pasur_rm_mode;
  * ROOT and ROOT_GLOBAL wait for the stream.  STREAM, and AUTO on rounds of 9e6
  * nodes or more, only enqueue work, but for the first call on a tree, which builds
  * an index of it and waits; after such a call on a tree they may be captured.
- * AUTO: ROOT for rounds of fewer than 9e6 nodes and, unless many of their
- *   nodes are below roots of more than 30,000 (F64: 15,000) nodes, for calls of
- *   at least 4 + nodes / 1.2e7 iterations on rounds of fewer than 2.5e8 nodes;
+ * AUTO: ROOT for rounds of fewer than 9e6 nodes and, on larger ones, for calls of
+ *   at least 5 + nodes / 1e7 iterations (three times as many where more than 1% of
+ *   the nodes are below roots of more than 60,000, F64 30,000), unless a root has
+ *   more than 30,000 + nodes / 1000 nodes;
  *   else STREAM; a call that is captured takes the one whose index is there.  In
  *   what STREAM notes of Sbar, AUTO's calls on one state are what each of them
  *   took. */

@@ -324,6 +324,9 @@ struct pasur_fgt {
   // per root, what a segment's LDS layout counts (4 ints: see pasur_seg.hip),
   // on the host; computed on first use
   int32_t *h_root_seg;
+  // the largest root's nodes (0: not computed yet) and those below large roots
+  // (per state type: see sweep_pays)
+  int64_t root_largest, root_tail[2];
   // the segments of the tree by itself, one index after another, built on first use
   pasur::SegIndex *seg_index;
   // split_ws: a double per node of split_nodes(), where pasur_tree_values_noalloc

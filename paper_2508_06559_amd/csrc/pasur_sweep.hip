@@ -43,6 +43,7 @@
 #include "pasur_parents.hpp"
 
 #include <algorithm>
+#include <mutex>
 #include <vector>
 
 namespace pasur {
@@ -1552,32 +1553,56 @@ int64_t nodes_of(const pasur_fgt *f) {
 // (1.5e6 nodes, 20 iterations: streaming 1.11, segments 0.44 ms).
 bool large_round(const pasur_fgt *f) { return nodes_of(f) >= (int64_t)9 * 1000 * 1000; }
 
+namespace {
+std::mutex g_sizes_mu;
+
+// The largest root's nodes, and the nodes below roots of more than kTail[dtype].
+constexpr int64_t kTail[2] = {60000, 30000};
+struct RootSizes {
+  int64_t largest, tail[2];
+};
+RootSizes root_sizes(const pasur_fgt *f) {
+  std::lock_guard<std::mutex> lock(g_sizes_mu);
+  pasur_fgt *const t = const_cast<pasur_fgt *>(f);
+  if (t->root_largest == 0) {
+    const int64_t nr = f->n_roots;
+    int64_t largest = 0, tail[2] = {0, 0};
+    for (int64_t j = 0; j < nr; ++j) {
+      int64_t n = 0;
+      for (int l = 0; l <= 8; ++l) {
+        const int32_t *o = f->h_root_off + (size_t)l * (nr + 1) + j;
+        n += o[1] - o[0];
+      }
+      largest = std::max(largest, n);
+      for (int k = 0; k < 2; ++k)
+        if (n > kTail[k]) tail[k] += n;
+    }
+    t->root_tail[0] = tail[0];
+    t->root_tail[1] = tail[1];
+    t->root_largest = std::max<int64_t>(largest, 1);
+  }
+  return {t->root_largest, {t->root_tail[0], t->root_tail[1]}};
+}
+}  // namespace
+
+// Measured on 49 rounds of 8e6 to 1.6e9 nodes, FP32, and 18 in FP64: a segment's
+// iteration takes 2.2 to 6.1 (3.3 to 7.9) ps per node, a sweep's 3.5 to 6.7 (6.1 to
+// 9.4) and up to 100 us of launches; what is done once per call 16 to 40 (26 to 54)
+// against 7 to 34 (10 to 77).
 bool sweep_pays(const pasur_fgt *f, int dtype, int n_iters) {
   const int64_t nodes = nodes_of(f);
-  // Huge ones, whose large roots fill the segments' launches unevenly (20
-  // iterations, streaming vs segments: 1.5e8 nodes 17.4 vs 15.7 ms, 6.8e8
-  // 60 vs 82 ms, 1.6e9 252 vs 290 ms).
-  if (nodes >= (int64_t)250 * 1000 * 1000) return true;
-  // A segment is read and written once per call, at the cost of 10 to 15
-  // iterations of the largest rounds; a sweep's set-up is cheaper, its
-  // iteration dearer.  Measured crossovers: 1.0e7 nodes 4 iterations, 1.4e7 5,
-  // 2.9e7 8, 3.5e7 9, 1.1e8 26, 1.2e8 14, 1.5e8 13 (1.2e8 nodes, streaming vs
-  // segments: 8 iterations 5.1 vs 5.8 ms, 20 iterations 10.4 vs 9.1 ms).
-  if (n_iters < 4 + nodes / (12 * 1000 * 1000)) return true;
-  // A segment iterated in global memory is some ten times slower: roots that
-  // don't fit with far arrays must be few.
-  const int64_t cap = dtype == PASUR_F32 ? 30000 : 15000;
-  const int64_t nr = f->n_roots;
-  int64_t beyond = 0;
-  for (int64_t j = 0; j < nr; ++j) {
-    int64_t n = 0;
-    for (int l = 0; l <= 8; ++l) {
-      const int32_t *o = f->h_root_off + (size_t)l * (nr + 1) + j;
-      n += o[1] - o[0];
-    }
-    if (n > cap) beyond += n;
-  }
-  return beyond > nodes / 100;
+  const RootSizes r = root_sizes(f);
+  // One workgroup iterates a root at 2 to 3 ns per node: a root of which that takes
+  // longer than the round's sweeps.
+  if (r.largest > 30000 + nodes / 1000) return true;
+  // Loading and storing the segments has to pay.  The crossovers lie below these
+  // iterations, the nearest to them: 1.1e8 nodes 14.1, 1.5e7 4.2, 5.1e8 32 (20
+  // iterations, streaming vs segments: 9.7e6 nodes 2.1 vs 0.9 ms, 1.5e8 17.2 vs
+  // 13.8; 40: 3.4e8 62.6 vs 53.5).  Where more than 1% of the nodes are below roots
+  // that keep all of the form in device memory, segments gain less per iteration:
+  // 6.8e8 nodes 36 (FP64 175), 1.9e8 29.
+  const int64_t least = 5 + nodes / (10 * 1000 * 1000);
+  return n_iters < (r.tail[dtype == PASUR_F32 ? 0 : 1] > nodes / 100 ? 3 * least : least);
 }
 
 int sweep_iterate(pasur_fgt *f, const pasur_cfr_state *st, const pasur_cfr_params *p,

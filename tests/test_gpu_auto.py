@@ -131,3 +131,49 @@ def test_auto_on_two_streams_and_from_two_threads():
         for a, b in zip(tensors(st) + st.Sbar[1:], tensors(ref) + ref.Sbar[1:]):
             assert torch.equal(a, b)
     s.free()
+
+
+def scheduled(pa, torch, rr, dtype, iters):
+    """The schedule that AUTO takes, by the kernels that it launches (on a state that
+    is not solved: what the launches compute does not matter here)."""
+    st = fresh(pa, torch, rr, dtype)
+    pa.profile_enable(True)
+    pa.cfr_iterate(st, iters)
+    kernels = set(int(k) for k in pa.profile_read()[0])
+    pa.profile_enable(False)
+    assert kernels <= {2, 3} or not kernels & {2, 3}, kernels
+    return "segments" if kernels & {2, 3} else "stream"
+
+
+# 3.4e8 nodes, 18% of them below roots of 15,000 to 27,000 nodes; 1.5e8; 1.9e8, 9%
+# below roots of more than 60,000; 1.2e8, small roots
+@pytest.mark.parametrize("seed,k,dtype_name,line", [
+    (48, 5, "PASUR_F32", 38), (40, 4, "PASUR_F64", 20), (4, 4, "PASUR_F32", 72),
+    (7, 4, "PASUR_F64", 17), (7, 4, "PASUR_F32", 17)])
+def test_auto_switches_by_size_iterations_and_roots(seed, k, dtype_name, line):
+    pa = require_gpu()
+    import torch
+    deck, roots = synth.full_game_root(seed)
+    s = pa.SubgameSolver(deck, 0, roots)
+    rr = s.rounds[k]
+    least = 5 + sum(rr.fgt.n) // 10_000_000
+    assert line in (least, 3 * least)
+    dtype = getattr(pa, dtype_name)
+    print(f"[auto] deal {seed} round {k + 1}, {sum(rr.fgt.n)} nodes, {dtype_name}", flush=True)
+    assert scheduled(pa, torch, rr, dtype, line - 1) == "stream"
+    assert scheduled(pa, torch, rr, dtype, line) == "segments"
+    s.free()
+
+
+def test_auto_streams_a_root_that_one_workgroup_would_take_too_long_for():
+    """One root of 1.6e7 nodes, iterated in place by one workgroup otherwise."""
+    from test_gpu_values import wide_start
+    pa = require_gpu()
+    import torch
+    deck, roots = wide_start()
+    s = pa.SubgameSolver(deck, 5, roots)
+    rr = s.rounds[0]
+    assert sum(rr.fgt.n) > 9_000_000
+    print(f"[auto] one root of {sum(rr.fgt.n)} nodes", flush=True)
+    assert scheduled(pa, torch, rr, pa.PASUR_F32, 100) == "stream"
+    s.free()
