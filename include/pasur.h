@@ -292,8 +292,15 @@ int pasur_plan_create(const pasur_fgt *const *fgts, const pasur_cfr_state *const
                       int64_t t_last, pasur_plan **out, void *stream);
 int pasur_plan_iterate(const pasur_plan *plan, int64_t t0, int n_iters, void *stream);
 /* info: segments, LDS-resident segments, dynamic LDS bytes, threads per
- * workgroup, edges, internal nodes, roots, level-7 nodes. */
+ * workgroup (of the launch with the most), edges, internal nodes, roots, level-7
+ * nodes. */
 int pasur_plan_info(const pasur_plan *plan, int64_t info[8]);
+/* How the segments run.  info: segments planned in LDS, with their far arrays in
+ * device memory, wholly there, and in place; launches, their least and most threads
+ * per workgroup; and how often, in launches that have ended, a segment ran in
+ * place though it was planned otherwise (a state that the solver's own calls do not
+ * make, as with sigma other than 1 along forced chains, may need it). */
+int pasur_plan_forms(const pasur_plan *plan, int64_t info[8]);
 /* pasur_leaf_utilities (no flags; d_V_next[i] may be NULL for round 5) and
  * pasur_cfr_init of n_items (tree, state) pairs of one dtype, in one launch per
  * eight; d_V_next may be NULL if every tree is a round 5.  Asynchronous. */

@@ -103,6 +103,7 @@ def lib():
         L.pasur_plan_create.argtypes = [vp, vp, i32, vp, i64, i64, C.POINTER(vp), vp]
         L.pasur_plan_iterate.argtypes = [vp, i64, i32, vp]
         L.pasur_plan_info.argtypes = [vp, vp]
+        L.pasur_plan_forms.argtypes = [vp, vp]
         L.pasur_plan_free.argtypes = [vp]
         L.pasur_plan_free.restype = None
         L.pasur_gemm_bf16.argtypes = [i32, i32, i32, vp, i64, i64, vp, i64, i64, vp, vp, i64, vp,
@@ -514,6 +515,13 @@ class Plan:
         _check(lib().pasur_plan_info(self.h, info), "pasur_plan_info")
         (self.n_segs, self.n_lds_segs, self.lds_bytes, self.block, self.edges, self.internal,
          self.roots, self.n7) = list(info)
+
+    def forms(self) -> dict:
+        """pasur_plan_forms: how the plan's segments run."""
+        info = (C.c_int64 * 8)()
+        _check(lib().pasur_plan_forms(self.h, info), "pasur_plan_forms")
+        return dict(zip(("lds", "far", "all_far", "in_place", "launches", "least_threads",
+                         "most_threads", "unplanned"), info))
 
     def iterate(self, t0: int, n_iters: int, stream=None):
         _check(lib().pasur_plan_iterate(self.h, t0, n_iters, _stream(stream)), "pasur_plan_iterate")

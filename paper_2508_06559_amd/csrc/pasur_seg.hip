@@ -56,6 +56,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 using namespace pasur;
@@ -1234,12 +1235,14 @@ __device__ __forceinline__ void seg_in_global(const ItemDesc<T> &D, int j0, int 
 
 // One workgroup per segment; the segment runs in its compact form when that fits
 // in the launch's dynamic LDS (lds_bytes), otherwise in global memory.  FAR: some
-// segments have far arrays.
+// segments have far arrays.  unplanned (may be NULL): counts segments in global
+// memory for which that was not planned (their state has more active nodes than
+// the tree's structure says).
 template <class T, int BLOCK, bool PAPER, bool FAR>
 __global__ void __launch_bounds__(BLOCK)
     k_cfr_seg(const ItemDesc<T> *__restrict__ items, const Seg *__restrict__ segs,
               const IterK *__restrict__ ks, unsigned char *far, int n_iters, int variant,
-              int rm_mode, double eps, uint32_t lds_bytes) {
+              int rm_mode, double eps, uint32_t lds_bytes, unsigned *unplanned) {
   const Seg sg = segs[blockIdx.x];
   const ItemDesc<T> &D = items[sg.item];
   seg_open(D, sg.j0, sg.j1);
@@ -1267,6 +1270,7 @@ __global__ void __launch_bounds__(BLOCK)
       return;
     }
   }
+  if (unplanned && sg.form != F_NONE && threadIdx.x == 0) atomicAdd(unplanned, 1u);
   seg_in_global<T, BLOCK, PAPER>(D, sg.j0, sg.j1, ks, n_iters, variant, rm_mode, eps);
 }
 
@@ -1311,7 +1315,7 @@ inline bool paper_variant(int variant, int rm_mode) {
 
 template <class T>
 using SegKernel = void (*)(const ItemDesc<T> *, const Seg *, const IterK *, unsigned char *, int,
-                           int, int, double, uint32_t);
+                           int, int, double, uint32_t, unsigned *);
 
 template <class T>
 SegKernel<T> seg_kernel(int block, bool paper, bool far) {
@@ -1371,8 +1375,9 @@ struct pasur_plan {
   Seg *d_segs;
   IterK *d_ks;
   uint32_t lds_bytes;
-  int64_t work[4];  // edges, internal nodes, roots, level-7 nodes
-  int64_t n_lds_segs;
+  unsigned *d_unplanned;
+  int64_t work[4];   // edges, internal nodes, roots, level-7 nodes
+  int64_t forms[4];  // segments of each form
   std::vector<SegLaunch> launches;
 };
 
@@ -1552,9 +1557,13 @@ void tree_segments(const pasur_fgt *f, int it, uint32_t t, int seg_nodes, int bl
   }
 }
 
-int64_t lds_segments(const std::vector<SegPlan> &segs) {
-  return std::count_if(segs.begin(), segs.end(),
-                       [](const SegPlan &sp) { return sp.seg.form == F_LDS; });
+void count_forms(int64_t forms[4], const std::vector<SegPlan> &segs) {
+  for (int k = 0; k < 4; ++k) forms[k] = 0;
+  for (const SegPlan &sp : segs) forms[sp.seg.form] += 1;
+}
+
+bool all_lds(const int64_t forms[4]) {
+  return forms[F_FAR] + forms[F_ALL_FAR] + forms[F_NONE] == 0;
 }
 
 void add_work(int64_t work[4], const pasur_fgt *f) {
@@ -1579,12 +1588,12 @@ int allow_lds(const std::vector<SegLaunch> &launches, bool paper) {
 template <class T>
 void launch_segments(const std::vector<SegLaunch> &launches, const void *items, const Seg *segs,
                      const IterK *ks, void *far, int n_iters, int variant, int rm_mode, double eps,
-                     hipStream_t s) {
+                     unsigned *unplanned, hipStream_t s) {
   const bool paper = paper_variant(variant, rm_mode);
   for (const SegLaunch &la : launches)
     seg_kernel<T>(la.block, paper, la.far)<<<(unsigned)la.count, la.block, la.lds_bytes, s>>>(
         (const ItemDesc<T> *)items, segs + la.first, ks, (unsigned char *)far, n_iters, variant,
-        rm_mode, eps, la.lds_bytes);
+        rm_mode, eps, la.lds_bytes, unplanned);
 }
 
 template <class T>
@@ -1600,7 +1609,6 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
     tree_segments(fgts[it], it, sizeof(T), p->seg_nodes, pl->block, force_global, segs);
     add_work(pl->work, fgts[it]);
   }
-  pl->n_lds_segs = lds_segments(segs);
   const int64_t far_bytes = order_segments(pl->launches, segs, p->block);
   if (far_bytes > 0 && block_alloc(&pl->far, (size_t)far_bytes) != PASUR_OK) {
     // no memory for far arrays: in global memory
@@ -1613,6 +1621,7 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
       }
     (void)order_segments(pl->launches, segs, p->block);
   }
+  count_forms(pl->forms, segs);
   std::vector<Seg> sorted(segs.size());
   uint32_t max_bytes = 0;
   for (size_t i = 0; i < segs.size(); ++i) {
@@ -1628,7 +1637,8 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   // one upload
   const size_t at_segs = align16(sizeof(ItemDesc<T>) * items.size());
   const size_t at_ks = at_segs + align16(sizeof(Seg) * sorted.size());
-  std::vector<unsigned char> stage(at_ks + sizeof(IterK) * ks.size());
+  const size_t at_unplanned = at_ks + sizeof(IterK) * ks.size();
+  std::vector<unsigned char> stage(at_unplanned + sizeof(unsigned), 0);
   std::memcpy(stage.data(), items.data(), sizeof(ItemDesc<T>) * items.size());
   std::memcpy(stage.data() + at_segs, sorted.data(), sizeof(Seg) * sorted.size());
   std::memcpy(stage.data() + at_ks, ks.data(), sizeof(IterK) * ks.size());
@@ -1636,6 +1646,7 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   pl->d_items = pl->mem;
   pl->d_segs = (Seg *)((unsigned char *)pl->mem + at_segs);
   pl->d_ks = (IterK *)((unsigned char *)pl->mem + at_ks);
+  pl->d_unplanned = (unsigned *)((unsigned char *)pl->mem + at_unplanned);
   PASUR_TRY_HIP(hipMemcpyAsync(pl->mem, stage.data(), stage.size(), hipMemcpyHostToDevice, s));
   const hipError_t e = hipStreamSynchronize(s);  // the staging vector goes out of scope
   if (e != hipSuccess) {
@@ -1782,7 +1793,7 @@ struct SegIndex {
   int dtype, block, seg_nodes;
   std::vector<SegLaunch> launches;
   void *mem;  // the segments, on the device
-  int64_t far_bytes, n_segs, n_lds_segs;
+  int64_t far_bytes, forms[4];
   SegIndex *next;
 };
 
@@ -1816,8 +1827,7 @@ int build_index(pasur_fgt *f, int dtype, int block, int seg_nodes, hipStream_t s
   x->dtype = dtype;
   x->block = block;
   x->seg_nodes = seg_nodes;
-  x->n_segs = (int64_t)segs.size();
-  x->n_lds_segs = lds_segments(segs);
+  count_forms(x->forms, segs);
   x->far_bytes = order_segments(x->launches, segs, block);
   std::vector<Seg> sorted(segs.size());
   for (size_t i = 0; i < segs.size(); ++i) sorted[i] = segs[i].seg;
@@ -1880,10 +1890,9 @@ int enqueue(const pasur_fgt *f, const SegIndex &x, const pasur_cfr_state *st,
   int64_t work[4] = {0, 0, 0, 0};
   add_work(work, f);
   {
-    ProfScope ps(x.n_lds_segs == x.n_segs ? 2 : 3, -1, s, work[0], work[1], work[2], work[3],
-                 n_iters);
+    ProfScope ps(all_lds(x.forms) ? 2 : 3, -1, s, work[0], work[1], work[2], work[3], n_iters);
     launch_segments<T>(x.launches, at, (const Seg *)x.mem, (const IterK *)(at + align16(sizeof(D))),
-                       mem, n_iters, p->variant, p->rm_mode, p->eps, s);
+                       mem, n_iters, p->variant, p->rm_mode, p->eps, nullptr, s);
   }
   const hipError_t e = hipGetLastError();
   if (capturing) (void)hipFreeAsync(mem, s);
@@ -1940,17 +1949,44 @@ extern "C" int pasur_plan_iterate(const pasur_plan *pl, int64_t t0, int n_iters,
   if (n_iters == 0) return PASUR_OK;
   hipStream_t s = (hipStream_t)stream;
   {
-    ProfScope ps(pl->n_lds_segs == pl->n_segs ? 2 : 3, -1, s, pl->work[0], pl->work[1],
-                 pl->work[2], pl->work[3], n_iters);
+    ProfScope ps(all_lds(pl->forms) ? 2 : 3, -1, s, pl->work[0], pl->work[1], pl->work[2],
+                 pl->work[3], n_iters);
     const IterK *const ks = pl->d_ks + (t0 - pl->t_first);
     if (pl->dtype == PASUR_F32)
       launch_segments<float>(pl->launches, pl->d_items, pl->d_segs, ks, pl->far, n_iters,
-                             pl->variant, pl->rm_mode, pl->eps, s);
+                             pl->variant, pl->rm_mode, pl->eps, pl->d_unplanned, s);
     else
       launch_segments<double>(pl->launches, pl->d_items, pl->d_segs, ks, pl->far, n_iters,
-                              pl->variant, pl->rm_mode, pl->eps, s);
+                              pl->variant, pl->rm_mode, pl->eps, pl->d_unplanned, s);
   }
   PASUR_TRY_HIP(hipGetLastError());
+  return PASUR_OK;
+}
+
+namespace {
+// The least and most threads per workgroup of a plan's launches.
+std::pair<int, int> threads(const pasur_plan *pl) {
+  std::pair<int, int> t(1024, 0);
+  for (const SegLaunch &la : pl->launches) {
+    t.first = std::min(t.first, la.block);
+    t.second = std::max(t.second, la.block);
+  }
+  return t;
+}
+}  // namespace
+
+extern "C" int pasur_plan_forms(const pasur_plan *pl, int64_t info[8]) {
+  if (!pl || !info) {
+    set_error("null argument");
+    return PASUR_E_INVAL;
+  }
+  for (int k = 0; k < 4; ++k) info[k] = pl->forms[k];
+  info[4] = (int64_t)pl->launches.size();
+  info[5] = threads(pl).first;
+  info[6] = threads(pl).second;
+  unsigned n = 0;
+  PASUR_TRY_HIP(hipMemcpy(&n, pl->d_unplanned, sizeof(n), hipMemcpyDeviceToHost));
+  info[7] = n;
   return PASUR_OK;
 }
 
@@ -1960,9 +1996,9 @@ extern "C" int pasur_plan_info(const pasur_plan *pl, int64_t info[8]) {
     return PASUR_E_INVAL;
   }
   info[0] = pl->n_segs;
-  info[1] = pl->n_lds_segs;
+  info[1] = pl->forms[F_LDS];
   info[2] = pl->lds_bytes;
-  info[3] = pl->block;
+  info[3] = threads(pl).second;
   info[4] = pl->work[0];
   info[5] = pl->work[1];
   info[6] = pl->work[2];
