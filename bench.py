@@ -38,39 +38,6 @@ sys.path.insert(0, ROOT)
 
 METRIC = "CFR node-updates/s at 1 GPU; secs to exploitability 1e-3, warm-start vs plain"
 
-# HBM bytes per launch of each workload's dominant kernel, from rocprofv3
-# FETCH_SIZE / WRITE_SIZE counters scaled by a plain-copy calibration (the
-# counter summaries under profiles/).  Valid only while the kernel's source
-# file is unchanged (sha256 recorded with the counters).
-TRAFFIC = {
-    # k_cfr_seg: not counted since its state is iterated in the compact form
-    "two-round": {"source": "paper_2508_06559_amd/csrc/pasur_seg.hip", "sha256": None, "bytes": None},
-    "batched": {"source": "paper_2508_06559_amd/csrc/pasur_seg.hip", "sha256": None, "bytes": None},
-    # the full game's dominant streaming kernel (one of round 6's launches)
-    "full-game": {"source": "paper_2508_06559_amd/csrc/pasur_sweep.hip",
-                  "sha256": "00091aad91bd74f519c7e61583ef271ae96578b86d799baaeeee6acee9f7377a",
-                  "bytes": 5.198e9},
-}
-
-
-def counted_traffic(args, workload="two-round"):
-    """HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE counters (copy
-    calibrated), valid only for the kernel source they were taken on."""
-    import hashlib
-    rec = TRAFFIC[workload]
-    if rec["sha256"] is None or args.state != "f32":
-        return None
-    with open(os.path.join(ROOT, rec["source"]), "rb") as fh:
-        if hashlib.sha256(fh.read()).hexdigest() != rec["sha256"]:
-            return None
-    if workload == "two-round" and (args.sched not in ("root", "auto") or
-                                    args.block not in (0, 1024)):
-        return None
-    if workload == "full-game" and args.sched != "auto":
-        return None
-    return rec["bytes"]
-
-
 def playout_problem(seed, rnd):
     """Deal ``seed`` and the root of round ``rnd`` reached by the seeded legal
     playout (synth.playout_draws), played by the library's own round trees."""
@@ -150,13 +117,34 @@ def sweep_bytes(kernel, level, work, T):
     return 0
 
 
+# What bounds the persistent segment kernel is FP64 instruction issue: its state
+# stays on chip (or in L2) for a call's iterations, so bytes of HBM say nothing.
+# FP64 operations per edge and iteration, none of them fused: the reach's product,
+# sigma * u and its sum, (u - u(h)) * reach, discount and sum of the regret, floor
+# and sum of the matching, the quotient, two products and a sum of the average.
+SEG_KERNELS = (2, 3)
+SEG_FLOPS = 13
+# 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (78.6 TFLOP/s in fused operations)
+FP64_PEAK_TFLOPS = 39.3
+
+
+def seg_roofline(name, edge_iters, seconds, launches):
+    """Roofline fields of the segment kernel's launches."""
+    achieved = SEG_FLOPS * edge_iters / seconds / 1e12
+    return {"bound": "valu_fp64", "kernel": name, "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS, "traffic": None,
+            "flops_per_edge_and_iteration": SEG_FLOPS, "avg_launch_us": seconds / launches * 1e6,
+            "launches": launches}
+
+
 KERNEL_NAMES = {0: "k_down", 1: "k_up", 2: "k_cfr_seg (all LDS)", 3: "k_cfr_seg (LDS + global)",
                 4: "k_sw_down_tile", 5: "k_sw_up_tile", 6: "k_sw_up_parent (dense)",
                 7: "k_sw_up_parent (list)", 8: "streaming set-up", 9: "k_sw_down_list (tail)",
                 10: "k_sw_up_parent (tail)", 11: "k_sw_up_tile (tail boundary)",
                 12: "k_sw_down_tile (tail boundary)", 13: "k_sw_down_list", 14: "k_sw_down_parent"}
 # rocprofv3 names of the kernel ids (FP32 state, the paper's variant)
-KERNEL_SYMBOLS = {2: "k_cfr_seg<float, 1024, true>", 3: "k_cfr_seg<float, 1024, true>",
+KERNEL_SYMBOLS = {2: "k_cfr_seg<float, BLOCK, true, false>",
+                  3: "k_cfr_seg<float, BLOCK, true, FAR>",
                   4: "k_sw_down_tile<float, true, false>", 5: "k_sw_up_tile<float, true, false>",
                   11: "k_sw_up_tile<float, true, true>", 12: "k_sw_down_tile<float, true, true>"}
 
@@ -248,10 +236,7 @@ def bench_batched(args):
     torch.cuda.synchronize()
     kern, lev, ms, work = pa.profile_read()
     pa.profile_enable(False)
-    tot_b = sum(launch_bytes(int(kern[i]), int(lev[i]), work[i], T) for i in range(len(kern)))
-    tot_t = sum(float(x) for x in ms) * 1e-3
     dom = int(np.argmax(ms))
-    db = launch_bytes(int(kern[dom]), int(lev[dom]), work[dom], T)
     dt = float(ms[dom]) * 1e-3
     ex = [float(((x[0] - x[1]) / 2).max().item()) for x in b.exploitability()[:4]]
     out = {
@@ -265,14 +250,9 @@ def bench_batched(args):
                    "state": args.state, "build_seconds": build_s,
                    "schedule": [r["best"] for r in sched["rounds"]],
                    "exploitability_points_first_deals": ex},
-        "roofline": {"bound": "hbm", "kernel": f"k_cfr_seg ({'float' if T == 4 else 'double'} state), "
-                                             f"largest launch",
-                     "achieved": db / dt / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": db / dt / 1e9 / HBM_PEAK_GBS, "traffic": counted_traffic(args, "batched"),
-                     "traffic_GBs": (counted_traffic(args, "batched") / dt / 1e9
-                                     if counted_traffic(args, "batched") is not None else None),
-                     "avg_launch_us": dt * 1e6, "algorithmic_bytes_per_launch": db,
-                     "all_sweeps_GBs": tot_b / tot_t / 1e9},
+        "roofline": seg_roofline(f"k_cfr_seg ({'float' if T == 4 else 'double'} state), the plan of "
+                                 f"the round that takes longest",
+                                 float(work[dom][0]) * float(work[dom][4]), dt, 1),
     }
     print(json.dumps(out), flush=True)
     b.free()
@@ -364,7 +344,9 @@ def bench_full(args):
                               "auto": pa.SCHED_AUTO}[args.sched], args.block)
     round_ms = []
 
-    def step(record_rounds=False, on_round=None):
+    round_forms = {}
+
+    def step(record_rounds=False, on_round=None, forms_of=None):
         s = pa.SubgameSolver(deck, 0, roots, dtype=dtype)
         ev = [] if record_rounds else None
         s.solve(iters, params, round_events=ev, on_round=on_round)
@@ -375,6 +357,12 @@ def bench_full(args):
         ex = float(((bra - brb) / 2).max().item())
         sizes = s.sizes()
         V0 = float(s.rounds[0].V[0].item())
+        if forms_of is not None:
+            for rr in s.rounds:
+                if rr.round in forms_of:
+                    plan = pa.Plan([rr.state], pa.paper_params(pa.SCHED_ROOT, args.block), 1, 1)
+                    round_forms[rr.round] = [plan.forms()["lds"], plan.n_segs]
+                    plan.free()
         s.free()
         return sizes, ex, V0
 
@@ -385,6 +373,11 @@ def bench_full(args):
         kern, lev, ms, work = pa.profile_read()
         return [(int(kern[i]), all_launch_bytes(int(kern[i]), int(lev[i]), work[i], T),
                  float(ms[i]) * 1e-3) for i in range(len(kern)) if int(kern[i]) != 8]
+
+    def seg_work(kernel):
+        """Edges times iterations of the recorded launches of a kernel id."""
+        kern, _, _, work = pa.profile_read()
+        return float(sum(work[i][0] * work[i][4] for i in range(len(kern)) if int(kern[i]) == kernel))
 
     def per_kernel(recs=None):
         """Algorithmic bytes, seconds and launches per kernel id."""
@@ -422,12 +415,12 @@ def bench_full(args):
             t = sum(x[2] for x in part)
             ran = {x[0] for x in part}
             round_sched[r] = "persistent segments" if ran & {2, 3} else "stream"
-            lds = sum(x[1] for x in part if x[0] == 2)  # k_cfr_seg, every segment in LDS
-            seg = sum(x[1] for x in part if x[0] in (2, 3))
-            round_alg[r] = (b, t, lds / seg if seg else None)
+            if not ran & {2, 3}:
+                round_alg[r] = (b, t)
             prev = cnt
         per_all = per_kernel([x for x in recs_all if x[0] != 8])
         dom = max(per_all, key=lambda k: per_all[k][1])
+        step(forms_of={r for r, x in round_sched.items() if x != "stream"})
         pa.profile_enable(True)
         pa.profile_select([dom])
     torch.cuda.synchronize()
@@ -438,38 +431,38 @@ def bench_full(args):
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
     per_t = per_kernel()
+    seg_edges = seg_work(dom if args.warmup else max(per_t, key=lambda k: per_t[k][1]))
     pa.profile_enable(False)
     if per_all is None:
         per_all = per_t
         dom = max(per_all, key=lambda k: per_all[k][1])
     for k, (b, t, c) in sorted(per_all.items(), key=lambda kv: -kv[1][1]):
-        log(f"[bench] {KERNEL_NAMES.get(k, k)}: {c} launches, {t:.3f} s, avg {t / c * 1e6:.1f} us, "
-            f"{b / c / 1e6:.3f} MB/launch, {b / t / 1e9:.1f} GB/s")
-    all_b = sum(v[0] for v in per_all.values())
-    all_t = sum(v[1] for v in per_all.values())
+        log(f"[bench] {KERNEL_NAMES.get(k, k)}: {c} launches, {t:.3f} s, avg {t / c * 1e6:.1f} us" +
+            ("" if k in SEG_KERNELS else f", {b / c / 1e6:.3f} MB/launch, {b / t / 1e9:.1f} GB/s"))
+    sweeps = [v for k, v in per_all.items() if k not in SEG_KERNELS]
+    all_b, all_t = sum(v[0] for v in sweeps), sum(v[1] for v in sweeps)
     db, dt, dc = per_t[dom]
     achieved = db / dt / 1e9
     edges = sum(sum(n[1:]) for n in sizes)
     nodes = sum(sum(n) for n in sizes)
     value = edges * iters * args.steps / el
-    tr = counted_traffic(args, "full-game")
     rounds = []
     for r, n in enumerate(sizes):
         e_r = sum(n[1:])
         ms_r = round_ms[5 - r] if len(round_ms) == 6 else None
-        b_r, t_r, lds_r = round_alg.get(r, (0.0, 0.0, None))
+        b_r, t_r = round_alg.get(r, (0.0, 0.0))
         rounds.append({"round": r + 1, "nodes": int(sum(n)), "edges": int(e_r),
                        # as the first warm-up step's launches show it
                        "schedule": round_sched.get(r, args.sched) if args.sched == "auto" else args.sched,
                        "dcfr_ms": ms_r,
                        "node_updates_per_s": e_r * iters / (ms_r * 1e-3) if ms_r else None,
-                       # algorithmic bytes of the round's sweep launches over
+                       # algorithmic bytes of a streamed round's launches over
                        # their summed launch time (first warm-up step)
                        "alg_GBs": b_r / t_r / 1e9 if t_r else None,
                        "alg_frac": b_r / t_r / 1e9 / HBM_PEAK_GBS if t_r else None,
-                       # share of the persistent kernel's algorithmic bytes in
-                       # launches that kept every segment's state in LDS
-                       "lds_resident_share": lds_r})
+                       # segments (roots) whose whole state is iterated in LDS,
+                       # and how many there are
+                       "segments_in_lds": round_forms.get(r)})
     out = {"metric": METRIC, "value": value, "unit": "node-updates/s",
            "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
            "ms_per_step": el / args.steps * 1e3, "higher_is_better": True, "scaling": "weak",
@@ -485,12 +478,13 @@ def bench_full(args):
                         "kernel": f"{KERNEL_SYMBOLS.get(dom, KERNEL_NAMES.get(dom, dom))}",
                         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": achieved / HBM_PEAK_GBS,
-                        "traffic": tr,
-                        "traffic_GBs": tr / (dt / dc) / 1e9 if tr is not None else None,
+                        "traffic": None,
                         "avg_launch_us": dt / dc * 1e6, "launches": dc,
                         "algorithmic_bytes_per_launch": db / dc,
-                        "all_sweeps_GBs": all_b / all_t / 1e9,
-                        "all_sweeps_frac": all_b / all_t / 1e9 / HBM_PEAK_GBS}}
+                        "all_sweeps_GBs": all_b / all_t / 1e9 if all_t else None,
+                        "all_sweeps_frac": all_b / all_t / 1e9 / HBM_PEAK_GBS if all_t else None}}
+    if dom in SEG_KERNELS:
+        out["roofline"] = seg_roofline(KERNEL_SYMBOLS[dom], seg_edges, dt, dc)
     if not args.no_cpu_baseline:
         threads = min(16, os.cpu_count() or 1)
         round_edges = [sum(n[1:]) for n in sizes]
@@ -1205,7 +1199,6 @@ def bench_variants(args):
     kern, lev, ms, work = pa.profile_read()
     pa.profile_enable(False)
     s.free()
-    db = sum(launch_bytes(int(kern[i]), int(lev[i]), work[i], T) for i in range(len(kern)))
     dt = sum(float(x) for x in ms) * 1e-3
     dcfr = res["dcfr"]
     out = {"metric": "seconds to exploitability 1e-3 by CFR update rule at 1 GPU",
@@ -1216,11 +1209,9 @@ def bench_variants(args):
            "config": {"workload": f"last two rounds of seeded deal {args.seed}, each CFR update rule over "
                                   f"the iteration grid {list(grid)}; seconds include building the trees",
                       "state": args.state, "rules": res},
-           "roofline": {"bound": "hbm", "kernel": "k_cfr_seg, generic variant instance (CFR+), "
-                                                  f"{'float' if T == 4 else 'double'} state",
-                        "achieved": db / dt / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": db / dt / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                        "avg_launch_us": dt / len(kern) * 1e6, "launches": len(kern)}}
+           "roofline": seg_roofline("k_cfr_seg, generic variant instance (CFR+), "
+                                    f"{'float' if T == 4 else 'double'} state",
+                                    float((work[:, 0] * work[:, 4]).sum()), dt, len(kern))}
     print(json.dumps(out), flush=True)
 
 
@@ -1369,11 +1360,11 @@ def main():
     dom = max(per, key=lambda k: per[k][1])
     db, dt, dc = per[dom]
     achieved = db / dt / 1e9
-    all_b = sum(v[0] for v in per.values())
-    all_t = sum(v[1] for v in per.values())
+    sweeps = [v for k, v in per.items() if k not in SEG_KERNELS]
+    all_b, all_t = sum(v[0] for v in sweeps), sum(v[1] for v in sweeps)
     for k, (b, t, c) in sorted(per.items()):
-        log(f"[bench] {KERNEL_NAMES[k]}: {c} launches, avg {t / c * 1e6:.1f} us, "
-            f"{b / c / 1e6:.3f} MB/launch, {b / t / 1e9:.1f} GB/s")
+        log(f"[bench] {KERNEL_NAMES[k]}: {c} launches, avg {t / c * 1e6:.1f} us" +
+            ("" if k in SEG_KERNELS else f", {b / c / 1e6:.3f} MB/launch, {b / t / 1e9:.1f} GB/s"))
 
     out = {
         "metric": METRIC,
@@ -1408,15 +1399,17 @@ def main():
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": counted_traffic(args),
-            "traffic_GBs": (counted_traffic(args) / (dt / dc) / 1e9
-                            if counted_traffic(args) is not None else None),
+            "traffic": None,
             "avg_launch_us": dt / dc * 1e6,
             "launches": dc,
             "algorithmic_bytes_per_launch": db / dc,
-            "all_sweeps_GBs": all_b / all_t / 1e9,
+            "all_sweeps_GBs": all_b / all_t / 1e9 if all_t else None,
         },
     }
+    if dom in SEG_KERNELS:
+        mine = [i for i in range(len(kern)) if int(kern[i]) == dom]
+        out["roofline"] = seg_roofline(out["roofline"]["kernel"],
+                                       float(sum(work[i][0] * work[i][4] for i in mine)), dt, dc)
     if not args.no_cpu_baseline:
         log("[bench] cpu baseline (oracle) ...")
         odeck, oroots = oracle_playout_problem(args.seed, 4)
