@@ -18,6 +18,7 @@ class Fake(C.Structure):
                   "host_mallocs", "syncs", "launches", "mallocs_async", "frees_async",
                   "unfinished", "event_waits")] +
                 [("free_bytes", C.c_int64 * 2), ("total_bytes", C.c_int64 * 2),
+                 ("copy_from", C.c_void_p), ("copy_bytes", C.c_int64),
                  ("words", C.c_int64 * 31), ("in_sync", C.c_void_p), ("in_free", C.c_void_p)])
 
 
