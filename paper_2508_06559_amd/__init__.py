@@ -164,16 +164,18 @@ def release_cache():
 def on_device(make):
     """make(), which allocates device tensors; once more after release_cache() if
     there is no room."""
+    import torch
     try:
         return make()
-    except _torch().OutOfMemoryError:
+    except torch.OutOfMemoryError:
         release_cache()
         return make()
 
 
 def device_empty(shape, dtype):
     """torch.empty on the GPU, through on_device."""
-    return on_device(lambda: _torch().empty(shape, dtype=dtype, device="cuda"))
+    import torch
+    return on_device(lambda: torch.empty(shape, dtype=dtype, device="cuda"))
 
 
 def _stream(stream=None):
@@ -308,20 +310,7 @@ class CfrState:
         torch = _torch()
         self.fgt = fgt
         self.dtype = dtype
-        tdt = torch.float32 if dtype == PASUR_F32 else torch.float64
-        n = fgt.n
-
-        def empty(n_l):
-            return device_empty(n_l, tdt)
-
-        self.sigma = [None] + [empty(n[l]) for l in range(1, 9)]
-        self.R = [None] + [empty(n[l]) for l in range(1, 9)]
-        self.Sbar = [None] + [empty(n[l]) for l in range(1, 9)]
-        self.reachA = [empty(n[l]) for l in range(8)] + [None]
-        self.reachB = [empty(n[l]) for l in range(8)] + [None]
-        self.u = [empty(n[l]) for l in range(9)]
-        self.vacc = device_empty(n[0], torch.float64).zero_()
-        self.sigma_bar = [None] + [empty(n[l]) for l in range(1, 9)]
+        on_device(lambda: self._allocate(torch))
         st = _State()
         st.dtype = dtype
         for name in ("sigma", "R", "Sbar", "reachA", "reachB", "u"):
@@ -334,6 +323,23 @@ class CfrState:
         self.t = 1
         self.es_t = 0
         self.es_ws = None
+
+    def _allocate(self, torch):
+        tdt = torch.float32 if self.dtype == PASUR_F32 else torch.float64
+        n = self.fgt.n
+        self.sigma = self.R = self.Sbar = self.reachA = self.reachB = self.u = self.sigma_bar = None
+
+        def empty(n_l):
+            return torch.empty(n_l, dtype=tdt, device="cuda")
+
+        self.sigma = [None] + [empty(n[l]) for l in range(1, 9)]
+        self.R = [None] + [empty(n[l]) for l in range(1, 9)]
+        self.Sbar = [None] + [empty(n[l]) for l in range(1, 9)]
+        self.reachA = [empty(n[l]) for l in range(8)] + [None]
+        self.reachB = [empty(n[l]) for l in range(8)] + [None]
+        self.u = [empty(n[l]) for l in range(9)]
+        self.vacc = torch.zeros(n[0], dtype=torch.float64, device="cuda")
+        self.sigma_bar = [None] + [empty(n[l]) for l in range(1, 9)]
 
     def bytes(self) -> int:
         ts = [*self.sigma[1:], *self.R[1:], *self.Sbar[1:], *self.reachA[:8], *self.reachB[:8],

@@ -190,23 +190,28 @@ def test_tensors_are_allocated_from_released_memory(monkeypatch):
     import paper_2508_06559_amd as pa
     log = []
 
-    class Torch:
-        OutOfMemoryError = torch.OutOfMemoryError
-        full = 1
+    room = [False]
 
-        @classmethod
-        def empty(cls, shape, dtype, device):
-            log.append("empty")
-            if cls.full:
-                raise torch.OutOfMemoryError("full")
-            return (shape, dtype, device)
+    def empty(shape, dtype, device):
+        log.append("empty")
+        if not room[0]:
+            raise torch.OutOfMemoryError("full")
+        return (shape, dtype, device)
 
-    monkeypatch.setattr(pa, "_torch", lambda: Torch)
-    monkeypatch.setattr(pa, "release_cache", lambda: (log.append("release"), setattr(Torch, "full", 0)))
-    assert pa.device_empty(3, torch.int8) == (3, torch.int8, "cuda")
-    assert log == ["empty", "release", "empty"]
-    Torch.full = 1
+    def release():
+        log.append("release")
+        room[0] = True
+
+    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(pa, "release_cache", release)
+    for allocate in (lambda: pa.device_empty(3, torch.int8),
+                     lambda: pa.on_device(lambda: torch.empty(3, dtype=torch.int8, device="cuda"))):
+        room[0] = False
+        assert allocate() == (3, torch.int8, "cuda")
+        assert log == ["empty", "release", "empty"]
+        del log[:]
+    room[0] = False
     monkeypatch.setattr(pa, "release_cache", lambda: log.append("release"))
     with pytest.raises(torch.OutOfMemoryError):
         pa.device_empty(3, torch.int8)
-    assert log == ["empty", "release", "empty"] + ["empty", "release", "empty"]
+    assert log == ["empty", "release", "empty"]
