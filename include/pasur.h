@@ -299,7 +299,9 @@ int pasur_plan_info(const pasur_plan *plan, int64_t info[8]);
  * device memory, wholly there, and in place; launches, their least and most threads
  * per workgroup; and how often, in launches that have ended, a segment ran in
  * place though it was planned otherwise (a state that the solver's own calls do not
- * make, as with sigma other than 1 along forced chains, may need it). */
+ * make, as with sigma other than 1 along forced chains, may need it, and a node of
+ * more than 63 moves does).  All are planned in place with PASUR_SCHED_ROOT_GLOBAL,
+ * and where a discount is not a number (an infinite power of t - 1). */
 int pasur_plan_forms(const pasur_plan *plan, int64_t info[8]);
 /* pasur_leaf_utilities (no flags; d_V_next[i] may be NULL for round 5) and
  * pasur_cfr_init of n_items (tree, state) pairs of one dtype, in one launch per

@@ -45,14 +45,16 @@
 // 64 deals (7.6e7 nodes), 50 iterations, 56 -> 16.2 ms with all that surrounds it.
 //
 // A segment too large for LDS keeps its far arrays in device memory (roots of
-// more than about 14,000 nodes, F64 7,000), or all of the form (32,000, F64
-// 16,000).  One that has no compact form (a node of more than 63 moves, more than
-// 65,535 edges) is iterated in place in global memory, one phase per level.
+// more than 9,000 to 14,000 nodes, by their shape, F64 half of that), or all of the
+// form (32,000, F64 16,000).  One that has no compact form (a node of more than 63
+// moves, more than 65,535 edges, discounts that are not numbers) is iterated in
+// place in global memory, one phase per level.
 #pragma clang fp contract(off)
 
 #include "pasur_internal.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -95,7 +97,7 @@ struct SegCounts {
 // tables and a map from tree nodes to active nodes take the edge arrays'
 // place.  A segment too large for this keeps rs, chain, kids, up and pos (its far
 // arrays) in device memory: each is read once per iteration or pass, in order,
-// while su and x are read at random.  That carries roots of 14,000 to 32,000
+// while su and x are read at random.  That carries roots of up to 32,000
 // nodes (f32) at a fifth of the time of iterating them in place.
 struct SegLds {
   uint32_t b6, b7;   // passive bits of levels 6 and 7
@@ -1562,6 +1564,16 @@ void count_forms(int64_t forms[4], const std::vector<SegPlan> &segs) {
   for (const SegPlan &sp : segs) forms[sp.seg.form] += 1;
 }
 
+// The compact form leaves a forced chain's regrets of zero alone.  They don't stay
+// zero where a discount is not a number: after an infinite power of t - 1 (an
+// exponent below zero at t = 1, or one so large that the power overflows).
+bool zeros_stay(const IterK *ks, int64_t n, int variant) {
+  if (variant != PASUR_DCFR) return true;
+  for (int64_t i = 0; i < n; ++i)
+    if (!std::isfinite(ks[i].dneg)) return false;
+  return true;
+}
+
 bool all_lds(const int64_t forms[4]) {
   return forms[F_FAR] + forms[F_ALL_FAR] + forms[F_NONE] == 0;
 }
@@ -1600,6 +1612,11 @@ template <class T>
 int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_state *const *states,
                const pasur_cfr_params *p, int force_global, hipStream_t s) {
   const int n_items = pl->n_items;
+  // iteration constants for t_first .. t_last, computed on the host
+  const int64_t nt = pl->t_last - pl->t_first + 1;
+  std::vector<IterK> ks((size_t)nt);
+  for (int64_t i = 0; i < nt; ++i) ks[(size_t)i] = iter_k(p, pl->t_first + i);
+  if (!zeros_stay(ks.data(), nt, p->variant)) force_global = 1;
   std::vector<ItemDesc<T>> items((size_t)n_items);
   std::vector<SegPlan> segs;
   for (int64_t k = 0; k < 4; ++k) pl->work[k] = 0;
@@ -1630,10 +1647,6 @@ int plan_build(pasur_plan *pl, const pasur_fgt *const *fgts, const pasur_cfr_sta
   }
   pl->n_segs = (int)sorted.size();
   pl->lds_bytes = max_bytes;
-  // iteration constants for t_first .. t_last, computed on the host
-  const int64_t nt = pl->t_last - pl->t_first + 1;
-  std::vector<IterK> ks((size_t)nt);
-  for (int64_t i = 0; i < nt; ++i) ks[(size_t)i] = iter_k(p, pl->t_first + i);
   // one upload
   const size_t at_segs = align16(sizeof(ItemDesc<T>) * items.size());
   const size_t at_ks = at_segs + align16(sizeof(Seg) * sorted.size());
@@ -1868,13 +1881,14 @@ int enqueue(const pasur_fgt *f, const SegIndex &x, const pasur_cfr_state *st,
             const pasur_cfr_params *p, int64_t t0, int n_iters, bool capturing, bool *done,
             hipStream_t s) {
   const bool paper = paper_variant(p->variant, p->rm_mode);
-  PASUR_TRY(allow_lds<T>(x.launches, paper));
   // far arrays, the item, the iterations' constants
   const ItemDesc<T> D = item_desc<T>(f, st);
   std::vector<unsigned char> stage(align16(sizeof(D)) + sizeof(IterK) * (size_t)n_iters);
   std::memcpy(stage.data(), &D, sizeof(D));
   IterK *const ks = (IterK *)(stage.data() + align16(sizeof(D)));
   for (int i = 0; i < n_iters; ++i) ks[i] = iter_k(p, t0 + i);
+  if (!zeros_stay(ks, n_iters, p->variant)) return PASUR_OK;
+  PASUR_TRY(allow_lds<T>(x.launches, paper));
   const size_t far_bytes = align16((size_t)x.far_bytes), bytes = far_bytes + stage.size() + 16;
   void *mem = nullptr;
   if (capturing) {

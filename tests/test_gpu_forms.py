@@ -131,3 +131,36 @@ def test_games_beyond_one_per_thread_match_the_oracle():
                     q = int(R["link"][q])
             assert got[g] == m, (pol, g)
     s.free()
+
+
+@pytest.mark.parametrize("beta,dtype_name", [(-1.0, "PASUR_F32"), (-1.0, "PASUR_F64"),
+                                             (400.0, "PASUR_F64")])
+def test_discounts_that_are_not_numbers(beta, dtype_name):
+    """0^beta for beta < 0 and 9^400 are infinite, their discounts NaN: regrets of
+    forced chains follow them as in the level-synchronous kernels, from the first
+    iteration on or from where the power overflows.  Such segments run in place."""
+    pa = require_gpu()
+    import torch
+    deck, roots = playout(pa, 8, 4)
+    s = pa.SubgameSolver(deck, 4, roots, dtype=getattr(pa, dtype_name))
+    rr = s.rounds[1]
+    out = []
+    for sched in (pa.SCHED_LEVEL_SYNC, pa.SCHED_ROOT):
+        p = pa.paper_params(sched)
+        p.beta = beta
+        st = pa.CfrState(rr.fgt, s.dtype)
+        for t in st.reachA[1:8] + st.reachB[1:8] + st.u[:8]:
+            t.zero_()
+        pa.leaf_utilities(rr.fgt, None, s.dtype, st.u[8])
+        pa.cfr_init(st)
+        pa.cfr_iterate(st, 4, p)
+        pa.cfr_iterate(st, 8, p)
+        torch.cuda.synchronize()
+        out.append(arrays(st))
+    assert any(np.isnan(a).any() for a in out[0])
+    plan = pa.Plan([st], p, 1, 12)
+    assert plan.forms()["in_place"] == plan.n_segs == rr.fgt.n[0]
+    plan.free()
+    for k, (a, b) in enumerate(zip(*out)):
+        assert np.array_equal(a, b, equal_nan=True), k
+    s.free()
