@@ -41,7 +41,7 @@
 //
 // Measured (FP32 unless said): seven roots of 3,200 nodes, FP64, 11.3 -> 4.5 us
 // per iteration against one phase per level over all nodes; 38,652 roots of 3,900
-// nodes, 0.53 ms per iteration (2.8e11 nodes/s, VALU 52 to 65% busy); a batch of
+// nodes, 0.53 ms per iteration (2.8e11 nodes/s, VALU 50 to 64% busy); a batch of
 // 64 deals (7.6e7 nodes), 50 iterations, 56 -> 16.2 ms with all that surrounds it.
 //
 // A segment too large for LDS keeps its far arrays in device memory (roots of
